@@ -68,6 +68,20 @@ __device__ __forceinline__ float wave_max_f32(float v) {
   return v;
 }
 
+// Where a result is defined as an fp64 sum of `count` terms in a given order,
+// rounded once to fp32, the sum may be formed in any order as long as every
+// order rounds to the same float.  Two sums of the same terms differ by at most
+// 2 (count - 1) u / (1 - (count - 1) u) times the sum of the terms' magnitudes
+// (u = 2^-53); `magnitudes` is that sum as computed, and the bound below leaves
+// room for its own rounding and for that of the two ends of the interval.
+// False (also for sums that are not finite): form the sum in the given order.
+__device__ __forceinline__ bool certain_f32(double sum, double magnitudes, uint32_t count, float &rounded) {
+  const double room = magnitudes * ((double)(2 * count + 16) * 0x1p-53);
+  const float low = (float)(sum - room), high = (float)(sum + room);
+  rounded = low;
+  return low == high && fabsf(low) < INFINITY && (low != 0.0f || room == 0.0);
+}
+
 // fp32 -> uint32 such that unsigned order equals numeric order (no NaN).
 __device__ __forceinline__ uint32_t order_u32(float f) {
   uint32_t u = __float_as_uint(f);

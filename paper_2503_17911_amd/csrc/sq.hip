@@ -11,35 +11,115 @@
 namespace ann {
 
 // ------------------------------------------------------------- codebook
-// Column-wise min/max over a slab of rows.  Thread t of a block walks columns
-// t, t+blockDim, ... so that a wavefront reads consecutive floats of one row.
-__global__ void sq_minmax_partial_kernel(const float *__restrict__ x, uint64_t n, uint32_t d, uint32_t rows_per_block,
-                                         float *__restrict__ pmin, float *__restrict__ pmax) {
-  uint64_t r0 = (uint64_t)blockIdx.x * rows_per_block;
-  uint64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
-  for (uint32_t j = threadIdx.x; j < d; j += blockDim.x) {
-    float mn = INFINITY, mx = -INFINITY;
-    for (uint64_t i = r0; i < r1; ++i) {
-      float v = x[i * d + j];
-      mn = fminf(mn, v);
-      mx = fmaxf(mx, v);
+// Column-wise min/max.  Bound: one read of x.  A workgroup takes a slab of
+// rows; its threads lie side by side over the row's VEC-wide pieces and, where
+// the row has fewer pieces than the workgroup threads, over several rows at a
+// time, with eight loads in flight per thread.  The partial results (about a
+// thousand slabs) are reduced by a workgroup per 16 columns whose 64 threads
+// per column walk the slabs in parallel.  1M x 128: 244 + 491 us (half of the
+// threads idle; one thread per column over all slabs) -> 107 + 5 us (4.8 TB/s).
+constexpr int kMinmaxThreads = 256, kMinmaxUnroll = 8;
+
+template <int VEC>
+__global__ __launch_bounds__(kMinmaxThreads) void sq_minmax_partial_kernel(const float *__restrict__ x, uint64_t n, uint32_t d,
+                                                                           uint64_t rows_per_block,
+                                                                           float *__restrict__ pmin, float *__restrict__ pmax) {
+  __shared__ float red[2][kMinmaxThreads * VEC];
+  const uint32_t pieces = d / VEC, p0 = blockIdx.y * kMinmaxThreads;
+  const uint32_t width = pieces - p0 < (uint32_t)kMinmaxThreads ? pieces - p0 : (uint32_t)kMinmaxThreads;
+  const uint32_t side = kMinmaxThreads / width;   // rows side by side
+  const uint32_t r = threadIdx.x / width, c = threadIdx.x % width;
+  const uint64_t r0 = (uint64_t)blockIdx.x * rows_per_block;
+  const uint64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
+  float mn[VEC], mx[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    mn[e] = INFINITY;
+    mx[e] = -INFINITY;
+  }
+  auto take = [&](const float *p, float (&v)[VEC]) {
+    if constexpr (VEC == 4) {
+      const float4 t = *reinterpret_cast<const float4 *>(p);
+      v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
+    } else {
+      v[0] = p[0];
     }
-    pmin[(uint64_t)blockIdx.x * d + j] = mn;
-    pmax[(uint64_t)blockIdx.x * d + j] = mx;
+  };
+  auto fold = [&](const float (&v)[VEC]) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      mn[e] = fminf(mn[e], v[e]);
+      mx[e] = fmaxf(mx[e], v[e]);
+    }
+  };
+  if (r < side) {
+    const float *col = x + (uint64_t)(p0 + c) * VEC;
+    uint64_t i = r0 + r;
+    for (; i + (uint64_t)(kMinmaxUnroll - 1) * side < r1; i += (uint64_t)kMinmaxUnroll * side) {
+      float v[kMinmaxUnroll][VEC];
+#pragma unroll
+      for (int u = 0; u < kMinmaxUnroll; ++u) take(col + (i + (uint64_t)u * side) * d, v[u]);
+#pragma unroll
+      for (int u = 0; u < kMinmaxUnroll; ++u) fold(v[u]);
+    }
+    for (; i < r1; i += side) {
+      float v[VEC];
+      take(col + i * d, v);
+      fold(v);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    red[0][threadIdx.x * VEC + e] = mn[e];
+    red[1][threadIdx.x * VEC + e] = mx[e];
+  }
+  __syncthreads();
+  if (threadIdx.x < width) {
+    for (uint32_t k = 1; k < side; ++k)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        mn[e] = fminf(mn[e], red[0][(k * width + threadIdx.x) * VEC + e]);
+        mx[e] = fmaxf(mx[e], red[1][(k * width + threadIdx.x) * VEC + e]);
+      }
+    const uint64_t at = (uint64_t)blockIdx.x * d + (uint64_t)(p0 + threadIdx.x) * VEC;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      pmin[at + e] = mn[e];
+      pmax[at + e] = mx[e];
+    }
   }
 }
 
-__global__ void sq_minmax_final_kernel(const float *__restrict__ pmin, const float *__restrict__ pmax, uint32_t nblocks,
-                                       uint32_t d, float levels, float *__restrict__ lo, float *__restrict__ delta) {
-  uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d) return;
+constexpr int kFinalCols = 16, kFinalRows = 64;
+
+__global__ __launch_bounds__(kFinalCols *kFinalRows) void sq_minmax_final_kernel(const float *__restrict__ pmin,
+                                                                                 const float *__restrict__ pmax, uint32_t nblocks,
+                                                                                 uint32_t d, float levels, float *__restrict__ lo,
+                                                                                 float *__restrict__ delta) {
+  __shared__ float smn[kFinalRows][kFinalCols], smx[kFinalRows][kFinalCols];
+  const uint32_t c = threadIdx.x % kFinalCols, r = threadIdx.x / kFinalCols, j = blockIdx.x * kFinalCols + c;
   float mn = INFINITY, mx = -INFINITY;
-  for (uint32_t b = 0; b < nblocks; ++b) {
-    mn = fminf(mn, pmin[(uint64_t)b * d + j]);
-    mx = fmaxf(mx, pmax[(uint64_t)b * d + j]);
+  if (j < d)
+#pragma unroll 8
+    for (uint32_t b = r; b < nblocks; b += kFinalRows) {
+      mn = fminf(mn, pmin[(uint64_t)b * d + j]);
+      mx = fmaxf(mx, pmax[(uint64_t)b * d + j]);
+    }
+  smn[r][c] = mn;
+  smx[r][c] = mx;
+  for (uint32_t h = kFinalRows / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if (r < h) {
+      smn[r][c] = fminf(smn[r][c], smn[r + h][c]);
+      smx[r][c] = fmaxf(smx[r][c], smx[r + h][c]);
+    }
   }
-  lo[j] = mn;
-  delta[j] = (mx > mn) ? __fdiv_rn(__fsub_rn(mx, mn), levels) : 1.0f;
+  if (r == 0 && j < d) {
+    mn = smn[0][c];
+    mx = smx[0][c];
+    lo[j] = mn;
+    delta[j] = (mx > mn) ? __fdiv_rn(__fsub_rn(mx, mn), levels) : 1.0f;
+  }
 }
 
 // ------------------------------------------------------------- truncated range
@@ -102,52 +182,158 @@ __global__ void truncated_range_kernel(const uint32_t *__restrict__ prefix, uint
 }
 
 // ------------------------------------------------------------- encoder
-// One wavefront per row.  Lanes quantize strided dimensions; the squared norm
-// of the decoded row is summed by one lane in dimension order in fp64 so that
-// it is reproducible bit for bit (each product of two floats is exact in fp64).
+// Bound: one read of x, one write of the codes (vector instructions are close
+// behind).  A group of LPR lanes takes a row, VEC dimensions per lane and piece
+// (a row of more than LPR * VEC dimensions has several pieces), and every lane
+// carries kEncRows rows at a time, so that many loads are in flight and what
+// depends on the column alone is read once for all of them.
+//
+// The quotient of two floats is taken as a product in fp64 with the reciprocal
+// of the step (one division per column and workgroup instead of one per
+// element) and rounded to fp32: the product is within 2^-51 of the quotient,
+// relatively, and a quotient of two floats is never closer than 2^-49 to the
+// middle between two floats, so the rounding is that of the division.
+//
+// The squared norm is defined as the fp64 sum in dimension order, rounded once
+// to fp32.  It is formed as a tree instead (certain_f32 says when both round to
+// the same float) and again by one lane in dimension order where the two may
+// differ: about one row in 2^28 / d.
+// 1M x 128, 8 bits: 782 us (one row per wavefront, the sum by one lane) -> 123 us (5.3 TB/s read and written);
+// 200,000 x 960, 4 bits: 1,179 us -> 271 us (3.2 TB/s; two to four pieces per row, the last not full).
+constexpr int kEncRows = 8;
+
+// Code of value v in a column with the given range and reciprocal step, and the value it decodes to.
 template <int BITS>
+__device__ __forceinline__ uint32_t sq_code(float v, float lo, float delta, double inv, float &decoded) {
+  constexpr uint32_t top = (1u << BITS) - 1u;
+  const float quot = (float)((double)__fsub_rn(v, lo) * inv);
+  const float u = __fadd_rn(quot, 0.5f);
+  // (a NaN counts as 0)
+  const uint32_t c = !(u > 0.0f) ? 0u : (u >= (float)(top + 1) ? top : (uint32_t)u);
+  decoded = __fadd_rn(lo, __fmul_rn(delta, (float)c));
+  return c;
+}
+
+// Squared norm of a decoded row in dimension order (rarely needed, see above).
+template <int BITS>
+__device__ __forceinline__ float sq_norm_in_order(const float *xr, uint32_t d, const float *lo, const float *delta, const double *inv) {
+  double acc = 0.0;
+#pragma nounroll
+  for (uint32_t j = 0; j < d; ++j) {
+    float v;
+    (void)sq_code<BITS>(xr[j], lo[j], delta[j], inv[j], v);
+    acc += (double)v * (double)v;
+  }
+  return (float)acc;
+}
+
+// SINGLE: one piece per row, the columns' ranges stay in registers.
+template <int BITS, int VEC, int LPR, bool SINGLE>
 __global__ __launch_bounds__(256) void sq_encode_kernel(const float *__restrict__ x, uint64_t n, uint32_t d,
                                                         const float *__restrict__ lo, const float *__restrict__ delta,
                                                         uint8_t *__restrict__ codes, float *__restrict__ norm_term) {
-  extern __shared__ float xhat_smem[];  // [waves per block][d]
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int waves_per_block = blockDim.x / kWave;
-  float *xhat = xhat_smem + (size_t)wave * d;
-  const uint32_t row_bytes = BITS == 8 ? d : d / 2;
-  const int maxc = (1 << BITS) - 1;
-  for (uint64_t i = (uint64_t)blockIdx.x * waves_per_block + wave; i < n; i += (uint64_t)gridDim.x * waves_per_block) {
-    const float *xr = x + i * d;
-    uint8_t *cr = codes + i * row_bytes;
-    if constexpr (BITS == 8) {
-      for (uint32_t j = lane; j < d; j += kWave) {
-        float u = __fadd_rn(__fdiv_rn(__fsub_rn(xr[j], lo[j]), delta[j]), 0.5f);
-        int c = !(u > 0.0f) ? 0 : (u >= (float)(maxc + 1) ? maxc : (int)floorf(u));
-        cr[j] = (uint8_t)c;
-        xhat[j] = __fadd_rn(lo[j], __fmul_rn(delta[j], (float)c));
-      }
-    } else {
-      for (uint32_t b = lane; b < row_bytes; b += kWave) {
-        int cc[2];
+  extern __shared__ double inv_s[];                        // [d]
+  float *lo_s = reinterpret_cast<float *>(inv_s + d);      // [d]
+  float *delta_s = lo_s + d;                               // [d]
+  for (uint32_t j = threadIdx.x; j < d; j += blockDim.x) {
+    const float dl = delta[j];
+    lo_s[j] = lo[j];
+    delta_s[j] = dl;
+    inv_s[j] = 1.0 / (double)dl;
+  }
+  __syncthreads();
+  constexpr int RPG = kWave / LPR;   // rows side by side in a wavefront
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, sub = lane % LPR, grp = lane / LPR;
+  const uint32_t row_bytes = BITS == 8 ? d : d / 2, nv = d / VEC;
+  const uint32_t pieces = SINGLE ? 1u : (nv + LPR - 1) / LPR;
+  const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / kWave);
+  float lo_r[VEC], delta_r[VEC];
+  double inv_r[VEC];
+  auto columns = [&](uint32_t j0) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          uint32_t j = 2 * b + h;
-          float u = __fadd_rn(__fdiv_rn(__fsub_rn(xr[j], lo[j]), delta[j]), 0.5f);
-          int c = !(u > 0.0f) ? 0 : (u >= (float)(maxc + 1) ? maxc : (int)floorf(u));
-          cc[h] = c;
-          xhat[j] = __fadd_rn(lo[j], __fmul_rn(delta[j], (float)c));
+    for (int e = 0; e < VEC; ++e) {
+      lo_r[e] = lo_s[j0 + e];
+      delta_r[e] = delta_s[j0 + e];
+      inv_r[e] = inv_s[j0 + e];
+    }
+  };
+  if (SINGLE) columns((uint32_t)sub < nv ? (uint32_t)sub * VEC : 0u);
+  for (uint64_t base = ((uint64_t)blockIdx.x * (blockDim.x / kWave) + wave) * (kEncRows * RPG); base < n;
+       base += waves * (kEncRows * RPG)) {
+    double acc[kEncRows];
+#pragma unroll
+    for (int r = 0; r < kEncRows; ++r) acc[r] = 0.0;
+    for (uint32_t p = 0; p < pieces; ++p) {
+      const uint32_t v = p * LPR + (uint32_t)sub;
+      const bool in = v < nv;
+      const uint32_t j0 = in ? v * VEC : 0u;
+      if (!SINGLE) columns(j0);
+      // (loads past the last row or the row's end are clamped into the array, so that none is conditional)
+      float xv[kEncRows][VEC];
+#pragma unroll
+      for (int r = 0; r < kEncRows; ++r) {
+        const uint64_t i = base + (uint32_t)(r * RPG + grp);
+        const float *at = x + (i < n ? i : n - 1) * d + j0;
+        if constexpr (VEC == 4) {
+          const float4 t = *reinterpret_cast<const float4 *>(at);
+          xv[r][0] = t.x, xv[r][1] = t.y, xv[r][2] = t.z, xv[r][3] = t.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) xv[r][e] = at[e];
         }
-        cr[b] = (uint8_t)(cc[0] | (cc[1] << 4));
+      }
+#pragma unroll
+      for (int r = 0; r < kEncRows; ++r) {
+        const uint64_t i = base + (uint32_t)(r * RPG + grp);
+        uint32_t word = 0;
+        double sum = acc[r];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          float dec;
+          word |= sq_code<BITS>(xv[r][e], lo_r[e], delta_r[e], inv_r[e], dec) << (BITS * e);
+          sum = fma((double)dec, (double)dec, sum);
+        }
+        acc[r] = in ? sum : acc[r];
+        if (in && i < n) {
+          uint8_t *to = codes + i * row_bytes + (BITS == 8 ? j0 : j0 / 2);
+          if constexpr (BITS * VEC == 32)
+            *reinterpret_cast<uint32_t *>(to) = word;
+          else if constexpr (BITS * VEC == 16)
+            *reinterpret_cast<uint16_t *>(to) = (uint16_t)word;
+          else
+            *to = (uint8_t)word;
+        }
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (norm_term && lane == 0) {
-      double acc = 0.0;
-      for (uint32_t j = 0; j < d; ++j) acc += (double)xhat[j] * (double)xhat[j];
-      norm_term[i] = (float)acc;
+    if (!norm_term) continue;
+    // Sums over the row's lanes, all rows of the lane together: an exchange
+    // with the lane next door halves the rows a lane still carries, so that
+    // after three of them lane `sub` holds a part of row sub % 8 alone.
+    static_assert(kEncRows == 8, "three halvings");
+    double part;
+    {
+      double h4[4], h2[2];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double keep = (sub & 1) ? acc[2 * k + 1] : acc[2 * k], give = (sub & 1) ? acc[2 * k] : acc[2 * k + 1];
+        h4[k] = keep + xor_lane_f64(give, 1);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const double keep = (sub & 2) ? h4[2 * k + 1] : h4[2 * k], give = (sub & 2) ? h4[2 * k] : h4[2 * k + 1];
+        h2[k] = keep + xor_lane_f64(give, 2);
+      }
+      const double keep = (sub & 4) ? h2[1] : h2[0], give = (sub & 4) ? h2[0] : h2[1];
+      part = keep + xor_lane_f64(give, 4);
+#pragma unroll
+      for (int m = 8; m < LPR; m <<= 1) part += xor_lane_f64(part, m);
     }
-    __builtin_amdgcn_wave_barrier();
+    const uint64_t i = base + (uint32_t)((sub & 7) * RPG + grp);
+    if (sub < 8 && i < n) {
+      float norm;
+      if (!certain_f32(part, part, d, norm)) norm = sq_norm_in_order<BITS>(x + i * d, d, lo_s, delta_s, inv_s);
+      norm_term[i] = norm;
+    }
   }
 }
 
@@ -271,21 +457,26 @@ ann_status ann_sq_train(const float *x, uint64_t n, uint32_t d, uint32_t bits, f
   if (!x || !lo || !delta) return fail(ANN_EINVAL, "ann_sq_train: NULL argument");
   if (n == 0 || d == 0) return fail(ANN_EINVAL, "ann_sq_train: empty input");
   if (bits != 8 && bits != 4) return fail(ANN_EINVAL, "ann_sq_train: bits must be 4 or 8");
-  const uint32_t rows_per_block = 512;
+  // about a thousand slabs (four workgroups per compute unit), none so short that a thread has fewer than eight rows
+  const bool vec4 = d % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+  const uint32_t pieces = vec4 ? d / 4 : d;
+  const uint32_t side = pieces < (uint32_t)kMinmaxThreads ? kMinmaxThreads / pieces : 1u;
+  uint64_t rows_per_block = (n + 1023) / 1024;
+  if (rows_per_block < (uint64_t)kMinmaxUnroll * side) rows_per_block = (uint64_t)kMinmaxUnroll * side;
   const uint32_t nblocks = (uint32_t)((n + rows_per_block - 1) / rows_per_block);
-  float *pmin = nullptr, *pmax = nullptr;
-  ANN_HIP(hipMalloc((void **)&pmin, (size_t)nblocks * d * sizeof(float)));
-  hipError_t e = hipMalloc((void **)&pmax, (size_t)nblocks * d * sizeof(float));
-  if (e != hipSuccess) {
-    (void)hipFree(pmin);
-    return hip_fail(e, "hipMalloc");
-  }
-  sq_minmax_partial_kernel<<<nblocks, 256, 0, st>>>(x, n, d, rows_per_block, pmin, pmax);
-  sq_minmax_final_kernel<<<(d + 255) / 256, 256, 0, st>>>(pmin, pmax, nblocks, d, (float)((1u << bits) - 1u), lo, delta);
-  e = hipGetLastError();
+  float *pmin = nullptr;
+  ANN_HIP(hipMalloc((void **)&pmin, (size_t)nblocks * d * 2 * sizeof(float)));
+  float *pmax = pmin + (size_t)nblocks * d;
+  const dim3 grid(nblocks, (pieces + kMinmaxThreads - 1) / kMinmaxThreads);
+  if (vec4)
+    sq_minmax_partial_kernel<4><<<grid, kMinmaxThreads, 0, st>>>(x, n, d, rows_per_block, pmin, pmax);
+  else
+    sq_minmax_partial_kernel<1><<<grid, kMinmaxThreads, 0, st>>>(x, n, d, rows_per_block, pmin, pmax);
+  sq_minmax_final_kernel<<<(d + kFinalCols - 1) / kFinalCols, kFinalCols * kFinalRows, 0, st>>>(
+      pmin, pmax, nblocks, d, (float)((1u << bits) - 1u), lo, delta);
+  hipError_t e = hipGetLastError();
   hipError_t e2 = hipStreamSynchronize(st);
   (void)hipFree(pmin);
-  (void)hipFree(pmax);
   if (e != hipSuccess) return hip_fail(e, "sq_minmax launch");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
@@ -341,14 +532,43 @@ ann_status ann_sq_encode(const float *x, uint64_t n, uint32_t d, uint32_t bits, 
   if (bits != 8 && bits != 4) return fail(ANN_EINVAL, "ann_sq_encode: bits must be 4 or 8");
   if (bits == 4 && (d & 1)) return fail(ANN_EINVAL, "ann_sq_encode: 4-bit codes need an even d");
   if (d > 2048) return fail(ANN_ECAPACITY, "ann_sq_encode: d = %u exceeds 2048", d);
-  const int block = 256, waves = block / kWave;
-  uint64_t want = (n + waves - 1) / waves;
-  int grid = (int)(want > 16384 ? 16384 : want);
-  size_t smem = (size_t)waves * d * sizeof(float);
-  if (bits == 8)
-    sq_encode_kernel<8><<<grid, block, smem, st>>>(x, n, d, lo, delta, codes, norm_term);
-  else
-    sq_encode_kernel<4><<<grid, block, smem, st>>>(x, n, d, lo, delta, codes, norm_term);
+  // pieces of four dimensions need 16-byte rows of x and codes that can be
+  // stored four (8 bits) or two (4 bits) bytes at a time
+  const bool vec4 = d % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(codes) % 4 == 0;
+  const uint32_t vec = vec4 ? 4u : (bits == 8 ? 1u : 2u), pieces = d / vec;
+  uint32_t lpr = 8;
+  while (lpr < pieces && lpr < (uint32_t)kWave) lpr <<= 1;
+  const uint64_t rows_per_block = (uint64_t)(256 / kWave) * kEncRows * (kWave / lpr);
+  const uint64_t want = (n + rows_per_block - 1) / rows_per_block;
+  const int grid = (int)(want > 2048 ? 2048 : want);   // eight workgroups per compute unit
+  const size_t smem = (size_t)d * (sizeof(double) + 2 * sizeof(float));
+#define ANN_ENC(B, V, L, S) sq_encode_kernel<B, V, L, S><<<grid, 256, smem, st>>>(x, n, d, lo, delta, codes, norm_term)
+#define ANN_ENC_LPR(B, V)                                    \
+  do {                                                       \
+    switch (lpr) {                                           \
+      case 8: ANN_ENC(B, V, 8, true); break;                 \
+      case 16: ANN_ENC(B, V, 16, true); break;               \
+      case 32: ANN_ENC(B, V, 32, true); break;               \
+      default:                                               \
+        if (pieces <= (uint32_t)kWave)                       \
+          ANN_ENC(B, V, 64, true);                           \
+        else                                                 \
+          ANN_ENC(B, V, 64, false);                          \
+    }                                                        \
+  } while (0)
+  if (bits == 8) {
+    if (vec4)
+      ANN_ENC_LPR(8, 4);
+    else
+      ANN_ENC_LPR(8, 1);
+  } else {
+    if (vec4)
+      ANN_ENC_LPR(4, 4);
+    else
+      ANN_ENC_LPR(4, 2);
+  }
+#undef ANN_ENC_LPR
+#undef ANN_ENC
   ANN_HIP(hipGetLastError());
   ANN_HIP(hipStreamSynchronize(st));
   return ANN_OK;

@@ -1,0 +1,70 @@
+"""Codebook and encoder kernels at the edges of their pieces and row groups,
+bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import gpu_harness
+    return gpu_harness
+
+
+def _values(n, d, seed):
+    rng = np.random.default_rng(seed)
+    return (rng.standard_normal((n, d)) * np.exp(rng.standard_normal(d))).astype(np.float32)
+
+
+def _fit(H, X, bits, offset=0):
+    """Train and encode with x and the codes `offset` elements behind a 256-byte boundary."""
+    import torch
+    import paper_2503_17911_amd as ann
+    n, d = X.shape
+    rb = d if bits == 8 else d // 2
+    xd = torch.empty(n * d + offset, device=H.DEV)
+    xd[offset:] = H.dev(X).reshape(-1)
+    codes = torch.zeros(n * rb + offset, dtype=torch.uint8, device=H.DEV)
+    lo, delta, norm = (torch.empty(m, device=H.DEV) for m in (d, d, n))
+    ann.ann_sq_train(xd[offset:], n, d, bits, lo, delta, H.stream_ptr())
+    ann.ann_sq_encode(xd[offset:], n, d, bits, lo, delta, codes[offset:], norm, H.stream_ptr())
+    return lo.cpu().numpy(), delta.cpu().numpy(), codes[offset:].cpu().numpy().reshape(n, rb), norm.cpu().numpy()
+
+
+def _same(got, want):
+    return (np.ascontiguousarray(got).view(np.uint32) == np.ascontiguousarray(want).view(np.uint32)).all()
+
+
+# one piece per row and several; 8 to 64 lanes a row; rows that do not fill a group; scalar pieces (d % 4, offset)
+@pytest.mark.parametrize("n,d,bits,offset", [(1, 1, 8, 0), (9, 3, 8, 0), (33, 4, 8, 0), (257, 32, 8, 0), (65, 36, 4, 0), (1027, 64, 8, 1),
+                                             (63, 65, 8, 0), (130, 66, 4, 0), (129, 256, 8, 0), (31, 260, 8, 0), (70, 1028, 4, 0),
+                                             (17, 2048, 8, 0), (19, 2048, 4, 3), (40000, 24, 8, 0), (12345, 10, 4, 2)])
+def test_edges(H, n, d, bits, offset):
+    X = _values(n, d, n + d)
+    lv = oracle.sq_fit(X, bits)
+    lo, delta, codes, norm = _fit(H, X, bits, offset)
+    assert _same(lo, lv.lo) and _same(delta, lv.delta)
+    assert (codes == lv.codes).all()
+    assert _same(norm, lv.norm_term)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_values_outside_the_range(H, bits):
+    """Values far outside the codebook's range and infinities clamp; a column of one value has step 1."""
+    import torch
+    import paper_2503_17911_amd as ann
+    X = _values(300, 72, 3)
+    X[:, 5] = 1.5
+    lv = oracle.sq_fit(X, bits)
+    Y = X.copy()
+    Y[::7] *= 1e6
+    Y[3, 4], Y[5, 6], Y[8, 9], Y[9, 9] = np.inf, -np.inf, 3e38, -3e38
+    want = oracle.sq_encode(Y, bits, lv.lo, lv.delta)
+    codes = torch.empty(want.codes.shape, dtype=torch.uint8, device=H.DEV)
+    norm = torch.empty(300, device=H.DEV)
+    ann.ann_sq_encode(H.dev(Y), 300, 72, bits, H.dev(lv.lo), H.dev(lv.delta), codes, norm, H.stream_ptr())
+    assert (codes.cpu().numpy() == want.codes).all()
+    assert _same(norm.cpu().numpy(), want.norm_term)
