@@ -1,17 +1,35 @@
 // Exact k nearest neighbours by exhaustive search: the ground truth NN_k of
-// the paper's recall measure (Section 6.1).  The Q.X^T contraction runs on the
-// matrix cores (fp32 MFMA 32x32x2); a threshold-and-buffer top-k in LDS keeps
-// k + margin candidates per (query, base slab); the candidates of all slabs
-// are then re-evaluated directly in fp64 (rerank kernel) and sorted by
-// (distance, id), so the decomposed fp32 scores only ever select candidates.
+// the paper's recall measure (Section 6.1).
 //
-// Three tile kernels, chosen by ann_bruteforce_topk: bf_own_kernel (k <= 16,
-// d % 4 == 0: 128 x 128 tiles, eight wavefronts, per-wavefront candidate
-// lists), bf_block_kernel (k <= 152: 128 x 128 or 64 x 256 tiles, four
-// wavefronts, one buffer per query) and bf_tile_kernel (anything: 32 x 128
-// tiles, scalar staging).  In the first two the slabs of a query publish their
-// kp-th best score in global memory and every slab filters with the smallest:
-// the kp-th best of a part bounds the kp-th best of the whole.
+// Scores that only select candidates: -2 q.x + |x|^2 (or -q.x) from a dense
+// contraction on the matrix cores, every fp32 value split into three bf16
+// parts and six of the nine partial products accumulated in fp32, which loses
+// no more than fp32 products do (see bf_score_kernel).  The k + 8 best of a
+// query and a few more (at most `f_max`) are re-evaluated in fp64 by the rerank
+// kernel and sorted by (distance, id).
+//
+// Selection without a top-k structure in the contraction kernel:
+//   few rows   all scores are written out and a selection kernel takes the best
+//              of every stretch of 4,096, another the best of those;
+//   otherwise  a stratified random sample of 4,096 rows gives every query a
+//              (score, id) bound that k + 8 rows of the sample reach; a sample
+//              sixteen times larger, of which only what reaches the bound is
+//              written, gives a tighter one, and so on until the sample would be
+//              the whole set; the last pass takes all rows in order and writes
+//              what reaches the last bound: about 16 (k + 8 .. f_max) entries per
+//              query whatever the distribution of the data, since the rank of a
+//              random sample's order statistic does not depend on it.
+// A query whose entries overflow their room (which random sampling makes
+// practically impossible) or values the split cannot carry (infinities in an
+// inner product) send the batch to bf_tile_kernel: fp32 products, a threshold
+// and a buffer per (query, base slab) in LDS.
+//
+// Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
+// kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
+// k = 10: 25.8 -> 19.3 ms; 2,000 x 200,000 x 768, k = 100: 13.9 -> 5.2 ms; 100 x
+// 10,000 x 128, k = 10: 2.56 -> 0.11 ms.
+#include <math.h>
+
 #include "ann_internal.hpp"
 #include "device_utils.hpp"
 
@@ -219,603 +237,633 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
   }
 }
 
+// ---------------------------------------------------------------------------
+// Scores on the bf16 matrix cores.
+//
+// A float is the sum of three bf16 values (8 + 8 + 8 bits; rounding to nearest
+// each time, the remainders are exact).  Of the nine products of two such sums
+// the three smallest (below 2^-25 of the product) are left out.  The fp32 matrix
+// rate is 157 TFLOP/s; six bf16 products at 2.5 PFLOP/s leave 417 of the same.
+// Root mean square error of a score against 64 bits, relative to that of the
+// scores (inner products of mixtures, 128 queries x 4,096 rows; in brackets:
+// fp32 products): d = 24 5.5e-8 (7.5e-8), 128 1.4e-7 (1.7e-7), 960 3.1e-7
+// (4.2e-7), 2,048 4.0e-7 (6.1e-7).
+//
+// A workgroup of four wavefronts takes QT queries x 128 base rows per tile.
+// The queries come split, in the order the matrix instruction wants them
+// (bf_split_queries_kernel), straight from global memory (they stay in the L2),
+// one step ahead of their use.  The base rows are fetched a K chunk (32
+// columns) ahead, split on the way into LDS (three planes of 64 bytes per row,
+// the 16-byte slots of a row permuted with the row number so that eight rows
+// read side by side hit all banks); their squared norms are summed on the way.
+// One barrier per chunk.  128 queries: a wavefront has 64 x 64 scores, four
+// accumulators; up to 64 queries: 32 rows x 64; up to 32: 32 x 32 (then the
+// kernel is bound by reading the base rows).
+//
+// Workgroup b runs on die b mod 8; the query tiles of one slab of rows are put
+// on one die, so that a row is fetched from memory by one L2 instead of eight.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-// The part_lists-th smallest of n_vals published values (+inf in score order:
-// nothing published): with every part (a slab's buffer, a wavefront's list)
-// publishing its part_rank-th best score, that many parts hold part_rank
-// entries each at or below it, so the query has part_lists * part_rank >= kp
-// entries at or below it - a bound on its kp-th best.
-__device__ __forceinline__ uint32_t bound_over_parts(const uint32_t *vals, uint32_t n_vals, uint32_t part_lists) {
-  constexpr int kMaxLists = 8;
-  uint32_t low[kMaxLists];   // the smallest published values, ascending
+constexpr int kSB = 128;          // base rows per tile
+constexpr int kSK = 32;           // columns per chunk
+constexpr int kPlane = kSB * kSK * 2;   // bytes of one plane of a chunk
+constexpr int kHitList = 96;      // entries a wavefront collects before they go to global memory
+constexpr uint32_t kSampleRows = 4096;   // first sample; also the stretch one selection workgroup takes
+constexpr uint32_t kSampleGrowth = 16;
+
+// a, b -> their three bf16 parts, a's in the low halves
+__device__ __forceinline__ void split3(float a, float b, uint32_t (&w)[3]) {
 #pragma unroll
-  for (int j = 0; j < kMaxLists; ++j) low[j] = 0xFFFFFFFFu;
-  for (uint32_t i = 0; i < n_vals; ++i) {
-    uint32_t v = vals[i];
-#pragma unroll
-    for (int j = 0; j < kMaxLists; ++j) {
-      const uint32_t lo_ = v < low[j] ? v : low[j];
-      v = v < low[j] ? low[j] : v;
-      low[j] = lo_;
+  for (int p = 0; p < 3; ++p) {
+    const floatx2 v = {a, b};
+    w[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+    if (p < 2) {
+      a = __fsub_rn(a, __uint_as_float(w[p] << 16));
+      b = __fsub_rn(b, __uint_as_float(w[p] & 0xFFFF0000u));
     }
   }
-  uint32_t t = 0xFFFFFFFFu;
-#pragma unroll
-  for (int j = 0; j < kMaxLists; ++j) t = (uint32_t)j == part_lists - 1 ? low[j] : t;
-  return t;
 }
-// tiles 3, 7, 15, 31, ... of a slab: often while the thresholds still move fast, rarely later
-__device__ __forceinline__ bool bound_refresh_due(uint32_t tile_no) { return tile_no >= 3 && (tile_no & (tile_no + 1)) == 0; }
 
-// Global -> LDS staging of one K chunk of a tile (QT query rows, then BT base
-// rows) by NT threads.  Rows are staged K-contiguous with pitch KC + 4 floats:
-// LDS is written and read 16 bytes at a time without bank conflicts.  The loads
-// are unconditional, with addresses clamped into the arrays (conditional loads
-// make the compiler wait for every outstanding load at each of them), and are
-// issued back to back; what lies outside the arrays is zeroed when the
-// registers are written to LDS.  An address is a base common to the workgroup
-// (the tile's first row) plus a 32-bit offset of the thread.
-template <int QT, int BT, int KC, int NT>
-struct TileStager {
-  static constexpr int ROWS = QT + BT, P = KC + 4;
-  static constexpr int C4 = KC / 4;      // float4 per staged row
-  static constexpr int RP = NT / C4;     // rows staged per pass of the workgroup
-  static constexpr int NLD = ROWS / RP;  // passes
-  static_assert(ROWS % RP == 0 && QT % RP == 0, "a pass is all queries or all base rows");
-  const float *q_base, *x;
-  float *stage_buf;   // [2][ROWS][P]
-  uint64_t b_end;     // end of the slab
-  uint32_t d, q_last; // q_last: last row of the batch, counted from the tile's first
-  int s_row, s_col;
-
-  __device__ __forceinline__ TileStager(const float *Q, const float *X, float *lds, uint32_t q0, uint32_t nq, uint32_t dim,
-                                        uint64_t slab_end, int tid)
-      : q_base(Q + (uint64_t)q0 * dim), x(X), stage_buf(lds), b_end(slab_end), d(dim), q_last(nq - 1 - q0),
-        s_row(tid / C4), s_col((tid % C4) * 4) {}
-
-  // rows of the tile that starts at base row t0 (at or past the slab's end: clamped loads, nothing kept), columns k0 ..
-  __device__ __forceinline__ void fetch(float4 (&reg)[NLD], uint32_t &keep, uint64_t t0, uint32_t k0) const {
-    const uint32_t kk = k0 + s_col;
-    const bool k_in = kk < d;
-    const uint32_t kc = k_in ? kk : 0;
-    const uint64_t t0c = t0 < b_end ? t0 : b_end - 1;
-    const float *x_base = x + t0c * d;
-    const uint64_t left = b_end - 1 - t0c;
-    const uint32_t x_last = left < (uint64_t)BT ? (uint32_t)left : (uint32_t)BT;   // last row of the slab, counted from the tile's first
-    keep = 0;
+// Queries split and laid out as the second operand of the 32x32x16 matrix
+// instruction: 16-byte unit (((q / 32) * KB + kb) * 3 + plane) * 64 + lane holds
+// columns kb * 16 + 8 * (lane / 32) .. + 7 of query lane % 32.  Zero past the
+// batch and past d.  An infinity raises the flag.
+__global__ __launch_bounds__(256) void bf_split_queries_kernel(const float *__restrict__ Q, uint32_t nq, uint32_t d, uint32_t kb_n,
+                                                               uint32_t q32_n, uint4 *__restrict__ out, uint32_t *__restrict__ flag) {
+  const uint64_t total = (uint64_t)q32_n * kb_n * 64;
+  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (uint64_t)gridDim.x * blockDim.x) {
+    const uint32_t lane = (uint32_t)(e % 64), kb = (uint32_t)(e / 64 % kb_n), q32 = (uint32_t)(e / 64 / kb_n);
+    const uint32_t qi = q32 * 32 + lane % 32, k0 = kb * 16 + 8 * (lane / 32);
+    float v[8];
+    bool inf = false;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const uint32_t row = (uint32_t)(s_row + RP * i);
-      if (row < (uint32_t)QT) {
-        const bool in = row <= q_last && k_in;
-        reg[i] = *reinterpret_cast<const float4 *>(q_base + ((row < q_last ? row : q_last) * d + kc));
-        keep |= in ? 1u << i : 0u;
+    for (int j = 0; j < 8; ++j) {
+      v[j] = qi < nq && k0 + j < d ? Q[(uint64_t)qi * d + k0 + j] : 0.0f;
+      inf = inf || fabsf(v[j]) >= 0x1.fep127f;
+    }
+    if (inf) atomicOr(flag, 1u);
+    uint32_t w[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split3(v[2 * j], v[2 * j + 1], w[j]);
+    uint4 *to = out + ((uint64_t)q32 * kb_n + kb) * 192 + lane;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) to[p * 64] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+  }
+}
+
+struct ScoreArgs {
+  const float *x;
+  const uint4 *qfrag;
+  uint64_t rows;     // rows of this pass: all of them, or a sample
+  double stretch;    // sample: rows of x per row of the sample; 0: all rows
+  uint32_t d, kb_n, nq, metric;
+  uint32_t q_tiles, slabs, tiles_per_slab;
+  float *scores;     // not NULL: every score goes here, [nq][ld]
+  uint32_t ld;
+  const uint64_t *bound;   // [nq] otherwise: (score, id) pairs up to the bound go to buf
+  uint64_t *buf;     // [nq][cap]
+  uint32_t *count;   // [nq]
+  uint32_t cap;
+  uint32_t *flag;
+};
+
+// Row of x that is row j of a sample: a random one of the j-th stretch of rows
+// (the stretches tile the whole set, so the rows are distinct).
+__device__ __forceinline__ uint64_t sample_row(uint64_t j, double stretch) {
+  uint32_t h = (uint32_t)j * 0x9E3779B1u;
+  h = (h ^ (h >> 15)) * 0x85EBCA77u;
+  h ^= h >> 13;
+  const uint64_t begin = (uint64_t)((double)j * stretch), end = (uint64_t)((double)(j + 1) * stretch);
+  return begin + __umulhi(h, (uint32_t)(end - begin));
+}
+
+template <bool VEC4, int MB, int NQ>
+__global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
+  constexpr int WB = MB == 2 ? 2 : 4;          // wavefronts side by side over the base rows
+  constexpr int QT32 = 4 / WB * NQ;            // blocks of 32 queries per tile
+  static_assert(WB * MB * 32 == kSB, "tile shape");
+  __shared__ __align__(16) unsigned char stage_s[2][3 * kPlane];
+  __shared__ float xn_s[2][kSB];
+  __shared__ uint64_t hit_s[4][kHitList];
+  __shared__ uint8_t hit_q_s[4][kHitList];
+
+  const uint32_t die = blockIdx.x & 7u, nth = blockIdx.x >> 3;
+  const uint32_t qt = nth % a.q_tiles, slab = nth / a.q_tiles * 8u + die;
+  const uint64_t tiles = (a.rows + kSB - 1) / kSB;
+  const uint64_t tile_begin = (uint64_t)slab * a.tiles_per_slab;
+  const uint64_t tile_end = tile_begin + a.tiles_per_slab < tiles ? tile_begin + a.tiles_per_slab : tiles;
+  if (slab >= a.slabs || tile_begin >= tile_end) return;
+
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave, half = lane / 32, l32 = lane % 32;
+  const int wb = wave % WB, wq = wave / WB;
+  const int s_row = tid / 8, s_col = (tid % 8) * 4;
+  const uint32_t n_chunks = a.kb_n / 2;
+  const uint4 *qf[NQ];
+#pragma unroll
+  for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wq * NQ + f) * a.kb_n * 192 + lane;
+
+  // ---- base rows: fetch (four floats of four rows per thread), split, stage
+  float4 reg[4];
+  float sq[4] = {0.f, 0.f, 0.f, 0.f};
+  auto fetch = [&](uint64_t tile, uint32_t c) {
+    const uint32_t k = c * kSK + s_col;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint64_t r = tile * kSB + s_row + 32 * i;
+      r = r < a.rows ? r : a.rows - 1;
+      if (a.stretch != 0.0) r = sample_row(r, a.stretch);
+      const float *p = a.x + r * a.d;
+      if constexpr (VEC4) {
+        reg[i] = *reinterpret_cast<const float4 *>(p + (k < a.d ? k : 0));
       } else {
-        const uint32_t r = row - QT;
-        const bool in = t0 < b_end && r <= x_last && k_in;
-        reg[i] = *reinterpret_cast<const float4 *>(x_base + ((r < x_last ? r : x_last) * d + kc));
-        keep |= in ? 1u << i : 0u;
+        reg[i] = make_float4(p[k < a.d ? k : 0], p[k + 1 < a.d ? k + 1 : 0], p[k + 2 < a.d ? k + 2 : 0], p[k + 3 < a.d ? k + 3 : 0]);
       }
     }
-  }
-  __device__ __forceinline__ void stage(const float4 (&reg)[NLD], uint32_t keep, int b) const {
+  };
+  auto stage = [&](int b, uint64_t tile, uint32_t c) {
+    const uint32_t k = c * kSK + s_col;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const bool in = (keep >> i) & 1u;
-      const float4 v = make_float4(in ? reg[i].x : 0.f, in ? reg[i].y : 0.f, in ? reg[i].z : 0.f, in ? reg[i].w : 0.f);
-      *reinterpret_cast<float4 *>(stage_buf + ((size_t)b * ROWS + s_row + RP * i) * P + s_col) = v;
+    for (int i = 0; i < 4; ++i) {
+      float4 v = reg[i];
+      if constexpr (VEC4) {
+        if (k >= a.d) v = make_float4(0.f, 0.f, 0.f, 0.f);
+      } else {
+        v.x = k < a.d ? v.x : 0.f;
+        v.y = k + 1 < a.d ? v.y : 0.f;
+        v.z = k + 2 < a.d ? v.z : 0.f;
+        v.w = k + 3 < a.d ? v.w : 0.f;
+      }
+      sq[i] = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, sq[i]))));
+      uint32_t w01[3], w23[3];
+      split3(v.x, v.y, w01);
+      split3(v.z, v.w, w23);
+      const int row = s_row + 32 * i;
+      const int at = row * 64 + (((s_col >> 3) ^ (row >> 1)) & 3) * 16 + (s_col & 4) * 2;
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<uint2 *>(stage_s[b] + p * kPlane + at) = make_uint2(w01[p], w23[p]);
+    }
+    if (c + 1 == n_chunks) {   // the rows are complete: their norms
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float t = sq[i];
+        t += __int_as_float(dpp_i32<kDppQuadXor1>(__float_as_int(t)));
+        t += __int_as_float(dpp_i32<kDppQuadXor2>(__float_as_int(t)));
+        t += __int_as_float(dpp_i32<kDppRowHalfMirror>(__float_as_int(t)));
+        sq[i] = 0.f;
+        if (tid % 8 == 0) {
+          const uint64_t r = tile * kSB + s_row + 32 * i;
+          // (an infinity in an inner product must not become a NaN: the fp32 kernel takes over)
+          if (a.metric != ANN_L2 && !(t < INFINITY)) atomicOr(a.flag, 1u);
+          xn_s[tile & 1][s_row + 32 * i] = r < a.rows ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
+        }
+      }
+    }
+  };
+
+  // ---- this lane's queries
+  float top[NQ];
+  uint64_t bound[NQ];
+#pragma unroll
+  for (int f = 0; f < NQ; ++f) {
+    const uint32_t q = (qt * QT32 + wq * NQ + f) * 32 + l32;
+    bound[f] = a.scores == nullptr && q < a.nq ? a.bound[q] : 0ull;
+    top[f] = a.scores == nullptr && q < a.nq ? unorder_f32((uint32_t)(bound[f] >> 32)) : -INFINITY;
+  }
+  uint64_t *hits = hit_s[wave];
+  uint8_t *hits_q = hit_q_s[wave];
+  int n_hits = 0;   // the same in all lanes
+  auto fence = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto flush = [&]() {
+    fence();
+    for (int e = lane; e < n_hits; e += kWave) {
+      const uint32_t q = qt * QT32 * 32 + hits_q[e];
+      const uint32_t pos = atomicAdd(&a.count[q], 1u);
+      if (pos < a.cap) a.buf[(uint64_t)q * a.cap + pos] = hits[e];
+    }
+    fence();
+    n_hits = 0;
+  };
+
+  floatx16 acc[MB][NQ];
+  auto clear = [&]() {
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int f = 0; f < NQ; ++f)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[m][f][i] = 0.f;
+  };
+  const float scale = a.metric == ANN_L2 ? -2.0f : -1.0f;
+  // acc[m][f][i]: base row (wb MB + m) 32 + 8 (i / 4) + 4 half + i % 4 of the tile against query l32 of block f
+  auto finish_tile = [&](uint64_t tile) {
+    const float *xn = xn_s[tile & 1];
+    float low[NQ];
+#pragma unroll
+    for (int f = 0; f < NQ; ++f) low[f] = INFINITY;
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int r0 = (wb * MB + m) * 32 + 8 * g + 4 * half;
+        const float4 x4 = *reinterpret_cast<const float4 *>(xn + r0);
+        const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+        for (int f = 0; f < NQ; ++f)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            // (a NaN becomes +inf: never selected)
+            acc[m][f][4 * g + e] = fminf(fmaf(scale, acc[m][f][4 * g + e], xv[e]), INFINITY);
+            low[f] = fminf(low[f], acc[m][f][4 * g + e]);
+          }
+      }
+    if (a.scores) {
+#pragma unroll
+      for (int f = 0; f < NQ; ++f) {
+        const uint32_t q = (qt * QT32 + wq * NQ + f) * 32 + l32;
+        if (q >= a.nq) continue;
+        float *to = a.scores + (uint64_t)q * a.ld + tile * kSB;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4 *>(to + (wb * MB + m) * 32 + 8 * g + 4 * half) =
+                make_float4(acc[m][f][4 * g], acc[m][f][4 * g + 1], acc[m][f][4 * g + 2], acc[m][f][4 * g + 3]);
+      }
+      return;
+    }
+#pragma unroll
+    for (int f = 0; f < NQ; ++f) {
+      if (__ballot(low[f] <= top[f]) == 0) continue;
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float score = acc[m][f][i];
+          if (__ballot(score <= top[f]) == 0) continue;
+          uint64_t id = tile * kSB + (wb * MB + m) * 32 + 8 * (i / 4) + 4 * half + i % 4;
+          if (a.stretch != 0.0) id = sample_row(id, a.stretch);
+          const uint64_t ent = ((uint64_t)order_u32(score) << 32) | (uint32_t)id;
+          const bool hit = score <= top[f] && ent <= bound[f];
+          const uint64_t hm = __ballot(hit);
+          const int n_new = __popcll(hm);
+          if (n_hits + n_new > kHitList) flush();
+          if (hit) {
+            const int pos = n_hits + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
+            hits[pos] = ent;
+            hits_q[pos] = (uint8_t)((wq * NQ + f) * 32 + l32);
+          }
+          n_hits += n_new;
+        }
+    }
+  };
+
+  auto load_q = [&](uint4 (&to)[NQ][3], uint32_t kb) {
+#pragma unroll
+    for (int f = 0; f < NQ; ++f)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) to[f][p] = qf[f][kb * 192 + p * 64];
+  };
+  auto multiply = [&](const uint4 (&q)[NQ][3], int b, int kbi) {
+    bf16x8 xa[MB][3];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      const int row = (wb * MB + m) * 32 + l32;
+      const int at = row * 64 + (((kbi * 2 + half) ^ (row >> 1)) & 3) * 16;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) xa[m][p] = *reinterpret_cast<const bf16x8 *>(stage_s[b] + p * kPlane + at);
+    }
+    // the small products first
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int f = 0; f < NQ; ++f)
+          acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[m][pa[t]], __builtin_bit_cast(bf16x8, q[f][pb[t]]), acc[m][f], 0, 0, 0);
+  };
+
+  uint4 q0[NQ][3], q1[NQ][3];
+  fetch(tile_begin, 0);
+  load_q(q0, 0);
+  stage(0, tile_begin, 0);
+  clear();
+  __syncthreads();
+  int cur = 0;
+  uint32_t c = 0;
+  for (uint64_t tile = tile_begin;;) {
+    const bool last_chunk = c + 1 == n_chunks;
+    const uint64_t next_tile = last_chunk ? tile + 1 : tile;
+    const uint32_t next_c = last_chunk ? 0 : c + 1;
+    const bool more = next_tile < tile_end;
+    fetch(more ? next_tile : tile_begin, next_c);   // (none left: a load that is never staged)
+    load_q(q1, 2 * c + 1);
+    multiply(q0, cur, 0);
+    load_q(q0, 2 * next_c);
+    multiply(q1, cur, 1);
+    if (last_chunk) {
+      finish_tile(tile);
+      clear();
+    }
+    if (!more) break;
+    stage(cur ^ 1, next_tile, next_c);
+    __syncthreads();
+    cur ^= 1;
+    tile = next_tile;
+    c = next_c;
+  }
+  if (n_hits > 0) flush();
+}
+
+// ---------------------------------------------------------------------------
+// Selection by bisection on the order-preserving bits of the scores: a bound
+// that at least `want` and at most `most` of the workgroup's entries reach.
+// Entries lie in registers, EPT per thread; a step counts the entries up to the
+// middle (one compare and one population count per register and wavefront).
+// With more than `most` equal scores at the bound the ids decide (ascending).
+// Entries with an ordered score above kMaxScore (+inf) are none.
+constexpr uint32_t kMaxScore = 0xFF7FFFFFu;   // FLT_MAX in score order
+constexpr int kSelThreads = 256;
+
+template <int EPT>
+struct Selector {
+  uint32_t key[EPT], id[EPT];
+  uint32_t *red;   // LDS [2][4]
+  int parity = 0;
+
+  __device__ __forceinline__ uint32_t total(uint32_t wave_count) {
+    if (threadIdx.x % kWave == 0) red[parity * 4 + threadIdx.x / kWave] = wave_count;
+    __syncthreads();
+    const uint32_t t = red[parity * 4] + red[parity * 4 + 1] + red[parity * 4 + 2] + red[parity * 4 + 3];
+    parity ^= 1;
+    return t;
+  }
+  __device__ __forceinline__ uint32_t count_up_to(uint32_t k) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) c += (uint32_t)__popcll(__ballot(key[e] <= k));
+    return total(c);
+  }
+  // (score << 32 | id) bound; n_kept: entries that reach it
+  __device__ __forceinline__ uint64_t run(uint32_t want, uint32_t most, uint32_t &n_kept) {
+    n_kept = count_up_to(kMaxScore);
+    if (n_kept <= most) return ((uint64_t)kMaxScore << 32) | 0xFFFFFFFFu;
+    // count(lo) < want, count(hi) > most
+    uint32_t lo = 0, hi = kMaxScore;
+    {
+      uint32_t mn = 0xFFFFFFFFu;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) mn = key[e] < mn ? key[e] : mn;
+      uint32_t mx = mn;   // the largest of the threads' minima: as many entries as threads reach it
+#pragma unroll
+      for (int x = 1; x < kWave; x <<= 1) {
+        const uint32_t o = (uint32_t)xor_lane_i32((int)mn, x), p = (uint32_t)xor_lane_i32((int)mx, x);
+        mn = o < mn ? o : mn;
+        mx = p > mx ? p : mx;
+      }
+      if (threadIdx.x % kWave == 0) {
+        red[parity * 4 + threadIdx.x / kWave] = mn;
+        red[8 + threadIdx.x / kWave] = mx;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kSelThreads / kWave; ++w) {
+        mn = red[parity * 4 + w] < mn ? red[parity * 4 + w] : mn;
+        mx = red[8 + w] > mx ? red[8 + w] : mx;
+      }
+      parity ^= 1;
+      if (mn > 0) lo = mn - 1;
+      if (most < (uint32_t)kSelThreads && mx < hi) hi = mx;
+    }
+    while (hi - lo > 1) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      const uint32_t c = count_up_to(mid);
+      if (c >= want && c <= most) {
+        n_kept = c;
+        return ((uint64_t)mid << 32) | 0xFFFFFFFFu;
+      }
+      if (c < want)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    // equal scores: `hi` is the score, too few entries are below it and too many reach it
+    const uint32_t below = count_up_to(lo);
+    uint32_t ilo = 0, ihi = 0xFFFFFFFFu;   // ids up to ilo - 1 are too few, up to ihi too many
+    for (;;) {
+      const uint32_t mid = ilo + (ihi - ilo) / 2;
+      uint32_t c = 0;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) c += (uint32_t)__popcll(__ballot(key[e] == hi && id[e] <= mid));
+      c = below + total(c);
+      if ((c >= want && c <= most) || ilo >= ihi) {
+        n_kept = c;
+        return ((uint64_t)hi << 32) | mid;
+      }
+      if (c < want)
+        ilo = mid + 1;
+      else
+        ihi = mid;
     }
   }
 };
 
-// ---------------------------------------------------------------------------
-// Larger tiles for the common case (d a multiple of 4, moderate k): a
-// workgroup of four wavefronts computes 64 WR queries x 64 WC base rows per
-// tile, every wavefront a 64 x 64 block as 2 x 2 MFMA 32x32 accumulators, so
-// four matrix instructions in a row never wait for each other and one LDS read
-// feeds two of them.  Rows are staged K-contiguous (pitch KC + 4 floats: 16-byte
-// LDS reads and writes without bank conflicts); the two halves of a wavefront
-// take the two halves of a K chunk, which only changes the order in which the
-// products are added.  The next chunk is fetched into registers before the
-// chunk's matrix work and written to the other LDS buffer after it: one barrier
-// per chunk.
-//
-// Top-k: per query a threshold and a buffer of cb (score, id) entries.  A score
-// below the threshold is appended; a row whose buffer is more than half way
-// from kp to cb is cut back to its kp best (threshold = the kp-th), by the
-// wavefront that owns the row.  An append that finds the buffer full stays
-// pending and is tried again after the cut.
-template <int WR, int WC, int KC, int EPL>
-__global__ __launch_bounds__(256) void bf_block_kernel(const float *__restrict__ X, const float *__restrict__ xnorm,
-                                                       uint64_t n, uint32_t d, const float *__restrict__ Q, uint32_t nq,
-                                                       uint32_t metric, uint64_t rows_per_slab, uint32_t kp, uint32_t cb,
-                                                       uint32_t *__restrict__ bound /*[nq]*/,
-                                                       uint32_t *__restrict__ part_best /*[nq][slabs]*/, uint32_t part_rank,
-                                                       uint32_t part_lists,
-                                                       uint32_t *__restrict__ cand_out /*[nq][slabs][kp]*/) {
-  constexpr int QT = 64 * WR, BT = 64 * WC;
-  using Stager = TileStager<QT, BT, KC, 256>;
-  constexpr int ROWS = Stager::ROWS, P = Stager::P, NLD = Stager::NLD;
-  static_assert(WR * WC == 4, "four wavefronts");
-  extern __shared__ float smem_f[];
-  float *stage_buf = smem_f;                                // [2][ROWS][P]
-  float *thr = stage_buf + 2 * ROWS * P;                    // [QT]
-  uint32_t *cnt = reinterpret_cast<uint32_t *>(thr + QT);   // [QT]
-  uint64_t *buf = reinterpret_cast<uint64_t *>(cnt + QT);   // [QT][cb]
-
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int wr = wave / WC, wc = wave % WC, half = lane / 32, l32 = lane % 32;
-  const uint32_t q0 = blockIdx.x * QT;
-  const uint32_t slab = blockIdx.y, n_slabs = gridDim.y;
-  const uint64_t b_begin = (uint64_t)slab * rows_per_slab;
-  const uint64_t b_end = b_begin + rows_per_slab < n ? b_begin + rows_per_slab : n;
-  const uint32_t limit = kp + (cb - kp) / 2;   // a longer buffer is cut back
-
-  for (int r = tid; r < QT; r += 256) {
-    thr[r] = q0 + r < nq ? INFINITY : -INFINITY;   // rows past the batch never take anything
-    cnt[r] = 0;
+// The best of one stretch of a query's scores.  Sample (stretch != 0): the bound
+// is all that is wanted.  Otherwise the entries go to out[q][blockIdx.y][most],
+// padded with all-ones.
+__global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const float *__restrict__ scores, uint32_t ld, uint64_t rows,
+                                                                       double stretch, uint32_t want, uint32_t most,
+                                                                       uint64_t *__restrict__ bound, uint64_t *__restrict__ out) {
+  constexpr int EPT = kSampleRows / kSelThreads;
+  __shared__ uint32_t red[16], wave_at[4];
+  const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const uint64_t r0 = (uint64_t)blockIdx.y * kSampleRows;
+  Selector<EPT> s;
+  s.red = red;
+#pragma unroll
+  for (int i = 0; i < EPT / 4; ++i) {
+    const uint64_t r = r0 + (uint32_t)(i * kSelThreads + tid) * 4;
+    // (ld is a multiple of 4 and at least rows; columns from rows on hold +inf up to the end of the last tile)
+    float4 v = make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+    if (r < rows) v = *reinterpret_cast<const float4 *>(scores + (uint64_t)q * ld + r);
+    const float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s.key[4 * i + e] = r + e < rows ? order_u32(vv[e]) : 0xFFFFFFFFu;
+      s.id[4 * i + e] = (uint32_t)(stretch != 0.0 ? sample_row(r + e, stretch) : r + e);
+    }
   }
-
-  const Stager stager(Q, X, stage_buf, q0, nq, d, b_end, tid);
-  float4 reg[NLD];
-  uint32_t keep = 0;
-  // Cut row `row` back to its kp smallest entries (ids differ, so no ties).
-  auto cut = [&](int row) {
-    const uint32_t c = cnt[row] < cb ? cnt[row] : cb;
-    if (c <= kp) {
-      if (lane == 0) cnt[row] = c;
-      return;
-    }
-    uint64_t *list = buf + (size_t)row * cb;
-    uint64_t mine[EPL];
-    uint32_t rank[EPL];
+  uint32_t n_kept;
+  const uint64_t b = s.run(want, most, n_kept);
+  if (out == nullptr) {
+    if (tid == 0) bound[q] = b;
+    return;
+  }
+  uint64_t *list = out + ((uint64_t)q * gridDim.y + blockIdx.y) * most;
+  uint32_t mine = 0;
 #pragma unroll
-    for (int u = 0; u < EPL; ++u) {
-      const uint32_t i = lane + u * kWave;
-      mine[u] = i < c ? list[i] : ~0ull;
-      rank[u] = 0;
-    }
-    for (uint32_t j = 0; j < c; ++j) {
-      const uint64_t o = list[j];
-#pragma unroll
-      for (int u = 0; u < EPL; ++u) rank[u] += o < mine[u] ? 1u : 0u;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int u = 0; u < EPL; ++u) {
-      const uint32_t i = lane + u * kWave;
-      if (i < c && rank[u] < kp) {
-        list[rank[u]] = mine[u];
-        // this slab's part_rank-th best, for the bound over several slabs (see the tile loop)
-        if (rank[u] == part_rank - 1 && q0 + row < nq) part_best[(uint64_t)(q0 + row) * n_slabs + slab] = (uint32_t)(mine[u] >> 32);
-        if (rank[u] == kp - 1) {
-          thr[row] = unorder_f32((uint32_t)(mine[u] >> 32));
-          // the kp-th best of one slab bounds the kp-th best overall: the slabs of a query share the smallest
-          if (q0 + row < nq) atomicMin(&bound[q0 + row], (uint32_t)(mine[u] >> 32));
-        }
-      }
-    }
-    if (lane == 0) cnt[row] = kp;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
-  // every row over `over` entries is cut by the wavefront that owns it (row % 4 == wave)
-  auto cut_rows_over = [&](uint32_t over) {
-    const int mine_row = wave + 4 * lane;   // lanes 0 .. QT/4-1 each look at one row
-    const bool need = lane < QT / 4 && cnt[mine_row] > over;
-    for (uint64_t m = __ballot(need); m; m &= m - 1) cut(wave + 4 * __builtin_ctzll(m));
-  };
-
-  const uint32_t n_chunks = (d + KC - 1) / KC;
-  const float scale = metric == ANN_L2 ? -2.0f : -1.0f;
-  int cur = 0;
-  if (b_begin < b_end) {
-    stager.fetch(reg, keep, b_begin, 0);
-    stager.stage(reg, keep, 0);
+  for (int e = 0; e < EPT; ++e) {
+    const uint64_t ent = ((uint64_t)s.key[e] << 32) | s.id[e];
+    mine += (uint32_t)__popcll(__ballot(s.key[e] <= kMaxScore && ent <= b));
   }
   __syncthreads();
-
-  uint32_t tile_no = 0;
-  for (uint64_t t0 = b_begin; t0 < b_end; t0 += BT, ++tile_no) {
-    // a tighter bound from several slabs' part_rank-th best scores joins the shared bound
-    if (bound_refresh_due(tile_no) && tid < QT && q0 + tid < nq) {
-      const uint32_t t = bound_over_parts(part_best + (uint64_t)(q0 + tid) * n_slabs, n_slabs, part_lists);
-      if (t < 0xFF800000u) atomicMin(&bound[q0 + tid], t);
-    }
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-    // norm terms of this lane's two columns; +inf keeps columns past the end out
-    float xn[2];
-    uint64_t col_id[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      col_id[b] = t0 + wc * 64 + b * 32 + l32;
-      xn[b] = col_id[b] < b_end ? (metric == ANN_L2 ? xnorm[col_id[b]] : 0.f) : INFINITY;
-    }
-    // what the other slabs of this thread's query have published (used after the matrix work)
-    const uint32_t shared_thr = bound[q0 + tid < nq ? q0 + tid : nq - 1];
-    for (uint32_t c = 0; c < n_chunks; ++c) {
-      const bool last_chunk = c + 1 == n_chunks;
-      const uint64_t nt0 = last_chunk ? t0 + BT : t0;
-      const bool more = nt0 < b_end;
-      stager.fetch(reg, keep, nt0, last_chunk ? 0 : (c + 1) * KC);   // (no tile left: clamped loads that are never staged)
-      const float *ap = stage_buf + ((size_t)cur * ROWS + wr * 64 + l32) * P + half * (KC / 2);
-      const float *bp = stage_buf + ((size_t)cur * ROWS + QT + wc * 64 + l32) * P + half * (KC / 2);
-#pragma unroll
-      for (int j = 0; j < KC / 8; ++j) {
-        const float4 a0 = *reinterpret_cast<const float4 *>(ap + 4 * j);
-        const float4 a1 = *reinterpret_cast<const float4 *>(ap + 32 * P + 4 * j);
-        const float4 b0 = *reinterpret_cast<const float4 *>(bp + 4 * j);
-        const float4 b1 = *reinterpret_cast<const float4 *>(bp + 32 * P + 4 * j);
-        const float av0[4] = {a0.x, a0.y, a0.z, a0.w}, av1[4] = {a1.x, a1.y, a1.z, a1.w};
-        const float bv0[4] = {b0.x, b0.y, b0.z, b0.w}, bv1[4] = {b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av0[e], bv0[e], acc[0][0], 0, 0, 0);
-          acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av0[e], bv1[e], acc[0][1], 0, 0, 0);
-          acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av1[e], bv0[e], acc[1][0], 0, 0, 0);
-          acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av1[e], bv1[e], acc[1][1], 0, 0, 0);
-        }
-      }
-      if (more) stager.stage(reg, keep, cur ^ 1);
-      __syncthreads();
-      cur ^= 1;
-    }
-
-    // acc[a][b][i] is query row wr*64 + a*32 + 8*(i/4) + 4*half + i%4 against
-    // base column col_id[b].  Bit b*16 + i of pend[a]: that score is below its
-    // row's threshold and not yet in the buffer.
-    if (tid < QT && q0 + tid < nq && unorder_f32(shared_thr) < thr[tid]) thr[tid] = unorder_f32(shared_thr);
-    __syncthreads();
-    uint32_t pend[2] = {0u, 0u};
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 t4 = *reinterpret_cast<const float4 *>(thr + wr * 64 + a * 32 + 8 * g + 4 * half);
-        const float tv[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-            pend[a] |= fmaf(scale, acc[a][b][4 * g + e], xn[b]) < tv[e] ? 1u << (b * 16 + 4 * g + e) : 0u;
-      }
-    bool any = (pend[0] | pend[1]) != 0;
-    if (__syncthreads_or(any ? 1 : 0) == 0) continue;   // nothing for any row of the tile
-    for (;;) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const uint32_t bit = 1u << (b * 16 + i);
-            if (pend[a] & bit) {
-              const int row = wr * 64 + a * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-              const float score = fmaf(scale, acc[a][b][i], xn[b]);
-              if (score < thr[row]) {   // the threshold may have dropped since the bit was set
-                const uint32_t pos = atomicAdd(&cnt[row], 1u);
-                if (pos < cb) {
-                  buf[(size_t)row * cb + pos] = ((uint64_t)order_u32(score) << 32) | (uint32_t)col_id[b];
-                  pend[a] &= ~bit;
-                }
-              } else {
-                pend[a] &= ~bit;
-              }
-            }
-          }
-      __syncthreads();
-      cut_rows_over(limit);
-      any = (pend[0] | pend[1]) != 0;
-      if (__syncthreads_or(any ? 1 : 0) == 0) break;
-    }
-  }
+  if (lane == 0) wave_at[wave] = mine;
   __syncthreads();
-  cut_rows_over(kp);
-  __syncthreads();
-  // hand the survivors of this slab to the exact stage
-  for (int e = tid; e < QT * (int)kp; e += 256) {
-    const int row = e / kp, j = e % kp;
-    const uint32_t qi = q0 + row;
-    if (qi < nq)
-      cand_out[((uint64_t)qi * n_slabs + slab) * kp + j] = (uint32_t)j < cnt[row] ? (uint32_t)buf[(size_t)row * cb + j] : ANN_PAD_ID;
+  uint32_t at = 0;
+  for (uint32_t w = 0; w < wave; ++w) at += wave_at[w];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const uint64_t ent = ((uint64_t)s.key[e] << 32) | s.id[e];
+    const bool keep = s.key[e] <= kMaxScore && ent <= b;
+    const uint64_t m = __ballot(keep);
+    if (keep) list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = ent;
+    at += (uint32_t)__popcll(m);
   }
+  for (uint32_t e = n_kept + tid; e < most; e += kSelThreads) list[e] = ~0ull;
 }
 
-
-// ---------------------------------------------------------------------------
-// Small k: a 128 x 128 tile per workgroup of eight wavefronts (two per SIMD, so
-// that one's LDS and barrier waits are covered by the other's matrix work),
-// every wavefront a 32 x 64 block (two MFMA 32x32 accumulators), with the top-k
-// state owned by single wavefronts so that nothing after the matrix work needs
-// a barrier.  Each wavefront keeps, for each of its 32 query rows, its own list
-// of the best candidates among the base columns it has seen (two lists per
-// query and slab, both handed to the exact stage).
-//
-// The accumulators take one more matrix step per tile whose only non-zero
-// products are 1 x (-|x|^2 / 2) (L2; 0 for inner product; -inf for columns past
-// the end), so that score = scale * acc with scale = -2 / -1, and "score below
-// the row's threshold" is one compare, acc > u[row] with u = thr / scale.
-// Hits are rare once the thresholds have settled: every lane collects a bit
-// mask of its hits and the wavefront takes them one per lane and round into
-// their rows' lists (LDS atomic for the slot); a list found full is cut back to
-// its kp best (rank counting over lanes), which lowers the row's threshold, and
-// the hit is tried again.  The lists of one query (its slabs, its two
-// wavefronts) publish their thresholds in global memory and use the smallest.
-//
-// QRES: for rows of up to 128 dimensions the query tile is read into LDS once
-// and stays there (K padded to whole chunks, row pitch + 4); only base rows are
-// staged with every chunk.  LIST: entries per (row, wavefront) list.
-constexpr int kOwnList = 32;     // entries per (row, wavefront) list
-constexpr int kOwnListRes = 24;  // the same when the query tile stays in LDS (d <= 128, k <= 10), which leaves less room
-constexpr int kOwnWaves = 8, kOwnRows = 32;   // wavefronts per workgroup, query rows per wavefront
-
-// number of set bits of mask below this lane's
-__device__ __forceinline__ int bf_lanes_below(uint64_t mask) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+// The best of a query's entries.  count == NULL: all `cap` of them (all-ones:
+// none).  cand == NULL: only the bound is updated (kept if fewer than `want`
+// entries were found) and the count cleared for the next pass; otherwise the
+// ids go to cand[q][most], padded.
+template <int EPT>
+__global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const uint64_t *__restrict__ buf, uint32_t *__restrict__ count,
+                                                                        uint32_t cap, uint32_t want, uint32_t most,
+                                                                        uint64_t *__restrict__ bound, uint32_t *__restrict__ cand,
+                                                                        uint32_t *__restrict__ flag) {
+  __shared__ uint32_t red[16], n_out;
+  const uint32_t q = blockIdx.x, tid = threadIdx.x;
+  const uint32_t found = count ? count[q] : cap;
+  const uint32_t n_ent = found < cap ? found : cap;
+  Selector<EPT> s;
+  s.red = red;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const uint32_t i = (uint32_t)e * kSelThreads + tid;
+    const uint64_t ent = i < n_ent ? buf[(uint64_t)q * cap + i] : ~0ull;
+    s.key[e] = (uint32_t)(ent >> 32);
+    s.id[e] = (uint32_t)ent;
+  }
+  if (tid == 0) n_out = 0;
+  uint32_t n_kept;
+  const uint64_t b = s.run(want, most, n_kept);   // (a barrier or more: everyone has read the count)
+  if (tid == 0 && found > cap) atomicOr(flag, 2u);
+  if (cand == nullptr) {
+    if (tid == 0) {
+      if (n_kept >= want && b < bound[q]) bound[q] = b;
+      count[q] = 0;
+    }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const uint64_t ent = ((uint64_t)s.key[e] << 32) | s.id[e];
+    if (s.key[e] <= kMaxScore && ent <= b) cand[(uint64_t)q * most + atomicAdd(&n_out, 1u)] = s.id[e];
+  }
+  for (uint32_t e = n_kept + tid; e < most; e += kSelThreads) cand[(uint64_t)q * most + e] = ANN_PAD_ID;
 }
 
-template <int KC, bool QRES, int LIST>
-__global__ __launch_bounds__(512) void bf_own_kernel(const float *__restrict__ X, const float *__restrict__ xnorm,
-                                                     uint64_t n, uint32_t d, const float *__restrict__ Q, uint32_t nq,
-                                                     uint32_t metric, uint64_t rows_per_slab, uint32_t kp,
-                                                     uint32_t *__restrict__ bound /*[nq]*/,
-                                                     uint32_t *__restrict__ cand_out /*[nq][slabs][2][kp]*/) {
-  constexpr int WC = 2, QT = 128, BT = 128;
-  constexpr int QS = QRES ? 0 : QT;   // query rows staged with every chunk (none when the query tile stays in LDS)
-  using Stager = TileStager<QS, BT, KC, 64 * kOwnWaves>;
-  constexpr int ROWS = Stager::ROWS, P = Stager::P, NLD = Stager::NLD;
-  constexpr int NR = kOwnWaves * kOwnRows;   // (row, wavefront) lists per workgroup
-  static_assert(kOwnWaves / WC * kOwnRows == QT, "tile shape");
-  extern __shared__ float smem_f[];
-  // QRES: the 128 queries of the tile stay in LDS for the whole kernel, K padded to whole chunks, row pitch + 4
-  const uint32_t q_pitch = (d + KC - 1) / KC * KC + 4;
-  float *q_res = smem_f;                                                      // [QT][q_pitch] (QRES)
-  float *stage_buf = smem_f + (QRES ? QT * q_pitch : 0);                      // [2][ROWS][P]
-  float *u_all = stage_buf + 2 * ROWS * P;                                    // [NR]  acc must exceed this
-  uint32_t *thr_all = reinterpret_cast<uint32_t *>(u_all + NR);               // [NR]  ordered score an entry must be below
-  uint32_t *cnt_all = thr_all + NR;                                           // [NR]
-  uint64_t *list_all = reinterpret_cast<uint64_t *>(cnt_all + NR);            // [NR][LIST]
-
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const int wr = wave / WC, wc = wave % WC, half = lane / 32, l32 = lane % 32;
-  const uint32_t q0 = blockIdx.x * QT;
-  const uint32_t slab = blockIdx.y, n_slabs = gridDim.y;
-  const uint64_t b_begin = (uint64_t)slab * rows_per_slab;
-  const uint64_t b_end = b_begin + rows_per_slab < n ? b_begin + rows_per_slab : n;
-  const float scale = metric == ANN_L2 ? -2.0f : -1.0f;
-  const float inv_scale = metric == ANN_L2 ? -0.5f : -1.0f;
-
-  // this wavefront's state (its rows are queries q0 + wr*32 + 0..31)
-  float *u = u_all + wave * kOwnRows;
-  uint32_t *thr = thr_all + wave * kOwnRows;
-  uint32_t *cnt = cnt_all + wave * kOwnRows;
-  uint64_t *list = list_all + (size_t)wave * kOwnRows * LIST;
-  if (lane < kOwnRows) {
-    const bool live = q0 + wr * kOwnRows + lane < nq;
-    u[lane] = live ? -INFINITY : INFINITY;   // rows past the batch never take anything
-    thr[lane] = order_u32(INFINITY);
-    cnt[lane] = 0;
-  }
-
-  if (QRES) {
-    const uint32_t p4 = (q_pitch - 4) / 4, d4 = d / 4;   // float4 per padded row, per row of Q
-    for (uint32_t e = tid; e < QT * p4; e += 64 * kOwnWaves) {
-      const uint32_t row = e / p4, c4 = e % p4;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (q0 + row < nq && c4 < d4) v = reinterpret_cast<const float4 *>(Q + (uint64_t)(q0 + row) * d)[c4];
-      *reinterpret_cast<float4 *>(q_res + row * q_pitch + 4 * c4) = v;
+// The whole search with fp32 products and a top-k per (query, slab): for batches
+// that the split products cannot serve.
+static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const float *q, uint32_t nq, uint32_t k, uint32_t metric,
+                                  uint32_t *out_ids, float *out_dist, uint32_t n_cu, hipStream_t st) {
+  const uint32_t kp = k + 8;               // candidates kept per (query, slab): k plus a margin for fp32 score error
+  const uint32_t cb = kp + kBT;
+  const bool vec4 = d % 4 == 0 && (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(q)) % 16 == 0;
+  const uint32_t q_tiles = (nq + kQT - 1) / kQT;
+  const uint64_t tiles = (n + kBT - 1) / kBT;
+  // Slabs of base rows: the grid (query tiles x slabs) should fill the chip a
+  // whole number of times (two workgroups per compute unit).  Among 3 to 8
+  // turns take the one whose last turn is fullest.
+  const uint32_t slots = n_cu * 2u;
+  uint32_t slabs = 1;
+  double best_fill = 0.0;
+  for (uint32_t turns = 3; turns <= 8; ++turns) {
+    const uint32_t s_ = slots * turns / q_tiles;
+    if (s_ == 0) continue;
+    const double fill = (double)q_tiles * s_ / ((double)slots * turns);
+    if (fill > best_fill + 0.01) {
+      best_fill = fill;
+      slabs = s_;
     }
   }
-  // two sets of staging registers: a chunk is fetched two steps before it is
-  // multiplied, so that a row that comes from HBM has two steps to arrive
-  const Stager stager(Q, X, stage_buf, q0, nq, d, b_end, tid);
-  float4 reg_a[NLD], reg_b[NLD];
-  uint32_t keep_a = 0, keep_b = 0;   // bit i: reg[i] lies inside the arrays
-  auto wave_sync = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
+  if (slabs > tiles) slabs = (uint32_t)tiles;
+  if (slabs * kp > 4096) slabs = 4096 / kp;
+  if (slabs < 1) slabs = 1;
+  const uint64_t rows_per_slab = ((tiles + slabs - 1) / slabs) * kBT;
+  slabs = (uint32_t)((n + rows_per_slab - 1) / rows_per_slab);
 
-  // Cut list `row` (c entries, c <= LIST) back to its kp smallest; returns the new length.
-  auto cut = [&](int row, uint32_t c) -> uint32_t {
-    uint64_t *l = list + (size_t)row * LIST;
-    const uint64_t mine = (uint32_t)lane < c ? l[lane < LIST ? lane : 0] : ~0ull;
-    const uint32_t mhi = (uint32_t)(mine >> 32), mlo = (uint32_t)mine;
-    uint32_t rank = 0;
-#pragma unroll
-    for (int j = 0; j < LIST; ++j) {
-      const uint64_t o = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mhi, j) << 32) |
-                         (uint32_t)__builtin_amdgcn_readlane((int)mlo, j);
-      rank += o < mine ? 1u : 0u;   // ids differ, so no two entries are equal
-    }
-    wave_sync();
-    if ((uint32_t)lane < c && rank < kp) {
-      l[rank] = mine;
-      if (rank == kp - 1) {
-        thr[row] = mhi;
-        u[row] = unorder_f32(mhi) * inv_scale;
-        atomicMin(&bound[q0 + wr * kOwnRows + row], mhi);   // (a list is only ever filled for a query of the batch)
-      }
-    }
-    wave_sync();
-    return c < kp ? c : kp;
-  };
+  const size_t smem = (size_t)2 * (kQT + kBT) * kLd * sizeof(float) + kQT * (sizeof(float) + sizeof(uint32_t)) +
+                      (size_t)kQT * cb * sizeof(uint64_t);
+  const void *fn = vec4 ? reinterpret_cast<const void *>(bf_tile_kernel<true>) : reinterpret_cast<const void *>(bf_tile_kernel<false>);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
+  const size_t n_cand_words = (size_t)nq * slabs * kp, n_norms = metric == ANN_L2 ? (size_t)n : 0;
+  uint32_t *cand = nullptr;
+  ANN_HIP(hipMalloc((void **)&cand, (n_cand_words + n_norms) * sizeof(uint32_t)));
+  float *xnorm = reinterpret_cast<float *>(cand + n_cand_words);
+  if (metric == ANN_L2) row_norm_kernel<<<2048, 256, 0, st>>>(x, n, d, xnorm);
+  const dim3 grid(q_tiles, slabs);
+  if (vec4)
+    bf_tile_kernel<true><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, cand);
+  else
+    bf_tile_kernel<false><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, cand);
+  e = hipGetLastError();
+  ann_status rc = e == hipSuccess ? rerank_device(x, n, d, metric, q, nq, cand, slabs * kp, slabs * kp, k, out_ids, out_dist, st)
+                                  : hip_fail(e, "brute-force tile kernel launch");
+  const hipError_t e2 = hipStreamSynchronize(st);
+  (void)hipFree(cand);
+  if (rc != ANN_OK) return rc;
+  if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
+  return ANN_OK;
+}
 
-  const uint32_t n_chunks = (d + KC - 1) / KC;
-  int cur = 0;
-  // the next (tile, chunk) to fetch; at the top of a step it is two steps ahead
-  // and the other register set holds the step in between
-  uint64_t f_t0 = b_begin;
-  uint32_t f_c = 0;
-  auto advance = [&]() {
-    if (++f_c == n_chunks) {
-      f_c = 0;
-      f_t0 += BT;
-    }
-  };
-  if (b_begin < b_end) {
-    stager.fetch(reg_a, keep_a, f_t0, 0);
-    advance();
-    stager.stage(reg_a, keep_a, 0);
-    stager.fetch(reg_a, keep_a, f_t0, f_c * KC);   // (past the end: clamped loads that are never staged)
-    advance();
-  }
-  __syncthreads();
-
-  // the tile being multiplied, its chunk, its accumulators
-  uint64_t t0 = b_begin;
-  uint32_t c = 0;
-  floatx16 acc[2];
-  float xn[2];         // norm terms of this lane's two columns (loaded at the start of a tile, used at its end)
-  uint32_t col_id[2];  // their ids
-  uint32_t shared_thr;  // lanes 0..31: the bound other lists have published for this lane's row (same timing)
-  const uint32_t my_q = q0 + wr * kOwnRows + (lane < kOwnRows ? lane : 0);
-  auto begin_tile = [&]() {
-    shared_thr = bound[my_q < nq ? my_q : nq - 1];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-      const uint64_t ci = t0 + wc * 64 + b * 32 + l32;
-      col_id[b] = (uint32_t)ci;
-      xn[b] = xnorm[ci < b_end ? ci : b_end - 1];   // (any readable array of n floats when the metric has no norm term)
-    }
-  };
-
-  auto finish_tile = [&]() {
-    {
-      // the extra matrix step: (1, 0) x (ext, 0) over its two K slots
-      const float one = half ? 0.f : 1.f;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        float ext = col_id[b] < b_end ? (metric == ANN_L2 ? -0.5f * xn[b] : 0.f) : -INFINITY;
-        if (half) ext = 0.f;
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(one, ext, acc[b], 0, 0, 0);
-      }
-    }
-    // The kp-th best score of any list of a query bounds the query's kp-th best
-    // overall, so the lists of a query (other slabs, the other wavefront) share
-    // the smallest threshold any of them has reached.
-    if (lane < kOwnRows && my_q < nq && shared_thr < thr[lane]) {
-      thr[lane] = shared_thr;
-      u[lane] = unorder_f32(shared_thr) * inv_scale;
-    }
-    wave_sync();
-    // acc[b][i]: row 8*(i/4) + 4*half + i%4 of this wavefront against column col_id[b].
-    // Bit 2*i + b of hits: that score is below its row's threshold.
-    uint32_t hits = 0;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 u4 = *reinterpret_cast<const float4 *>(u + 8 * g + 4 * half);
-      const float uv[4] = {u4.x, u4.y, u4.z, u4.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) hits |= acc[b][4 * g + e] > uv[e] ? 1u << (2 * (4 * g + e) + b) : 0u;
-    }
-    // One hit per lane and round: into the row's list (LDS atomic for the
-    // slot); a list found full is cut back to its kp best, which lowers the
-    // row's threshold, and the hit is tried again.
-    while (__ballot(hits != 0)) {
-      const bool active = hits != 0;
-      const int bit = active ? __builtin_ctz(hits) : 0;
-      hits &= hits - 1;
-      float v = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) v = bit == 2 * i + b ? acc[b][i] : v;
-      const int i_el = bit >> 1;
-      const int erow = 8 * (i_el >> 2) + 4 * half + (i_el & 3);
-      const uint64_t ent = ((uint64_t)order_u32(scale * v) << 32) | (col_id[0] + ((uint32_t)(bit & 1) << 5));   // column b is col_id[0] + 32 b (a select between the two array elements became an indexed read from scratch memory)
-      bool pending = active && (uint32_t)(ent >> 32) < thr[erow];
-      while (__ballot(pending)) {
-        if (pending) {
-          const uint32_t pos = atomicAdd(&cnt[erow], 1u);
-          if (pos < (uint32_t)LIST) {
-            list[(size_t)erow * LIST + pos] = ent;
-            pending = false;
-          }
-        }
-        wave_sync();
-        uint64_t todo = __ballot(pending);
-        if (todo == 0) break;
-        while (todo) {
-          const int row = __builtin_amdgcn_readlane(erow, __builtin_ctzll(todo));
-          todo &= ~__ballot(pending && erow == row);
-          const uint32_t left = cut(row, LIST);   // the count ran past the list's end: the list is full
-          if (lane == 0) cnt[row] = left;
-        }
-        wave_sync();
-        pending = pending && (uint32_t)(ent >> 32) < thr[erow];
-      }
-    }
-  };
-
-  // One chunk: fetch the chunk two steps ahead into r_fetch, multiply the
-  // staged one, stage the next from r_stage.  Returns whether a step follows.
-  auto one_step = [&](const float4 (&r_stage)[NLD], uint32_t k_stage, float4 (&r_fetch)[NLD], uint32_t &k_fetch) -> bool {
-    const bool last_chunk = c + 1 == n_chunks;
-    const bool more = !last_chunk || t0 + BT < b_end;
-    stager.fetch(r_fetch, k_fetch, f_t0, f_c * KC);   // (past the end: clamped loads that are never staged)
-    advance();
-    const float *ap = QRES ? q_res + (size_t)(wr * kOwnRows + l32) * q_pitch + c * KC + half * (KC / 2)
-                           : stage_buf + ((size_t)cur * ROWS + wr * kOwnRows + l32) * P + half * (KC / 2);
-    const float *bp = stage_buf + ((size_t)cur * ROWS + QS + wc * 64 + l32) * P + half * (KC / 2);
-#pragma unroll
-    for (int j = 0; j < KC / 8; ++j) {
-      const float4 a0 = *reinterpret_cast<const float4 *>(ap + 4 * j);
-      const float4 b0 = *reinterpret_cast<const float4 *>(bp + 4 * j);
-      const float4 b1 = *reinterpret_cast<const float4 *>(bp + 32 * P + 4 * j);
-      const float av0[4] = {a0.x, a0.y, a0.z, a0.w};
-      const float bv0[4] = {b0.x, b0.y, b0.z, b0.w}, bv1[4] = {b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av0[e], bv0[e], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av0[e], bv1[e], acc[1], 0, 0, 0);
-      }
-    }
-    if (more) stager.stage(r_stage, k_stage, cur ^ 1);
-    __syncthreads();
-    cur ^= 1;
-    if (last_chunk) {
-      finish_tile();
-      t0 += BT;
-      c = 0;
-      if (more) begin_tile();
-    } else {
-      ++c;
-    }
-    return more;
-  };
-  if (b_begin < b_end) {
-    begin_tile();
-    for (;;) {
-      if (!one_step(reg_a, keep_a, reg_b, keep_b)) break;
-      if (!one_step(reg_b, keep_b, reg_a, keep_a)) break;
+// One pass of the score kernel over a.rows rows: tile shape by the number of
+// queries, slabs so that the last turn of workgroups (two per compute unit) is
+// nearly full.
+static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream_t st) {
+  const uint32_t qt = a.nq > 64 ? 128u : (a.nq > 32 ? 64u : 32u);
+  a.q_tiles = (a.nq + qt - 1) / qt;
+  const uint64_t tiles = (a.rows + kSB - 1) / kSB;
+  const uint64_t slots = 2ull * n_cu;
+  // a workgroup's time in tiles, with half a tile for its start
+  double best = 0.0;
+  uint64_t slabs = 1, tps = tiles;
+  const uint64_t most = 8 * slots / a.q_tiles + 8;
+  for (uint64_t s = 1; s <= most && s <= tiles; s = s < 8 ? s + 1 : s + 8) {
+    const uint64_t t = (tiles + s - 1) / s, used = (tiles + t - 1) / t;
+    const double cost = (double)((used * a.q_tiles + slots - 1) / slots) * ((double)t + 0.5);
+    if (s == 1 || cost < best * 0.99) {
+      best = cost;
+      slabs = used;
+      tps = t;
     }
   }
-  // every list down to kp, then to the exact stage
-  wave_sync();
-  for (int row = 0; row < kOwnRows; ++row) {
-    uint32_t c = cnt[row] < (uint32_t)LIST ? cnt[row] : (uint32_t)LIST;
-    if (c > kp) c = cut(row, c);
-    const uint32_t qi = q0 + wr * kOwnRows + row;
-    if (qi < nq && (uint32_t)lane < kp) {
-      // an entry above what the query's lists have agreed on by now is not among its kp best
-      const uint64_t ent = list[(size_t)row * LIST + lane];
-      const bool keep = (uint32_t)lane < c && (uint32_t)(ent >> 32) <= bound[qi];
-      cand_out[(((uint64_t)qi * n_slabs + slab) * WC + wc) * kp + lane] = keep ? (uint32_t)ent : ANN_PAD_ID;
-    }
-  }
+  a.slabs = (uint32_t)slabs;
+  a.tiles_per_slab = (uint32_t)tps;
+  const uint32_t grid = a.q_tiles * (((uint32_t)slabs + 7) / 8 * 8);
+#define ANN_BS(V)                                                     \
+  do {                                                                \
+    if (qt == 128)                                                    \
+      bf_score_kernel<V, 2, 2><<<grid, 256, 0, st>>>(a);              \
+    else if (qt == 64)                                                \
+      bf_score_kernel<V, 1, 2><<<grid, 256, 0, st>>>(a);              \
+    else                                                              \
+      bf_score_kernel<V, 1, 1><<<grid, 256, 0, st>>>(a);              \
+  } while (0)
+  if (vec4)
+    ANN_BS(true);
+  else
+    ANN_BS(false);
+#undef ANN_BS
+  ANN_HIP(hipGetLastError());
+  return ANN_OK;
 }
 
 }  // namespace ann
@@ -830,139 +878,124 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   if (metric != ANN_L2 && metric != ANN_IP) return fail(ANN_EINVAL, "ann_bruteforce_topk: unknown metric %u", metric);
   if (k > 256) return fail(ANN_ECAPACITY, "ann_bruteforce_topk: k = %u exceeds 256", k);
   if (d > 2048) return fail(ANN_ECAPACITY, "ann_bruteforce_topk: d = %u exceeds 2048", d);
-
-  const uint32_t kp = k + 8;               // candidates kept per (query, slab): k plus a margin for fp32 score error
-  // Tile shape: 128 queries x 128 base rows, with lists owned by single
-  // wavefronts for k up to 16 and a shared 64-entry buffer per query for k up
-  // to 24; 64 x 256 with a longer buffer for larger k; and the 32 x 128 kernel with scalar staging for what is left (d not a multiple of
-  // 4, k above 152).
-  int shape = 0;
-  uint32_t cb = kp + kBT, q_rows = kQT, b_rows = kBT;
-  // rows can be read 16 bytes at a time
-  const bool vec4 = d % 4 == 0 && (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(q)) % 16 == 0;
-  uint32_t lists = 1;   // candidate lists per (query, slab)
-  if (vec4 && kp + 8 <= (uint32_t)kOwnList) {
-    shape = 3;
-    cb = kOwnList;
-    q_rows = 128;
-    b_rows = 128;
-    lists = 2;
-  } else if (vec4 && kp + 32 <= 64) {
-    shape = 1;
-    cb = 64;
-    q_rows = 128;
-    b_rows = 128;
-  } else if (vec4 && kp + 32 <= 192) {
-    shape = 2;
-    cb = kp + 48 <= 192 ? kp + 48 : 192;
-    q_rows = 64;
-    b_rows = 256;
-  }
-  if (shape == 0 && cb > 8 * kWave) return fail(ANN_ECAPACITY, "ann_bruteforce_topk: internal buffer too small for k = %u", k);
-  const uint32_t q_tiles = (nq + q_rows - 1) / q_rows;
-  const uint64_t tiles = (n + b_rows - 1) / b_rows;
-  // Slabs of base rows: the grid (query tiles x slabs) should fill the chip a
-  // whole number of times - workgroups take equal time, so three left over for
-  // a fifth turn cost as much as a full one.  Among 3 to 8 turns take the one
-  // whose last turn is fullest (one workgroup per compute unit with the large
-  // tiles' LDS, two with the small tile).
   int n_cu = 256;
   {
     int dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (n_cu <= 0) n_cu = 256;
   }
-  const uint32_t slots = (uint32_t)n_cu * (shape == 0 ? 2u : 1u);
-  uint32_t slabs = 1;
-  double best_fill = 0.0;
-  for (uint32_t turns = 3; turns <= 8; ++turns) {
-    const uint32_t s_ = slots * turns / q_tiles;
-    if (s_ == 0) continue;
-    const double fill = (double)q_tiles * s_ / ((double)slots * turns);
-    if (fill > best_fill + 0.01) {
-      best_fill = fill;
-      slabs = s_;
-    }
-  }
-  if (slabs > tiles) slabs = (uint32_t)tiles;
-  if (slabs * lists * kp > 4096) slabs = 4096 / (lists * kp);
-  if (slabs < 1) slabs = 1;
-  uint64_t rows_per_slab = ((tiles + slabs - 1) / slabs) * b_rows;
-  slabs = (uint32_t)((n + rows_per_slab - 1) / rows_per_slab);
+  // k and a margin for the error of the scores; the selection stops as soon as it has between `want` and `most`
+  const uint32_t want = k + 8, most = want + (want / 2 > 14 ? want / 2 : 14);
+  const bool vec4 = d % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+  const uint32_t kb_n = (d + kSK - 1) / kSK * 2;
 
-  float *xnorm = nullptr;
-  uint32_t *cand = nullptr;
-  size_t smem;
-  const void *fn;
-  // (short rows and small k: the query tile stays in LDS and only base rows are staged)
-  const bool q_res = shape == 3 && d <= 128 && kp + 6 <= (uint32_t)kOwnListRes;
-  if (q_res) {
-    smem = (size_t)128 * ((d + 31) / 32 * 32 + 4) * sizeof(float) + (size_t)2 * 128 * (32 + 4) * sizeof(float) + 3 * 256 * 4 +
-           (size_t)256 * kOwnListRes * sizeof(uint64_t);
-    fn = reinterpret_cast<const void *>(bf_own_kernel<32, true, kOwnListRes>);
-  } else if (shape == 3) {
-    smem = (size_t)2 * 256 * (32 + 4) * sizeof(float) + 3 * 256 * 4 + (size_t)256 * kOwnList * sizeof(uint64_t);
-    fn = reinterpret_cast<const void *>(bf_own_kernel<32, false, kOwnList>);
-  } else if (shape == 1) {
-    smem = (size_t)2 * 256 * (32 + 4) * sizeof(float) + 128 * 8 + (size_t)128 * cb * sizeof(uint64_t);
-    fn = reinterpret_cast<const void *>(bf_block_kernel<2, 2, 32, 1>);
-  } else if (shape == 2) {
-    smem = (size_t)2 * 320 * (16 + 4) * sizeof(float) + 64 * 8 + (size_t)64 * cb * sizeof(uint64_t);
-    fn = reinterpret_cast<const void *>(bf_block_kernel<1, 4, 16, 3>);
+  // All scores written out: up to four stretches, or up to 2^24 scores (64 MB) whose
+  // stretches' best fit one selection workgroup (8,192 entries).  Beyond, bounds
+  // from samples: each pass writes at most kSampleGrowth .. 32 times the entries
+  // of its bound (five standard deviations of the sample's order statistic are
+  // added for the room).
+  const uint64_t stretches = (n + kSampleRows - 1) / kSampleRows;
+  const bool dense = stretches <= 4 || ((uint64_t)nq * n <= (1ull << 24) && stretches * most <= 8192);
+  const double spread = (double)most + 5.0 * sqrt((double)most);
+  double growth = 1.0;
+  uint32_t samples = 0, cap;   // samples: passes before the last one
+  if (dense) {
+    cap = (uint32_t)(stretches * most);
   } else {
-    smem = (size_t)2 * (kQT + kBT) * kLd * sizeof(float) + kQT * (sizeof(float) + sizeof(uint32_t)) +
-           (size_t)kQT * cb * sizeof(uint64_t);
-    fn = vec4 ? reinterpret_cast<const void *>(bf_tile_kernel<true>) : reinterpret_cast<const void *>(bf_tile_kernel<false>);
+    double limit = 8192.0 / spread;
+    if (limit > 32.0) limit = 32.0;
+    const double ratio = (double)n / kSampleRows;
+    samples = (uint32_t)ceil(log(ratio) / log(limit));
+    if (samples < 1) samples = 1;
+    growth = pow(ratio, 1.0 / samples);
+    cap = 2048;
+    while ((double)cap < growth * spread && cap < 8192) cap <<= 1;
   }
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
-  // candidates, then one shared bound per query (the large-tile kernels)
-  const size_t n_cand_words = (size_t)nq * slabs * lists * kp;
-  // (then, for the 4-wavefront kernels, every slab's part_rank-th best per query: see bound_over_parts; in the
-  // 8-wavefront kernel the loads of that bound cost more than the few hits it would save)
-  const uint32_t part_lists = slabs < 8 ? slabs : 8;
-  const uint32_t part_rank = (kp + part_lists - 1) / part_lists;
-  const size_t n_part_words = shape == 1 || shape == 2 ? (size_t)nq * slabs : 0;
-  ANN_HIP(hipMalloc((void **)&cand, (n_cand_words + nq + n_part_words) * sizeof(uint32_t)));
-  uint32_t *bound = cand + n_cand_words;
-  uint32_t *part_best = bound + nq;
-  if (shape != 0) {
-    const size_t n_fill = nq + n_part_words;
-    fill_u32_kernel<<<(uint32_t)((n_fill + 255) / 256), 256, 0, st>>>(bound, (uint32_t)n_fill, 0xFF800000u);   // +inf in score order
-  }
-  if (metric == ANN_L2) {
-    e = hipMalloc((void **)&xnorm, (size_t)n * sizeof(float));
-    if (e != hipSuccess) {
-      (void)hipFree(cand);
-      return hip_fail(e, "hipMalloc");
+  const uint64_t ld = dense ? (n + kSB - 1) / kSB * kSB : kSampleRows;
+  // queries per round: at most half a GiB of scores and entries
+  const uint64_t per_query = ld * 4 + (uint64_t)cap * 8;
+  uint64_t round = (512ull << 20) / per_query / 128 * 128;
+  if (round < 128) round = 128;
+  if (round > nq) round = nq;
+  const uint64_t q32 = (round + 127) / 128 * 4;
+
+  auto up = [](uint64_t v) { return (v + 255) & ~255ull; };
+  const uint64_t b_qfrag = up(q32 * kb_n * 192 * 16), b_scores = up(round * ld * 4), b_buf = up(round * cap * 8), b_bound = up(round * 8),
+                 b_count = up(round * 4), b_cand = up(round * most * 4);
+  unsigned char *base = nullptr;
+  ANN_HIP(hipMalloc((void **)&base, b_qfrag + b_scores + b_buf + b_bound + b_count + b_cand + 256));
+  uint4 *qfrag = reinterpret_cast<uint4 *>(base);
+  float *scores = reinterpret_cast<float *>(base + b_qfrag);
+  uint64_t *buf = reinterpret_cast<uint64_t *>(base + b_qfrag + b_scores);
+  uint64_t *bound = reinterpret_cast<uint64_t *>(base + b_qfrag + b_scores + b_buf);
+  uint32_t *count = reinterpret_cast<uint32_t *>(base + b_qfrag + b_scores + b_buf + b_bound);
+  uint32_t *cand = reinterpret_cast<uint32_t *>(base + b_qfrag + b_scores + b_buf + b_bound + b_count);
+  uint32_t *flag = reinterpret_cast<uint32_t *>(base + b_qfrag + b_scores + b_buf + b_bound + b_count + b_cand);
+
+  auto one_round = [&](uint64_t q0, uint32_t m) -> ann_status {
+    const float *qr = q + q0 * d;
+    const uint32_t blocks32 = (m + 127) / 128 * 4;
+    const uint64_t units = (uint64_t)blocks32 * kb_n * 64;
+    bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, st>>>(qr, m, d, kb_n, blocks32, qfrag, flag);
+    ScoreArgs a{};
+    a.x = x;
+    a.qfrag = qfrag;
+    a.d = d;
+    a.kb_n = kb_n;
+    a.nq = m;
+    a.metric = metric;
+    a.ld = (uint32_t)ld;
+    a.bound = bound;
+    a.buf = buf;
+    a.count = count;
+    a.cap = cap;
+    a.flag = flag;
+    auto select_entries = [&](uint32_t *cnt, uint32_t *to) {
+      if (cap <= 2048)
+        bf_select_entries_kernel<8><<<m, kSelThreads, 0, st>>>(buf, cnt, cap, want, most, bound, to, flag);
+      else if (cap <= 4096)
+        bf_select_entries_kernel<16><<<m, kSelThreads, 0, st>>>(buf, cnt, cap, want, most, bound, to, flag);
+      else
+        bf_select_entries_kernel<32><<<m, kSelThreads, 0, st>>>(buf, cnt, cap, want, most, bound, to, flag);
+    };
+    ann_status rc;
+    if (dense) {
+      a.rows = n;
+      a.scores = scores;
+      rc = launch_scores(a, vec4, (uint32_t)n_cu, st);
+      if (rc != ANN_OK) return rc;
+      bf_select_scores_kernel<<<dim3(m, (uint32_t)stretches), kSelThreads, 0, st>>>(scores, a.ld, n, 0, want, most, bound, buf);
+      select_entries(nullptr, cand);
+    } else {
+      fill_u32_kernel<<<(m + 255) / 256, 256, 0, st>>>(count, m, 0u);
+      double rows = (double)kSampleRows;
+      for (uint32_t t = 0; t <= samples; ++t, rows *= growth) {
+        const bool last = t == samples;
+        a.rows = last ? n : (t == 0 ? (uint64_t)kSampleRows : (uint64_t)rows);
+        a.stretch = last ? 0.0 : (double)n / (double)a.rows;
+        a.scores = t == 0 ? scores : nullptr;
+        rc = launch_scores(a, vec4, (uint32_t)n_cu, st);
+        if (rc != ANN_OK) return rc;
+        if (t == 0)
+          bf_select_scores_kernel<<<dim3(m, 1), kSelThreads, 0, st>>>(scores, a.ld, a.rows, a.stretch, want, most, bound, nullptr);
+        else
+          select_entries(count, last ? cand : nullptr);
+      }
     }
-    row_norm_kernel<<<2048, 256, 0, st>>>(x, n, d, xnorm);
-  }
-  const dim3 grid(q_tiles, slabs);
-  if (q_res)
-    bf_own_kernel<32, true, kOwnListRes><<<grid, 64 * kOwnWaves, smem, st>>>(x, metric == ANN_L2 ? xnorm : x, n, d, q, nq, metric,
-                                                                             rows_per_slab, kp, bound, cand);
-  else if (shape == 3)
-    bf_own_kernel<32, false, kOwnList><<<grid, 64 * kOwnWaves, smem, st>>>(x, metric == ANN_L2 ? xnorm : x, n, d, q, nq, metric,
-                                                                            rows_per_slab, kp, bound, cand);
-  else if (shape == 1)
-    bf_block_kernel<2, 2, 32, 1><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, bound, part_best,
-                                                          part_rank, part_lists, cand);
-  else if (shape == 2)
-    bf_block_kernel<1, 4, 16, 3><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, bound, part_best,
-                                                          part_rank, part_lists, cand);
-  else if (vec4)
-    bf_tile_kernel<true><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, cand);
-  else
-    bf_tile_kernel<false><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, cand);
-  e = hipGetLastError();
-  ann_status rc = e == hipSuccess ? rerank_device(x, n, d, metric, q, nq, cand, slabs * lists * kp, slabs * lists * kp, k, out_ids,
-                                                  out_dist, st)
-                                  : hip_fail(e, "brute-force tile kernel launch");
-  hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(cand);
-  (void)hipFree(xnorm);
+    ANN_HIP(hipGetLastError());
+    return rerank_device(x, n, d, metric, qr, m, cand, most, most, k, out_ids + q0 * k, out_dist + q0 * k, st);
+  };
+
+  fill_u32_kernel<<<1, 64, 0, st>>>(flag, 1, 0u);
+  ann_status rc = ANN_OK;
+  for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += round) rc = one_round(q0, (uint32_t)(nq - q0 < round ? nq - q0 : round));
+  uint32_t raised = 0;
+  hipError_t e = rc == ANN_OK ? hipMemcpyAsync(&raised, flag, sizeof(raised), hipMemcpyDeviceToHost, st) : hipSuccess;
+  const hipError_t e2 = hipStreamSynchronize(st);
+  (void)hipFree(base);
   if (rc != ANN_OK) return rc;
+  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
+  if (raised) return bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
   return ANN_OK;
 }

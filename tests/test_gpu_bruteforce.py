@@ -1,0 +1,88 @@
+"""Exhaustive search at the edges of its tiles, stretches and samples, against
+the oracle (ids equal except between distances that differ by rounding)."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import gpu_harness
+    return gpu_harness
+
+
+def _points(n, d, seed):
+    rng = np.random.default_rng(seed)
+    return rng.standard_normal((n, d), dtype=np.float32)
+
+
+def _check(H, X, Q, k, metric):
+    gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
+    kk = min(k, X.shape[0])
+    oid, odist = oracle.bruteforce_topk(X, Q, kk, metric=metric)
+    H.check_rerank(gid[:, :kk], gdist[:, :kk], oid, odist.astype(np.float32), rel=1e-6)
+    assert (gid[:, kk:] == 0xFFFFFFFF).all()
+
+
+# tiles of 32, 64 and 128 queries; one stretch of scores, several, samples (one and two), scalar and padded columns
+@pytest.mark.parametrize("n,d,nq,k,metric", [
+    (1, 1, 1, 1, oracle.L2), (127, 3, 33, 256, oracle.L2), (4096, 31, 64, 10, oracle.IP), (4097, 32, 65, 17, oracle.L2),
+    (9000, 33, 129, 100, oracle.L2), (16384, 4, 5, 256, oracle.IP), (16385, 8, 1100, 5, oracle.L2), (40000, 12, 500, 16, oracle.L2),
+    (150001, 5, 130, 50, oracle.IP), (300000, 20, 60, 10, oracle.L2), (70000, 6, 260, 256, oracle.L2)])
+def test_sizes(H, n, d, nq, k, metric):
+    _check(H, _points(n, d, n + d), _points(nq, d, k), k, metric)
+
+
+@pytest.mark.parametrize("order", ["near_last", "near_first", "by_cluster"])
+def test_ordered_rows(H, order):
+    """Rows sorted by distance from the queries, or cluster by cluster: what a sample must not depend on."""
+    n, d, nq = 120_000, 8, 200
+    X, Q = _points(n, d, 1), _points(nq, d, 2) * 0.1
+    if order == "by_cluster":
+        X = (X * 0.05 + np.repeat(_points(100, d, 3), n // 100, axis=0)).astype(np.float32)
+        Q = (Q + X[:: n // nq]).astype(np.float32)
+    else:
+        at = np.argsort((X ** 2).sum(1))
+        X = np.ascontiguousarray(X[at if order == "near_first" else at[::-1]])
+    _check(H, X, Q, 10, oracle.L2)
+
+
+def test_equal_rows(H):
+    """More equal distances than any buffer holds: the smallest ids win."""
+    n, nq = 60_000, 400
+    X = np.repeat(_points(3, 16, 5), n // 3, axis=0)
+    X = np.ascontiguousarray(X[np.random.default_rng(6).permutation(n)])
+    Q = _points(nq, 16, 7)
+    gid, gdist = H.gpu_bruteforce(X, Q, 20, oracle.L2)
+    oid, odist = oracle.bruteforce_topk(X, Q, 20, metric=oracle.L2)
+    assert (gid == oid).all()
+    assert np.allclose(gdist, odist, rtol=1e-6)
+
+
+def test_infinite_products(H):
+    """An infinite coordinate in an inner product: infinitely near or far, as fp32 products have it."""
+    X, Q = np.abs(_points(3000, 24, 8)) + 0.1, np.abs(_points(40, 24, 9)) + 0.1
+    X[7, 3], X[11, 5] = np.inf, -np.inf
+    gid, gdist = H.gpu_bruteforce(X, Q, 5, oracle.IP)
+    assert (gid[:, 0] == 7).all() and np.isneginf(gdist[:, 0]).all()
+    keep = np.ones(3000, bool)
+    keep[[7, 11]] = False
+    oid, odist = oracle.bruteforce_topk(X[keep], Q, 4, metric=oracle.IP)
+    H.check_rerank(gid[:, 1:], gdist[:, 1:], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
+
+
+def test_rows_that_are_not_aligned(H):
+    import torch
+    import paper_2503_17911_amd as ann
+    n, d, nq, k = 5000, 64, 70, 10
+    X, Q = _points(n, d, 10), _points(nq, d, 11)
+    buf = torch.empty(n * d + 1, device=H.DEV)
+    buf[1:] = H.dev(X).reshape(-1)
+    ids = torch.empty((nq, k), dtype=torch.int32, device=H.DEV)
+    dist = torch.empty((nq, k), device=H.DEV)
+    ann.ann_bruteforce_topk(buf[1:], n, d, H.dev(Q), nq, k, ann.L2, ids, dist, H.stream_ptr())
+    oid, odist = oracle.bruteforce_topk(X, Q, k, metric=oracle.L2)
+    H.check_rerank(H.as_u32(ids), dist.cpu().numpy(), oid, odist.astype(np.float32), rel=1e-6)
