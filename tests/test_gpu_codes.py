@@ -68,3 +68,15 @@ def test_values_outside_the_range(H, bits):
     ann.ann_sq_encode(H.dev(Y), 300, 72, bits, H.dev(lv.lo), H.dev(lv.delta), codes, norm, H.stream_ptr())
     assert (codes.cpu().numpy() == want.codes).all()
     assert _same(norm.cpu().numpy(), want.norm_term)
+
+
+# columns that do not fill a workgroup's 32, rows that do not fill its 16, equal values, signed zeros
+@pytest.mark.parametrize("n,d,bits,coverage", [(2, 1, 8, 0.99), (255, 31, 8, 0.9), (257, 33, 8, 0.99), (5000, 65, 8, 0.75), (70001, 3, 8, 0.99),
+                                               (4097, 34, 4, 0.999)])
+def test_truncated_edges(H, n, d, bits, coverage):
+    X = _values(n, d, n * 3 + d)
+    X[:, 0] = np.round(X[:, 0])
+    X[::2, d - 1] = -0.0
+    lo_o, delta_o = oracle.sq_train_truncated(X, bits, coverage)
+    lo, delta, _, _ = H.gpu_sq_fit(X, bits, coverage=coverage)
+    assert (lo == lo_o).all() and _same(delta, delta_o)
