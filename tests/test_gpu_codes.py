@@ -80,3 +80,29 @@ def test_truncated_edges(H, n, d, bits, coverage):
     lo_o, delta_o = oracle.sq_train_truncated(X, bits, coverage)
     lo, delta, _, _ = H.gpu_sq_fit(X, bits, coverage=coverage)
     assert (lo == lo_o).all() and _same(delta, delta_o)
+
+
+@pytest.mark.parametrize("degree", [1, 2, 7, 8, 9, 16, 31, 33, 64])
+def test_adjacency_checks(H, degree):
+    """Every pair of slots of a row is compared, every id is checked, and rows in order are taken."""
+    import paper_2503_17911_amd as ann
+    n, d = 300, 8
+    rng = np.random.default_rng(degree)
+    X = _values(n, d, degree)
+    lv = oracle.sq_fit(X, 8)
+    good = np.stack([rng.permutation(n)[:degree] for _ in range(n)]).astype(np.uint32)
+    good[rng.random(good.shape) < 0.2] = 0xFFFFFFFF
+    H.GpuIndex(X, good, 0, [lv], oracle.L2).close()
+    pairs = [(a, b) for a in range(degree) for b in range(a + 1, degree)]
+    for a, b in [pairs[i] for i in rng.permutation(len(pairs))[:20]] + pairs[-1:]:
+        adj = good.copy()
+        adj[n - 1] = 0xFFFFFFFF
+        adj[n - 1, a] = adj[n - 1, b] = 7
+        with pytest.raises(ann.AnnError) as e:
+            H.GpuIndex(X, adj, 0, [lv], oracle.L2)
+        assert e.value.status == ann.EINVAL and "twice" in str(e.value)
+    adj = good.copy()
+    adj[n - 1, degree - 1] = n
+    with pytest.raises(ann.AnnError) as e:
+        H.GpuIndex(X, adj, 0, [lv], oracle.L2)
+    assert e.value.status == ann.EINVAL and ">= n" in str(e.value)
