@@ -84,6 +84,13 @@ ann_status hip_fail(hipError_t e, const char *what);
     if (e_ != hipSuccess) return ::ann::hip_fail(e_, #call); \
   } while (0)
 
+// Device memory for index arrays, workspaces and temporaries (host.hip): hipMalloc
+// and hipFree with freed blocks kept for the next request, up to 2 GiB per process.
+// device_free needs what hipFree enforces: nothing enqueued on the device uses
+// the block any more.  (NULL is a no-op.)
+hipError_t device_alloc(void **ptr, size_t bytes);
+void device_free(void *ptr);
+
 // Kernel-layout length of one byte plane of a folded query for a level: every 16-byte chunk of
 // codes needs 16 (8-bit) or 32 (4-bit) query bytes; zero-padded to the number
 // of chunks the kernels' lanes cover.

@@ -854,7 +854,7 @@ static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const 
   if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
   const size_t n_cand_words = (size_t)nq * slabs * kp, n_norms = metric == ANN_L2 ? (size_t)n : 0;
   uint32_t *cand = nullptr;
-  ANN_HIP(hipMalloc((void **)&cand, (n_cand_words + n_norms) * sizeof(uint32_t)));
+  ANN_HIP(device_alloc((void **)&cand, (n_cand_words + n_norms) * sizeof(uint32_t)));
   float *xnorm = reinterpret_cast<float *>(cand + n_cand_words);
   if (metric == ANN_L2) row_norm_kernel<<<2048, 256, 0, st>>>(x, n, d, xnorm);
   const dim3 grid(q_tiles, slabs);
@@ -866,7 +866,7 @@ static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const 
   ann_status rc = e == hipSuccess ? rerank_device(x, n, d, metric, q, nq, cand, slabs * kp, slabs * kp, k, out_ids, out_dist, st)
                                   : hip_fail(e, "brute-force tile kernel launch");
   const hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(cand);
+  device_free(cand);
   if (rc != ANN_OK) return rc;
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
@@ -979,7 +979,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   const uint64_t b_qfrag = up(q32 * kb_n * 192 * 16), b_scores = up(round * ld * 4), b_buf = up(round * cap * 8), b_bound = up(round * 8),
                  b_count = up(round * 4), b_cand = up(round * most * 4);
   unsigned char *base = nullptr;
-  ANN_HIP(hipMalloc((void **)&base, b_qfrag + b_scores + b_buf + b_bound + b_count + b_cand + 256));
+  ANN_HIP(device_alloc((void **)&base, b_qfrag + b_scores + b_buf + b_bound + b_count + b_cand + 256));
   uint4 *qfrag = reinterpret_cast<uint4 *>(base);
   float *scores = reinterpret_cast<float *>(base + b_qfrag);
   uint64_t *buf = reinterpret_cast<uint64_t *>(base + b_qfrag + b_scores);
@@ -1050,7 +1050,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   uint32_t raised = 0;
   hipError_t e = rc == ANN_OK ? hipMemcpyAsync(&raised, flag, sizeof(raised), hipMemcpyDeviceToHost, st) : hipSuccess;
   const hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(base);
+  device_free(base);
   if (rc != ANN_OK) return rc;
   if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");

@@ -279,17 +279,17 @@ ann_status ann_build_entry_table(ann_index *index, uint32_t n_pivots, void *stre
   if (!index) return fail(ANN_EINVAL, "ann_build_entry_table: index is NULL");
   if (n_pivots == 0 || n_pivots > index->n) return fail(ANN_EINVAL, "ann_build_entry_table: n_pivots must be in [1, n]");
   ANN_HIP(hipDeviceSynchronize());
-  (void)hipFree(index->pivot_codes);
-  (void)hipFree(index->pivot_norm);
-  (void)hipFree(index->pivot_ids);
+  device_free(index->pivot_codes);
+  device_free(index->pivot_norm);
+  device_free(index->pivot_ids);
   index->pivot_codes = nullptr;
   index->pivot_norm = nullptr;
   index->pivot_ids = nullptr;
   index->n_pivots = 0;
   const LevelDev &L = index->level[0];
-  ANN_HIP(hipMalloc((void **)&index->pivot_codes, (size_t)n_pivots * L.row_stride));
-  ANN_HIP(hipMalloc((void **)&index->pivot_ids, (size_t)n_pivots * sizeof(uint32_t)));
-  if (index->key_metric == ANN_L2) ANN_HIP(hipMalloc((void **)&index->pivot_norm, (size_t)n_pivots * sizeof(float)));
+  ANN_HIP(device_alloc((void **)&index->pivot_codes, (size_t)n_pivots * L.row_stride));
+  ANN_HIP(device_alloc((void **)&index->pivot_ids, (size_t)n_pivots * sizeof(uint32_t)));
+  if (index->key_metric == ANN_L2) ANN_HIP(device_alloc((void **)&index->pivot_norm, (size_t)n_pivots * sizeof(float)));
   const uint64_t total = (uint64_t)n_pivots * (L.row_stride / 16);
   const int grid = (int)((total + 255) / 256 > 65535 ? 65535 : (total + 255) / 256);
   gather_pivots_kernel<<<grid, 256, 0, st>>>(L.codes, index->key_metric == ANN_L2 ? L.norm_term : nullptr, index->n, n_pivots,

@@ -25,6 +25,97 @@ ann_status hip_fail(hipError_t e, const char *what) {
   return fail(code, "%s: %s", what, hipGetErrorString(e));
 }
 
+// ---------------------------------------------------------------- device memory
+// The driver clears freed memory before it hands it out again, at about 54 GB/s:
+// a program that uploads and frees indexes (or runs exhaustive searches) one
+// after the other soon waits for that in every hipFree - 20 ms for the 1.1 GB of a
+// 200,000 x 960 index, where the whole build takes 3 - besides about 0.8 ms for
+// unmapping.  So freed blocks are kept, at most kKeepBytes and kKeepBlocks of
+// them in the process: a request takes the smallest kept block on its device that
+// is large enough and not more than a quarter too large; the blocks kept longest
+// are given back when there are more, and all of them when an allocation fails.
+namespace {
+
+struct KeptBlock {
+  void *ptr = nullptr;
+  size_t bytes = 0;
+  int device = 0;
+};
+constexpr int kKeepBlocks = 64;
+constexpr size_t kKeepBytes = (size_t)2 << 30;
+std::mutex g_kept_mutex;
+KeptBlock g_kept[kKeepBlocks];   // oldest first
+int g_n_kept = 0;
+size_t g_kept_bytes = 0;
+
+// Takes block i off the list.
+KeptBlock take_kept(int i) {
+  const KeptBlock b = g_kept[i];
+  for (int j = i; j + 1 < g_n_kept; ++j) g_kept[j] = g_kept[j + 1];
+  --g_n_kept;
+  g_kept_bytes -= b.bytes;
+  return b;
+}
+
+}  // namespace
+
+hipError_t device_alloc(void **ptr, size_t bytes) {
+  *ptr = nullptr;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const size_t unit = bytes >= ((size_t)1 << 20) ? (size_t)2 << 20 : (size_t)4096;
+  const size_t want = (bytes + unit - 1) / unit * unit;
+  {
+    std::lock_guard<std::mutex> lock(g_kept_mutex);
+    int best = -1;
+    for (int i = 0; i < g_n_kept; ++i)
+      if (g_kept[i].device == dev && g_kept[i].bytes >= want && g_kept[i].bytes - want <= want / 4 &&
+          (best < 0 || g_kept[i].bytes < g_kept[best].bytes))
+        best = i;
+    if (best >= 0) {
+      *ptr = take_kept(best).ptr;
+      return hipSuccess;
+    }
+  }
+  e = hipMalloc(ptr, want);
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();
+  for (;;) {
+    KeptBlock b;
+    {
+      std::lock_guard<std::mutex> lock(g_kept_mutex);
+      if (g_n_kept == 0) break;
+      b = take_kept(0);
+    }
+    (void)hipFree(b.ptr);
+  }
+  return hipMalloc(ptr, want);
+}
+
+void device_free(void *ptr) {
+  if (!ptr) return;
+  hipDeviceptr_t base = nullptr;
+  KeptBlock b;
+  hipPointerAttribute_t at{};
+  if (hipMemGetAddressRange(&base, &b.bytes, (hipDeviceptr_t)ptr) != hipSuccess || hipPointerGetAttributes(&at, ptr) != hipSuccess ||
+      b.bytes > kKeepBytes) {
+    (void)hipFree(ptr);
+    return;
+  }
+  b.ptr = ptr;
+  b.device = at.device;
+  KeptBlock back[kKeepBlocks];
+  int n_back = 0;
+  {
+    std::lock_guard<std::mutex> lock(g_kept_mutex);
+    while (g_n_kept == kKeepBlocks || g_kept_bytes + b.bytes > kKeepBytes) back[n_back++] = take_kept(0);
+    g_kept[g_n_kept++] = b;
+    g_kept_bytes += b.bytes;
+  }
+  for (int i = 0; i < n_back; ++i) (void)hipFree(back[i].ptr);
+}
+
 // ---------------------------------------------------------------- pack kernels
 // codes [n][row_bytes] -> [n][row_stride]; 8-bit codes are stored biased by
 // 128 (c ^ 0x80 read as int8 is c - 128) so the signed packed-dot instruction
@@ -140,36 +231,36 @@ template <typename T>
 ann_status dev_copy(T **dst, const T *src, size_t count, bool src_on_host, hipStream_t st) {
   *dst = nullptr;
   if (count == 0) return ANN_OK;
-  ANN_HIP(hipMalloc((void **)dst, count * sizeof(T)));
+  ANN_HIP(device_alloc((void **)dst, count * sizeof(T)));
   ANN_HIP(hipMemcpyAsync(*dst, src, count * sizeof(T), src_on_host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
                          st));
   return ANN_OK;
 }
 
 void free_workspace(Workspace &w) {
-  (void)hipFree(w.tq);
-  (void)hipFree(w.s);
-  (void)hipFree(w.qlo);
-  (void)hipFree(w.sum_t);
+  device_free(w.tq);
+  device_free(w.s);
+  device_free(w.qlo);
+  device_free(w.sum_t);
   w = Workspace{};
 }
 
 void destroy(ann_index *ix) {
   if (!ix) return;
-  (void)hipFree(ix->vectors);
-  (void)hipFree(ix->adjacency);
-  (void)hipFree(ix->labels);
-  (void)hipFree(ix->adjacency_norms);
-  (void)hipFree(ix->pivot_codes);
-  (void)hipFree(ix->prs_codes);
-  (void)hipFree(ix->prs_norm);
-  (void)hipFree(ix->pivot_norm);
-  (void)hipFree(ix->pivot_ids);
+  device_free(ix->vectors);
+  device_free(ix->adjacency);
+  device_free(ix->labels);
+  device_free(ix->adjacency_norms);
+  device_free(ix->pivot_codes);
+  device_free(ix->prs_codes);
+  device_free(ix->prs_norm);
+  device_free(ix->pivot_norm);
+  device_free(ix->pivot_ids);
   for (int l = 0; l < ANN_MAX_LEVELS; ++l) {
-    (void)hipFree(ix->level[l].codes);
-    (void)hipFree(ix->level[l].lo);
-    (void)hipFree(ix->level[l].delta);
-    (void)hipFree(ix->level[l].norm_term);
+    device_free(ix->level[l].codes);
+    device_free(ix->level[l].lo);
+    device_free(ix->level[l].delta);
+    device_free(ix->level[l].norm_term);
   }
   for (StreamWorkspaces &sw : ix->stream_ws)
     for (Workspace &w : sw.ws) free_workspace(w);
@@ -219,10 +310,10 @@ ann_status workspace_for(ann_index *ix, uint32_t level, uint32_t nq, hipStream_t
   uint32_t cap = nq < 1024 ? 1024 : nq;
   w.tq_plane = tq_plane_for(ix->level[level]);
   w.tq_stride = w.tq_plane * (ix->query_bits == 15 ? 2u : 1u);
-  ANN_HIP(hipMalloc((void **)&w.tq, (size_t)cap * w.tq_stride));
-  ANN_HIP(hipMalloc((void **)&w.s, (size_t)cap * sizeof(float)));
-  ANN_HIP(hipMalloc((void **)&w.qlo, (size_t)cap * sizeof(float)));
-  ANN_HIP(hipMalloc((void **)&w.sum_t, (size_t)cap * 2 * sizeof(int32_t)));
+  ANN_HIP(device_alloc((void **)&w.tq, (size_t)cap * w.tq_stride));
+  ANN_HIP(device_alloc((void **)&w.s, (size_t)cap * sizeof(float)));
+  ANN_HIP(device_alloc((void **)&w.qlo, (size_t)cap * sizeof(float)));
+  ANN_HIP(device_alloc((void **)&w.sum_t, (size_t)cap * 2 * sizeof(int32_t)));
   w.nq_cap = cap;
   return ANN_OK;
 }
@@ -282,11 +373,12 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
   uint64_t *raw_offs = nullptr;
   float *raw_labels = nullptr;
   auto cleanup = [&](ann_status r) {
-    (void)hipFree(bad_dev);
-    (void)hipFree(raw_codes);
-    (void)hipFree(raw_cols);
-    (void)hipFree(raw_offs);
-    (void)hipFree(raw_labels);
+    if (r != ANN_OK) (void)hipDeviceSynchronize();  // what has been enqueued may still use the buffers
+    device_free(bad_dev);
+    device_free(raw_codes);
+    device_free(raw_cols);
+    device_free(raw_offs);
+    device_free(raw_labels);
     if (r != ANN_OK) destroy(ix);
     return r;
   };
@@ -301,7 +393,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
     if (e_ != hipSuccess) return cleanup(hip_fail(e_, #call));    \
   } while (0)
 
-  ANN_TRY_HIP(hipMalloc((void **)&bad_dev, sizeof(uint32_t)));
+  ANN_TRY_HIP(device_alloc((void **)&bad_dev, sizeof(uint32_t)));
   ANN_TRY_HIP(hipMemsetAsync(bad_dev, 0, sizeof(uint32_t), st));
 
   if (desc->vectors) ANN_TRY(dev_copy(&ix->vectors, desc->vectors, (size_t)n * desc->d, host, st));
@@ -336,7 +428,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
       ANN_TRY(dev_copy(&raw_codes, S.codes, (size_t)n * L.row_bytes, true, st));
       src = raw_codes;
     }
-    ANN_TRY_HIP(hipMalloc((void **)&L.codes, (size_t)n * L.row_stride));
+    ANN_TRY_HIP(device_alloc((void **)&L.codes, (size_t)n * L.row_stride));
     const uint64_t total = n * (L.row_stride / 16);
     const uint32_t flip = S.bits == 8 ? 0x80u : 0u;
     const uintptr_t together = reinterpret_cast<uintptr_t>(src) | L.row_bytes;
@@ -349,7 +441,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
     ANN_TRY_HIP(hipGetLastError());
     if (host) {
       ANN_TRY_HIP(hipStreamSynchronize(st));
-      (void)hipFree(raw_codes);
+      device_free(raw_codes);
       raw_codes = nullptr;
     }
   }
@@ -366,7 +458,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
       offs = raw_offs;
       cols = raw_cols;
     }
-    ANN_TRY_HIP(hipMalloc((void **)&ix->adjacency, total_adj * sizeof(uint32_t)));
+    ANN_TRY_HIP(device_alloc((void **)&ix->adjacency, total_adj * sizeof(uint32_t)));
     pack_csr_kernel<uint32_t><<<grid_for(total_adj, 256), 256, 0, st>>>(cols, offs, ix->adjacency, n, desc->degree,
                                                                          ANN_PAD_ID, bad_dev);
     ANN_TRY_HIP(hipGetLastError());
@@ -376,7 +468,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
         ANN_TRY(dev_copy(&raw_labels, desc->edge_labels, (size_t)nnz, true, st));
         lab = raw_labels;
       }
-      ANN_TRY_HIP(hipMalloc((void **)&ix->labels, total_adj * sizeof(float)));
+      ANN_TRY_HIP(device_alloc((void **)&ix->labels, total_adj * sizeof(float)));
       pack_csr_kernel<float><<<grid_for(total_adj, 256), 256, 0, st>>>(lab, offs, ix->labels, n, desc->degree, 0.0f,
                                                                         bad_dev);
       ANN_TRY_HIP(hipGetLastError());
@@ -420,19 +512,19 @@ ann_status ann_build_prs_ratio(ann_index *index, float ratio, void *stream) {
   if (index->prs_codes && index->prs_slots == stored) return ANN_OK;
   if (index->prs_codes) {
     ANN_HIP(hipDeviceSynchronize());  // a search may still be reading the old copy
-    (void)hipFree(index->prs_codes);
-    (void)hipFree(index->prs_norm);
+    device_free(index->prs_codes);
+    device_free(index->prs_norm);
     index->prs_codes = nullptr;
     index->prs_norm = nullptr;
     index->prs_slots = 0;
   }
   const LevelDev &L = index->level[0];
   const uint64_t entries = index->n * stored;
-  ANN_HIP(hipMalloc((void **)&index->prs_codes, (size_t)entries * L.row_stride));
+  ANN_HIP(device_alloc((void **)&index->prs_codes, (size_t)entries * L.row_stride));
   if (index->key_metric == ANN_L2) {
-    hipError_t e = hipMalloc((void **)&index->prs_norm, (size_t)entries * sizeof(float));
+    hipError_t e = device_alloc((void **)&index->prs_norm, (size_t)entries * sizeof(float));
     if (e != hipSuccess) {
-      (void)hipFree(index->prs_codes);
+      device_free(index->prs_codes);
       index->prs_codes = nullptr;
       return hip_fail(e, "hipMalloc");
     }
@@ -454,13 +546,13 @@ ann_status ann_build_row_norms(ann_index *index, void *stream) {
   const LevelDev &L = index->level[0];
   if (index->key_metric != ANN_L2 || !L.norm_term)
     return fail(ANN_EINVAL, "ann_build_row_norms: the index's keys use no norm term (inner-product keys)");
-  ANN_HIP(hipMalloc((void **)&index->adjacency_norms, (size_t)index->n * index->degree * 2 * sizeof(uint32_t)));
+  ANN_HIP(device_alloc((void **)&index->adjacency_norms, (size_t)index->n * index->degree * 2 * sizeof(uint32_t)));
   build_row_norms_kernel<<<grid_for(index->n * index->degree, 256), 256, 0, st>>>(index->adjacency, L.norm_term, index->n,
                                                                                   index->degree, index->adjacency_norms);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
-    (void)hipFree(index->adjacency_norms);
+    device_free(index->adjacency_norms);
     index->adjacency_norms = nullptr;
     return hip_fail(e, "build_row_norms_kernel");
   }
@@ -485,7 +577,11 @@ ann_status ann_reserve_workspace(ann_index *index, uint32_t max_nq, void *stream
 
 ann_status ann_free_index(ann_index *index) {
   if (!index) return ANN_OK;
+  int dev = index->device;
+  (void)hipGetDevice(&dev);
+  if (dev != index->device) (void)hipSetDevice(index->device);
   (void)hipDeviceSynchronize();
+  if (dev != index->device) (void)hipSetDevice(dev);
   destroy(index);
   return ANN_OK;
 }

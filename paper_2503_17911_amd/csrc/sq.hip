@@ -505,7 +505,7 @@ ann_status ann_sq_train(const float *x, uint64_t n, uint32_t d, uint32_t bits, f
   if (rows_per_block < (uint64_t)kMinmaxUnroll * side) rows_per_block = (uint64_t)kMinmaxUnroll * side;
   const uint32_t nblocks = (uint32_t)((n + rows_per_block - 1) / rows_per_block);
   float *pmin = nullptr;
-  ANN_HIP(hipMalloc((void **)&pmin, (size_t)nblocks * d * 2 * sizeof(float)));
+  ANN_HIP(device_alloc((void **)&pmin, (size_t)nblocks * d * 2 * sizeof(float)));
   float *pmax = pmin + (size_t)nblocks * d;
   const dim3 grid(nblocks, (pieces + kMinmaxThreads - 1) / kMinmaxThreads);
   if (vec4)
@@ -516,7 +516,7 @@ ann_status ann_sq_train(const float *x, uint64_t n, uint32_t d, uint32_t bits, f
       pmin, pmax, nblocks, d, (float)((1u << bits) - 1u), lo, delta);
   hipError_t e = hipGetLastError();
   hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(pmin);
+  device_free(pmin);
   if (e != hipSuccess) return hip_fail(e, "sq_minmax launch");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
@@ -532,7 +532,7 @@ ann_status ann_sq_train_truncated(const float *x, uint64_t n, uint32_t d, uint32
   const uint64_t k = (uint64_t)floor((1.0 - coverage) * (double)(n - 1));
   uint32_t *hist = nullptr;  // [2][d][256], then prefix[2][d] and rank[2][d]
   const size_t n_hist = (size_t)512 * d;
-  ANN_HIP(hipMalloc((void **)&hist, (n_hist + (size_t)4 * d) * sizeof(uint32_t)));
+  ANN_HIP(device_alloc((void **)&hist, (n_hist + (size_t)4 * d) * sizeof(uint32_t)));
   uint32_t *prefix = hist + n_hist, *rank = prefix + (size_t)2 * d;
   // about a thousand workgroups (two fit a compute unit), of 256 to 4,096 rows
   const uint32_t groups = (d + kSelCols - 1) / kSelCols;
@@ -547,7 +547,7 @@ ann_status ann_sq_train_truncated(const float *x, uint64_t n, uint32_t d, uint32
   truncated_range_kernel<<<(d + 255) / 256, 256, 0, st>>>(prefix, d, (float)((1u << bits) - 1u), lo, delta);
   hipError_t e = hipGetLastError();
   const hipError_t e2 = hipStreamSynchronize(st);
-  (void)hipFree(hist);
+  device_free(hist);
   if (e != hipSuccess) return hip_fail(e, "ann_sq_train_truncated");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
