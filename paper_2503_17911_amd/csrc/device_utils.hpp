@@ -82,6 +82,39 @@ __device__ __forceinline__ bool certain_f32(double sum, double magnitudes, uint3
   return low == high && fabsf(low) < INFINITY && (low != 0.0f || room == 0.0);
 }
 
+// acc + the lanes' terms, added one after the other (the whole wavefront takes
+// part and all lanes get the result; a lane without a term brings 0).  `room`:
+// 64 doubles of LDS that belong to the wavefront.  Through LDS the 64 terms come
+// ahead of the chain of additions; lane by lane (v_readlane) an addition took
+// 90 cycles.
+__device__ __forceinline__ double add_in_order(double acc, double term, double *room) {
+  room[lane_id()] = term;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int h = 0; h < 64; h += 32) {
+    double t[32];
+#pragma unroll
+    for (int l = 0; l < 32; ++l) t[l] = room[h + l];
+#pragma unroll
+    for (int l = 0; l < 32; ++l) acc += t[l];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return acc;
+}
+
+// Inner product of two rows, summed in fp64 in dimension order and rounded
+// once, by a whole wavefront.
+__device__ __forceinline__ float dot_in_order(const float *a, const float *b, uint32_t d, double *room) {
+  double acc = 0.0;
+  for (uint32_t base = 0; base < d; base += 64) {
+    const uint32_t j = base + (uint32_t)lane_id();
+    acc = add_in_order(acc, j < d ? (double)a[j] * (double)b[j] : 0.0, room);
+  }
+  return (float)acc;
+}
+
 // fp32 -> uint32 such that unsigned order equals numeric order (no NaN).
 __device__ __forceinline__ uint32_t order_u32(float f) {
   uint32_t u = __float_as_uint(f);

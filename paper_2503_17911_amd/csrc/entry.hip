@@ -126,11 +126,10 @@ __global__ __launch_bounds__(kFsThreads) void fold_scan_kernel(
     int32_t *__restrict__ sum_t_ws, const uint8_t *__restrict__ pcodes, const float *__restrict__ pnorm,
     const uint32_t *__restrict__ pids, uint32_t n_pivots, uint32_t row_stride, uint32_t metric,
     uint32_t *__restrict__ out) {
-  extern __shared__ double smem_d[];
-  const uint32_t pp = d + 1;                       // row pitch of prod (doubles): the serial sums of 32 lanes hit 32 banks
+  extern __shared__ uint64_t smem_u[];
+  __shared__ double order_room[kFsThreads / kWave][kWave];
   const uint32_t tp = row_stride + 8;              // row pitch of tql (bytes)
-  double *prod = smem_d;                                             // [32][pp]
-  uint64_t *red = reinterpret_cast<uint64_t *>(prod + kFsQueries * pp);  // [4][32]
+  uint64_t *red = smem_u;                                            // [4][32]
   float *s_l = reinterpret_cast<float *>(red + 4 * kFsQueries);      // [32]
   float *qlo_l = s_l + kFsQueries;                                   // [32]
   int *bias_l = reinterpret_cast<int *>(qlo_l + kFsQueries);         // [32]
@@ -154,20 +153,35 @@ __global__ __launch_bounds__(kFsThreads) void fold_scan_kernel(
       r = __fdiv_rn(127.0f, amax);
     }
     int sum = 0;
+    double dot = 0.0, mag = 0.0;   // sum of q_j lo_j (every product is exact in fp64) and of its terms' magnitudes
     for (uint32_t j = part; j < row_stride; j += 8) {
       int ti = 0;
       if (j < d) {
         const float a = __fmul_rn(delta[j], qrow[j]);
         ti = __float2int_rn(__fmul_rn(a, r));  // round half to even
         ti = ti > 127 ? 127 : (ti < -127 ? -127 : ti);
-        prod[qr * pp + j] = (double)qrow[j] * (double)lo[j];
+        const double p = (double)qrow[j] * (double)lo[j];
+        dot += p;
+        mag += fabs(p);
       }
       tql[qr * tp + j] = (uint8_t)(int8_t)ti;
       sum += ti;
     }
 #pragma unroll
     for (int m = 1; m < 8; m <<= 1) sum += xor_lane_i32(sum, m);
+    dot = group_sum_f64<8>(dot);
+    mag = group_sum_f64<8>(mag);
+    float qlo;
+    // (queries whose sum might round differently in dimension order: by the whole wavefront, which holds eight queries)
+    for (uint64_t todo = __ballot(!certain_f32(dot, mag, d, qlo) && part == 0); todo; todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo);
+      const uint32_t other = q0 + wave * (kWave / 8) + l / 8;
+      const float in_order = dot_in_order(q + (uint64_t)(other < nq ? other : nq - 1) * d, lo, d, order_room[wave]);
+      qlo = lane == l ? in_order : qlo;
+    }
     if (part == 0) {
+      qlo_l[qr] = qlo;
+      if (q0 + qr < nq) qlo_ws[q0 + qr] = qlo;
       s_l[qr] = s;
       bias_l[qr] = 128 * sum;
       if (q0 + qr < nq) {
@@ -177,14 +191,6 @@ __global__ __launch_bounds__(kFsThreads) void fold_scan_kernel(
     }
   }
   __syncthreads();
-  if (tid < kFsQueries) {
-    // every product of two floats is exact in fp64; added in dimension order, which fixes the rounding
-    double acc = 0.0;
-    for (uint32_t j = 0; j < d; ++j) acc += prod[tid * pp + j];
-    const float qlo = (float)acc;
-    qlo_l[tid] = qlo;
-    if (q0 + tid < nq) qlo_ws[q0 + tid] = qlo;
-  }
   // the folded queries in the layout the search kernels load (8-bit: dimension order, zero-padded)
   for (uint32_t e = tid; e < kFsQueries * (tq_stride / 8); e += kFsThreads) {
     const uint32_t qr = e / (tq_stride / 8), c8 = e % (tq_stride / 8);
@@ -314,13 +320,7 @@ ann_status ann_entry_scan(ann_index *index, const float *q, uint32_t nq, uint32_
     ann_status rc = workspace_for(index, 0, nq, st, lease);
     if (rc != ANN_OK) return rc;
     Workspace *fw = lease.ws;
-    const size_t smem = (size_t)kFsQueries * (index->d + 1) * sizeof(double) + 4 * kFsQueries * sizeof(uint64_t) +
-                        3 * kFsQueries * 4 + (size_t)kFsQueries * (L.row_stride + 8);
-    if (smem > 48 * 1024) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fold_scan_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
-    }
+    const size_t smem = 4 * kFsQueries * sizeof(uint64_t) + 3 * kFsQueries * 4 + (size_t)kFsQueries * (L.row_stride + 8);
     fold_scan_kernel<<<(nq + kFsQueries - 1) / kFsQueries, kFsThreads, smem, st>>>(
         q, nq, index->d, L.lo, L.delta, fw->tq, fw->tq_stride, fw->s, fw->qlo, fw->sum_t, index->pivot_codes,
         index->pivot_norm, index->pivot_ids, index->n_pivots, L.row_stride, index->key_metric, out_entry_ids);

@@ -239,7 +239,7 @@ __global__ void truncated_range_kernel(const uint32_t *__restrict__ prefix, uint
 // the same float) and again by one lane in dimension order where the two may
 // differ: about one row in 2^28 / d.
 // 1M x 128, 8 bits: 782 us (one row per wavefront, the sum by one lane) -> 123 us (5.3 TB/s read and written);
-// 200,000 x 960, 4 bits: 1,179 us -> 271 us (3.2 TB/s; two to four pieces per row, the last not full).
+// 200,000 x 960, 4 bits: 1,179 us -> 189 us (4.6 TB/s).
 constexpr int kEncRows = 8;
 
 // Code of value v in a column with the given range and reciprocal step, and the value it decodes to.
@@ -254,15 +254,16 @@ __device__ __forceinline__ uint32_t sq_code(float v, float lo, float delta, doub
   return c;
 }
 
-// Squared norm of a decoded row in dimension order (rarely needed, see above).
+// Squared norm of a decoded row in dimension order, by a whole wavefront (rarely needed, see above).
 template <int BITS>
-__device__ __forceinline__ float sq_norm_in_order(const float *xr, uint32_t d, const float *lo, const float *delta, const double *inv) {
+__device__ __forceinline__ float sq_norm_in_order(const float *xr, uint32_t d, const float *lo, const float *delta, const double *inv,
+                                                  double *room) {
   double acc = 0.0;
-#pragma nounroll
-  for (uint32_t j = 0; j < d; ++j) {
-    float v;
-    (void)sq_code<BITS>(xr[j], lo[j], delta[j], inv[j], v);
-    acc += (double)v * (double)v;
+  for (uint32_t base = 0; base < d; base += kWave) {
+    const uint32_t j = base + (uint32_t)lane_id();
+    float v = 0.0f;
+    if (j < d) (void)sq_code<BITS>(xr[j], lo[j], delta[j], inv[j], v);
+    acc = add_in_order(acc, j < d ? (double)v * (double)v : 0.0, room);
   }
   return (float)acc;
 }
@@ -273,6 +274,7 @@ __global__ __launch_bounds__(256) void sq_encode_kernel(const float *__restrict_
                                                         const float *__restrict__ lo, const float *__restrict__ delta,
                                                         uint8_t *__restrict__ codes, float *__restrict__ norm_term) {
   extern __shared__ double inv_s[];                        // [d]
+  __shared__ double order_room[4][kWave];
   float *lo_s = reinterpret_cast<float *>(inv_s + d);      // [d]
   float *delta_s = lo_s + d;                               // [d]
   for (uint32_t j = threadIdx.x; j < d; j += blockDim.x) {
@@ -369,19 +371,29 @@ __global__ __launch_bounds__(256) void sq_encode_kernel(const float *__restrict_
       for (int m = 8; m < LPR; m <<= 1) part += xor_lane_f64(part, m);
     }
     const uint64_t i = base + (uint32_t)((sub & 7) * RPG + grp);
-    if (sub < 8 && i < n) {
-      float norm;
-      if (!certain_f32(part, part, d, norm)) norm = sq_norm_in_order<BITS>(x + i * d, d, lo_s, delta_s, inv_s);
-      norm_term[i] = norm;
+    const bool mine = sub < 8 && i < n;
+    float norm;
+    const bool sure = certain_f32(part, part, d, norm);
+    if (mine && sure) norm_term[i] = norm;
+    for (uint64_t todo = __ballot(mine && !sure); todo; todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo);
+      const uint64_t row = base + (uint32_t)(((l % LPR) & 7) * RPG + l / LPR);
+      const float in_order = sq_norm_in_order<BITS>(x + row * d, d, lo_s, delta_s, inv_s, order_room[wave]);
+      if (lane == 0) norm_term[row] = in_order;
     }
   }
 }
 
 // ------------------------------------------------------------- query folding
 // One wavefront per query.  a_j = delta_j q_j; s = max|a|/127; t_j =
-// rint(a_j * (127/max|a|)) in [-127,127]; qlo = sum_j q_j lo_j in fp64 in
-// dimension order.  Writes the folded query in the layout the
+// rint(a_j * (127/max|a|)) in [-127,127]; qlo = sum_j q_j lo_j, the fp64 sum in
+// dimension order rounded once to fp32.  Writes the folded query in the layout the
 // search kernels load (see chunk_dot) and optionally as plain [nq][d] int8.
+// Bound: latency.  The three arrays are read once, four loads each in flight, the
+// products kept in LDS and the bytes written four at a time; the sum is formed by
+// all lanes (certain_f32 tells whether dimension order could round to another
+// float; then it is formed that way).  1,000 x 960: 28 us (a load, a byte and one
+// lane's addition after the other) -> 13.
 template <int BITS>
 __global__ __launch_bounds__(64) void query_prep_kernel(const float *__restrict__ q, uint32_t nq, uint32_t d,
                                                         const float *__restrict__ lo, const float *__restrict__ delta,
@@ -398,60 +410,85 @@ __global__ __launch_bounds__(64) void query_prep_kernel(const float *__restrict_
   if (qi >= nq) return;
   const int lane = threadIdx.x;
   const float *qr = q + (uint64_t)qi * d;
+  extern __shared__ float a_s[];   // [d] the products delta_j q_j
+  __shared__ double order_room[kWave];
   float amax = 0.0f;
-  for (uint32_t j = lane; j < d; j += kWave) amax = fmaxf(amax, fabsf(__fmul_rn(delta[j], qr[j])));
+  double part = 0.0, mag = 0.0;    // sum of q_j lo_j (every product is exact in fp64) and of its terms' magnitudes
+  constexpr int kBatch = 4;        // loads in flight per lane and array
+  for (uint32_t base = 0; base < d; base += kBatch * kWave) {
+    float qv[kBatch], dv[kBatch], lv[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const uint32_t j = base + u * kWave + lane, jc = j < d ? j : d - 1;
+      qv[u] = qr[jc];
+      dv[u] = delta[jc];
+      lv[u] = lo[jc];
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const uint32_t j = base + u * kWave + lane;
+      if (j >= d) continue;
+      const float a = __fmul_rn(dv[u], qv[u]);
+      a_s[j] = a;
+      amax = fmaxf(amax, fabsf(a));
+      const double p = (double)qv[u] * (double)lv[u];
+      part += p;
+      mag += fabs(p);
+    }
+  }
   amax = wave_max_f32(amax);
   float s = 1.0f, r = 0.0f;
   if (amax > 0.0f) {
     s = __fdiv_rn(amax, top);
     r = __fdiv_rn(top, amax);
   }
-  uint8_t *tq_row = tq + (uint64_t)qi * tq_stride;
+  __syncthreads();
+  uint32_t *tq_row = reinterpret_cast<uint32_t *>(tq + (uint64_t)qi * tq_stride);
   int sum = 0, sum_lo = 0;
   const int limit = q15 ? 16256 : 127;
-  for (uint32_t j = lane; j < tq_plane; j += kWave) {
-    // byte j of the kernel layout holds dimension dim(j)
-    uint32_t dim;
-    if constexpr (BITS == 8) {
-      dim = j;
-    } else {
-      uint32_t chunk = j / 32, within = j % 32, word = (within % 16) / 4, byte = within % 4, odd = within / 16;
-      dim = chunk * 32 + word * 8 + byte * 2 + odd;
-    }
-    int ti = 0;
-    if (dim < d) {
-      float a = __fmul_rn(delta[dim], qr[dim]);
-      ti = __float2int_rn(__fmul_rn(a, r));  // round half to even
-      ti = ti > limit ? limit : (ti < -limit ? -limit : ti);
-      if (t_plain) {
-        if (q15)
-          reinterpret_cast<int16_t *>(t_plain)[(uint64_t)qi * d + dim] = (int16_t)ti;
-        else
-          t_plain[(uint64_t)qi * d + dim] = (int8_t)ti;
+  // four bytes of the kernel layout per lane and step
+  for (uint32_t w = lane; w < tq_plane / 4; w += kWave) {
+    uint32_t word = 0, word_lo = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // byte 4 w + e holds dimension dim
+      uint32_t dim;
+      if constexpr (BITS == 8)
+        dim = 4 * w + e;
+      else
+        dim = w / 8 * 32 + w % 4 * 8 + e * 2 + w % 8 / 4;
+      int ti = 0;
+      if (dim < d) {
+        ti = __float2int_rn(__fmul_rn(a_s[dim], r));  // round half to even
+        ti = ti > limit ? limit : (ti < -limit ? -limit : ti);
+        if (t_plain) {
+          if (q15)
+            reinterpret_cast<int16_t *>(t_plain)[(uint64_t)qi * d + dim] = (int16_t)ti;
+          else
+            t_plain[(uint64_t)qi * d + dim] = (int8_t)ti;
+        }
+      }
+      if (q15) {
+        const int low = ((ti + 64) & 127) - 64, high = (ti - low) >> 7;
+        word |= (uint32_t)(uint8_t)(int8_t)high << (8 * e);
+        word_lo |= (uint32_t)(uint8_t)(int8_t)low << (8 * e);
+        sum += high;
+        sum_lo += low;
+      } else {
+        word |= (uint32_t)(uint8_t)(int8_t)ti << (8 * e);
+        sum += ti;
       }
     }
-    if (q15) {
-      const int low = ((ti + 64) & 127) - 64, high = (ti - low) >> 7;
-      tq_row[j] = (uint8_t)(int8_t)high;
-      tq_row[tq_plane + j] = (uint8_t)(int8_t)low;
-      sum += high;
-      sum_lo += low;
-    } else {
-      tq_row[j] = (uint8_t)(int8_t)ti;
-      sum += ti;
-    }
+    tq_row[w] = word;
+    if (q15) tq_row[tq_plane / 4 + w] = word_lo;
   }
   sum = group_sum_i32<64>(sum);
   sum_lo = group_sum_i32<64>(sum_lo);
-  // every product of two floats is exact in fp64; they are formed by all lanes
-  // and then added by one lane in dimension order, which fixes the rounding
-  extern __shared__ double prod[];
-  for (uint32_t j = lane; j < d; j += kWave) prod[j] = (double)qr[j] * (double)lo[j];
-  __syncthreads();
+  part = group_sum_f64<64>(part);
+  mag = group_sum_f64<64>(mag);
+  float qlo;
+  if (!certain_f32(part, mag, d, qlo)) qlo = dot_in_order(qr, lo, d, order_room);   // (the same in all lanes)
   if (lane == 0) {
-    double acc = 0.0;
-    for (uint32_t j = 0; j < d; ++j) acc += prod[j];
-    float qlo = (float)acc;
     s_ws[qi] = s;
     qlo_ws[qi] = qlo;
     sum_t_ws[qi] = sum;
@@ -464,7 +501,7 @@ __global__ __launch_bounds__(64) void query_prep_kernel(const float *__restrict_
 ann_status launch_query_prep_into(const ann_index *ix, uint32_t level, const float *q, uint32_t nq, const Workspace &w,
                                   int8_t *t_plain, float *s_out, float *qlo_out, hipStream_t st) {
   const LevelDev &L = ix->level[level];
-  const size_t smem = (size_t)ix->d * sizeof(double);
+  const size_t smem = (size_t)ix->d * sizeof(float);
   if (L.bits == 8)
     query_prep_kernel<8><<<nq, 64, smem, st>>>(q, nq, ix->d, L.lo, L.delta, w.tq, w.tq_stride, w.tq_plane, w.nq_cap, w.s, w.qlo, w.sum_t,
                                                t_plain, s_out, qlo_out);

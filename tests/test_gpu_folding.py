@@ -1,0 +1,38 @@
+"""The folded query's constant term where its terms cancel (the sum's order then
+decides the rounding) and at lengths that do not fill a wavefront."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [2, 63, 64, 66, 130, 256, 960])
+def test_cancelling_terms(d):
+    import gpu_harness as H
+    rng = np.random.default_rng(d)
+    n, nq = 64, 75
+    X = rng.standard_normal((n, d)).astype(np.float32) * 100
+    adj = np.stack([rng.permutation(n)[:8] for _ in range(n)]).astype(np.uint32)
+    lv = oracle.sq_fit(X, 8)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    # project out the codebook's minima: qlo is a small difference of large terms
+    lo = lv.lo.astype(np.float64)
+    Q = (Q - (Q @ lo)[:, None] * lo / (lo @ lo)).astype(np.float32)
+    Q[5] = 0.0
+    ix = H.GpuIndex(X, adj, 0, [lv], oracle.L2)
+    t, s, qlo = ix.query_prep(Q)
+    want = np.zeros(nq, np.float32)
+    for i in range(nq):
+        acc = 0.0
+        for j in range(d):
+            acc += float(Q[i, j]) * float(lv.lo[j])
+        want[i] = np.float32(acc)
+    assert (qlo.view(np.uint32) == want.view(np.uint32)).all()
+    # the kernel that folds and scans pivots together leaves the same folding: the search after it returns the oracle's keys
+    ix.entry_scan(Q, 16, 1)
+    got = ix.search(Q, 20, reuse_folded_queries=True, same_queries_as_last_call=True)
+    oi, ok, od, _ = oracle.search_batch(lv, d, adj, 0, Q, 20)
+    assert (got[0] == oi).all() and (got[1].view(np.uint32) == ok.view(np.uint32)).all()
+    ix.close()
