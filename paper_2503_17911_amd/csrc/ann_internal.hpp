@@ -71,6 +71,7 @@ struct ann_index {
   uint64_t ws_clock = 0;
   std::mutex ws_mutex;  // guards the stream -> workspace table
   int device = 0;
+  int n_cu = 256;  // compute units of the device
 };
 
 namespace ann {

@@ -365,6 +365,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
   ix->n_levels = desc->n_levels;
   ix->entry_point = desc->entry_point;
   (void)hipGetDevice(&ix->device);
+  if (hipDeviceGetAttribute(&ix->n_cu, hipDeviceAttributeMultiprocessorCount, ix->device) != hipSuccess || ix->n_cu <= 0) ix->n_cu = 256;
 
   ann_status rc = ANN_OK;
   uint32_t *bad_dev = nullptr;

@@ -137,6 +137,23 @@ ann_status launch_search_with(const ann_index *index, uint32_t nq, const ann_sea
   // FAST multi-expansion kernels: the staging area (64 m entries, at least 32 per expansion) must hold a step's ids
   const bool ids_fit = index->degree <= 32 || 64 * m >= (int)(64 * p_built);
   const bool fast = packed && !a.filtered && !a.prs_codes && !a.q15 && (!multi || (ids_fit && p == p_built));
+  if (fast && multi) {
+    // Small batches: four or two wavefronts per query as long as all queries are
+    // then resident at once (registers and LDS blocks of 1,280 bytes, 128 to a
+    // compute unit).  Search call alone, one / two / four wavefronts: 200,000 x 960
+    // 4-bit rows, ef = 256: 1,000 queries 567 / 422 / 367 us, 1,500 587 / 496 /
+    // (not resident) 584; 768-dimensional, ef = 512: 1,000 queries 1,200 / 892 /
+    // 758, 1,800 1,361 / (not resident) 1,518; 128-byte rows, ef = 128: 1,000 queries
+    // 405 / 385 / 378, one query 127 / 122 / 119.  Eight are faster still for
+    // 100 queries of the first (225 against 257) and slower from 500 on: not built.
+    for (int team = 4; team >= 2; team /= 2) {
+      const size_t smem = search_smem_bytes(m, (int)p_built, true, vis_log2, index->degree, w.tq_stride, team);
+      const uint32_t by_lds = (uint32_t)(128 / ((smem + 1279) / 1280)), by_waves = 4u * kTeamWaves / (uint32_t)team;
+      if (nq > (uint32_t)index->n_cu * (by_lds < by_waves ? by_lds : by_waves)) continue;
+      return team == 4 ? launch_search_team4(a, L.bits, L.search_lanes, m, wide_step, st)
+                       : launch_search_team2(a, L.bits, L.search_lanes, m, wide_step, st);
+    }
+  }
   if (wide_step)
     return fast ? launch_search_fast_wide(a, L.bits, L.search_lanes, m, st)
                 : launch_search_general_wide(a, L.bits, L.search_lanes, m, st);

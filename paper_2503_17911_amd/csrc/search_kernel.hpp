@@ -45,6 +45,9 @@
 #ifndef ANN_U
 #define ANN_U 2  // groups of code rows requested together in the multi-expansion kernels
 #endif
+#ifndef ANN_U_TEAM
+#define ANN_U_TEAM 2  // the same per wavefront where several share a query (1,000 queries, 480-byte rows: two 367 us, three 372, four 420)
+#endif
 #ifndef ANN_FEW
 #define ANN_FEW 4  // up to this many candidates are merged by merge_few(), more by merge()
 #endif
@@ -57,6 +60,8 @@
 namespace ann {
 
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+// Wavefronts per SIMD the kernels with several wavefronts per query are compiled for (128 registers).
+constexpr int kTeamWaves = 4;
 
 struct SearchArgs {
   const uint8_t *codes;
@@ -138,11 +143,12 @@ __host__ __device__ inline uint32_t cand_entries(uint32_t degree, int pmax) {
   return (degree <= 32 ? 32u : 64u) * (uint32_t)pmax;
 }
 
-// LDS bytes for one query: merge buffer, staging, visited set, candidate ids, folded query.
+// LDS bytes for one query: merge buffer, staging, visited set, candidate ids, folded query; with several
+// wavefronts per query also the step's keys and the number of candidates.
 __host__ __device__ inline size_t search_smem_bytes(int m, int pmax, bool fast, uint32_t vis_log2, uint32_t degree,
-                                                    uint32_t tq_stride) {
+                                                    uint32_t tq_stride, int team = 1) {
   return (size_t)(merge_buf_entries(m) + stage_area_entries(m, pmax, fast)) * 8 + ((size_t)1 << vis_log2) * 4 +
-         (fast ? 0 : (size_t)cand_entries(degree, pmax) * 8) + tq_stride;
+         (fast ? 0 : (size_t)cand_entries(degree, pmax) * 8) + tq_stride + (team > 1 ? (size_t)cand_entries(degree, pmax) * 8 + 16 : 0);
 }
 
 // FAST: the configuration that matters for throughput, with the run-time
@@ -150,7 +156,12 @@ __host__ __device__ inline size_t search_smem_bytes(int m, int pmax, bool fast, 
 // layout, PMAX expansions per step; degree <= 32 when PMAX > 1, degree <= 64
 // with four or more pool registers per lane).  The general
 // kernel (FAST = false) takes every switch from SearchArgs.
-template <int BITS, int LPR, int M, int PMAX, bool FAST>
+//
+// TEAM: wavefronts per query.  The first runs the algorithm; with more than one
+// the others only evaluate their share of a step's candidates (two barriers per
+// step), so that all rows of a step are requested at once instead of in rounds.
+// For batches that leave compute units idle (see ann_search_batch's choice).
+template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1>
 struct SearchWave {
   static constexpr int G = kWave / LPR;      // code rows evaluated side by side
   static constexpr int CPL = 4;              // 16-byte chunks of a row per lane
@@ -159,7 +170,7 @@ struct SearchWave {
   // candidates, so two are requested together (1M x 960 4-bit: 6 % faster;
   // four groups, or four in the multi-expansion kernels, cost more in
   // registers than they gain)
-  static constexpr int U = PMAX > 1 ? ANN_U : (LPR >= 8 ? 2 : 1);
+  static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? ANN_U : (LPR >= 8 ? 2 : 1));
   static constexpr int TQW = TqRegs<BITS>::kWords;
 
   // the i-th unvisited neighbour of the current step: id in the upper word,
@@ -191,6 +202,8 @@ struct SearchWave {
   uint32_t *vis;   // LDS [cap]
   uint64_t *cand;  // LDS: unvisited neighbours of this step
   const int *tql;  // LDS: the folded query, TQW words per 16-byte code chunk
+  uint64_t *res;   // LDS (TEAM > 1): the step's candidates as (key, id) pairs, in list order
+  int *step_n;     // LDS (TEAM > 1): candidates of the step; negative: the search has ended
   int lane, sub, grp;
   uint32_t coff[CPL];  // byte offsets of this lane's chunks inside a code row
   uint32_t vis_mask, vis_shift, vis_limit;
@@ -218,6 +231,8 @@ struct SearchWave {
     vis = reinterpret_cast<uint32_t *>(stage + stage_area_entries(M, PMAX, FAST));
     cand = FAST ? stage : reinterpret_cast<uint64_t *>(vis + cap);
     tql = reinterpret_cast<const int *>(vis + cap + (FAST ? 0 : 2 * cand_entries(a.degree, PMAX)));
+    res = reinterpret_cast<uint64_t *>(const_cast<int *>(tql) + a.tq_stride / 4);
+    step_n = reinterpret_cast<int *>(res + (TEAM > 1 ? cand_entries(a.degree, PMAX) : 0));
     vis_mask = cap - 1;
     vis_shift = 32 - a.vis_log2;
     vis_limit = use_cache() ? 0xFFFFFFFFu : cap - cap / 4;  // the cache is never rebuilt
@@ -675,6 +690,55 @@ struct SearchWave {
     n_q = 0;
   }
 
+  // Requests the code row (and norm term) of candidate ci.  Lanes past the end
+  // of the list take its last node again: no branch is needed around loads.
+  __device__ __forceinline__ void request_row(int ci, int n_cand, uint4 (&row)[CPL], float &nrm, uint32_t &vid) const {
+    const uint64_t ce = cand_at(ci < n_cand ? ci : n_cand - 1);
+    vid = (uint32_t)(ce >> 32);
+    const uint8_t *rp = a.codes + (uint64_t)vid * a.row_stride;
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) row[j] = *reinterpret_cast<const uint4 *>(rp + coff[j]);
+    nrm = a.adj_norms ? __uint_as_float((uint32_t)ce) : (a.norm_term ? a.norm_term[vid] : 0.0f);
+  }
+
+  // TEAM > 1: everything written to LDS before is there for all wavefronts of the query after.
+  __device__ __forceinline__ void team_barrier() const {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  }
+
+  // TEAM > 1: keys of this wavefront's share of the step's candidates (every TEAM-th group of G) to res[].
+  __device__ __forceinline__ void evaluate_share(int n_cand, int wave) {
+    for (int base = wave * G; base < n_cand; base += TEAM * G * U) {
+      uint4 rows[U][CPL];
+      float nrm[U];
+      uint32_t vid[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (base + u * TEAM * G < n_cand) request_row(base + u * TEAM * G + grp, n_cand, rows[u], nrm[u], vid[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (base + u * TEAM * G < n_cand) {
+          const int ci = base + u * TEAM * G + grp;
+          const float key = row_key(rows[u], nrm[u]);
+          if (sub == 0 && ci < n_cand) res[ci] = pack64(order_u32(key), vid[u] << 1);
+        }
+    }
+  }
+
+  // TEAM > 1: what the wavefronts but the first do.
+  __device__ __forceinline__ void help(uint32_t qi, int wave) {
+    load_query_terms(qi);
+    for (;;) {
+      team_barrier();
+      const int n_cand = *step_n;
+      if (n_cand < 0) return;
+      evaluate_share(n_cand, wave);
+      team_barrier();
+    }
+  }
+
   // tau_l for the n_cand nodes in cand[], then merge the ones that can enter
   // the pool.
   __device__ __forceinline__ void evaluate_and_merge(int n_cand) {
@@ -683,24 +747,28 @@ struct SearchWave {
     n_dist += n_cand;
     wave_sync();
     int n_q = 0;
+    if constexpr (TEAM > 1) {
+      if (lane == 0) *step_n = n_cand;
+      team_barrier();
+      evaluate_share(n_cand, 0);
+      team_barrier();
+      for (int base = 0; base < n_cand; base += kWave) {
+        const uint64_t c64 = base + lane < n_cand ? res[base + lane] : ~0ull;
+        const bool q = base + lane < n_cand && c64 < worst;
+        const uint64_t bm = __ballot(q);
+        if (q) stage[n_q + lanes_below(bm)] = c64;
+        n_q += __popcll(bm);
+      }
+      merge_staged(n_q);
+      return;
+    }
     for (int base = 0; base < n_cand; base += G * U) {
       uint4 rows[U][CPL];
       float nrm[U];
       uint32_t vid[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (base + u * G < n_cand) {
-          // lanes past the end of the list recompute its last node; the
-          // duplicate is ignored below, and no branch is needed around loads
-          const int ci = base + u * G + grp;
-          const uint64_t ce = cand_at(ci < n_cand ? ci : n_cand - 1);
-          vid[u] = (uint32_t)(ce >> 32);
-          const uint8_t *rp = a.codes + (uint64_t)vid[u] * a.row_stride;
-#pragma unroll
-          for (int j = 0; j < CPL; ++j) rows[u][j] = *reinterpret_cast<const uint4 *>(rp + coff[j]);
-          nrm[u] = a.adj_norms ? __uint_as_float((uint32_t)ce) : (a.norm_term ? a.norm_term[vid[u]] : 0.0f);
-        }
-      }
+      for (int u = 0; u < U; ++u)
+        if (base + u * G < n_cand) request_row(base + u * G + grp, n_cand, rows[u], nrm[u], vid[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (base + u * G < n_cand) {
@@ -768,6 +836,14 @@ struct SearchWave {
     }
   }
 
+  // What of the folded query a wavefront keeps in registers.
+  __device__ __forceinline__ void load_query_terms(uint32_t qi) {
+    s = a.s[qi];
+    qlo = a.qlo[qi];
+    bias = BITS == 8 ? 128 * a.sum_t[qi] : 0;
+    bias_lo = BITS == 8 && a.sum_t_lo ? 128 * a.sum_t_lo[qi] : 0;
+  }
+
   __device__ __forceinline__ void run(uint32_t qi) {
     // the folded query goes to LDS: it is read again for every group of rows
     // (keeping it in registers costs a wavefront of occupancy)
@@ -781,10 +857,7 @@ struct SearchWave {
       const uint32_t e = a.ef_per_query[qi];
       ef_q = e == 0 ? 1 : (e < a.ef ? (int)e : (int)a.ef);
     }
-    s = a.s[qi];
-    qlo = a.qlo[qi];
-    bias = BITS == 8 ? 128 * a.sum_t[qi] : 0;
-    bias_lo = BITS == 8 && a.sum_t_lo ? 128 * a.sum_t_lo[qi] : 0;
+    load_query_terms(qi);
 #pragma unroll
     for (int r = 0; r < M; ++r) {
       pk[r] = kEmpty;
@@ -960,6 +1033,11 @@ struct SearchWave {
       evaluate_and_merge(n_cand);
     }
 
+    if constexpr (TEAM > 1) {
+      if (lane == 0) *step_n = -1;
+      team_barrier();
+    }
+
     // results (pool index r*64 + lane: coalesced)
     int kept = 0;
 #pragma unroll
@@ -1014,6 +1092,47 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(M <= 2 ? (FA
   w.run(qi);
 }
 
+// The same with TEAM wavefronts per query (multi-expansion FAST kernels).
+template <int BITS, int LPR, int M, int PMAX, int TEAM>
+__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(kTeamWaves))) void search_team_kernel(SearchArgs args) {
+  extern __shared__ uint64_t smem[];
+  if (blockIdx.x >= args.nq) return;
+  const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
+  if (qi >= args.nq) return;
+  SearchWave<BITS, LPR, M, PMAX, true, TEAM> w(args, smem);
+  const int wave = (int)threadIdx.x / kWave;
+  if (wave == 0)
+    w.run(qi);
+  else
+    w.help(qi, wave);
+}
+
+template <int BITS, int LPR, int PMAX, int TEAM>
+static ann_status launch_team_m(const SearchArgs &a, int m, hipStream_t st) {
+  const size_t smem = search_smem_bytes(m, PMAX, true, a.vis_log2, a.degree, a.tq_stride, TEAM);
+  switch (m) {
+    case 1: search_team_kernel<BITS, LPR, 1, PMAX, TEAM><<<a.nq, 64 * TEAM, smem, st>>>(a); break;
+    case 2: search_team_kernel<BITS, LPR, 2, PMAX, TEAM><<<a.nq, 64 * TEAM, smem, st>>>(a); break;
+    case 4: search_team_kernel<BITS, LPR, 4, PMAX, TEAM><<<a.nq, 64 * TEAM, smem, st>>>(a); break;
+    case 8: search_team_kernel<BITS, LPR, 8, PMAX, TEAM><<<a.nq, 64 * TEAM, smem, st>>>(a); break;
+    default: return fail(ANN_EUNSUPPORTED, "no kernel for pool registers per lane = %d", m);
+  }
+  ANN_HIP(hipGetLastError());
+  return ANN_OK;
+}
+
+template <int BITS, int PMAX, int TEAM>
+static ann_status launch_team_lpr(const SearchArgs &a, uint32_t lpr, int m, hipStream_t st) {
+  switch (lpr) {
+    case 1: return launch_team_m<BITS, 1, PMAX, TEAM>(a, m, st);
+    case 2: return launch_team_m<BITS, 2, PMAX, TEAM>(a, m, st);
+    case 4: return launch_team_m<BITS, 4, PMAX, TEAM>(a, m, st);
+    case 8: return launch_team_m<BITS, 8, PMAX, TEAM>(a, m, st);
+    case 16: return launch_team_m<BITS, 16, PMAX, TEAM>(a, m, st);
+    default: return fail(ANN_EUNSUPPORTED, "no kernel for %u lanes per code row", lpr);
+  }
+}
+
 template <int BITS, int LPR, int PMAX, bool FAST>
 static ann_status launch_m(const SearchArgs &args, int m, hipStream_t st) {
   const size_t smem = search_smem_bytes(m, PMAX, FAST, args.vis_log2, args.degree, args.tq_stride);
@@ -1061,9 +1180,19 @@ static ann_status launch_search(const SearchArgs &a, uint32_t bits, uint32_t lpr
   }
 }
 
+template <int TEAM>
+static ann_status launch_team(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st) {
+  if (wide_step)
+    return bits == 8 ? launch_team_lpr<8, kMaxExpansionsPerStep, TEAM>(a, lpr, m, st) : launch_team_lpr<4, kMaxExpansionsPerStep, TEAM>(a, lpr, m, st);
+  return bits == 8 ? launch_team_lpr<8, kDefaultExpansionsPerStep, TEAM>(a, lpr, m, st)
+                   : launch_team_lpr<4, kDefaultExpansionsPerStep, TEAM>(a, lpr, m, st);
+}
+
 ann_status launch_search_fast(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool multi, hipStream_t st);
 ann_status launch_search_general(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool multi, hipStream_t st);
 ann_status launch_search_fast_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
 ann_status launch_search_general_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
+ann_status launch_search_team4(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st);
+ann_status launch_search_team2(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st);
 
 }  // namespace ann

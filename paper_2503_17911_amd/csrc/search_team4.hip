@@ -1,0 +1,8 @@
+// Search kernels with four wavefronts per query (see search_kernel.hpp).
+#include "search_kernel.hpp"
+
+namespace ann {
+ann_status launch_search_team4(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st) {
+  return launch_team<4>(a, bits, lpr, m, wide_step, st);
+}
+}  // namespace ann
