@@ -10,6 +10,7 @@
 namespace ann {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
+constexpr uint32_t kTeamQueries = 2048;   // up to this many queries, four wavefronts share one (256 compute units, eight workgroups each)
 
 __device__ __forceinline__ uint64_t pack_vi(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
 
@@ -52,8 +53,12 @@ __device__ __forceinline__ void rank_all(const uint64_t *list, uint32_t n, int l
 // tau_h on the original vectors.  L2: sum (q - x)^2; IP: -(q . x).  Products
 // and sums in fp64 (each lane sums a strided share, then a butterfly), one
 // rounding to fp32 at the end.
-template <int LPR, bool VEC4>
-__global__ __launch_bounds__(64) void rerank_kernel(const float *__restrict__ X, uint32_t d, uint32_t metric,
+//
+// W: wavefronts per query.  One keeps the chip busy when there are thousands of
+// queries; with fewer, four share a query's rows (rounds dealt out in turn) and
+// its ranking: 1,000 queries x 80 rows x 960, 92 -> 58 us.
+template <int LPR, bool VEC4, int W>
+__global__ __launch_bounds__(64 * W) void rerank_kernel(const float *__restrict__ X, uint32_t d, uint32_t metric,
                                                     const float *__restrict__ Q, uint32_t nq, uint64_t n,
                                                     const uint32_t *__restrict__ cand_ids, uint32_t n_max,
                                                     uint32_t cand_stride, uint32_t k, uint32_t *__restrict__ out_ids,
@@ -67,10 +72,11 @@ __global__ __launch_bounds__(64) void rerank_kernel(const float *__restrict__ X,
   // half of the list's memory: result j is written after id j has been read
   // (results come in order, at most one per id), and result j ends at byte
   // 8 j + 8 <= 4 n_max + 4 i, where id i >= j + 1 begins, as long as j < n_max
-  uint32_t *ids_s = reinterpret_cast<uint32_t *>(list) + n_max;
+  // (several wavefronts: behind the list, since results are then written in any order)
+  uint32_t *ids_s = reinterpret_cast<uint32_t *>(list) + (W > 1 ? 2 * n_max : n_max);
   const uint32_t qi = blockIdx.x;
   if (qi >= nq) return;
-  const int lane = threadIdx.x, chunk = lane % LPR, grp = lane / LPR;
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, chunk = lane % LPR, grp = lane / LPR;
   constexpr int G = kWave / LPR;
   // Length of the prefix that is re-evaluated.  Fixed (n_max), or chosen per
   // query from the low-precision keys: every candidate whose key is not above
@@ -86,21 +92,30 @@ __global__ __launch_bounds__(64) void rerank_kernel(const float *__restrict__ X,
       n_cand = (uint32_t)group_sum_i32<64>((int)cnt);
       n_cand = n_cand < n_min ? n_min : n_cand;
     }
-    if (out_n && lane == 0) out_n[qi] = n_cand;
+    if (out_n && threadIdx.x == 0) out_n[qi] = n_cand;
   }
-  for (uint32_t j = lane; j < d; j += kWave) qs[j] = Q[(uint64_t)qi * d + j];
+  for (uint32_t j = threadIdx.x; j < d; j += kWave * W) qs[j] = Q[(uint64_t)qi * d + j];
   // the ids go to LDS with the query, so that a round of rows costs one
   // memory round trip instead of two (id, then row)
   const uint32_t *cand = cand_ids + (uint64_t)qi * cand_stride;
-  for (uint32_t i = lane; i < n_cand; i += kWave) {
+  for (uint32_t i = threadIdx.x; i < n_cand; i += kWave * W) {
     const uint32_t v = cand[i];
     ids_s[i] = v >= n ? kNone : v;   // (padding is 0xFFFFFFFF >= n)
   }
   __syncthreads();
   uint32_t n_valid = 0;   // candidates that name a node: their entries are kept in order at the front of the list
-  // the row sums of one round (G candidates side by side) go to the list; acc is this lane's share of candidate v
-  auto append = [&](uint32_t v, double acc) {
+  // the row sums of one round (G candidates side by side) go to the list; acc is this lane's share of candidate v,
+  // which is candidate ci (several wavefronts: its place in the list)
+  auto append = [&](uint32_t ci, uint32_t v, double acc) {
     acc = group_sum_f64<LPR>(acc);
+    if constexpr (W > 1) {
+      if (chunk == 0 && ci < n_cand) {
+        float dist = (float)(metric == ANN_L2 ? acc : -acc);
+        if ((__float_as_uint(dist) & 0x7FFFFFFFu) == 0) dist = 0.0f;
+        list[ci] = v != kNone ? pack_vi(order_u32(dist), v) : ~0ull;
+      }
+      return;
+    }
     const bool have = chunk == 0 && v != kNone;
     const uint64_t hm = __ballot(have);
     if (have) {
@@ -121,7 +136,7 @@ __global__ __launch_bounds__(64) void rerank_kernel(const float *__restrict__ X,
       // covers the three rounds; the sums are formed in the order of the loop below.
       constexpr int kRounds = 3;
       const float4 *x4 = reinterpret_cast<const float4 *>(X);
-      for (uint32_t base = 0; base < n_cand; base += kRounds * G) {
+      for (uint32_t base = wave * kRounds * G; base < n_cand; base += W * kRounds * G) {
         uint32_t vv[kRounds];
         float4 xr[kRounds][4];
 #pragma unroll
@@ -163,13 +178,13 @@ __global__ __launch_bounds__(64) void rerank_kernel(const float *__restrict__ X,
               }
             }
           }
-          append(vv[r], acc);
+          append(base + r * G + grp, vv[r], acc);
         }
       }
       done = true;
     }
   }
-  for (uint32_t base = 0; !done && base < n_cand; base += G) {
+  for (uint32_t base = wave * G; !done && base < n_cand; base += W * G) {
     const uint32_t ci = base + grp;
     const uint32_t v = ci < n_cand ? ids_s[ci] : kNone;
     double acc = 0.0;
@@ -204,9 +219,29 @@ __global__ __launch_bounds__(64) void rerank_kernel(const float *__restrict__ X,
         }
       }
     }
-    append(v, acc);
+    append(ci, v, acc);
   }
   __syncthreads();
+  if constexpr (W > 1) {
+    // padding (all-ones) ranks last, in order of position: as many lanes as the query has entries
+    for (uint32_t i = threadIdx.x; i < n_cand; i += kWave * W) {
+      const uint64_t e = list[i];
+      uint32_t rank = 0;
+      for (uint32_t j = 0; j < n_cand; ++j) {
+        const uint64_t o = list[j];
+        rank += o < e || (o == e && j < i) ? 1u : 0u;
+      }
+      if (rank < k) {
+        out_ids[(uint64_t)qi * k + rank] = (uint32_t)e;
+        out_dist[(uint64_t)qi * k + rank] = e == ~0ull ? INFINITY : unorder_f32((uint32_t)(e >> 32));
+      }
+    }
+    for (uint32_t r = n_cand + threadIdx.x; r < k; r += kWave * W) {
+      out_ids[(uint64_t)qi * k + r] = kNone;
+      out_dist[(uint64_t)qi * k + r] = INFINITY;
+    }
+    return;
+  }
   // only the entries that name a node are ranked (padding sorts last anyway)
   rank_all(list, n_valid, lane, [&](uint32_t rank, uint32_t, uint64_t e) {
     if (rank < k) {
@@ -304,12 +339,12 @@ __global__ __launch_bounds__(64) void rescore_kernel(const uint8_t *__restrict__
   });
 }
 
-template <bool VEC4>
+template <bool VEC4, int W>
 static void launch_rerank(uint32_t lpr, const float *X, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
                           uint64_t n, const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k,
                           uint32_t *out_ids, float *out_dist, size_t smem, hipStream_t st, const float *cand_keys,
                           uint32_t n_min, float gamma, uint32_t *out_n) {
-#define ANN_RR(L) rerank_kernel<L, VEC4><<<nq, 64, smem, st>>>(X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, cand_keys, n_min, gamma, out_n)
+#define ANN_RR(L) rerank_kernel<L, VEC4, W><<<nq, 64 * W, smem, st>>>(X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, cand_keys, n_min, gamma, out_n)
   switch (lpr) {
     case 8: ANN_RR(8); break;
     case 16: ANN_RR(16); break;
@@ -327,11 +362,24 @@ ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric
   // four 16-byte pieces of a row per lane: 128 dimensions -> 8 lanes per row, 8 rows side by side
   uint32_t chunks = (d + 3) / 4, lpr = 8;
   while (lpr * 4 < chunks && lpr < 64) lpr <<= 1;
-  const size_t smem = (size_t)n_cand * sizeof(uint64_t) + (size_t)((d + 3) / 4) * 16;
-  if (d % 4 == 0)
-    launch_rerank<true>(lpr, X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, smem, st, cand_keys, n_min, gamma, out_n);
-  else
-    launch_rerank<false>(lpr, X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, smem, st, cand_keys, n_min, gamma, out_n);
+  // Four wavefronts per query where the batch fits the chip that way (eight
+  // workgroups to a compute unit) and a query has more rows than one wavefront
+  // requests together (three rounds).
+  const bool team = nq <= kTeamQueries && n_cand > 3 * (kWave / lpr) && n_cand <= 1024;
+  const size_t smem = (size_t)n_cand * (sizeof(uint64_t) + (team ? sizeof(uint32_t) : 0)) + (size_t)((d + 3) / 4) * 16;
+#define ANN_LR(V, W) launch_rerank<V, W>(lpr, X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, smem, st, cand_keys, n_min, gamma, out_n)
+  if (d % 4 == 0) {
+    if (team)
+      ANN_LR(true, 4);
+    else
+      ANN_LR(true, 1);
+  } else {
+    if (team)
+      ANN_LR(false, 4);
+    else
+      ANN_LR(false, 1);
+  }
+#undef ANN_LR
   ANN_HIP(hipGetLastError());
   return ANN_OK;
 }
