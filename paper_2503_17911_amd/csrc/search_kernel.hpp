@@ -161,7 +161,15 @@ __host__ __device__ inline size_t search_smem_bytes(int m, int pmax, bool fast, 
 // the others only evaluate their share of a step's candidates (two barriers per
 // step), so that all rows of a step are requested at once instead of in rounds.
 // For batches that leave compute units idle (see ann_search_batch's choice).
-template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1>
+//
+// QREG: this lane's part of the folded query stays in registers (16 or 32 of
+// them) instead of being read from LDS for every group of rows: where the kernel's
+// register budget has room without spilling.  4,000 queries x 768 4-bit, ef = 512:
+// 2,594 -> 2,395 us; 1,000 x 960 4-bit, one expansion per step, ef = 64: 450 -> 345.
+// With two pool registers and 8-bit codes a wavefront per SIMD is lost (10,000
+// queries on 1M x 128: 733 -> 864 us), with eight and several wavefronts per query it
+// spills (754 -> 767).
+template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1, bool QREG = false>
 struct SearchWave {
   static constexpr int G = kWave / LPR;      // code rows evaluated side by side
   static constexpr int CPL = 4;              // 16-byte chunks of a row per lane
@@ -202,6 +210,7 @@ struct SearchWave {
   uint32_t *vis;   // LDS [cap]
   uint64_t *cand;  // LDS: unvisited neighbours of this step
   const int *tql;  // LDS: the folded query, TQW words per 16-byte code chunk
+  int qreg[QREG ? CPL : 1][TQW];
   uint64_t *res;   // LDS (TEAM > 1): the step's candidates as (key, id) pairs, in list order
   int *step_n;     // LDS (TEAM > 1): candidates of the step; negative: the search has ended
   int lane, sub, grp;
@@ -244,6 +253,10 @@ struct SearchWave {
     int dot = 0;
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
+      if constexpr (QREG) {
+        dot += chunk_dot<BITS>(row[j], qreg[j]);
+        continue;
+      }
       int t[TQW];
       const int4 *tp = reinterpret_cast<const int4 *>(plane + (sub + j * LPR) * TQW);
 #pragma unroll
@@ -269,8 +282,9 @@ struct SearchWave {
     return key_from_idot15(a.metric, s, qlo, dot, dot_lo, nrm);
   }
 
+  // (the visited set starts on a 16-byte boundary and has 64 slots or more)
   __device__ __forceinline__ void clear_table() {
-    for (uint32_t i = lane; i <= vis_mask; i += kWave) vis[i] = kEmpty;
+    for (uint32_t i = lane; i <= vis_mask / 4; i += kWave) reinterpret_cast<uint4 *>(vis)[i] = make_uint4(kEmpty, kEmpty, kEmpty, kEmpty);
   }
 
   // Two-way cache of node ids with full-width entries: a set is two adjacent
@@ -335,24 +349,26 @@ struct SearchWave {
     }
   }
 
-  // Membership test without insertion.
-  __device__ __forceinline__ bool lookup(uint32_t id) {
-    if (use_cache()) {
-      if (use_packed()) {
-        uint32_t tag;
-        const uint32_t *set = packed_set(id, tag);
-        return packed_hit(*set, tag);
-      }
-      const uint32_t *set = &vis[((id * 0x9E3779B1u) >> vis_shift) & ~1u];
-      return set[0] == id || set[1] == id;
-    }
+  // The table (not the cache): the free slot where id's probing ends, or false
+  // if id is there; and taking that slot, or a later one if another lane was
+  // faster (false if that lane had the same id).
+  __device__ __forceinline__ bool table_find_open(uint32_t id, uint32_t &slot) const {
     const uint32_t h = id * 0x9E3779B1u;
-    uint32_t slot = h >> vis_shift;
     const uint32_t stride = ((h >> 4) | 1u) & vis_mask;
+    slot = h >> vis_shift;
     for (;;) {
       const uint32_t cur = vis[slot];
-      if (cur == id) return true;
-      if (cur == kEmpty) return false;
+      if (cur == kEmpty) return true;
+      if (cur == id) return false;
+      slot = (slot + stride) & vis_mask;
+    }
+  }
+  __device__ __forceinline__ bool table_take(uint32_t id, uint32_t slot) {
+    const uint32_t stride = (((id * 0x9E3779B1u) >> 4) | 1u) & vis_mask;
+    for (;;) {
+      const uint32_t old = atomicCAS(&vis[slot], kEmpty, id);
+      if (old == kEmpty) return true;
+      if (old == id) return false;
       slot = (slot + stride) & vis_mask;
     }
   }
@@ -638,14 +654,16 @@ struct SearchWave {
 
   // The same with the cap of Algorithm 1's inner condition |N| < m_s: only the
   // first m_s unvisited ids (in lane = stored order) are taken and marked;
-  // the others stay unvisited.
+  // the others stay unvisited.  (Only with the table; without a cap below the
+  // degree filter_ids does the same with one probing instead of two.)
   __device__ __forceinline__ void filter_ids_capped(uint32_t nb, uint32_t nrm, uint32_t m_s, int &n_cand) {
     const bool valid = nb != kEmpty && nb < a.n;
-    const bool open = valid && !lookup(nb);
+    uint32_t slot = 0;
+    const bool open = valid && table_find_open(nb, slot);
     const uint64_t om = __ballot(open);
     const bool take = open && (uint32_t)lanes_below(om) < m_s;
     wave_sync();
-    const bool fresh = take && test_and_set(nb);
+    const bool fresh = take && table_take(nb, slot);
     const uint64_t fm = __ballot(fresh);
     if (fresh) cand_at(n_cand + lanes_below(fm)) = pack64(nb, nrm);
     n_cand += __popcll(fm);
@@ -838,6 +856,20 @@ struct SearchWave {
 
   // What of the folded query a wavefront keeps in registers.
   __device__ __forceinline__ void load_query_terms(uint32_t qi) {
+    if constexpr (QREG) {
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        const int4 *src = reinterpret_cast<const int4 *>(a.tq + (uint64_t)qi * a.tq_stride + (uint32_t)(sub + j * LPR) * (TQW * 4u));
+#pragma unroll
+        for (int w = 0; w < TQW / 4; ++w) {
+          const int4 v = src[w];
+          qreg[j][4 * w] = v.x;
+          qreg[j][4 * w + 1] = v.y;
+          qreg[j][4 * w + 2] = v.z;
+          qreg[j][4 * w + 3] = v.w;
+        }
+      }
+    }
     s = a.s[qi];
     qlo = a.qlo[qi];
     bias = BITS == 8 ? 128 * a.sum_t[qi] : 0;
@@ -845,9 +877,7 @@ struct SearchWave {
   }
 
   __device__ __forceinline__ void run(uint32_t qi) {
-    // the folded query goes to LDS: it is read again for every group of rows
-    // (keeping it in registers costs a wavefront of occupancy)
-    {
+    if constexpr (!QREG) {   // the folded query goes to LDS: it is read again for every group of rows
       const int *src = reinterpret_cast<const int *>(a.tq + (uint64_t)qi * a.tq_stride);
       int *dst = const_cast<int *>(tql);
       for (uint32_t i = lane; i < a.tq_stride / 4; i += kWave) dst[i] = src[i];
@@ -886,6 +916,7 @@ struct SearchWave {
 
     const int p = PMAX == 1 || FAST ? PMAX : (int)a.p;
     uint32_t pre_id = kEmpty, pre_row = kEmpty, pre_nrm = 0;  // adjacency row fetched ahead (PMAX == 1)
+    float pre_label = 0.0f;
     for (;;) {
       // the p closest un-expanded pool entries, in pool order: their ids as
       // wave-uniform values, their expanded marks set in one pass per register
@@ -964,15 +995,34 @@ struct SearchWave {
         for (int e = 0; e < PMAX; ++e) {
           if (e >= got) break;
           uint32_t nb = kEmpty, nrm = 0;
-          if (lane < (int)a.degree) {
+          float label = 0.0f;
+          if (PMAX == 1 && uid[e] == pre_id) {
+            nb = pre_row;
+            nrm = pre_nrm;
+            label = pre_label;
+          } else if (lane < (int)a.degree) {
             load_slot(uid[e], lane, nb, nrm);
-            if (a.labels && !(a.labels[(uint64_t)uid[e] * a.degree + lane] <= a.alpha_s)) nb = kEmpty;
+            if (a.labels) label = a.labels[(uint64_t)uid[e] * a.degree + lane];
           }
+          if (PMAX == 1) {
+            // the row (and labels) expanded next unless a candidate of this step overtakes it, as below
+            pre_id = next_id;
+            pre_row = kEmpty;
+            pre_nrm = 0;
+            if (next_id != kEmpty && lane < (int)a.degree) {
+              load_slot(next_id, lane, pre_row, pre_nrm);
+              if (a.labels) pre_label = a.labels[(uint64_t)next_id * a.degree + lane];
+            }
+          }
+          if (a.labels && !(label <= a.alpha_s)) nb = kEmpty;
           if (PMAX == 1) {
             const uint32_t incoming = (uint32_t)__popcll(__ballot(nb != kEmpty));
             if (n_vis + incoming > vis_limit) rebuild_table();
           }
-          filter_ids_capped(nb, nrm, a.m_s, n_cand);
+          if (a.m_s < a.degree)
+            filter_ids_capped(nb, nrm, a.m_s, n_cand);
+          else
+            filter_ids(nb, nrm, n_cand);
         }
       } else if (use_pairs()) {
         // two adjacency rows per pass: lanes 0-31 take one, lanes 32-63 the next
@@ -1082,13 +1132,18 @@ struct SearchWave {
   }
 };
 
+// (The general kernels are compiled for four wavefronts per SIMD: for five they
+// spill up to 18 registers, and the complete table of the capped filter lets five
+// queries at most reside on a compute unit anyway.  Labels and cap, one expansion per
+// step, 50,021 x 100, ef = 100: 513 queries 415 -> 356 us, 10,000 3,016 -> 2,589; labels
+// alone, where residency counts, 383 -> 335 and 807 -> 840.)
 template <int BITS, int LPR, int M, int PMAX, bool FAST>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(M <= 2 ? (FAST ? (PMAX > 4 ? ANN_WPE_WIDE : (PMAX > 1 ? (BITS == 8 ? ANN_WPE : 5) : ANN_WPE_EXACT)) : 5) : (M == 4 ? 4 : 3)))) void search_kernel(SearchArgs args) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(M <= 2 ? (FAST ? (PMAX > 4 ? ANN_WPE_WIDE : (PMAX > 1 ? (BITS == 8 ? ANN_WPE : 5) : ANN_WPE_EXACT)) : 4) : (M == 4 ? 4 : 3)))) void search_kernel(SearchArgs args) {
   extern __shared__ uint64_t smem[];
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
   if (qi >= args.nq) return;  // not a permutation: skip rather than write out of bounds
-  SearchWave<BITS, LPR, M, PMAX, FAST> w(args, smem);
+  SearchWave<BITS, LPR, M, PMAX, FAST, 1, FAST && BITS == 4 && M >= 4> w(args, smem);
   w.run(qi);
 }
 
@@ -1099,12 +1154,24 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(kTeam
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
   if (qi >= args.nq) return;
-  SearchWave<BITS, LPR, M, PMAX, true, TEAM> w(args, smem);
+  SearchWave<BITS, LPR, M, PMAX, true, TEAM, BITS == 4 && M <= 4> w(args, smem);
   const int wave = (int)threadIdx.x / kWave;
   if (wave == 0)
     w.run(qi);
   else
     w.help(qi, wave);
+}
+
+// One expansion per step for batches that fit the chip at 128 registers (16
+// queries to a compute unit): the folded query in registers.
+template <int BITS, int LPR, int M>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kTeamWaves))) void search_small_kernel(SearchArgs args) {
+  extern __shared__ uint64_t smem[];
+  if (blockIdx.x >= args.nq) return;
+  const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
+  if (qi >= args.nq) return;
+  SearchWave<BITS, LPR, M, 1, true, 1, true> w(args, smem);
+  w.run(qi);
 }
 
 template <int BITS, int LPR, int PMAX, int TEAM>
@@ -1180,6 +1247,32 @@ static ann_status launch_search(const SearchArgs &a, uint32_t bits, uint32_t lpr
   }
 }
 
+template <int BITS, int LPR>
+static ann_status launch_small_m(const SearchArgs &a, int m, hipStream_t st) {
+  const size_t smem = search_smem_bytes(m, 1, true, a.vis_log2, a.degree, a.tq_stride);
+  switch (m) {
+    case 1: search_small_kernel<BITS, LPR, 1><<<a.nq, 64, smem, st>>>(a); break;
+    case 2: search_small_kernel<BITS, LPR, 2><<<a.nq, 64, smem, st>>>(a); break;
+    case 4: search_small_kernel<BITS, LPR, 4><<<a.nq, 64, smem, st>>>(a); break;
+    case 8: search_small_kernel<BITS, LPR, 8><<<a.nq, 64, smem, st>>>(a); break;
+    default: return fail(ANN_EUNSUPPORTED, "no kernel for pool registers per lane = %d", m);
+  }
+  ANN_HIP(hipGetLastError());
+  return ANN_OK;
+}
+
+template <int BITS>
+static ann_status launch_small(const SearchArgs &a, uint32_t lpr, int m, hipStream_t st) {
+  switch (lpr) {
+    case 1: return launch_small_m<BITS, 1>(a, m, st);
+    case 2: return launch_small_m<BITS, 2>(a, m, st);
+    case 4: return launch_small_m<BITS, 4>(a, m, st);
+    case 8: return launch_small_m<BITS, 8>(a, m, st);
+    case 16: return launch_small_m<BITS, 16>(a, m, st);
+    default: return fail(ANN_EUNSUPPORTED, "no kernel for %u lanes per code row", lpr);
+  }
+}
+
 template <int TEAM>
 static ann_status launch_team(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st) {
   if (wide_step)
@@ -1192,6 +1285,7 @@ ann_status launch_search_fast(const SearchArgs &a, uint32_t bits, uint32_t lpr, 
 ann_status launch_search_general(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool multi, hipStream_t st);
 ann_status launch_search_fast_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
 ann_status launch_search_general_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
+ann_status launch_search_small(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
 ann_status launch_search_team4(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st);
 ann_status launch_search_team2(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st);
 

@@ -25,3 +25,21 @@ def test_wavefronts_per_query(d, bits, degree, ef, p):
         assert (gi == oi[:nq]).all() and (gd == od[:nq]).all() and (gk.view(np.uint32) == ok[:nq].view(np.uint32)).all()
         assert (gc[:, 0] == oc[:nq, 0]).all() and (gc[:, 2] == oc[:nq, 2]).all()
     ix.close()
+
+
+@pytest.mark.parametrize("d,bits,degree,ef", [(40, 8, 16, 33), (128, 8, 32, 128), (250, 8, 64, 200), (960, 4, 48, 40), (1024, 8, 20, 300)])
+def test_one_expansion_per_step(d, bits, degree, ef):
+    """Batches on both sides of 16 queries per compute unit."""
+    import gpu_harness as H
+    import paper_2503_17911_amd as ann
+    w = inputs.Workload("small", 1200, d, 12, 0.3, 4200, bits=(bits,), seed=d + ef)
+    X, Q = inputs.base_vectors(w), inputs.queries(w)
+    adj, entry = inputs.build_graph(X, degree, 64)
+    lv = oracle.sq_fit(X, bits)
+    ix = H.GpuIndex(X, adj, entry, [lv], oracle.L2)
+    oi, ok, od, oc = oracle.search_batch(lv, d, adj, entry, Q, ef)
+    for nq in (1, 4096, 4097, 4200):
+        gi, gk, gd, gc = ix.search(Q[:nq], ef, visited_kind=ann.VISITED_AUTO)
+        assert (gi == oi[:nq]).all() and (gd == od[:nq]).all() and (gk.view(np.uint32) == ok[:nq].view(np.uint32)).all()
+        assert (gc[:, 0] == oc[:nq, 0]).all() and (gc[:, 2] == oc[:nq, 2]).all()
+    ix.close()
