@@ -449,8 +449,8 @@ ann_status ann_rerank_adaptive(ann_index *index, const float *q, uint32_t nq, co
  * on the matrix cores selects k + margin candidates per query, which are then
  * re-evaluated directly in fp64 and sorted by (distance, id).
  *   x [n][d], q [nq][d] fp32; out_ids/out_dist [nq][k]; k <= 256, d <= 2048,
- *   n < 2^31.  The fastest path needs d to be a multiple of 4, 16-byte aligned
- *   x and q, and k <= 16; any d and k within the limits work.
+ *   n < 2^31.  Rows are read 16 bytes at a time if d is a multiple of 4 and x is
+ *   16-byte aligned; any d and k within the limits work.
  * Allocates temporaries and synchronises the stream before returning.
  */
 ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d, const float *q, uint32_t nq, uint32_t k,
