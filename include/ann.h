@@ -447,7 +447,11 @@ ann_status ann_rerank_adaptive(ann_index *index, const float *q, uint32_t nq, co
  * Exact k nearest neighbours NN_k of every query by exhaustive search (the
  * ground truth of the paper's recall, Section 6.1): a dense Q.X^T contraction
  * on the matrix cores selects k + margin candidates per query, which are then
- * re-evaluated directly in fp64 and sorted by (distance, id).
+ * re-evaluated directly in fp64 and sorted by (distance, id).  Where the rounding
+ * of the contraction leaves open whether another row is nearer (vectors far from
+ * the origin, many rows at the same distance), the query is taken up again with
+ * centred vectors and more candidates; only where thousands of rows lie within
+ * that rounding of the k-th do fp32 products decide among them.
  *   x [n][d], q [nq][d] fp32; out_ids/out_dist [nq][k]; k <= 256, d <= 2048,
  *   n < 2^31.  Rows are read 16 bytes at a time if d is a multiple of 4 and x is
  *   16-byte aligned; any d and k within the limits work.

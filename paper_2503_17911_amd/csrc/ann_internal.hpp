@@ -92,6 +92,20 @@ ann_status hip_fail(hipError_t e, const char *what);
 hipError_t device_alloc(void **ptr, size_t bytes);
 void device_free(void *ptr);
 
+// Exhaustive search: what the rerank kernel needs to list the queries whose k-th
+// distance does not lie below every row that is no candidate.
+struct Certainty {
+  const float *below = nullptr;   // [nq] no other row is nearer than this; NULL: not asked for
+  uint32_t *n_listed = nullptr, *list = nullptr;
+  uint32_t first_query = 0;       // number of the batch's first query
+};
+
+// Exact distances of every query's candidates, the k best in (distance, id) order (rerank.hip).
+ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
+                         const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k, uint32_t *out_ids,
+                         float *out_dist, hipStream_t st, const float *cand_keys = nullptr, uint32_t n_min = 0,
+                         float gamma = 0.0f, uint32_t *out_n = nullptr, const Certainty &certain = {});
+
 // Kernel-layout length of one byte plane of a folded query for a level: every 16-byte chunk of
 // codes needs 16 (8-bit) or 32 (4-bit) query bytes; zero-padded to the number
 // of chunks the kernels' lanes cover.

@@ -4,41 +4,39 @@
 // Scores that only select candidates: -2 q.x + |x|^2 (or -q.x) from a dense
 // contraction on the matrix cores, every fp32 value split into three bf16
 // parts and six of the nine partial products accumulated in fp32, which loses
-// no more than fp32 products do (see bf_score_kernel).  The k + 8 best of a
-// query and a few more (at most `f_max`) are re-evaluated in fp64 by the rerank
-// kernel and sorted by (distance, id).
+// no more than fp32 products do (see bf_score_kernel).  Between `want` = k + 8 and
+// `most`, half as many again, of a query's best rows are re-evaluated in fp64 by
+// the rerank kernel and sorted by (distance, id).
 //
 // Selection without a top-k structure in the contraction kernel:
 //   few rows   all scores are written out and a selection kernel takes the best
 //              of every stretch of 4,096, another the best of those;
-//   otherwise  a stratified random sample of 4,096 rows gives every query a
-//              (score, id) bound that k + 8 rows of the sample reach; a sample
-//              sixteen times larger, of which only what reaches the bound is
-//              written, gives a tighter one, and so on until the sample would be
-//              the whole set; the last pass takes all rows in order and writes
-//              what reaches the last bound: about 16 (k + 8 .. f_max) entries per
-//              query whatever the distribution of the data, since the rank of a
+//   otherwise  a stratified random sample of 4,096 or 8,192 rows gives every
+//              query a (score, id) bound that k + 8 rows of the sample reach; a
+//              sample `growth` times larger (at most 32 times), of which only
+//              what reaches the bound is written, gives a tighter one, and so on
+//              until the sample would be the whole set; the last pass takes all
+//              rows in order and writes what reaches the last bound: about
+//              `growth` times k + 8 .. `most_bound` entries per query (room for
+//              `cap`) whatever the distribution of the data, since the rank of a
 //              random sample's order statistic does not depend on it.
-// A query whose entries overflow their room (which random sampling makes
-// practically impossible) or values the split cannot carry (infinities in an
-// inner product) send the batch to bf_tile_kernel: fp32 products, a threshold
-// and a buffer per (query, base slab) in LDS.
+// A result is certain if its k-th distance is smaller than the score of the first
+// row left out allows, less the error that score may have.  Ordinary data leave
+// many times that error between the k-th row and the first left out (no query of
+// the calls below was uncertain); those that are not certain (vectors far from
+// the origin, many equal distances, entries beyond their room) are taken up
+// again, see settle().
 //
 // Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
 // kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
-// k = 10: 25.8 -> 19.3 ms; 2,000 x 200,000 x 768, k = 100: 13.9 -> 5.2 ms; 100 x
-// 10,000 x 128, k = 10: 2.56 -> 0.11 ms.
+// k = 10: 25.8 -> 15.5 ms; 2,000 x 200,000 x 768, k = 100: 13.9 -> 3.8 ms; 100 x
+// 10,000 x 128, k = 10: 2.56 -> 0.07 ms.
 #include <math.h>
 
 #include "ann_internal.hpp"
 #include "device_utils.hpp"
 
 namespace ann {
-
-ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
-                         const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k, uint32_t *out_ids,
-                         float *out_dist, hipStream_t st, const float *cand_keys = nullptr, uint32_t n_min = 0,
-                         float gamma = 0.0f, uint32_t *out_n = nullptr);
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
@@ -245,9 +243,15 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 // the three smallest (below 2^-25 of the product) are left out.  The fp32 matrix
 // rate is 157 TFLOP/s; six bf16 products at 2.5 PFLOP/s leave 417 of the same.
 // Root mean square error of a score against 64 bits, relative to that of the
-// scores (inner products of mixtures, 128 queries x 4,096 rows; in brackets:
-// fp32 products): d = 24 5.5e-8 (7.5e-8), 128 1.4e-7 (1.7e-7), 960 3.1e-7
-// (4.2e-7), 2,048 4.0e-7 (6.1e-7).
+// scores (128 queries x 4,096 rows; in brackets: fp32 products and norms):
+//   inner products of mixtures   d = 24 5.5e-8 (7.5e-8), 128 1.4e-7 (1.7e-7),
+//                                960 3.1e-7 (4.2e-7), 2,048 4.0e-7 (6.1e-7)
+//   L2, centred normal vectors   128 5.6e-8 (6.0e-8), 960 5.0e-8 (5.5e-8),
+//                                2,048 5.8e-8 (6.3e-8)
+//   L2, offset of 1,000 spreads  128 2.2e-7 (3.0e-7), 960 8.7e-7 (8.6e-7),
+//                                2,048 1.3e-6 (1.2e-6)
+// (likewise for uniform, unit-norm and stretched vectors).  Only the last two are
+// larger than with fp32 products; such results are settled with centred rows.
 //
 // A workgroup of four wavefronts takes QT queries x 128 base rows per tile.
 // The queries come split, in the order the matrix instruction wants them
@@ -296,21 +300,26 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t (&w)[3]) {
 // Queries split and laid out as the second operand of the 32x32x16 matrix
 // instruction: 16-byte unit (((q / 32) * KB + kb) * 3 + plane) * 64 + lane holds
 // columns kb * 16 + 8 * (lane / 32) .. + 7 of query lane % 32.  Zero past the
-// batch and past d.  An infinity raises the flag.
+// batch and past d.  centre (NULL: none) is subtracted.  Also the start of every
+// query's selection (bound NULL: not wanted): no bound, no entries.
 __global__ __launch_bounds__(256) void bf_split_queries_kernel(const float *__restrict__ Q, uint32_t nq, uint32_t d, uint32_t kb_n,
-                                                               uint32_t q32_n, uint4 *__restrict__ out, uint32_t *__restrict__ flag) {
+                                                               uint32_t q32_n, const float *__restrict__ centre, uint4 *__restrict__ out,
+                                                               uint64_t *__restrict__ bound, uint32_t *__restrict__ count) {
   const uint64_t total = (uint64_t)q32_n * kb_n * 64;
   for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (uint64_t)gridDim.x * blockDim.x) {
     const uint32_t lane = (uint32_t)(e % 64), kb = (uint32_t)(e / 64 % kb_n), q32 = (uint32_t)(e / 64 / kb_n);
     const uint32_t qi = q32 * 32 + lane % 32, k0 = kb * 16 + 8 * (lane / 32);
     float v[8];
-    bool inf = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      v[j] = qi < nq && k0 + j < d ? Q[(uint64_t)qi * d + k0 + j] : 0.0f;
-      inf = inf || fabsf(v[j]) >= 0x1.fep127f;
+      const bool in = qi < nq && k0 + j < d;
+      v[j] = in ? Q[(uint64_t)qi * d + k0 + j] : 0.0f;
+      if (centre && in) v[j] = __fsub_rn(v[j], centre[k0 + j]);
     }
-    if (inf) atomicOr(flag, 1u);
+    if (bound && kb == 0 && lane < 32 && qi < nq) {
+      bound[qi] = ~0ull;
+      count[qi] = 0;
+    }
     uint32_t w[4][3];
 #pragma unroll
     for (int j = 0; j < 4; ++j) split3(v[2 * j], v[2 * j + 1], w[j]);
@@ -319,6 +328,15 @@ __global__ __launch_bounds__(256) void bf_split_queries_kernel(const float *__re
     for (int p = 0; p < 3; ++p) to[p * 64] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
   }
 }
+
+// What a call learns on the device and the host reads at its end (or between steps).
+struct CallState {
+  uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
+  uint32_t far_rows;      // inner product: not zero if a row's squared norm is no float
+  uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
+  uint32_t most_entries;  // of a query in the last pass over uncertain queries
+  uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
+};
 
 struct ScoreArgs {
   const float *x;
@@ -333,7 +351,8 @@ struct ScoreArgs {
   uint64_t *buf;     // [nq][cap]
   uint32_t *count;   // [nq]
   uint32_t cap;
-  uint32_t *flag;
+  const float *centre;     // [d] subtracted from every row (kernels with CENTRE)
+  CallState *state;        // inner product: norms are noted here (NULL: not in this pass)
 };
 
 // Row of x that is row j of a sample: a random one of the j-th stretch of rows
@@ -346,14 +365,14 @@ __device__ __forceinline__ uint64_t sample_row(uint64_t j, double stretch) {
   return begin + __umulhi(h, (uint32_t)(end - begin));
 }
 
-template <bool VEC4, int MB, int NQ>
+template <bool VEC4, int MB, int NQ, bool CENTRE>
 __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   constexpr int WB = 4 / MB;                   // wavefronts side by side over the base rows
   constexpr int QT32 = 4 / WB * NQ;            // blocks of 32 queries per tile
   static_assert(WB * MB * 32 == kSB, "tile shape");
   constexpr int NR = kSB / 32;                 // base rows per thread
   __shared__ __align__(16) unsigned char stage_s[2][3 * kPlane];
-  __shared__ float xn_s[2][kSB];
+  __shared__ __align__(16) float xn_s[2][kSB];
   __shared__ uint64_t hit_s[4][kHitList];
   __shared__ uint8_t hit_q_s[4][kHitList];
 
@@ -379,7 +398,8 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   // Nothing here branches: the steps below are one block of instructions, in
   // which the splitting fills the issue slots between matrix instructions.
   float4 reg[NR];
-  float sq[NR] = {};
+  float sq[NR] = {}, sq_low[NR] = {};   // squared norm so far, and what its additions rounded away
+  float max_norm = 0.f;   // inner product: largest squared norm seen
   const float *row_at[NR];
   auto new_rows = [&](uint64_t tile) {
 #pragma unroll
@@ -405,20 +425,28 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   // (columns past d hold other values of the row: the queries are zero there, and the norms leave them out)
   auto stage = [&](int b, uint32_t c) {
     const uint32_t k = c * kSK + s_col;
+    float4 mid = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (CENTRE) mid = make_float4(a.centre[k < a.d ? k : 0], a.centre[k + 1 < a.d ? k + 1 : 0], a.centre[k + 2 < a.d ? k + 2 : 0], a.centre[k + 3 < a.d ? k + 3 : 0]);
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      const float4 v = reg[i];
+      float4 v = reg[i];
+      if constexpr (CENTRE) v = make_float4(__fsub_rn(v.x, mid.x), __fsub_rn(v.y, mid.y), __fsub_rn(v.z, mid.z), __fsub_rn(v.w, mid.w));
+      float t;
       if constexpr (VEC4) {
-        const float t = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, sq[i]))));
-        sq[i] = k < a.d ? t : sq[i];
+        t = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w)));
+        t = k < a.d ? t : 0.f;
       } else {
         const float e[4] = {v.x, v.y, v.z, v.w};
+        t = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float t = fmaf(e[j], e[j], sq[i]);
-          sq[i] = k + j < a.d ? t : sq[i];
+          const float u = fmaf(e[j], e[j], t);
+          t = k + j < a.d ? u : t;
         }
       }
+      const float sum = sq[i] + t;   // (the sum so far is the larger part, but for the first chunks)
+      sq_low[i] += t - (sum - sq[i]);
+      sq[i] = sum;
       uint32_t w01[3], w23[3];
       split3(v.x, v.y, w01);
       split3(v.z, v.w, w23);
@@ -433,16 +461,24 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   auto put_norms = [&](uint64_t tile) {
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      float t = sq[i];
+      float t = sq[i] + sq_low[i];
+      t = sq[i] < INFINITY ? t : sq[i];
       t += __int_as_float(dpp_i32<kDppQuadXor1>(__float_as_int(t)));
       t += __int_as_float(dpp_i32<kDppQuadXor2>(__float_as_int(t)));
       t += __int_as_float(dpp_i32<kDppRowHalfMirror>(__float_as_int(t)));
-      sq[i] = 0.f;
+      sq[i] = sq_low[i] = 0.f;
       if (tid % 8 == 0) {
+        // Rows whose squared norm is no float are left out of the scores.  L2: they are infinitely far.  Inner
+        // product: they may be near (the fp32 kernel takes over).
         const uint64_t r = tile * kSB + s_row + 32 * i;
-        // (an infinity in an inner product must not become a NaN: the fp32 kernel takes over)
-        if (a.metric != ANN_L2 && !(t < INFINITY)) atomicOr(a.flag, 1u);
-        xn_s[tile & 1][s_row + 32 * i] = r < a.rows ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
+        const bool in = r < a.rows && t < INFINITY;
+        xn_s[tile & 1][s_row + 32 * i] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
+        if (a.metric != ANN_L2 && a.state != nullptr) {
+          if (in)
+            max_norm = fmaxf(max_norm, t);
+          else if (r < a.rows)
+            atomicOr(&a.state->far_rows, 1u);
+        }
       }
     }
   };
@@ -465,13 +501,25 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   };
   auto flush = [&]() {
     fence();
+    bool over = false;
     for (int e = lane; e < n_hits; e += kWave) {
       const uint32_t q = qt * QT32 * 32 + hits_q[e];
       const uint32_t pos = atomicAdd(&a.count[q], 1u);
-      if (pos < a.cap) a.buf[(uint64_t)q * a.cap + pos] = hits[e];
+      if (pos < a.cap)
+        a.buf[(uint64_t)q * a.cap + pos] = hits[e];
+      else
+        over = true;
     }
     fence();
     n_hits = 0;
+    // a query with more entries than room has to be treated otherwise: no more of them
+    if (__ballot(over) != 0) {
+#pragma unroll
+      for (int f = 0; f < NQ; ++f) {
+        const uint32_t q = (qt * QT32 + wq * NQ + f) * 32 + l32;
+        if (q < a.nq && *(volatile uint32_t *)&a.count[q] > a.cap) top[f] = -INFINITY;
+      }
+    }
   };
 
   floatx16 acc[MB][NQ];
@@ -627,6 +675,22 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
     cur ^= 1;
   }
   if (n_hits > 0) flush();
+  if (a.metric != ANN_L2 && a.state != nullptr) {
+    max_norm = wave_max_f32(max_norm);
+    if (lane == 0) atomicMax(&a.state->max_norm, __float_as_uint(max_norm));
+  }
+}
+
+// How far the score of a row with |x| <= nx may lie from its value, |q| = nq (of
+// the centred vectors where they are).  Each of the kb_n blocks of 16 columns
+// takes six matrix instructions, each of which rounds an accumulator that never
+// exceeds |q| |x|; 32 roundings more stand for the products left out, the norm,
+// the subtraction of the centre and the last addition.  The second term: what
+// the instruction may drop of values below the smallest normal number.  The
+// largest error seen is 0.13 of it (seven distributions, d = 24 to 2,048).
+__device__ __forceinline__ double score_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric) {
+  const double terms = 6.0 * kb_n + 32.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
+  return terms * 0x1p-24 * size + 0x1p-124 * (double)d * (1.0 + nq + nx);
 }
 
 // ---------------------------------------------------------------------------
@@ -724,7 +788,7 @@ struct Selector {
 
 // The best of one stretch of a query's scores.  Sample (stretch != 0): the bound
 // is all that is wanted.  Otherwise the entries go to out[q][blockIdx.y][most],
-// padded with all-ones.
+// padded with all-ones, and the bound is the smallest of the stretches'.
 template <int EPT>
 __global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const float *__restrict__ scores, uint32_t ld, uint64_t rows,
                                                                        double stretch, uint32_t want, uint32_t most,
@@ -753,6 +817,7 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const flo
     if (tid == 0) bound[q] = b;
     return;
   }
+  if (tid == 0) atomicMin(reinterpret_cast<unsigned long long *>(&bound[q]), (unsigned long long)b);
   uint64_t *list = out + ((uint64_t)q * gridDim.y + blockIdx.y) * most;
   uint32_t mine = 0;
 #pragma unroll
@@ -776,17 +841,50 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const flo
   for (uint32_t e = n_kept + tid; e < most; e += kSelThreads) list[e] = ~0ull;
 }
 
+// What the last selection of a batch needs to tell how far its result is certain.
+struct CertainArgs {
+  const float *q;      // [nq][d]
+  const float *centre; // [d] what rows (and, L2, queries) were centred by, or NULL
+  uint32_t d, kb_n, metric;
+  const CallState *state;
+  float *below;        // [nq] out
+};
+
 // The best of a query's entries.  count == NULL: all `cap` of them (all-ones:
 // none).  cand == NULL: only the bound is updated (kept if fewer than `want`
 // entries were found) and the count cleared for the next pass; otherwise the
-// ids go to cand[q][most], padded.
+// ids go to cand[q][most], padded, and c.below[q] says up to which distance no
+// other row can be nearer: the value of the first pair left out less what its
+// score may be too large by.  (A row nearer than a distance D has |x| <= |q| +
+// sqrt(D), whatever other rows measure; in an inner product the largest row
+// counts.)  Infinity: nothing was left out, or the query has a NaN and no scores.
 template <int EPT>
 __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const uint64_t *__restrict__ buf, uint32_t *__restrict__ count,
                                                                         uint32_t cap, uint32_t want, uint32_t most,
                                                                         uint64_t *__restrict__ bound, uint32_t *__restrict__ cand,
-                                                                        uint32_t *__restrict__ flag) {
+                                                                        CertainArgs c) {
   __shared__ uint32_t red[16], n_out;
+  __shared__ double norm_s[kSelThreads / kWave], along_s[kSelThreads / kWave];
   const uint32_t q = blockIdx.x, tid = threadIdx.x;
+  if (cand != nullptr) {
+    double sq = 0.0, along = 0.0;   // (inner product of centred rows: all scores lack q . centre)
+    for (uint32_t j = tid; j < c.d; j += kSelThreads) {
+      float v = c.q[(uint64_t)q * c.d + j];
+      if (c.centre) {
+        if (c.metric == ANN_L2)
+          v = __fsub_rn(v, c.centre[j]);
+        else
+          along += (double)v * c.centre[j];
+      }
+      sq += fabsf(v) < 0x1.fep127f || v != v ? (double)v * v : INFINITY;   // (larger ones have no three parts)
+    }
+    sq = group_sum_f64<kWave>(sq);
+    if (c.centre) along = group_sum_f64<kWave>(along);
+    if (tid % kWave == 0) {   // (read after the selection's barriers)
+      norm_s[tid / kWave] = sq;
+      along_s[tid / kWave] = along;
+    }
+  }
   const uint32_t found = count ? count[q] : cap;
   const uint32_t n_ent = found < cap ? found : cap;
   Selector<EPT> s;
@@ -801,13 +899,29 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
   if (tid == 0) n_out = 0;
   uint32_t n_kept;
   const uint64_t b = s.run(want, most, n_kept);   // (a barrier or more: everyone has read the count)
-  if (tid == 0 && found > cap) atomicOr(flag, 2u);
   if (cand == nullptr) {
     if (tid == 0) {
       if (n_kept >= want && b < bound[q]) bound[q] = b;
       count[q] = 0;
     }
     return;
+  }
+  if (tid == 0) {
+    double sq = 0.0, along = 0.0;
+    for (int w = 0; w < kSelThreads / kWave; ++w) {
+      sq += norm_s[w];
+      along += along_s[w];
+    }
+    const uint64_t out = b < bound[q] ? b : bound[q];
+    // (norms in fp32, rounded up: one thread computes this while the others are done)
+    const float more = 1.0f + 0x1p-20f, nq = __fsqrt_rn((float)sq) * more;
+    const double value = unorder_f32((uint32_t)(out >> 32)), dist = c.metric == ANN_L2 ? sq + value : value - along;
+    const float nx = (c.metric == ANN_L2 ? nq + __fsqrt_rn(fmaxf((float)dist, 0.0f)) : __fsqrt_rn(__uint_as_float(c.state->max_norm))) * more;
+    float below = (float)(dist - score_room(nq, nx, c.d, c.kb_n, c.metric));
+    if (found > cap) below = -INFINITY;   // entries were lost
+    if ((uint32_t)(out >> 32) >= kMaxScore || sq != sq) below = INFINITY;
+    if (sq == INFINITY) below = -INFINITY;
+    c.below[q] = below;
   }
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
@@ -876,7 +990,7 @@ static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const 
 // queries, slabs so that the last turn of workgroups (two per compute unit) is
 // nearly full.
 static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream_t st) {
-  const uint32_t qt = a.nq > 64 ? 128u : (a.nq > 32 ? 64u : 32u);
+  const uint32_t qt = a.nq > 64 || (a.centre && a.nq > 32) ? 128u : (a.nq > 32 ? 64u : 32u);
   a.q_tiles = (a.nq + qt - 1) / qt;
   const uint64_t tiles = (a.rows + kSB - 1) / kSB;
   const uint64_t slots = 2ull * n_cu;
@@ -900,12 +1014,16 @@ static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream
   const uint32_t grid = a.q_tiles * (((uint32_t)slabs + 7) / 8 * 8);
 #define ANN_BS(V)                                                     \
   do {                                                                \
-    if (qt == 128)                                                    \
-      bf_score_kernel<V, 4, 1><<<grid, 256, 0, st>>>(a);              \
+    if (a.centre && qt == 128)                                        \
+      bf_score_kernel<V, 4, 1, true><<<grid, 256, 0, st>>>(a);        \
+    else if (a.centre)                                                \
+      bf_score_kernel<V, 1, 1, true><<<grid, 256, 0, st>>>(a);        \
+    else if (qt == 128)                                               \
+      bf_score_kernel<V, 4, 1, false><<<grid, 256, 0, st>>>(a);       \
     else if (qt == 64)                                                \
-      bf_score_kernel<V, 1, 2><<<grid, 256, 0, st>>>(a);              \
+      bf_score_kernel<V, 1, 2, false><<<grid, 256, 0, st>>>(a);       \
     else                                                              \
-      bf_score_kernel<V, 1, 1><<<grid, 256, 0, st>>>(a);              \
+      bf_score_kernel<V, 1, 1, false><<<grid, 256, 0, st>>>(a);       \
   } while (0)
   if (vec4)
     ANN_BS(true);
@@ -913,6 +1031,365 @@ static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream
     ANN_BS(false);
 #undef ANN_BS
   ANN_HIP(hipGetLastError());
+  return ANN_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Queries whose result is not certain (see bf_select_entries_kernel): vectors far
+// from the origin, where the squares cancel, or many rows at the same distance.
+// First the whole selection again with centred rows and queries (distances do not
+// change, nor does the order of inner products), which brings the scores' error
+// down to that of the spread.  What is still uncertain then: the k-th distance
+// found so far bounds the score of every row that can be among the k nearest, so
+// a pass over all rows, of which everything up to that bound is re-evaluated,
+// settles a query if it finds at most kRoom rows; with more, the best of those
+// that were found bound the next pass.  What does not settle that way (thousands
+// of rows at one distance, infinities in a query) goes to bf_tile_kernel, as
+// before there were bounds.
+// 10,000 queries x 1M x 128, k = 10, 300 or 2,300 spreads from the origin: 30 ms
+// (15.4 if certain at once; fp32 products alone took 25.6 and lost neighbours).
+
+constexpr uint32_t kRoom = 4096;       // rows re-evaluated per uncertain query and pass
+constexpr uint32_t kMaxPasses = 4;
+
+// Mean of a sample of the rows, column by column (values that are not of ordinary size left out).
+__global__ __launch_bounds__(1024) void bf_centre_kernel(const float *__restrict__ x, uint32_t rows, double stretch, uint32_t d,
+                                                         float *__restrict__ centre) {
+  __shared__ double sum_s[16][64];
+  __shared__ uint32_t n_s[16][64];
+  const uint32_t c = threadIdx.x % 64, r = threadIdx.x / 64, j = blockIdx.x * 64 + c;
+  double sum = 0.0;
+  uint32_t n = 0;
+  if (j < d)
+    for (uint32_t i = r; i < rows; i += 16) {
+      const float v = x[sample_row(i, stretch) * d + j];
+      if (fabsf(v) < 0x1p50f) sum += v, ++n;
+    }
+  sum_s[r][c] = sum;
+  n_s[r][c] = n;
+  __syncthreads();
+  if (r == 0 && j < d) {
+    for (int k = 1; k < 16; ++k) sum += sum_s[k][c], n += n_s[k][c];
+    centre[j] = n ? (float)(sum / n) : 0.0f;
+  }
+}
+
+// One wavefront per uncertain query: its coordinates side by side with the
+// others', and the bound of the pass.  Zero: no pass can settle it.
+__global__ __launch_bounds__(64) void bf_gather_uncertain_kernel(const float *__restrict__ Q, uint32_t d, uint32_t kb_n, uint32_t k, uint32_t metric,
+                                                                 const float *__restrict__ centre, const uint32_t *__restrict__ list,
+                                                                 const float *__restrict__ out_dist, const CallState *__restrict__ state,
+                                                                 float *__restrict__ Qg, uint64_t *__restrict__ bound,
+                                                                 uint32_t *__restrict__ count) {
+  const uint32_t i = blockIdx.x, q = list[i];
+  double sq = 0.0, along = 0.0;
+  bool bad = false;
+  for (uint32_t j = lane_id(); j < d; j += kWave) {
+    const float v = Q[(uint64_t)q * d + j], c = centre ? centre[j] : 0.0f, vc = metric == ANN_L2 ? __fsub_rn(v, c) : v;
+    Qg[(uint64_t)i * d + j] = v;
+    sq += (double)vc * vc;
+    along += (double)v * c;
+    bad = bad || !(fabsf(v) < 0x1.fep127f) || !(fabsf(vc) < 0x1.fep127f);
+  }
+  if (bound == nullptr) return;
+  sq = group_sum_f64<kWave>(sq);
+  along = group_sum_f64<kWave>(along);
+  bad = __ballot(bad) != 0;
+  if (lane_id() != 0) return;
+  count[i] = 0;
+  const double far = out_dist[(uint64_t)q * k + k - 1], up = far + fabs(far) * 0x1p-22 + 0x1p-140;   // (rounded to a float on the way)
+  const double nq = sqrt(sq), nx = metric == ANN_L2 ? nq + sqrt(fmax(up, 0.0)) : sqrt((double)__uint_as_float(state->max_norm));
+  const double value = (metric == ANN_L2 ? up - sq : up + along) + score_room(nq, nx, d, kb_n, metric);
+  uint64_t b = ((uint64_t)kMaxScore << 32) | 0xFFFFFFFFu;
+  if (value < 0x1.fffffep127) {
+    float f = (float)value;
+    if ((double)f < value) f = nextafterf(f, INFINITY);
+    b = ((uint64_t)order_u32(f) << 32) | 0xFFFFFFFFu;
+  }
+  bound[i] = bad ? 0ull : b;
+}
+
+// The entries of a pass as candidates, padded; one workgroup per query.
+__global__ __launch_bounds__(256) void bf_entries_to_candidates_kernel(const uint64_t *__restrict__ buf, const uint32_t *__restrict__ count,
+                                                                       uint32_t *__restrict__ cand, CallState *__restrict__ state) {
+  const uint32_t q = blockIdx.x, n = count[q] < kRoom ? count[q] : kRoom;
+  for (uint32_t e = threadIdx.x; e < kRoom; e += 256) cand[(uint64_t)q * kRoom + e] = e < n ? (uint32_t)buf[(uint64_t)q * kRoom + e] : ANN_PAD_ID;
+  if (threadIdx.x == 0) atomicMax(&state->most_entries, n);
+}
+
+// Queries of a selection that are uncertain, by their place in it -> their numbers.
+__global__ void bf_next_list_kernel(const uint32_t *__restrict__ places, const uint32_t *__restrict__ list, CallState *__restrict__ state,
+                                    uint32_t *__restrict__ next) {
+  for (uint32_t i = threadIdx.x; i < state->n_uncertain; i += blockDim.x) next[atomicAdd(&state->n_next, 1u)] = list[places[i]];
+  __syncthreads();
+  if (threadIdx.x == 0) state->n_uncertain = 0;
+}
+
+// Results of a pass to their queries' places; one wavefront per query.  A query
+// with more entries than room goes to the next pass if its k-th distance fell.
+// bound == NULL: results of the fp32 kernel, taken unless a pass found better.
+__global__ __launch_bounds__(64) void bf_scatter_uncertain_kernel(const uint32_t *__restrict__ list, uint32_t k, const uint64_t *__restrict__ bound,
+                                                                  const uint32_t *__restrict__ count, const uint32_t *__restrict__ ids,
+                                                                  const float *__restrict__ dist, uint32_t *__restrict__ out_ids,
+                                                                  float *__restrict__ out_dist, CallState *__restrict__ state,
+                                                                  uint32_t *__restrict__ next, uint32_t *__restrict__ fp32) {
+  const uint32_t i = blockIdx.x, q = list[i];
+  const float was = out_dist[(uint64_t)q * k + k - 1], is = dist[(uint64_t)i * k + k - 1];
+  bool take;
+  if (bound == nullptr) {
+    take = is <= was;
+  } else {
+    const bool all = bound[i] != 0 && count[i] <= kRoom, better = bound[i] != 0 && is < was;
+    take = all || better;
+    if (!all && lane_id() == 0) {
+      if (better)
+        next[atomicAdd(&state->n_next, 1u)] = q;
+      else
+        fp32[atomicAdd(&state->n_fp32, 1u)] = q;
+    }
+  }
+  __syncthreads();   // (one wavefront: everyone has read the old distance)
+  if (!take) return;
+  for (uint32_t j = lane_id(); j < k; j += kWave) {
+    out_ids[(uint64_t)q * k + j] = ids[(uint64_t)i * k + j];
+    out_dist[(uint64_t)q * k + j] = dist[(uint64_t)i * k + j];
+  }
+}
+
+// Device memory for `most` items or, when there is not that much, half as many and so on down to `least`.
+template <typename Bytes>
+static hipError_t alloc_some(void **ptr, uint64_t &items, uint64_t least, Bytes bytes) {
+  for (;;) {
+    const hipError_t e = device_alloc(ptr, bytes(items));
+    if (e != hipErrorOutOfMemory || items <= least) return e;
+    (void)hipGetLastError();
+    items = items / 2 > least ? items / 2 : least;
+  }
+}
+
+struct Truth {
+  const float *x;
+  uint64_t n;
+  uint32_t d;
+  const float *q;
+  uint32_t k, metric;
+  uint32_t *out_ids;
+  float *out_dist;
+  uint32_t n_cu;
+  hipStream_t st;
+};
+
+static uint64_t up256(uint64_t v) { return (v + 255) & ~255ull; }
+
+// How a call's candidates are selected, and the buffers for a round of queries.
+struct Selection {
+  uint32_t want, most, most_bound;   // see ann_bruteforce_topk
+  uint32_t kb_n, cap, first, samples;
+  uint64_t stretches, ld;
+  bool vec4, dense;
+  double growth;
+  uint4 *qfrag;
+  float *scores, *below;
+  uint64_t *buf, *bound;
+  uint32_t *count, *cand;
+  CallState *state;
+};
+
+// One round: the k nearest rows of the m queries at qr.
+static ann_status select_round(const Truth &t, const Selection &s, const float *qr, uint32_t m, const float *centre,
+                               uint32_t *out_ids, float *out_dist, uint32_t *uncertain, uint32_t first_query) {
+  const uint32_t blocks32 = (m + 127) / 128 * 4;
+  const uint64_t units = (uint64_t)blocks32 * s.kb_n * 64;
+  bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, t.st>>>(
+      qr, m, t.d, s.kb_n, blocks32, t.metric == ANN_L2 ? centre : nullptr, s.qfrag, s.bound, s.count);
+  ScoreArgs a{};
+  a.x = t.x;
+  a.qfrag = s.qfrag;
+  a.d = t.d;
+  a.kb_n = s.kb_n;
+  a.nq = m;
+  a.metric = t.metric;
+  a.ld = (uint32_t)s.ld;
+  a.bound = s.bound;
+  a.buf = s.buf;
+  a.count = s.count;
+  a.cap = s.cap;
+  a.centre = centre;
+  const CertainArgs certain{qr, centre, t.d, s.kb_n, t.metric, s.state, s.below};
+  auto select_entries = [&](uint32_t *cnt, uint32_t *to, uint32_t up_to) {
+    if (s.cap <= 2048)
+      bf_select_entries_kernel<8><<<m, kSelThreads, 0, t.st>>>(s.buf, cnt, s.cap, s.want, up_to, s.bound, to, certain);
+    else if (s.cap <= 4096)
+      bf_select_entries_kernel<16><<<m, kSelThreads, 0, t.st>>>(s.buf, cnt, s.cap, s.want, up_to, s.bound, to, certain);
+    else
+      bf_select_entries_kernel<32><<<m, kSelThreads, 0, t.st>>>(s.buf, cnt, s.cap, s.want, up_to, s.bound, to, certain);
+  };
+  ann_status rc;
+  if (s.dense) {
+    a.rows = t.n;
+    a.scores = s.scores;
+    a.state = s.state;
+    rc = launch_scores(a, s.vec4, t.n_cu, t.st);
+    if (rc != ANN_OK) return rc;
+    bf_select_scores_kernel<kSampleRows / kSelThreads><<<dim3(m, (uint32_t)s.stretches), kSelThreads, 0, t.st>>>(s.scores, a.ld, t.n, 0, s.want, s.most,
+                                                                                                                 s.bound, s.buf);
+    select_entries(nullptr, s.cand, s.most);
+  } else {
+    double rows = (double)s.first;
+    for (uint32_t p = 0; p <= s.samples; ++p, rows *= s.growth) {
+      const bool last = p == s.samples;
+      a.rows = last ? t.n : (p == 0 ? (uint64_t)s.first : (uint64_t)rows);
+      a.stretch = last ? 0.0 : (double)t.n / (double)a.rows;
+      a.scores = p == 0 ? s.scores : nullptr;
+      a.state = last ? s.state : nullptr;
+      rc = launch_scores(a, s.vec4, t.n_cu, t.st);
+      if (rc != ANN_OK) return rc;
+      if (p == 0 && s.first == kSampleRows)
+        bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
+                                                                                        nullptr);
+      else if (p == 0)
+        bf_select_scores_kernel<2 * kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound,
+                                                                                            s.bound, nullptr);
+      else
+        select_entries(s.count, last ? s.cand : nullptr, last ? s.most : s.most_bound);
+    }
+  }
+  ANN_HIP(hipGetLastError());
+  return rerank_device(t.x, t.n, t.d, t.metric, qr, m, s.cand, s.most, s.most, t.k, out_ids, out_dist, t.st, nullptr, 0, 0.0f, nullptr,
+                       Certainty{s.below, &s.state->n_uncertain, uncertain, first_query});
+}
+
+// The fp32 kernel for the listed queries.
+static ann_status fp32_for(const Truth &t, const uint32_t *list, uint32_t m_all) {
+  uint64_t m = m_all < 8192 ? m_all : 8192;
+  auto bytes = [&](uint64_t c) { return up256(c * t.d * 4) + up256(c * t.k * 4) * 2; };
+  unsigned char *base = nullptr;
+  const hipError_t e = alloc_some((void **)&base, m, 1, bytes);
+  if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  float *qg = reinterpret_cast<float *>(base);
+  uint32_t *ids = reinterpret_cast<uint32_t *>(base + up256(m * t.d * 4));
+  float *dist = reinterpret_cast<float *>(base + up256(m * t.d * 4) + up256(m * t.k * 4));
+  ann_status rc = ANN_OK;
+  for (uint64_t i0 = 0; i0 < m_all && rc == ANN_OK; i0 += m) {
+    const uint32_t c = (uint32_t)(m_all - i0 < m ? m_all - i0 : m);
+    bf_gather_uncertain_kernel<<<c, 64, 0, t.st>>>(t.q, t.d, 0, t.k, t.metric, nullptr, list + i0, t.out_dist, nullptr, qg, nullptr, nullptr);
+    rc = bruteforce_fp32(t.x, t.n, t.d, qg, c, t.k, t.metric, ids, dist, t.n_cu, t.st);
+    if (rc == ANN_OK)
+      bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, nullptr, nullptr, ids, dist, t.out_ids, t.out_dist, nullptr, nullptr, nullptr);
+  }
+  const hipError_t e1 = hipGetLastError(), e2 = hipStreamSynchronize(t.st);
+  device_free(base);
+  if (rc != ANN_OK) return rc;
+  if (e1 != hipSuccess) return hip_fail(e1, "fp32 kernel for uncertain queries");
+  if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
+  return ANN_OK;
+}
+
+// The uncertain queries list[0 .. n_list), `round` of them at a time in s: the
+// selection with centred rows, passes over what that leaves, and the fp32 kernel
+// for what these do.
+static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uint32_t *list, uint32_t n_list) {
+  CallState *const state = s.state;
+  // buffers for m queries at a time, the other lists and the centre
+  uint64_t m = n_list < 2048 ? n_list : 2048;
+  if (m > round) m = round;
+  auto parts = [&](uint64_t c, uint64_t (&at)[8]) {
+    const uint64_t size[8] = {c * kRoom * 8, c * kRoom * 4, c * t.d * 4, c * t.k * 4, c * t.k * 4, c * 4, 2ull * n_list * 4, (uint64_t)t.d * 4};
+    uint64_t total = 0;
+    for (int i = 0; i < 8; ++i) {
+      at[i] = total;
+      total += up256(size[i]);
+    }
+    return total;
+  };
+  uint64_t at[8];
+  unsigned char *base = nullptr;
+  hipError_t e = alloc_some((void **)&base, m, 1, [&](uint64_t c) { return parts(c, at); });
+  if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  parts(m, at);
+  uint64_t *buf = reinterpret_cast<uint64_t *>(base + at[0]);
+  uint32_t *cand = reinterpret_cast<uint32_t *>(base + at[1]), *ids = reinterpret_cast<uint32_t *>(base + at[3]);
+  float *qg = reinterpret_cast<float *>(base + at[2]), *dist = reinterpret_cast<float *>(base + at[4]);
+  uint32_t *places = reinterpret_cast<uint32_t *>(base + at[5]), *other = reinterpret_cast<uint32_t *>(base + at[6]), *fp32 = other + n_list;
+  float *centre = reinterpret_cast<float *>(base + at[7]);
+
+  const uint32_t sample = t.n < kSampleRows ? (uint32_t)t.n : kSampleRows;
+  bf_centre_kernel<<<(t.d + 63) / 64, 1024, 0, t.st>>>(t.x, sample, (double)t.n / sample, t.d, centre);
+  fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_uncertain, 1, 0u);
+  fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->max_norm, 1, 0u);   // (each selection finds that of the centred rows)
+
+  auto select_chunk = [&](uint32_t i0, uint32_t c) -> ann_status {
+    bf_gather_uncertain_kernel<<<c, 64, 0, t.st>>>(t.q, t.d, s.kb_n, t.k, t.metric, nullptr, list + i0, t.out_dist, nullptr, qg, nullptr, nullptr);
+    const ann_status rc = select_round(t, s, qg, c, centre, ids, dist, places, 0);
+    if (rc != ANN_OK) return rc;
+    bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, nullptr, nullptr, ids, dist, t.out_ids, t.out_dist, nullptr, nullptr, nullptr);
+    bf_next_list_kernel<<<1, 1024, 0, t.st>>>(places, list + i0, state, other);
+    ANN_HIP(hipGetLastError());
+    return ANN_OK;
+  };
+  auto pass_chunk = [&](uint32_t i0, uint32_t c) -> ann_status {
+    fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->most_entries, 1, 0u);
+    bf_gather_uncertain_kernel<<<c, 64, 0, t.st>>>(t.q, t.d, s.kb_n, t.k, t.metric, centre, list + i0, t.out_dist, state, qg, s.bound, s.count);
+    const uint32_t blocks32 = (c + 127) / 128 * 4;
+    const uint64_t units = (uint64_t)blocks32 * s.kb_n * 64;
+    bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, t.st>>>(
+        qg, c, t.d, s.kb_n, blocks32, t.metric == ANN_L2 ? centre : nullptr, s.qfrag, nullptr, nullptr);
+    ScoreArgs a{};
+    a.x = t.x;
+    a.qfrag = s.qfrag;
+    a.rows = t.n;
+    a.d = t.d;
+    a.kb_n = s.kb_n;
+    a.nq = c;
+    a.metric = t.metric;
+    a.bound = s.bound;
+    a.buf = buf;
+    a.count = s.count;
+    a.cap = kRoom;
+    a.centre = centre;
+    ann_status rc = launch_scores(a, s.vec4, t.n_cu, t.st);
+    if (rc != ANN_OK) return rc;
+    bf_entries_to_candidates_kernel<<<c, 256, 0, t.st>>>(buf, s.count, cand, state);
+    uint32_t most = 0;
+    ANN_HIP(hipMemcpyAsync(&most, &state->most_entries, sizeof(most), hipMemcpyDeviceToHost, t.st));
+    ANN_HIP(hipStreamSynchronize(t.st));
+    rc = rerank_device(t.x, t.n, t.d, t.metric, qg, c, cand, most ? most : 1, kRoom, t.k, ids, dist, t.st);
+    if (rc != ANN_OK) return rc;
+    bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, s.bound, s.count, ids, dist, t.out_ids, t.out_dist, state, other, fp32);
+    ANN_HIP(hipGetLastError());
+    return ANN_OK;
+  };
+  ann_status rc = ANN_OK;
+  uint32_t n_fp32 = 0;
+  for (uint32_t pass = 0; n_list > 0 && rc == ANN_OK; ++pass) {
+    if (pass > kMaxPasses) {
+      rc = fp32_for(t, list, n_list);
+      break;
+    }
+    for (uint64_t i0 = 0; i0 < n_list && rc == ANN_OK; i0 += m) {
+      const uint32_t c = (uint32_t)(n_list - i0 < m ? n_list - i0 : m);
+      rc = pass == 0 ? select_chunk((uint32_t)i0, c) : pass_chunk((uint32_t)i0, c);
+    }
+    if (rc != ANN_OK) break;
+    uint32_t left[2] = {0, 0};
+    e = hipMemcpyAsync(left, &state->n_next, sizeof(left), hipMemcpyDeviceToHost, t.st);
+    if (e == hipSuccess) e = hipStreamSynchronize(t.st);
+    if (e != hipSuccess) {
+      rc = hip_fail(e, "hipMemcpyAsync");
+      break;
+    }
+    n_list = left[0];
+    n_fp32 = left[1];
+    fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_next, 1, 0u);
+    uint32_t *was = list;
+    list = other;
+    other = was;
+  }
+  if (rc == ANN_OK && n_fp32 > 0) rc = fp32_for(t, fp32, n_fp32);
+  e = hipStreamSynchronize(t.st);
+  device_free(base);
+  if (rc != ANN_OK) return rc;
+  if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   return ANN_OK;
 }
 
@@ -968,92 +1445,66 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
     while ((double)cap < growth * spread && cap < 8192) cap <<= 1;
   }
   const uint64_t ld = dense ? (n + kSB - 1) / kSB * kSB : first;
-  // queries per round: at most half a GiB of scores and entries
+  // queries per round: at most half a GiB of scores and entries, less if the card has no room
   const uint64_t per_query = ld * 4 + (uint64_t)cap * 8;
   uint64_t round = (512ull << 20) / per_query / 128 * 128;
   if (round < 128) round = 128;
   if (round > nq) round = nq;
-  const uint64_t q32 = (round + 127) / 128 * 4;
-
-  auto up = [](uint64_t v) { return (v + 255) & ~255ull; };
-  const uint64_t b_qfrag = up(q32 * kb_n * 192 * 16), b_scores = up(round * ld * 4), b_buf = up(round * cap * 8), b_bound = up(round * 8),
-                 b_count = up(round * 4), b_cand = up(round * most * 4);
-  unsigned char *base = nullptr;
-  ANN_HIP(device_alloc((void **)&base, b_qfrag + b_scores + b_buf + b_bound + b_count + b_cand + 256));
-  uint4 *qfrag = reinterpret_cast<uint4 *>(base);
-  float *scores = reinterpret_cast<float *>(base + b_qfrag);
-  uint64_t *buf = reinterpret_cast<uint64_t *>(base + b_qfrag + b_scores);
-  uint64_t *bound = reinterpret_cast<uint64_t *>(base + b_qfrag + b_scores + b_buf);
-  uint32_t *count = reinterpret_cast<uint32_t *>(base + b_qfrag + b_scores + b_buf + b_bound);
-  uint32_t *cand = reinterpret_cast<uint32_t *>(base + b_qfrag + b_scores + b_buf + b_bound + b_count);
-  uint32_t *flag = reinterpret_cast<uint32_t *>(base + b_qfrag + b_scores + b_buf + b_bound + b_count + b_cand);
-
-  auto one_round = [&](uint64_t q0, uint32_t m) -> ann_status {
-    const float *qr = q + q0 * d;
-    const uint32_t blocks32 = (m + 127) / 128 * 4;
-    const uint64_t units = (uint64_t)blocks32 * kb_n * 64;
-    bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, st>>>(qr, m, d, kb_n, blocks32, qfrag, flag);
-    ScoreArgs a{};
-    a.x = x;
-    a.qfrag = qfrag;
-    a.d = d;
-    a.kb_n = kb_n;
-    a.nq = m;
-    a.metric = metric;
-    a.ld = (uint32_t)ld;
-    a.bound = bound;
-    a.buf = buf;
-    a.count = count;
-    a.cap = cap;
-    a.flag = flag;
-    auto select_entries = [&](uint32_t *cnt, uint32_t *to, uint32_t up_to) {
-      if (cap <= 2048)
-        bf_select_entries_kernel<8><<<m, kSelThreads, 0, st>>>(buf, cnt, cap, want, up_to, bound, to, flag);
-      else if (cap <= 4096)
-        bf_select_entries_kernel<16><<<m, kSelThreads, 0, st>>>(buf, cnt, cap, want, up_to, bound, to, flag);
-      else
-        bf_select_entries_kernel<32><<<m, kSelThreads, 0, st>>>(buf, cnt, cap, want, up_to, bound, to, flag);
-    };
-    ann_status rc;
-    if (dense) {
-      a.rows = n;
-      a.scores = scores;
-      rc = launch_scores(a, vec4, (uint32_t)n_cu, st);
-      if (rc != ANN_OK) return rc;
-      bf_select_scores_kernel<kSampleRows / kSelThreads><<<dim3(m, (uint32_t)stretches), kSelThreads, 0, st>>>(scores, a.ld, n, 0, want, most, bound, buf);
-      select_entries(nullptr, cand, most);
-    } else {
-      fill_u32_kernel<<<(m + 255) / 256, 256, 0, st>>>(count, m, 0u);
-      double rows = (double)first;
-      for (uint32_t t = 0; t <= samples; ++t, rows *= growth) {
-        const bool last = t == samples;
-        a.rows = last ? n : (t == 0 ? (uint64_t)first : (uint64_t)rows);
-        a.stretch = last ? 0.0 : (double)n / (double)a.rows;
-        a.scores = t == 0 ? scores : nullptr;
-        rc = launch_scores(a, vec4, (uint32_t)n_cu, st);
-        if (rc != ANN_OK) return rc;
-        if (t == 0 && first == kSampleRows)
-          bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, st>>>(scores, a.ld, a.rows, a.stretch, want, most_bound, bound, nullptr);
-        else if (t == 0)
-          bf_select_scores_kernel<2 * kSampleRows / kSelThreads><<<m, kSelThreads, 0, st>>>(scores, a.ld, a.rows, a.stretch, want, most_bound, bound, nullptr);
-        else
-          select_entries(count, last ? cand : nullptr, last ? most : most_bound);
-      }
+  auto parts = [&](uint64_t m, uint64_t (&at)[9]) {
+    const uint64_t size[9] = {(m + 127) / 128 * 4 * kb_n * 192 * 16, m * ld * 4, m * cap * 8, m * 8, m * 4, m * most * 4, m * 4, sizeof(CallState),
+                              (uint64_t)nq * 4};
+    uint64_t total = 0;
+    for (int i = 0; i < 9; ++i) {
+      at[i] = total;
+      total += up256(size[i]);
     }
-    ANN_HIP(hipGetLastError());
-    return rerank_device(x, n, d, metric, qr, m, cand, most, most, k, out_ids + q0 * k, out_dist + q0 * k, st);
+    return total;
   };
+  uint64_t at[9];
+  unsigned char *base = nullptr;
+  hipError_t e = alloc_some((void **)&base, round, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
+  if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  parts(round, at);
+  CallState *const state = reinterpret_cast<CallState *>(base + at[7]);
+  uint32_t *const uncertain = reinterpret_cast<uint32_t *>(base + at[8]);
+  Selection s{};
+  s.want = want;
+  s.most = most;
+  s.most_bound = most_bound;
+  s.kb_n = kb_n;
+  s.cap = cap;
+  s.first = first;
+  s.samples = samples;
+  s.stretches = stretches;
+  s.ld = ld;
+  s.vec4 = vec4;
+  s.dense = dense;
+  s.growth = growth;
+  s.qfrag = reinterpret_cast<uint4 *>(base + at[0]);
+  s.scores = reinterpret_cast<float *>(base + at[1]);
+  s.buf = reinterpret_cast<uint64_t *>(base + at[2]);
+  s.bound = reinterpret_cast<uint64_t *>(base + at[3]);
+  s.count = reinterpret_cast<uint32_t *>(base + at[4]);
+  s.cand = reinterpret_cast<uint32_t *>(base + at[5]);
+  s.below = reinterpret_cast<float *>(base + at[6]);
+  s.state = state;
+  const Truth t{x, n, d, q, k, metric, out_ids, out_dist, (uint32_t)n_cu, st};
 
-  fill_u32_kernel<<<1, 64, 0, st>>>(flag, 1, 0u);
+  fill_u32_kernel<<<1, 64, 0, st>>>(&state->n_uncertain, sizeof(CallState) / 4, 0u);
   ann_status rc = ANN_OK;
-  for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += round) rc = one_round(q0, (uint32_t)(nq - q0 < round ? nq - q0 : round));
-  uint32_t raised = 0;
-  hipError_t e = rc == ANN_OK ? hipMemcpyAsync(&raised, flag, sizeof(raised), hipMemcpyDeviceToHost, st) : hipSuccess;
+  for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += round) {
+    const uint32_t m = (uint32_t)(nq - q0 < round ? nq - q0 : round);
+    rc = select_round(t, s, q + q0 * d, m, nullptr, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
+  }
+  uint32_t found[2] = {0, 0};   // uncertain queries, far rows
+  e = rc == ANN_OK ? hipMemcpyAsync(found, state, sizeof(found), hipMemcpyDeviceToHost, st) : hipSuccess;
   const hipError_t e2 = hipStreamSynchronize(st);
+  if (rc == ANN_OK && e != hipSuccess) rc = hip_fail(e, "hipMemcpyAsync");
+  if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipStreamSynchronize");
+  if (rc == ANN_OK && found[1] > 0)
+    rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
+  else if (rc == ANN_OK && found[0] > 0)
+    rc = settle(t, s, round, uncertain, found[0]);
   device_free(base);
-  if (rc != ANN_OK) return rc;
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
-  if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
-  if (raised) return bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
-  return ANN_OK;
+  return rc;
 }

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64 * W) void rerank_kernel(const float *__restrict_
                                                     uint32_t cand_stride, uint32_t k, uint32_t *__restrict__ out_ids,
                                                     float *__restrict__ out_dist,
                                                     const float *__restrict__ cand_keys, uint32_t n_min, float gamma,
-                                                    uint32_t *__restrict__ out_n) {
+                                                    uint32_t *__restrict__ out_n, Certainty certain) {
   extern __shared__ uint64_t smem64[];
   float *qs = reinterpret_cast<float *>(smem64);             // [d], 16-byte aligned
   uint64_t *list = smem64 + ((d + 3) / 4) * 2;               // [n_max]
@@ -103,6 +103,7 @@ __global__ __launch_bounds__(64 * W) void rerank_kernel(const float *__restrict_
     ids_s[i] = v >= n ? kNone : v;   // (padding is 0xFFFFFFFF >= n)
   }
   __syncthreads();
+  const float below = certain.below ? certain.below[qi] : 0.0f;
   uint32_t n_valid = 0;   // candidates that name a node: their entries are kept in order at the front of the list
   // the row sums of one round (G candidates side by side) go to the list; acc is this lane's share of candidate v,
   // which is candidate ci (several wavefronts: its place in the list)
@@ -222,6 +223,11 @@ __global__ __launch_bounds__(64 * W) void rerank_kernel(const float *__restrict_
     append(ci, v, acc);
   }
   __syncthreads();
+  // the k-th distance, told by one thread: the query is listed if a row that is no candidate might be nearer
+  auto check = [&](float kth) {
+    if (certain.below == nullptr) return;
+    if (!(kth < below || below == INFINITY)) certain.list[atomicAdd(certain.n_listed, 1u)] = certain.first_query + qi;
+  };
   if constexpr (W > 1) {
     // padding (all-ones) ranks last, in order of position: as many lanes as the query has entries
     for (uint32_t i = threadIdx.x; i < n_cand; i += kWave * W) {
@@ -233,25 +239,31 @@ __global__ __launch_bounds__(64 * W) void rerank_kernel(const float *__restrict_
       }
       if (rank < k) {
         out_ids[(uint64_t)qi * k + rank] = (uint32_t)e;
-        out_dist[(uint64_t)qi * k + rank] = e == ~0ull ? INFINITY : unorder_f32((uint32_t)(e >> 32));
+        const float dist = e == ~0ull ? INFINITY : unorder_f32((uint32_t)(e >> 32));
+        out_dist[(uint64_t)qi * k + rank] = dist;
+        if (rank == k - 1) check(dist);
       }
     }
     for (uint32_t r = n_cand + threadIdx.x; r < k; r += kWave * W) {
       out_ids[(uint64_t)qi * k + r] = kNone;
       out_dist[(uint64_t)qi * k + r] = INFINITY;
+      if (r == k - 1) check(INFINITY);
     }
     return;
   }
   // only the entries that name a node are ranked (padding sorts last anyway)
   rank_all(list, n_valid, lane, [&](uint32_t rank, uint32_t, uint64_t e) {
     if (rank < k) {
+      const float dist = unorder_f32((uint32_t)(e >> 32));
       out_ids[(uint64_t)qi * k + rank] = (uint32_t)e;
-      out_dist[(uint64_t)qi * k + rank] = unorder_f32((uint32_t)(e >> 32));
+      out_dist[(uint64_t)qi * k + rank] = dist;
+      if (rank == k - 1) check(dist);
     }
   });
   for (uint32_t r = n_valid + lane; r < k; r += kWave) {
     out_ids[(uint64_t)qi * k + r] = kNone;
     out_dist[(uint64_t)qi * k + r] = INFINITY;
+    if (r == k - 1) check(INFINITY);
   }
 }
 
@@ -343,8 +355,8 @@ template <bool VEC4, int W>
 static void launch_rerank(uint32_t lpr, const float *X, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
                           uint64_t n, const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k,
                           uint32_t *out_ids, float *out_dist, size_t smem, hipStream_t st, const float *cand_keys,
-                          uint32_t n_min, float gamma, uint32_t *out_n) {
-#define ANN_RR(L) rerank_kernel<L, VEC4, W><<<nq, 64 * W, smem, st>>>(X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, cand_keys, n_min, gamma, out_n)
+                          uint32_t n_min, float gamma, uint32_t *out_n, const Certainty &certain) {
+#define ANN_RR(L) rerank_kernel<L, VEC4, W><<<nq, 64 * W, smem, st>>>(X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, cand_keys, n_min, gamma, out_n, certain)
   switch (lpr) {
     case 8: ANN_RR(8); break;
     case 16: ANN_RR(16); break;
@@ -358,7 +370,7 @@ static void launch_rerank(uint32_t lpr, const float *X, uint32_t d, uint32_t met
 ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
                          const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k, uint32_t *out_ids,
                          float *out_dist, hipStream_t st, const float *cand_keys, uint32_t n_min, float gamma,
-                         uint32_t *out_n) {
+                         uint32_t *out_n, const Certainty &certain) {
   // four 16-byte pieces of a row per lane: 128 dimensions -> 8 lanes per row, 8 rows side by side
   uint32_t chunks = (d + 3) / 4, lpr = 8;
   while (lpr * 4 < chunks && lpr < 64) lpr <<= 1;
@@ -367,7 +379,7 @@ ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric
   // requests together (three rounds).
   const bool team = nq <= kTeamQueries && n_cand > 3 * (kWave / lpr) && n_cand <= 1024;
   const size_t smem = (size_t)n_cand * (sizeof(uint64_t) + (team ? sizeof(uint32_t) : 0)) + (size_t)((d + 3) / 4) * 16;
-#define ANN_LR(V, W) launch_rerank<V, W>(lpr, X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, smem, st, cand_keys, n_min, gamma, out_n)
+#define ANN_LR(V, W) launch_rerank<V, W>(lpr, X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, smem, st, cand_keys, n_min, gamma, out_n, certain)
   if (d % 4 == 0) {
     if (team)
       ANN_LR(true, 4);

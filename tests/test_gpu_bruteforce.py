@@ -62,6 +62,18 @@ def test_equal_rows(H):
     assert np.allclose(gdist, odist, rtol=1e-6)
 
 
+@pytest.mark.parametrize("n,d,nq,k,offset,metric", [
+    (100_000, 128, 100, 10, 200.0, oracle.L2), (100_000, 128, 100, 10, 300.0, oracle.L2), (200_000, 50, 60, 10, 1000.0, oracle.L2),
+    (9000, 64, 150, 100, 3000.0, oracle.L2), (60_000, 96, 40, 256, 500.0, oracle.L2), (100_000, 33, 70, 10, 2000.0, oracle.IP)])
+def test_vectors_far_from_the_origin(H, n, d, nq, k, offset, metric):
+    """Norms and products so large that the scores' rounding exceeds the gaps between neighbours: every true
+    neighbour is found all the same (distances to the oracle's of the same rank within the rounding of one)."""
+    rng = np.random.default_rng(int(offset) + d)
+    common = (offset * (1.0 + 0.1 * rng.standard_normal(d))).astype(np.float32)
+    X, Q = _points(n, d, 21) + common, _points(nq, d, 22) + (common if metric == oracle.L2 else 0.0)
+    _check(H, X.astype(np.float32), Q.astype(np.float32), k, metric)
+
+
 def test_infinite_products(H):
     """An infinite coordinate in an inner product: infinitely near or far, as fp32 products have it."""
     X, Q = np.abs(_points(3000, 24, 8)) + 0.1, np.abs(_points(40, 24, 9)) + 0.1
@@ -86,3 +98,69 @@ def test_rows_that_are_not_aligned(H):
     ann.ann_bruteforce_topk(buf[1:], n, d, H.dev(Q), nq, k, ann.L2, ids, dist, H.stream_ptr())
     oid, odist = oracle.bruteforce_topk(X, Q, k, metric=oracle.L2)
     H.check_rerank(H.as_u32(ids), dist.cpu().numpy(), oid, odist.astype(np.float32), rel=1e-6)
+
+
+def _sampled_rows(n, rows):
+    """Rows of a sample of `rows` rows (bruteforce.hip, sample_row)."""
+    j = np.arange(rows, dtype=np.uint64)
+    m32 = np.uint64(0xFFFFFFFF)
+    h = j * np.uint64(0x9E3779B1) & m32
+    h = (h ^ (h >> np.uint64(15))) * np.uint64(0x85EBCA77) & m32
+    h ^= h >> np.uint64(13)
+    stretch = n / rows
+    begin, end = (j * stretch).astype(np.uint64), ((j + np.uint64(1)) * stretch).astype(np.uint64)
+    return (begin + (h * (end - begin) >> np.uint64(32))).astype(np.int64)
+
+
+@pytest.mark.parametrize("d,nq,k,metric", [(16, 70, 10, oracle.L2), (18, 33, 100, oracle.L2), (13, 130, 10, oracle.IP), (32, 9, 256, oracle.L2)])
+def test_sample_of_far_rows(H, d, nq, k, metric):
+    """Every sampled row is far and the others are near: more entries reach the sample's bound than there is room for."""
+    n = 20_000
+    X, Q = _points(n, d, 31), _points(nq, d, 32)
+    far = _sampled_rows(n, 4096)
+    assert np.unique(far).size == 4096
+    if metric == oracle.L2:
+        X[far] += 100.0
+    else:
+        Q = np.abs(Q)
+        X[far] = -np.abs(X[far]) - 5.0
+    _check(H, X, Q, k, metric)
+
+
+@pytest.mark.parametrize("d,nq,k,metric", [(18, 140, 100, oracle.L2), (16, 30, 10, oracle.L2), (7, 50, 256, oracle.L2), (12, 50, 100, oracle.IP)])
+def test_more_equal_rows_than_are_reevaluated(H, d, nq, k, metric):
+    """Three points, 10,000 rows each, more than a pass takes up: the smallest ids win."""
+    n = 30_000
+    X = np.repeat(_points(3, d, 41), n // 3, axis=0)
+    X = np.ascontiguousarray(X[np.random.default_rng(42).permutation(n)])
+    Q = _points(nq, d, 43)
+    gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
+    oid, odist = oracle.bruteforce_topk(X, Q, k, metric=metric)
+    assert (gid == oid).all()
+    assert np.allclose(gdist, odist, rtol=1e-6)
+
+
+def _check_but(H, X, Q, k, metric, rows, queries, gid, gdist):
+    """As _check, for queries not in `queries`, against an oracle that does not see `rows`."""
+    keep, ask = np.ones(len(X), bool), np.ones(len(Q), bool)
+    keep[rows], ask[queries] = False, False
+    oid, odist = oracle.bruteforce_topk(X[keep], Q[ask], k, metric=metric)
+    H.check_rerank(gid[ask], gdist[ask], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
+
+
+@pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
+def test_more_queries_than_one_round_takes(H, metric):
+    """16,384 queries to a round here; uncertain queries and a row without a norm in both rounds."""
+    n, d, nq, k = 20_000, 6, 17_000, 10
+    X, Q = _points(n, d, 71), _points(nq, d, 72)
+    X[19_000:19_040] = X[18_000]
+    Q[[3, 16_800]] = X[18_000] * (1.0 if metric == oracle.L2 else 50.0)
+    skip = [4, 16_700]
+    Q[skip, 1] = np.inf
+    rows = []
+    if metric == oracle.IP:
+        rows = [123]
+        X[123, 2] = np.inf
+        Q[:, 2] = -np.abs(Q[:, 2]) - 0.01
+    gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
+    _check_but(H, X, Q, k, metric, rows, skip, gid, gdist)
