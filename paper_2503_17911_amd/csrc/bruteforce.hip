@@ -330,12 +330,14 @@ __global__ __launch_bounds__(256) void bf_split_queries_kernel(const float *__re
 }
 
 // What a call learns on the device and the host reads at its end (or between steps).
+constexpr uint32_t kFarRows = 3840;   // (with 256 results they fit the 4,096 candidates of a rerank)
 struct CallState {
   uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
-  uint32_t far_rows;      // inner product: not zero if a row's squared norm is no float
+  uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
   uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
   uint32_t most_entries;  // of a query in the last pass over uncertain queries
   uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
+  uint32_t far_row[kFarRows];
 };
 
 struct ScoreArgs {
@@ -353,6 +355,7 @@ struct ScoreArgs {
   uint32_t cap;
   const float *centre;     // [d] subtracted from every row (kernels with CENTRE)
   CallState *state;        // inner product: norms are noted here (NULL: not in this pass)
+  bool list_far;           // and the rows without one listed
 };
 
 // Row of x that is row j of a sample: a random one of the j-th stretch of rows
@@ -469,15 +472,17 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
       sq[i] = sq_low[i] = 0.f;
       if (tid % 8 == 0) {
         // Rows whose squared norm is no float are left out of the scores.  L2: they are infinitely far.  Inner
-        // product: they may be near (the fp32 kernel takes over).
+        // product: with a NaN they have no score; the others may be near, and are listed for the exact stage.
         const uint64_t r = tile * kSB + s_row + 32 * i;
         const bool in = r < a.rows && t < INFINITY;
         xn_s[tile & 1][s_row + 32 * i] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
         if (a.metric != ANN_L2 && a.state != nullptr) {
-          if (in)
+          if (in) {
             max_norm = fmaxf(max_norm, t);
-          else if (r < a.rows)
-            atomicOr(&a.state->far_rows, 1u);
+          } else if (r < a.rows && t == INFINITY && qt == 0 && a.list_far) {
+            const uint32_t at = atomicAdd(&a.state->far_rows, 1u);
+            if (at < kFarRows) a.state->far_row[at] = (uint32_t)r;
+          }
         }
       }
     }
@@ -1156,6 +1161,29 @@ __global__ __launch_bounds__(64) void bf_scatter_uncertain_kernel(const uint32_t
   }
 }
 
+// Inner product with rows whose squared norm is no float: they are no part of
+// the passes.  One wavefront per query: its results so far, and behind them those of
+// these rows that fp32 products find near (neither a NaN nor infinitely far).
+__global__ __launch_bounds__(64) void bf_far_rows_kernel(const float *__restrict__ x, uint32_t d, const float *__restrict__ Q, uint32_t k,
+                                                         const CallState *__restrict__ state, uint32_t n_far, const uint32_t *__restrict__ out_ids,
+                                                         uint32_t *__restrict__ cand) {
+  const uint32_t q = blockIdx.x, width = k + n_far;
+  const uint32_t *mine = out_ids + (uint64_t)q * k;
+  uint32_t *to = cand + (uint64_t)q * width;
+  for (uint32_t j = lane_id(); j < k; j += kWave) to[j] = mine[j];
+  for (uint32_t f = 0; f < n_far; ++f) {
+    const uint32_t row = state->far_row[f];
+    float acc = 0.0f;
+    for (uint32_t j = lane_id(); j < d; j += kWave) acc = fmaf(x[(uint64_t)row * d + j], Q[(uint64_t)q * d + j], acc);
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) acc += __int_as_float(xor_lane_i32(__float_as_int(acc), m));
+    bool there = false;   // (bf_tile_kernel knows these rows)
+    for (uint32_t j = lane_id(); j < k; j += kWave) there = there || mine[j] == row;
+    there = __ballot(there) != 0;
+    if (lane_id() == 0) to[k + f] = -acc < INFINITY && !there ? row : ANN_PAD_ID;
+  }
+}
+
 // Device memory for `most` items or, when there is not that much, half as many and so on down to `least`.
 template <typename Bytes>
 static hipError_t alloc_some(void **ptr, uint64_t &items, uint64_t least, Bytes bytes) {
@@ -1196,7 +1224,7 @@ struct Selection {
 };
 
 // One round: the k nearest rows of the m queries at qr.
-static ann_status select_round(const Truth &t, const Selection &s, const float *qr, uint32_t m, const float *centre,
+static ann_status select_round(const Truth &t, const Selection &s, const float *qr, uint32_t m, const float *centre, bool list_far,
                                uint32_t *out_ids, float *out_dist, uint32_t *uncertain, uint32_t first_query) {
   const uint32_t blocks32 = (m + 127) / 128 * 4;
   const uint64_t units = (uint64_t)blocks32 * s.kb_n * 64;
@@ -1215,6 +1243,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
   a.count = s.count;
   a.cap = s.cap;
   a.centre = centre;
+  a.list_far = list_far;
   const CertainArgs certain{qr, centre, t.d, s.kb_n, t.metric, s.state, s.below};
   auto select_entries = [&](uint32_t *cnt, uint32_t *to, uint32_t up_to) {
     if (s.cap <= 2048)
@@ -1320,7 +1349,7 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
 
   auto select_chunk = [&](uint32_t i0, uint32_t c) -> ann_status {
     bf_gather_uncertain_kernel<<<c, 64, 0, t.st>>>(t.q, t.d, s.kb_n, t.k, t.metric, nullptr, list + i0, t.out_dist, nullptr, qg, nullptr, nullptr);
-    const ann_status rc = select_round(t, s, qg, c, centre, ids, dist, places, 0);
+    const ann_status rc = select_round(t, s, qg, c, centre, false, ids, dist, places, 0);
     if (rc != ANN_OK) return rc;
     bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, nullptr, nullptr, ids, dist, t.out_ids, t.out_dist, nullptr, nullptr, nullptr);
     bf_next_list_kernel<<<1, 1024, 0, t.st>>>(places, list + i0, state, other);
@@ -1390,6 +1419,28 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   device_free(base);
   if (rc != ANN_OK) return rc;
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+  return ANN_OK;
+}
+
+// Adds the listed far rows to every query's results.
+static ann_status add_far_rows(const Truth &t, uint32_t nq, uint32_t n_far, const CallState *state) {
+  const uint32_t width = t.k + n_far;
+  uint64_t m = nq;
+  const uint64_t fit = (256ull << 20) / (width * 4);
+  if (m > fit) m = fit;
+  uint32_t *cand = nullptr;
+  const hipError_t e = alloc_some((void **)&cand, m, 1, [&](uint64_t c) { return c * width * 4; });
+  if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  ann_status rc = ANN_OK;
+  for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += m) {
+    const uint32_t c = (uint32_t)(nq - q0 < m ? nq - q0 : m);
+    bf_far_rows_kernel<<<c, 64, 0, t.st>>>(t.x, t.d, t.q + q0 * t.d, t.k, state, n_far, t.out_ids + q0 * t.k, cand);
+    rc = rerank_device(t.x, t.n, t.d, t.metric, t.q + q0 * t.d, c, cand, width, width, t.k, t.out_ids + q0 * t.k, t.out_dist + q0 * t.k, t.st);
+  }
+  const hipError_t e2 = hipStreamSynchronize(t.st);
+  device_free(cand);
+  if (rc != ANN_OK) return rc;
+  if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
 }
 
@@ -1490,21 +1541,23 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   s.state = state;
   const Truth t{x, n, d, q, k, metric, out_ids, out_dist, (uint32_t)n_cu, st};
 
-  fill_u32_kernel<<<1, 64, 0, st>>>(&state->n_uncertain, sizeof(CallState) / 4, 0u);
+  fill_u32_kernel<<<1, 64, 0, st>>>(&state->n_uncertain, 6, 0u);   // (the counters in front of the list of rows)
   ann_status rc = ANN_OK;
   for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += round) {
     const uint32_t m = (uint32_t)(nq - q0 < round ? nq - q0 : round);
-    rc = select_round(t, s, q + q0 * d, m, nullptr, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
+    rc = select_round(t, s, q + q0 * d, m, nullptr, q0 == 0, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
   }
   uint32_t found[2] = {0, 0};   // uncertain queries, far rows
   e = rc == ANN_OK ? hipMemcpyAsync(found, state, sizeof(found), hipMemcpyDeviceToHost, st) : hipSuccess;
   const hipError_t e2 = hipStreamSynchronize(st);
   if (rc == ANN_OK && e != hipSuccess) rc = hip_fail(e, "hipMemcpyAsync");
   if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipStreamSynchronize");
-  if (rc == ANN_OK && found[1] > 0)
+  if (rc == ANN_OK && found[1] > kFarRows) {
     rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
-  else if (rc == ANN_OK && found[0] > 0)
-    rc = settle(t, s, round, uncertain, found[0]);
+  } else if (rc == ANN_OK) {
+    if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0]);
+    if (rc == ANN_OK && found[1] > 0) rc = add_far_rows(t, nq, found[1], state);
+  }
   device_free(base);
   return rc;
 }

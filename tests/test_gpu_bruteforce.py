@@ -148,6 +148,50 @@ def _check_but(H, X, Q, k, metric, rows, queries, gid, gdist):
     H.check_rerank(gid[ask], gdist[ask], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
 
 
+@pytest.mark.parametrize("n,nq", [(5000, 200), (25_000, 200)])
+@pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
+def test_rows_and_queries_that_are_no_numbers(H, n, nq, metric):
+    """A row with a NaN is nobody's neighbour; a query with one has none; an infinite coordinate of a query
+    concerns that query alone."""
+    d, k = 20, 9
+    X, Q = _points(n, d, 51), _points(nq, d, 52)
+    X[[5, 4000], [3, 7]] = np.nan
+    Q[11, 2], Q[17, 4], Q[150, 19] = np.nan, np.inf, 3.4e38
+    gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
+    _check_but(H, X, Q, k, metric, [5, 4000], [11, 17, 150], gid, gdist)
+    assert (gid[11] == 0xFFFFFFFF).all() and np.isposinf(gdist[11]).all()
+    if metric == oracle.IP:
+        near = np.flatnonzero(X[:, 4] > 0)
+        assert (gid[17] == near[~np.isin(near, [5, 4000])][:k]).all() and np.isneginf(gdist[17]).all()
+    else:
+        assert np.isposinf(gdist[17]).all()
+
+
+@pytest.mark.parametrize("n,nq,n_far", [(3000, 40, 300), (40_000, 300, 3), (40_000, 70, 3840), (40_000, 70, 3841)])
+def test_rows_without_a_finite_norm(H, n, nq, n_far):
+    """Inner product: infinite coordinates, and finite ones whose squares are not, are as near or far as their products say."""
+    d, k = 24, 12
+    X, Q = np.abs(_points(n, d, 61)) + 0.1, np.abs(_points(nq, d, 62)) + 0.1
+    far = np.sort(np.random.default_rng(63).permutation(n)[:n_far])
+    X[far[0::3], 3] = -np.inf
+    X[far[1::3], 5] = 2e25
+    X[far[2::3], 7] = np.inf
+    gid, gdist = H.gpu_bruteforce(X, Q, k, oracle.IP)
+    inf, big = far[2::3], far[1::3]
+    n_inf = min(k, len(inf))
+    assert (gid[:, :n_inf] == inf[:n_inf]).all() and np.isneginf(gdist[:, :n_inf]).all()
+    exact = -(X[big].astype(np.float64) @ Q.astype(np.float64).T).T.astype(np.float32)
+    order = np.lexsort((np.broadcast_to(big, exact.shape), exact))[:, :k - n_inf]
+    n_big = order.shape[1]
+    assert np.allclose(gdist[:, n_inf:n_inf + n_big], np.take_along_axis(exact, order, 1), rtol=1e-6)
+    rest = k - n_inf - n_big
+    if rest:
+        keep = np.ones(n, bool)
+        keep[far] = False
+        oid, odist = oracle.bruteforce_topk(X[keep], Q, rest, metric=oracle.IP)
+        H.check_rerank(gid[:, -rest:], gdist[:, -rest:], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
+
+
 @pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
 def test_more_queries_than_one_round_takes(H, metric):
     """16,384 queries to a round here; uncertain queries and a row without a norm in both rounds."""
@@ -164,3 +208,28 @@ def test_more_queries_than_one_round_takes(H, metric):
         Q[:, 2] = -np.abs(Q[:, 2]) - 0.01
     gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
     _check_but(H, X, Q, k, metric, rows, skip, gid, gdist)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_one_row_that_is_no_number_costs_little(H, value):
+    """Inner product: the other rows' products stay on the bf16 matrix cores (6 times the time otherwise)."""
+    import time
+    import torch
+    import paper_2503_17911_amd as ann
+    n, d, nq, k = 300_000, 64, 4000, 10
+    g = torch.Generator(device=H.DEV).manual_seed(1)
+    X, Q = torch.randn(n, d, generator=g, device=H.DEV), torch.randn(nq, d, generator=g, device=H.DEV)
+    ids, dist = torch.empty((nq, k), dtype=torch.int32, device=H.DEV), torch.empty((nq, k), device=H.DEV)
+
+    def best():
+        took = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ann.ann_bruteforce_topk(X, n, d, Q, nq, k, ann.IP, ids, dist, H.stream_ptr())
+            took.append(time.perf_counter() - t)
+        return min(took)
+
+    plain = best()
+    X[1234, 5] = value
+    assert best() < 2.5 * plain
