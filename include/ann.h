@@ -235,7 +235,7 @@ typedef struct {
  * ann_sq_level and, if norm_term != NULL, the squared norms of the decoded rows
  * (fp64 accumulation in dimension order, rounded once).
  *   x [n][d] fp32; bits 8 or 4 (d even for 4).  Both calls allocate a small
- *   temporary and synchronise the stream before returning.
+ *   temporary (see ann_trim_memory) and synchronise the stream before returning.
  */
 ann_status ann_sq_train(const float *x, uint64_t n, uint32_t d, uint32_t bits, float *lo, float *delta,
                         void *stream);
@@ -263,6 +263,16 @@ ann_status ann_sq_encode(const float *x, uint64_t n, uint32_t d, uint32_t bits, 
  */
 ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index **out);
 ann_status ann_free_index(ann_index *index); /* synchronises the device; NULL is a no-op */
+
+/*
+ * Device memory that indexes and temporaries have given up is kept for the next
+ * request of this library (the driver clears freed memory before it hands it out
+ * again, which takes longer than building an index): up to 2 GiB and 64 blocks
+ * per process, given back oldest first beyond that and altogether when an
+ * allocation of this library fails.  ann_trim_memory gives all of it back now,
+ * for other allocators in the process.  From any thread; never fails.
+ */
+ann_status ann_trim_memory(void);
 
 /*
  * Size the folded-query workspaces of `stream` (every code level of the index)
@@ -455,7 +465,8 @@ ann_status ann_rerank_adaptive(ann_index *index, const float *q, uint32_t nq, co
  *   x [n][d], q [nq][d] fp32; out_ids/out_dist [nq][k]; k <= 256, d <= 2048,
  *   n < 2^31.  Rows are read 16 bytes at a time if d is a multiple of 4 and x is
  *   16-byte aligned; any d and k within the limits work.
- * Allocates temporaries and synchronises the stream before returning.
+ * Allocates temporaries (about half a GiB for large batches, less if the device
+ * has no room; see ann_trim_memory) and synchronises the stream before returning.
  */
 ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d, const float *q, uint32_t nq, uint32_t k,
                                uint32_t metric, uint32_t *out_ids, float *out_dist, void *stream);

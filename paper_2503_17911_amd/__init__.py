@@ -28,7 +28,7 @@ DESC_QUERY_15BIT = 4
 OK, EINVAL, ENOMEM, EDEVICE, EUNSUPPORTED, ECAPACITY = range(6)
 _STATUS_NAMES = ["ANN_OK", "ANN_EINVAL", "ANN_ENOMEM", "ANN_EDEVICE", "ANN_EUNSUPPORTED", "ANN_ECAPACITY"]
 
-EXPORTED_SYMBOLS = ["ann_sq_train", "ann_sq_train_truncated", "ann_sq_encode", "ann_upload_index", "ann_free_index", "ann_query_prep",
+EXPORTED_SYMBOLS = ["ann_sq_train", "ann_sq_train_truncated", "ann_sq_encode", "ann_upload_index", "ann_free_index", "ann_trim_memory", "ann_query_prep",
                     "ann_search_batch", "ann_rescore", "ann_rerank", "ann_rerank_adaptive", "ann_bruteforce_topk", "ann_build_entry_table",
                     "ann_entry_scan", "ann_build_prs", "ann_build_prs_ratio", "ann_build_row_norms", "ann_schedule_queries", "ann_reserve_workspace",
                     "ann_search_batch_static", "ann_default_expansions_per_step", "ann_last_error", "ann_version"]
@@ -74,6 +74,7 @@ def _load_library() -> ctypes.CDLL:
     lib.ann_sq_encode.argtypes = [vp, u64, u32, u32, vp, vp, vp, vp, vp]
     lib.ann_upload_index.argtypes = [ctypes.POINTER(IndexDesc), vp, ctypes.POINTER(vp)]
     lib.ann_free_index.argtypes = [vp]
+    lib.ann_trim_memory.argtypes = []
     lib.ann_query_prep.argtypes = [vp, u32, vp, u32, vp, vp, vp, vp]
     lib.ann_search_batch.argtypes = [vp, vp, u32, ctypes.POINTER(SearchParams), vp, u32, vp, vp, vp, vp, vp]
     lib.ann_search_batch_static.argtypes = lib.ann_search_batch.argtypes
@@ -167,6 +168,10 @@ def ann_upload_index(*, n, d, degree, metric, vectors, levels, adjacency, entry_
 
 def ann_free_index(index):
     _check(_lib.ann_free_index(index))
+
+
+def ann_trim_memory():
+    _check(_lib.ann_trim_memory())
 
 
 def ann_query_prep(index, level, q, nq, t, s, qlo, stream=None):

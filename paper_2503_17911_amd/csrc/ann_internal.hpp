@@ -87,10 +87,11 @@ ann_status hip_fail(hipError_t e, const char *what);
 
 // Device memory for index arrays, workspaces and temporaries (host.hip): hipMalloc
 // and hipFree with freed blocks kept for the next request, up to 2 GiB per process.
-// device_free needs what hipFree enforces: nothing enqueued on the device uses
-// the block any more.  (NULL is a no-op.)
+// idle: the caller knows that nothing enqueued on the device uses the block any
+// more; without that (a synchronisation failed) it is hipFree's to wait.  (NULL is
+// a no-op.)
 hipError_t device_alloc(void **ptr, size_t bytes);
-void device_free(void *ptr);
+void device_free(void *ptr, bool idle);
 
 // Exhaustive search: what the rerank kernel needs to list the queries whose k-th
 // distance does not lie below every row that is no candidate.

@@ -35,6 +35,7 @@
 
 #include "ann_internal.hpp"
 #include "device_utils.hpp"
+#include "kept_blocks.hpp"
 
 namespace ann {
 
@@ -985,7 +986,7 @@ static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const 
   ann_status rc = e == hipSuccess ? rerank_device(x, n, d, metric, q, nq, cand, slabs * kp, slabs * kp, k, out_ids, out_dist, st)
                                   : hip_fail(e, "brute-force tile kernel launch");
   const hipError_t e2 = hipStreamSynchronize(st);
-  device_free(cand);
+  device_free(cand, e2 == hipSuccess);
   if (rc != ANN_OK) return rc;
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
@@ -1184,15 +1185,17 @@ __global__ __launch_bounds__(64) void bf_far_rows_kernel(const float *__restrict
   }
 }
 
-// Device memory for `most` items or, when there is not that much, half as many and so on down to `least`.
+// Device memory for `items` of something or, when there is not that much, for fewer.
 template <typename Bytes>
 static hipError_t alloc_some(void **ptr, uint64_t &items, uint64_t least, Bytes bytes) {
-  for (;;) {
-    const hipError_t e = device_alloc(ptr, bytes(items));
-    if (e != hipErrorOutOfMemory || items <= least) return e;
-    (void)hipGetLastError();
-    items = items / 2 > least ? items / 2 : least;
-  }
+  return alloc_some(
+      items, least, bytes,
+      [ptr](size_t b) {
+        const hipError_t e = device_alloc(ptr, b);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
+      },
+      hipErrorOutOfMemory);
 }
 
 struct Truth {
@@ -1307,7 +1310,7 @@ static ann_status fp32_for(const Truth &t, const uint32_t *list, uint32_t m_all)
       bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, nullptr, nullptr, ids, dist, t.out_ids, t.out_dist, nullptr, nullptr, nullptr);
   }
   const hipError_t e1 = hipGetLastError(), e2 = hipStreamSynchronize(t.st);
-  device_free(base);
+  device_free(base, e2 == hipSuccess);
   if (rc != ANN_OK) return rc;
   if (e1 != hipSuccess) return hip_fail(e1, "fp32 kernel for uncertain queries");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
@@ -1416,7 +1419,7 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   }
   if (rc == ANN_OK && n_fp32 > 0) rc = fp32_for(t, fp32, n_fp32);
   e = hipStreamSynchronize(t.st);
-  device_free(base);
+  device_free(base, e == hipSuccess);
   if (rc != ANN_OK) return rc;
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   return ANN_OK;
@@ -1438,7 +1441,7 @@ static ann_status add_far_rows(const Truth &t, uint32_t nq, uint32_t n_far, cons
     rc = rerank_device(t.x, t.n, t.d, t.metric, t.q + q0 * t.d, c, cand, width, width, t.k, t.out_ids + q0 * t.k, t.out_dist + q0 * t.k, t.st);
   }
   const hipError_t e2 = hipStreamSynchronize(t.st);
-  device_free(cand);
+  device_free(cand, e2 == hipSuccess);
   if (rc != ANN_OK) return rc;
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
@@ -1552,12 +1555,14 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   const hipError_t e2 = hipStreamSynchronize(st);
   if (rc == ANN_OK && e != hipSuccess) rc = hip_fail(e, "hipMemcpyAsync");
   if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipStreamSynchronize");
+  bool idle = e2 == hipSuccess;
   if (rc == ANN_OK && found[1] > kFarRows) {
     rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
   } else if (rc == ANN_OK) {
     if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0]);
     if (rc == ANN_OK && found[1] > 0) rc = add_far_rows(t, nq, found[1], state);
+    if (rc != ANN_OK) idle = hipStreamSynchronize(st) == hipSuccess;
   }
-  device_free(base);
+  device_free(base, idle);
   return rc;
 }

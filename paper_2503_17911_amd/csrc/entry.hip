@@ -285,9 +285,9 @@ ann_status ann_build_entry_table(ann_index *index, uint32_t n_pivots, void *stre
   if (!index) return fail(ANN_EINVAL, "ann_build_entry_table: index is NULL");
   if (n_pivots == 0 || n_pivots > index->n) return fail(ANN_EINVAL, "ann_build_entry_table: n_pivots must be in [1, n]");
   ANN_HIP(hipDeviceSynchronize());
-  device_free(index->pivot_codes);
-  device_free(index->pivot_norm);
-  device_free(index->pivot_ids);
+  device_free(index->pivot_codes, true);
+  device_free(index->pivot_norm, true);
+  device_free(index->pivot_ids, true);
   index->pivot_codes = nullptr;
   index->pivot_norm = nullptr;
   index->pivot_ids = nullptr;

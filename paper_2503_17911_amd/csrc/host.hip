@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "ann_internal.hpp"
+#include "kept_blocks.hpp"
 
 namespace ann {
 
@@ -30,31 +31,22 @@ ann_status hip_fail(hipError_t e, const char *what) {
 // a program that uploads and frees indexes (or runs exhaustive searches) one
 // after the other soon waits for that in every hipFree - 20 ms for the 1.1 GB of a
 // 200,000 x 960 index, where the whole build takes 3 - besides about 0.8 ms for
-// unmapping.  So freed blocks are kept, at most kKeepBytes and kKeepBlocks of
-// them in the process: a request takes the smallest kept block on its device that
-// is large enough and not more than a quarter too large; the blocks kept longest
-// are given back when there are more, and all of them when an allocation fails.
+// unmapping.  So freed blocks are kept (kept_blocks.hpp says which and how many);
+// all of them are given back when an allocation fails and by ann_trim_memory.
 namespace {
 
-struct KeptBlock {
-  void *ptr = nullptr;
-  size_t bytes = 0;
-  int device = 0;
-};
-constexpr int kKeepBlocks = 64;
-constexpr size_t kKeepBytes = (size_t)2 << 30;
 std::mutex g_kept_mutex;
-KeptBlock g_kept[kKeepBlocks];   // oldest first
-int g_n_kept = 0;
-size_t g_kept_bytes = 0;
+KeptBlocks g_kept;
 
-// Takes block i off the list.
-KeptBlock take_kept(int i) {
-  const KeptBlock b = g_kept[i];
-  for (int j = i; j + 1 < g_n_kept; ++j) g_kept[j] = g_kept[j + 1];
-  --g_n_kept;
-  g_kept_bytes -= b.bytes;
-  return b;
+void give_back_kept() {
+  for (;;) {
+    KeptBlock b;
+    {
+      std::lock_guard<std::mutex> lock(g_kept_mutex);
+      if (!g_kept.take_oldest(b)) return;
+    }
+    (void)hipFree(b.ptr);
+  }
 }
 
 }  // namespace
@@ -68,52 +60,38 @@ hipError_t device_alloc(void **ptr, size_t bytes) {
   const size_t want = (bytes + unit - 1) / unit * unit;
   {
     std::lock_guard<std::mutex> lock(g_kept_mutex);
-    int best = -1;
-    for (int i = 0; i < g_n_kept; ++i)
-      if (g_kept[i].device == dev && g_kept[i].bytes >= want && g_kept[i].bytes - want <= want / 4 &&
-          (best < 0 || g_kept[i].bytes < g_kept[best].bytes))
-        best = i;
-    if (best >= 0) {
-      *ptr = take_kept(best).ptr;
+    KeptBlock b;
+    if (g_kept.take(dev, want, b)) {
+      *ptr = b.ptr;
       return hipSuccess;
     }
   }
   e = hipMalloc(ptr, want);
   if (e != hipErrorOutOfMemory) return e;
   (void)hipGetLastError();
-  for (;;) {
-    KeptBlock b;
-    {
-      std::lock_guard<std::mutex> lock(g_kept_mutex);
-      if (g_n_kept == 0) break;
-      b = take_kept(0);
-    }
-    (void)hipFree(b.ptr);
-  }
+  give_back_kept();
   return hipMalloc(ptr, want);
 }
 
-void device_free(void *ptr) {
+void device_free(void *ptr, bool idle) {
   if (!ptr) return;
   hipDeviceptr_t base = nullptr;
   KeptBlock b;
   hipPointerAttribute_t at{};
-  if (hipMemGetAddressRange(&base, &b.bytes, (hipDeviceptr_t)ptr) != hipSuccess || hipPointerGetAttributes(&at, ptr) != hipSuccess ||
-      b.bytes > kKeepBytes) {
+  if (!idle || hipMemGetAddressRange(&base, &b.bytes, (hipDeviceptr_t)ptr) != hipSuccess || hipPointerGetAttributes(&at, ptr) != hipSuccess ||
+      !KeptBlocks::fits(b.bytes)) {
     (void)hipFree(ptr);
     return;
   }
   b.ptr = ptr;
   b.device = at.device;
-  KeptBlock back[kKeepBlocks];
-  int n_back = 0;
+  KeptBlock out[kKeepBlocks];
+  int n_out = 0;
   {
     std::lock_guard<std::mutex> lock(g_kept_mutex);
-    while (g_n_kept == kKeepBlocks || g_kept_bytes + b.bytes > kKeepBytes) back[n_back++] = take_kept(0);
-    g_kept[g_n_kept++] = b;
-    g_kept_bytes += b.bytes;
+    n_out = g_kept.put(b, out);
   }
-  for (int i = 0; i < n_back; ++i) (void)hipFree(back[i].ptr);
+  for (int i = 0; i < n_out; ++i) (void)hipFree(out[i].ptr);
 }
 
 // ---------------------------------------------------------------- pack kernels
@@ -237,33 +215,34 @@ ann_status dev_copy(T **dst, const T *src, size_t count, bool src_on_host, hipSt
   return ANN_OK;
 }
 
-void free_workspace(Workspace &w) {
-  device_free(w.tq);
-  device_free(w.s);
-  device_free(w.qlo);
-  device_free(w.sum_t);
+void free_workspace(Workspace &w, bool idle) {
+  device_free(w.tq, idle);
+  device_free(w.s, idle);
+  device_free(w.qlo, idle);
+  device_free(w.sum_t, idle);
   w = Workspace{};
 }
 
-void destroy(ann_index *ix) {
+// idle: nothing enqueued on the device can be using the index.
+void destroy(ann_index *ix, bool idle) {
   if (!ix) return;
-  device_free(ix->vectors);
-  device_free(ix->adjacency);
-  device_free(ix->labels);
-  device_free(ix->adjacency_norms);
-  device_free(ix->pivot_codes);
-  device_free(ix->prs_codes);
-  device_free(ix->prs_norm);
-  device_free(ix->pivot_norm);
-  device_free(ix->pivot_ids);
+  device_free(ix->vectors, idle);
+  device_free(ix->adjacency, idle);
+  device_free(ix->labels, idle);
+  device_free(ix->adjacency_norms, idle);
+  device_free(ix->pivot_codes, idle);
+  device_free(ix->prs_codes, idle);
+  device_free(ix->prs_norm, idle);
+  device_free(ix->pivot_norm, idle);
+  device_free(ix->pivot_ids, idle);
   for (int l = 0; l < ANN_MAX_LEVELS; ++l) {
-    device_free(ix->level[l].codes);
-    device_free(ix->level[l].lo);
-    device_free(ix->level[l].delta);
-    device_free(ix->level[l].norm_term);
+    device_free(ix->level[l].codes, idle);
+    device_free(ix->level[l].lo, idle);
+    device_free(ix->level[l].delta, idle);
+    device_free(ix->level[l].norm_term, idle);
   }
   for (StreamWorkspaces &sw : ix->stream_ws)
-    for (Workspace &w : sw.ws) free_workspace(w);
+    for (Workspace &w : sw.ws) free_workspace(w, idle);
   delete ix;
 }
 
@@ -306,7 +285,7 @@ ann_status workspace_for(ann_index *ix, uint32_t level, uint32_t nq, hipStream_t
   // moves it out of the path); it waits for work that may still be using the
   // old buffers
   ANN_HIP(hipDeviceSynchronize());
-  free_workspace(w);
+  free_workspace(w, true);
   uint32_t cap = nq < 1024 ? 1024 : nq;
   w.tq_plane = tq_plane_for(ix->level[level]);
   w.tq_stride = w.tq_plane * (ix->query_bits == 15 ? 2u : 1u);
@@ -374,13 +353,14 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
   uint64_t *raw_offs = nullptr;
   float *raw_labels = nullptr;
   auto cleanup = [&](ann_status r) {
-    if (r != ANN_OK) (void)hipDeviceSynchronize();  // what has been enqueued may still use the buffers
-    device_free(bad_dev);
-    device_free(raw_codes);
-    device_free(raw_cols);
-    device_free(raw_offs);
-    device_free(raw_labels);
-    if (r != ANN_OK) destroy(ix);
+    // (after a failure what has been enqueued may still use the buffers)
+    const bool idle = r == ANN_OK || hipDeviceSynchronize() == hipSuccess;
+    device_free(bad_dev, idle);
+    device_free(raw_codes, idle);
+    device_free(raw_cols, idle);
+    device_free(raw_offs, idle);
+    device_free(raw_labels, idle);
+    if (r != ANN_OK) destroy(ix, idle);
     return r;
   };
 #define ANN_TRY(expr)                      \
@@ -442,7 +422,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
     ANN_TRY_HIP(hipGetLastError());
     if (host) {
       ANN_TRY_HIP(hipStreamSynchronize(st));
-      device_free(raw_codes);
+      device_free(raw_codes, true);
       raw_codes = nullptr;
     }
   }
@@ -513,8 +493,8 @@ ann_status ann_build_prs_ratio(ann_index *index, float ratio, void *stream) {
   if (index->prs_codes && index->prs_slots == stored) return ANN_OK;
   if (index->prs_codes) {
     ANN_HIP(hipDeviceSynchronize());  // a search may still be reading the old copy
-    device_free(index->prs_codes);
-    device_free(index->prs_norm);
+    device_free(index->prs_codes, true);
+    device_free(index->prs_norm, true);
     index->prs_codes = nullptr;
     index->prs_norm = nullptr;
     index->prs_slots = 0;
@@ -525,7 +505,7 @@ ann_status ann_build_prs_ratio(ann_index *index, float ratio, void *stream) {
   if (index->key_metric == ANN_L2) {
     hipError_t e = device_alloc((void **)&index->prs_norm, (size_t)entries * sizeof(float));
     if (e != hipSuccess) {
-      device_free(index->prs_codes);
+      device_free(index->prs_codes, true);
       index->prs_codes = nullptr;
       return hip_fail(e, "hipMalloc");
     }
@@ -553,7 +533,7 @@ ann_status ann_build_row_norms(ann_index *index, void *stream) {
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
-    device_free(index->adjacency_norms);
+    device_free(index->adjacency_norms, false);
     index->adjacency_norms = nullptr;
     return hip_fail(e, "build_row_norms_kernel");
   }
@@ -581,9 +561,14 @@ ann_status ann_free_index(ann_index *index) {
   int dev = index->device;
   (void)hipGetDevice(&dev);
   if (dev != index->device) (void)hipSetDevice(index->device);
-  (void)hipDeviceSynchronize();
+  const bool idle = hipDeviceSynchronize() == hipSuccess;
   if (dev != index->device) (void)hipSetDevice(dev);
-  destroy(index);
+  destroy(index, idle);
+  return ANN_OK;
+}
+
+ann_status ann_trim_memory(void) {
+  give_back_kept();
   return ANN_OK;
 }
 

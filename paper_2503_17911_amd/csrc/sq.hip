@@ -553,7 +553,7 @@ ann_status ann_sq_train(const float *x, uint64_t n, uint32_t d, uint32_t bits, f
       pmin, pmax, nblocks, d, (float)((1u << bits) - 1u), lo, delta);
   hipError_t e = hipGetLastError();
   hipError_t e2 = hipStreamSynchronize(st);
-  device_free(pmin);
+  device_free(pmin, e2 == hipSuccess);
   if (e != hipSuccess) return hip_fail(e, "sq_minmax launch");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;
@@ -584,7 +584,7 @@ ann_status ann_sq_train_truncated(const float *x, uint64_t n, uint32_t d, uint32
   truncated_range_kernel<<<(d + 255) / 256, 256, 0, st>>>(prefix, d, (float)((1u << bits) - 1u), lo, delta);
   hipError_t e = hipGetLastError();
   const hipError_t e2 = hipStreamSynchronize(st);
-  device_free(hist);
+  device_free(hist, e2 == hipSuccess);
   if (e != hipSuccess) return hip_fail(e, "ann_sq_train_truncated");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
   return ANN_OK;

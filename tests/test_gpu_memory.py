@@ -38,3 +38,25 @@ def test_indexes_of_changing_sizes(threads):
 
     with ThreadPoolExecutor(threads) as pool:
         assert all(pool.map(work, range(threads)))
+
+
+def test_kept_memory_is_given_back():
+    import gpu_harness as H
+    import torch
+    import paper_2503_17911_amd as ann
+    n, d, degree = 400_000, 128, 16
+    lv = [(8, torch.zeros(n, d, dtype=torch.uint8, device=H.DEV), torch.zeros(d, device=H.DEV), torch.ones(d, device=H.DEV),
+           torch.zeros(n, device=H.DEV))]
+    adj = torch.stack([(torch.arange(n, device=H.DEV) + 1 + j) % n for j in range(degree)], 1).to(torch.int32)
+    ann.ann_trim_memory()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    ix = ann.ann_upload_index(n=n, d=d, degree=degree, metric=ann.L2, vectors=None, levels=lv, adjacency=adj, entry_point=0, stream=H.stream_ptr())
+    held = before - torch.cuda.mem_get_info()[0]
+    assert held >= n * (d + 4 * degree)
+    ann.ann_free_index(ix)
+    kept = before - torch.cuda.mem_get_info()[0]
+    assert kept <= held
+    ann.ann_trim_memory()
+    assert before - torch.cuda.mem_get_info()[0] <= 0
+    ann.ann_trim_memory()

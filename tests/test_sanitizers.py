@@ -53,3 +53,11 @@ def test_library_argument_checks_under_sanitizers(tmp_path):
          str(tmp_path / "stub.o"), "-o", str(exe)])
     out = run([str(exe)], env=dict(ENV, ASAN_OPTIONS="detect_leaks=0"))   # the HIP runtime keeps its own allocations
     assert "0 unexpected results" in out.stdout
+
+
+def test_kept_blocks_and_shrinking_requests_under_sanitizers(tmp_path):
+    """Which blocks of device memory are kept, handed out and given back, at 64 blocks and at 2 GiB."""
+    exe = tmp_path / "kept_blocks_driver"
+    run(["g++", "-std=c++17", "-static-libasan", "-static-libubsan", *SAN, "-I", str(ROOT / "paper_2503_17911_amd" / "csrc"),
+         str(ROOT / "tests" / "sanitize" / "kept_blocks_driver.cpp"), "-o", str(exe)])
+    assert "clean" in run([str(exe)], env=ENV).stdout
