@@ -158,6 +158,9 @@ ann_status launch_search_with(const ann_index *index, uint32_t nq, const ann_sea
   // with 128 registers, which keeps the folded query in them.  100 queries x 128 8-bit,
   // ef = 64: 138 -> 134 us, 4,000: 192 -> 188; x 960 4-bit: 335 -> 281, 768 -> 583.
   if (fast && !multi && nq <= (uint32_t)index->n_cu * 4u * kTeamWaves) return launch_search_small(a, L.bits, L.search_lanes, m, st);
+  if (a.filtered)
+    return wide_step ? launch_search_filtered_wide(a, L.bits, L.search_lanes, m, st)
+                     : launch_search_filtered(a, L.bits, L.search_lanes, m, multi, st);
   if (wide_step)
     return fast ? launch_search_fast_wide(a, L.bits, L.search_lanes, m, st)
                 : launch_search_general_wide(a, L.bits, L.search_lanes, m, st);

@@ -3,6 +3,6 @@
 
 namespace ann {
 ann_status launch_search_fast_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st) {
-  return launch_search<true, true>(a, bits, lpr, m, true, st);
+  return launch_search<true, false, true>(a, bits, lpr, m, true, st);
 }
 }  // namespace ann

@@ -96,7 +96,8 @@ struct SearchArgs {
   float alpha_s;
 };
 
-// A workgroup of these kernels is one wavefront, and a wavefront's LDS
+// All but the evaluation of a step is one wavefront's work (with several to a
+// query, the first's; they meet at barriers, see TEAM), and a wavefront's LDS
 // instructions are carried out in the order they were issued: what one lane
 // wrote is there for any lane's later read.  So all that is needed between a
 // write and a dependent read by another lane is that the compiler keeps the
@@ -155,7 +156,9 @@ __host__ __device__ inline size_t search_smem_bytes(int m, int pmax, bool fast, 
 // switches folded away (two-way visited cache, no edge filter, plain
 // layout, PMAX expansions per step; degree <= 32 when PMAX > 1, degree <= 64
 // with four or more pool registers per lane).  The general
-// kernel (FAST = false) takes every switch from SearchArgs.
+// kernel (FAST = false) takes every switch from SearchArgs, but for the edge
+// filter: FILTER kernels have it (labels, the cap m_s, or both; plain layout),
+// the others do not, and need fewer registers for that.
 //
 // TEAM: wavefronts per query.  The first runs the algorithm; with more than one
 // the others only evaluate their share of a step's candidates (two barriers per
@@ -169,7 +172,7 @@ __host__ __device__ inline size_t search_smem_bytes(int m, int pmax, bool fast, 
 // With two pool registers and 8-bit codes a wavefront per SIMD is lost (10,000
 // queries on 1M x 128: 733 -> 864 us), with eight and several wavefronts per query it
 // spills (754 -> 767).
-template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1, bool QREG = false>
+template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1, bool QREG = false, bool FILTER = false>
 struct SearchWave {
   static constexpr int G = kWave / LPR;      // code rows evaluated side by side
   static constexpr int CPL = 4;              // 16-byte chunks of a row per lane
@@ -197,8 +200,7 @@ struct SearchWave {
 
   __device__ __forceinline__ bool use_cache() const { return FAST || a.vis_cache != 0; }
   __device__ __forceinline__ bool use_packed() const { return FAST || a.vis_packed != 0; }
-  __device__ __forceinline__ bool use_prs() const { return !FAST && a.prs_codes != nullptr; }
-  __device__ __forceinline__ bool use_filter() const { return !FAST && a.filtered != 0; }
+  __device__ __forceinline__ bool use_prs() const { return !FAST && !FILTER && a.prs_codes != nullptr; }
   // two adjacency rows of at most 32 slots per pass (FAST kernels with up to
   // two pool registers per lane are only launched for such degrees: their
   // staging area holds 32 PMAX ids; with four or more it holds 64 PMAX)
@@ -988,7 +990,7 @@ struct SearchWave {
         continue;
       }
       int n_cand = 0;
-      if (use_filter()) {
+      if constexpr (FILTER) {
         // label test and per-expansion cap: rows one after the other, in
         // the order of the picked entries
 #pragma unroll
@@ -1132,18 +1134,26 @@ struct SearchWave {
   }
 };
 
-// (The general kernels are compiled for four wavefronts per SIMD: for five they
-// spill up to 18 registers, and the complete table of the capped filter lets five
-// queries at most reside on a compute unit anyway.  Labels and cap, one expansion per
-// step, 50,021 x 100, ef = 100: 513 queries 415 -> 356 us, 10,000 3,016 -> 2,589; labels
-// alone, where residency counts, 383 -> 335 and 807 -> 840.)
-template <int BITS, int LPR, int M, int PMAX, bool FAST>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(M <= 2 ? (FAST ? (PMAX > 4 ? ANN_WPE_WIDE : (PMAX > 1 ? (BITS == 8 ? ANN_WPE : 5) : ANN_WPE_EXACT)) : 4) : (M == 4 ? 4 : 3)))) void search_kernel(SearchArgs args) {
+// Wavefronts per SIMD a kernel is compiled for.  General kernels: five where that
+// spills little, which is 8-bit codes without the filter; with 4-bit codes, with
+// the filter, and with eight expansions and two pool registers four are faster, or no
+// slower, at every batch size.  10,000 queries, ef = 128, four / five: 200,000 x 128
+// 8-bit: two expansions per step 773 / 658 us, wide cache 576 / 514, 15-bit query
+// 633 / 560; six expansions 572 / 636, labels 1,300 / 1,395 (without the rest of
+// the general kernel: 1,189); 100,000 x 480 4-bit: wide cache 1,254 / 2,269.
+constexpr int waves_per_simd(int bits, int m, int pmax, bool fast, bool filter) {
+  if (m > 2) return m == 4 ? 4 : 3;
+  if (fast) return pmax > 4 ? ANN_WPE_WIDE : (pmax > 1 ? (bits == 8 ? ANN_WPE : 5) : ANN_WPE_EXACT);
+  return bits == 8 && !filter && !(pmax > 4 && m == 2) ? 5 : 4;
+}
+
+template <int BITS, int LPR, int M, int PMAX, bool FAST, bool FILTER>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(BITS, M, PMAX, FAST, FILTER)))) void search_kernel(SearchArgs args) {
   extern __shared__ uint64_t smem[];
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
   if (qi >= args.nq) return;  // not a permutation: skip rather than write out of bounds
-  SearchWave<BITS, LPR, M, PMAX, FAST, 1, FAST && BITS == 4 && M >= 4> w(args, smem);
+  SearchWave<BITS, LPR, M, PMAX, FAST, 1, FAST && BITS == 4 && M >= 4, FILTER> w(args, smem);
   w.run(qi);
 }
 
@@ -1200,28 +1210,28 @@ static ann_status launch_team_lpr(const SearchArgs &a, uint32_t lpr, int m, hipS
   }
 }
 
-template <int BITS, int LPR, int PMAX, bool FAST>
+template <int BITS, int LPR, int PMAX, bool FAST, bool FILTER>
 static ann_status launch_m(const SearchArgs &args, int m, hipStream_t st) {
   const size_t smem = search_smem_bytes(m, PMAX, FAST, args.vis_log2, args.degree, args.tq_stride);
   switch (m) {
-    case 1: search_kernel<BITS, LPR, 1, PMAX, FAST><<<args.nq, 64, smem, st>>>(args); break;
-    case 2: search_kernel<BITS, LPR, 2, PMAX, FAST><<<args.nq, 64, smem, st>>>(args); break;
-    case 4: search_kernel<BITS, LPR, 4, PMAX, FAST><<<args.nq, 64, smem, st>>>(args); break;
-    case 8: search_kernel<BITS, LPR, 8, PMAX, FAST><<<args.nq, 64, smem, st>>>(args); break;
+    case 1: search_kernel<BITS, LPR, 1, PMAX, FAST, FILTER><<<args.nq, 64, smem, st>>>(args); break;
+    case 2: search_kernel<BITS, LPR, 2, PMAX, FAST, FILTER><<<args.nq, 64, smem, st>>>(args); break;
+    case 4: search_kernel<BITS, LPR, 4, PMAX, FAST, FILTER><<<args.nq, 64, smem, st>>>(args); break;
+    case 8: search_kernel<BITS, LPR, 8, PMAX, FAST, FILTER><<<args.nq, 64, smem, st>>>(args); break;
     default: return fail(ANN_EUNSUPPORTED, "no kernel for pool registers per lane = %d", m);
   }
   ANN_HIP(hipGetLastError());
   return ANN_OK;
 }
 
-template <int BITS, int PMAX, bool FAST>
+template <int BITS, int PMAX, bool FAST, bool FILTER>
 static ann_status launch_lpr(const SearchArgs &args, uint32_t lpr, int m, hipStream_t st) {
   switch (lpr) {
-    case 1: return launch_m<BITS, 1, PMAX, FAST>(args, m, st);
-    case 2: return launch_m<BITS, 2, PMAX, FAST>(args, m, st);
-    case 4: return launch_m<BITS, 4, PMAX, FAST>(args, m, st);
-    case 8: return launch_m<BITS, 8, PMAX, FAST>(args, m, st);
-    case 16: return launch_m<BITS, 16, PMAX, FAST>(args, m, st);
+    case 1: return launch_m<BITS, 1, PMAX, FAST, FILTER>(args, m, st);
+    case 2: return launch_m<BITS, 2, PMAX, FAST, FILTER>(args, m, st);
+    case 4: return launch_m<BITS, 4, PMAX, FAST, FILTER>(args, m, st);
+    case 8: return launch_m<BITS, 8, PMAX, FAST, FILTER>(args, m, st);
+    case 16: return launch_m<BITS, 16, PMAX, FAST, FILTER>(args, m, st);
     default: return fail(ANN_EUNSUPPORTED, "no kernel for %u lanes per code row", lpr);
   }
 }
@@ -1234,16 +1244,16 @@ static ann_status launch_lpr(const SearchArgs &args, uint32_t lpr, int m, hipStr
 constexpr int kMaxExpansionsPerStep = 8;
 constexpr int kDefaultExpansionsPerStep = 4;
 
-// One translation unit per (FAST, PMAX > 4) instantiates its kernels through this.
-template <bool FAST, bool WIDE_STEP>
+// One translation unit per (FAST, FILTER, PMAX > 4) instantiates its kernels through this.
+template <bool FAST, bool FILTER, bool WIDE_STEP>
 static ann_status launch_search(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool multi, hipStream_t st) {
   if constexpr (WIDE_STEP) {
-    return bits == 8 ? launch_lpr<8, kMaxExpansionsPerStep, FAST>(a, lpr, m, st)
-                     : launch_lpr<4, kMaxExpansionsPerStep, FAST>(a, lpr, m, st);
+    return bits == 8 ? launch_lpr<8, kMaxExpansionsPerStep, FAST, FILTER>(a, lpr, m, st)
+                     : launch_lpr<4, kMaxExpansionsPerStep, FAST, FILTER>(a, lpr, m, st);
   } else {
-    if (!multi) return bits == 8 ? launch_lpr<8, 1, FAST>(a, lpr, m, st) : launch_lpr<4, 1, FAST>(a, lpr, m, st);
-    return bits == 8 ? launch_lpr<8, kDefaultExpansionsPerStep, FAST>(a, lpr, m, st)
-                     : launch_lpr<4, kDefaultExpansionsPerStep, FAST>(a, lpr, m, st);
+    if (!multi) return bits == 8 ? launch_lpr<8, 1, FAST, FILTER>(a, lpr, m, st) : launch_lpr<4, 1, FAST, FILTER>(a, lpr, m, st);
+    return bits == 8 ? launch_lpr<8, kDefaultExpansionsPerStep, FAST, FILTER>(a, lpr, m, st)
+                     : launch_lpr<4, kDefaultExpansionsPerStep, FAST, FILTER>(a, lpr, m, st);
   }
 }
 
@@ -1285,6 +1295,8 @@ ann_status launch_search_fast(const SearchArgs &a, uint32_t bits, uint32_t lpr, 
 ann_status launch_search_general(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool multi, hipStream_t st);
 ann_status launch_search_fast_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
 ann_status launch_search_general_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
+ann_status launch_search_filtered(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool multi, hipStream_t st);
+ann_status launch_search_filtered_wide(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
 ann_status launch_search_small(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st);
 ann_status launch_search_team4(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st);
 ann_status launch_search_team2(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, bool wide_step, hipStream_t st);
