@@ -104,7 +104,7 @@ struct Certainty {
 // Exact distances of every query's candidates, the k best in (distance, id) order (rerank.hip).
 ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
                          const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k, uint32_t *out_ids,
-                         float *out_dist, hipStream_t st, const float *cand_keys = nullptr, uint32_t n_min = 0,
+                         float *out_dist, uint32_t n_cu, hipStream_t st, const float *cand_keys = nullptr, uint32_t n_min = 0,
                          float gamma = 0.0f, uint32_t *out_n = nullptr, const Certainty &certain = {});
 
 // Kernel-layout length of one byte plane of a folded query for a level: every 16-byte chunk of

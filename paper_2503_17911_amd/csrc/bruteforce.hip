@@ -268,8 +268,9 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 //
 // Workgroup b runs on die b mod 8; slabs of rows belong to dies, and a die takes
 // 16 query tiles (1.6 MB of parts at 128 dimensions) through all its slabs before
-// the next 16, so that both stay in its L2 (all tiles at once: 66 GB fetched per
-// pass instead of 10, 6 % slower).
+// the next 16, so that both stay in its 4 MB of L2 (all tiles at once: 66 GB fetched
+// per pass instead of 10, 6 % slower).  From about 340 dimensions on 16 tiles'
+// parts are more than that; other group sizes have not been measured there.
 //
 // 10,112 queries x 1M x 128, a pass without entries: 13.4 ms = 193 TFLOP/s of fp32
 // work = 1,160 on the matrix cores, at the 1.96 GHz the card runs such work (peak
@@ -983,7 +984,7 @@ static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const 
   else
     bf_tile_kernel<false><<<grid, 256, smem, st>>>(x, xnorm, n, d, q, nq, metric, rows_per_slab, kp, cb, cand);
   e = hipGetLastError();
-  ann_status rc = e == hipSuccess ? rerank_device(x, n, d, metric, q, nq, cand, slabs * kp, slabs * kp, k, out_ids, out_dist, st)
+  ann_status rc = e == hipSuccess ? rerank_device(x, n, d, metric, q, nq, cand, slabs * kp, slabs * kp, k, out_ids, out_dist, n_cu, st)
                                   : hip_fail(e, "brute-force tile kernel launch");
   const hipError_t e2 = hipStreamSynchronize(st);
   device_free(cand, e2 == hipSuccess);
@@ -1287,7 +1288,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
     }
   }
   ANN_HIP(hipGetLastError());
-  return rerank_device(t.x, t.n, t.d, t.metric, qr, m, s.cand, s.most, s.most, t.k, out_ids, out_dist, t.st, nullptr, 0, 0.0f, nullptr,
+  return rerank_device(t.x, t.n, t.d, t.metric, qr, m, s.cand, s.most, s.most, t.k, out_ids, out_dist, t.n_cu, t.st, nullptr, 0, 0.0f, nullptr,
                        Certainty{s.below, &s.state->n_uncertain, uncertain, first_query});
 }
 
@@ -1385,7 +1386,7 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
     uint32_t most = 0;
     ANN_HIP(hipMemcpyAsync(&most, &state->most_entries, sizeof(most), hipMemcpyDeviceToHost, t.st));
     ANN_HIP(hipStreamSynchronize(t.st));
-    rc = rerank_device(t.x, t.n, t.d, t.metric, qg, c, cand, most ? most : 1, kRoom, t.k, ids, dist, t.st);
+    rc = rerank_device(t.x, t.n, t.d, t.metric, qg, c, cand, most ? most : 1, kRoom, t.k, ids, dist, t.n_cu, t.st);
     if (rc != ANN_OK) return rc;
     bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, s.bound, s.count, ids, dist, t.out_ids, t.out_dist, state, other, fp32);
     ANN_HIP(hipGetLastError());
@@ -1438,7 +1439,7 @@ static ann_status add_far_rows(const Truth &t, uint32_t nq, uint32_t n_far, cons
   for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += m) {
     const uint32_t c = (uint32_t)(nq - q0 < m ? nq - q0 : m);
     bf_far_rows_kernel<<<c, 64, 0, t.st>>>(t.x, t.d, t.q + q0 * t.d, t.k, state, n_far, t.out_ids + q0 * t.k, cand);
-    rc = rerank_device(t.x, t.n, t.d, t.metric, t.q + q0 * t.d, c, cand, width, width, t.k, t.out_ids + q0 * t.k, t.out_dist + q0 * t.k, t.st);
+    rc = rerank_device(t.x, t.n, t.d, t.metric, t.q + q0 * t.d, c, cand, width, width, t.k, t.out_ids + q0 * t.k, t.out_dist + q0 * t.k, t.n_cu, t.st);
   }
   const hipError_t e2 = hipStreamSynchronize(t.st);
   device_free(cand, e2 == hipSuccess);

@@ -10,7 +10,7 @@
 namespace ann {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr uint32_t kTeamQueries = 2048;   // up to this many queries, four wavefronts share one (256 compute units, eight workgroups each)
+constexpr uint32_t kTeamQueries = 8;   // up to this many queries per compute unit, four wavefronts share one (all workgroups are resident then)
 
 __device__ __forceinline__ uint64_t pack_vi(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
 
@@ -369,7 +369,7 @@ static void launch_rerank(uint32_t lpr, const float *X, uint32_t d, uint32_t met
 // Shared by ann_rerank and the final stage of ann_bruteforce_topk.
 ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric, const float *Q, uint32_t nq,
                          const uint32_t *cand, uint32_t n_cand, uint32_t stride, uint32_t k, uint32_t *out_ids,
-                         float *out_dist, hipStream_t st, const float *cand_keys, uint32_t n_min, float gamma,
+                         float *out_dist, uint32_t n_cu, hipStream_t st, const float *cand_keys, uint32_t n_min, float gamma,
                          uint32_t *out_n, const Certainty &certain) {
   // four 16-byte pieces of a row per lane: 128 dimensions -> 8 lanes per row, 8 rows side by side
   uint32_t chunks = (d + 3) / 4, lpr = 8;
@@ -377,7 +377,7 @@ ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric
   // Four wavefronts per query where the batch fits the chip that way (eight
   // workgroups to a compute unit) and a query has more rows than one wavefront
   // requests together (three rounds).
-  const bool team = nq <= kTeamQueries && n_cand > 3 * (kWave / lpr) && n_cand <= 1024;
+  const bool team = nq <= kTeamQueries * n_cu && n_cand > 3 * (kWave / lpr) && n_cand <= 1024;
   const size_t smem = (size_t)n_cand * (sizeof(uint64_t) + (team ? sizeof(uint32_t) : 0)) + (size_t)((d + 3) / 4) * 16;
 #define ANN_LR(V, W) launch_rerank<V, W>(lpr, X, d, metric, Q, nq, n, cand, n_cand, stride, k, out_ids, out_dist, smem, st, cand_keys, n_min, gamma, out_n, certain)
   if (d % 4 == 0) {
@@ -411,7 +411,7 @@ ann_status ann_rerank(ann_index *index, const float *q, uint32_t nq, const uint3
   if (cand_stride < n_cand) return fail(ANN_EINVAL, "ann_rerank: cand_stride = %u < n_cand = %u", cand_stride, n_cand);
   if (n_cand > 4096) return fail(ANN_ECAPACITY, "ann_rerank: n_cand = %u exceeds 4096", n_cand);
   return rerank_device(index->vectors, index->n, index->d, index->metric, q, nq, cand_ids, n_cand, cand_stride, k,
-                       out_ids, out_dist, (hipStream_t)stream, nullptr, 0, 0.0f, nullptr);
+                       out_ids, out_dist, (uint32_t)index->n_cu, (hipStream_t)stream, nullptr, 0, 0.0f, nullptr);
 }
 
 ann_status ann_rerank_adaptive(ann_index *index, const float *q, uint32_t nq, const uint32_t *cand_ids,
@@ -427,7 +427,7 @@ ann_status ann_rerank_adaptive(ann_index *index, const float *q, uint32_t nq, co
   if (n_max > 4096) return fail(ANN_ECAPACITY, "ann_rerank_adaptive: n_max = %u exceeds 4096", n_max);
   if (!(gamma >= 0.0f)) return fail(ANN_EINVAL, "ann_rerank_adaptive: gamma must be >= 0");
   return rerank_device(index->vectors, index->n, index->d, index->metric, q, nq, cand_ids, n_max, cand_stride, k,
-                       out_ids, out_dist, (hipStream_t)stream, cand_keys, n_min, gamma, out_n);
+                       out_ids, out_dist, (uint32_t)index->n_cu, (hipStream_t)stream, cand_keys, n_min, gamma, out_n);
 }
 
 ann_status ann_rescore(ann_index *index, uint32_t level, const float *q, uint32_t nq, const uint32_t *cand_ids,
