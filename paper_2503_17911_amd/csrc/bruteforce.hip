@@ -247,8 +247,8 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 // scores (128 queries x 4,096 rows; in brackets: fp32 products and norms):
 //   inner products of mixtures   d = 24 5.5e-8 (7.5e-8), 128 1.4e-7 (1.7e-7),
 //                                960 3.1e-7 (4.2e-7), 2,048 4.0e-7 (6.1e-7)
-//   L2, centred normal vectors   128 5.6e-8 (6.0e-8), 960 5.0e-8 (5.5e-8),
-//                                2,048 5.8e-8 (6.3e-8)
+//   L2, centred normal vectors   128 5.7e-8 (6.0e-8), 960 5.2e-8 (5.5e-8),
+//                                2,048 6.2e-8 (6.3e-8)
 //   L2, offset of 1,000 spreads  128 2.2e-7 (3.0e-7), 960 8.7e-7 (8.6e-7),
 //                                2,048 1.3e-6 (1.2e-6)
 // (likewise for uniform, unit-norm and stretched vectors).  Only the last two are
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   // Nothing here branches: the steps below are one block of instructions, in
   // which the splitting fills the issue slots between matrix instructions.
   float4 reg[NR];
-  float sq[NR] = {}, sq_low[NR] = {};   // squared norm so far, and what its additions rounded away
+  float sq[NR] = {}, sq_other[NR] = {};   // squared norm: the sums over the last chunk and every second before it, and over the others
   float max_norm = 0.f;   // inner product: largest squared norm seen
   const float *row_at[NR];
   auto new_rows = [&](uint64_t tile) {
@@ -449,8 +449,8 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
           t = k + j < a.d ? u : t;
         }
       }
-      const float sum = sq[i] + t;   // (the sum so far is the larger part, but for the first chunks)
-      sq_low[i] += t - (sum - sq[i]);
+      const float sum = sq_other[i] + t;
+      sq_other[i] = sq[i];
       sq[i] = sum;
       uint32_t w01[3], w23[3];
       split3(v.x, v.y, w01);
@@ -466,12 +466,11 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   auto put_norms = [&](uint64_t tile) {
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      float t = sq[i] + sq_low[i];
-      t = sq[i] < INFINITY ? t : sq[i];
+      float t = sq[i] + sq_other[i];
       t += __int_as_float(dpp_i32<kDppQuadXor1>(__float_as_int(t)));
       t += __int_as_float(dpp_i32<kDppQuadXor2>(__float_as_int(t)));
       t += __int_as_float(dpp_i32<kDppRowHalfMirror>(__float_as_int(t)));
-      sq[i] = sq_low[i] = 0.f;
+      sq[i] = sq_other[i] = 0.f;
       if (tid % 8 == 0) {
         // Rows whose squared norm is no float are left out of the scores.  L2: they are infinitely far.  Inner
         // product: with a NaN they have no score; the others may be near, and are listed for the exact stage.
@@ -684,7 +683,8 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   if (n_hits > 0) flush();
   if (a.metric != ANN_L2 && a.state != nullptr) {
     max_norm = wave_max_f32(max_norm);
-    if (lane == 0) atomicMax(&a.state->max_norm, __float_as_uint(max_norm));
+    // (2,000 wavefronts at one address take 8 us; most find a value that is large enough)
+    if (lane == 0 && *(volatile uint32_t *)&a.state->max_norm < __float_as_uint(max_norm)) atomicMax(&a.state->max_norm, __float_as_uint(max_norm));
   }
 }
 
