@@ -238,7 +238,7 @@ __global__ void truncated_range_kernel(const uint32_t *__restrict__ prefix, uint
 // to fp32.  It is formed as a tree instead (certain_f32 says when both round to
 // the same float) and again by one lane in dimension order where the two may
 // differ: about one row in 2^28 / d.
-// 1M x 128, 8 bits: 782 us (one row per wavefront, the sum by one lane) -> 123 us (5.3 TB/s read and written);
+// 1M x 128, 8 bits: 782 us (one row per wavefront, the sum by one lane) -> 114 us (5.7 TB/s read and written);
 // 200,000 x 960, 4 bits: 1,179 us -> 189 us (4.6 TB/s).
 constexpr int kEncRows = 8;
 
