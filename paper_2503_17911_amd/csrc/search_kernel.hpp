@@ -1141,14 +1141,20 @@ struct SearchWave {
 // 8-bit: two expansions per step 773 / 658 us, wide cache 576 / 514, 15-bit query
 // 633 / 560; six expansions 572 / 636, labels 1,300 / 1,395 (without the rest of
 // the general kernel: 1,189); 100,000 x 480 4-bit: wide cache 1,254 / 2,269.
-constexpr int waves_per_simd(int bits, int m, int pmax, bool fast, bool filter) {
+// Four pool registers and long 4-bit rows: three, since four spill up to 26 registers (ef = 256, four / three: 200,000
+// x 768, degree 48, eight expansions 4,761 / 3,315 us, wide cache and one expansion 6,486 / 4,024); with rows of one lane
+// four (x 100, wide cache and four expansions 1,000 / 1,171), with two only for one expansion (x 200: one 3,433 /
+// 2,901, four 1,196 / 1,311).  Two pool registers, one expansion and rows of eight lanes: three as well (ef = 128, wide
+// cache: x 768 2,346 / 2,158, x 480 1,208 / 1,223).
+constexpr int waves_per_simd(int bits, int lpr, int m, int pmax, bool fast, bool filter) {
+  if (bits == 4 && !fast && !filter && ((m == 4 && (lpr >= 4 || (lpr == 2 && pmax == 1))) || (m == 2 && lpr >= 8 && pmax == 1))) return 3;
   if (m > 2) return m == 4 ? 4 : 3;
   if (fast) return pmax > 4 ? ANN_WPE_WIDE : (pmax > 1 ? (bits == 8 ? ANN_WPE : 5) : ANN_WPE_EXACT);
   return bits == 8 && !filter && !(pmax > 4 && m == 2) ? 5 : 4;
 }
 
 template <int BITS, int LPR, int M, int PMAX, bool FAST, bool FILTER>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(BITS, M, PMAX, FAST, FILTER)))) void search_kernel(SearchArgs args) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(BITS, LPR, M, PMAX, FAST, FILTER)))) void search_kernel(SearchArgs args) {
   extern __shared__ uint64_t smem[];
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
