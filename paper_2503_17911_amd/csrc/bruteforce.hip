@@ -3,8 +3,9 @@
 //
 // Scores that only select candidates: -2 q.x + |x|^2 (or -q.x) from a dense
 // contraction on the matrix cores, every fp32 value split into three bf16
-// parts and six of the nine partial products accumulated in fp32, which loses
-// no more than fp32 products do (see bf_score_kernel).  Between `want` = k + 8 and
+// parts and six of the nine partial products accumulated in fp32, or into two
+// half-precision parts and three of the four products; neither loses more than
+// fp32 products do (see bf_score_kernel).  Between `want` = k + 8 and
 // `most`, half as many again, of a query's best rows are re-evaluated in fp64 by
 // the rerank kernel and sorted by (distance, id).
 //
@@ -29,8 +30,8 @@
 //
 // Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
 // kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
-// k = 10: 25.8 -> 15.5 ms; 2,000 x 200,000 x 768, k = 100: 13.9 -> 3.8 ms; 100 x
-// 10,000 x 128, k = 10: 2.56 -> 0.07 ms.
+// k = 10: 25.8 -> 8.0 ms (15.5 with three parts); 2,000 x 200,000 x 768, k = 100:
+// 13.9 -> 2.45 ms (3.8); 100 x 10,000 x 128, k = 10: 2.56 -> 0.07 ms.
 #include <math.h>
 
 #include "ann_internal.hpp"
@@ -237,9 +238,9 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Scores on the bf16 matrix cores.
+// Scores on the 16-bit matrix cores.
 //
-// A float is the sum of three bf16 values (8 + 8 + 8 bits; rounding to nearest
+// PARTS = 3: a float is the sum of three bf16 values (8 + 8 + 8 bits; rounding to nearest
 // each time, the remainders are exact).  Of the nine products of two such sums
 // the three smallest (below 2^-25 of the product) are left out.  The fp32 matrix
 // rate is 157 TFLOP/s; six bf16 products at 2.5 PFLOP/s leave 417 of the same.
@@ -253,6 +254,23 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 //                                2,048 1.3e-6 (1.2e-6)
 // (likewise for uniform, unit-norm and stretched vectors).  Only the last two are
 // larger than with fp32 products; such results are settled with centred rows.
+//
+// PARTS = 2: half precision carries 11 bits, so two parts hold a float but for one
+// bit (a remainder below 2^-23 of it), if its size allows: rows times one power of
+// two, each query times its own, have norms of about 2^12, of 2^16 that the format ends at;
+// what falls below its smallest value, 2^-24, is 2^-36 of the norm.  Rows 8 times larger than
+// the largest of a sample are left out (L2: a result they might belong to is uncertain; inner product:
+// they are listed, and the call is repeated with three parts if they are many).  The product of the
+// two second parts, below 2^-22 of the product, is left out.  That is half the products, and
+// half the roundings of the accumulators, which are the larger error from 65 columns on.
+// Error as above, three parts / two (two and norms in fp64, bf_pair_kernel):
+//   L2 of mixtures   d = 72 7.3e-8 / 6.8e-8, 128 1.04e-7 / 8.5e-8, 960 2.1e-7 / 1.8e-7,
+//                    2,048 3.0e-7 / 2.7e-7
+//   inner products   128 1.4e-7 / 1.0e-7, 960 3.1e-7 / 2.6e-7; centred normal 128 1.6e-7 /
+//                    1.4e-7, 48 9.1e-8 / 1.04e-7, 24 6.0e-8 / 9.2e-8 (there three are taken)
+//   offset of 1,000 spreads, L2   128 2.2e-7 / 1.8e-7, 960 8.7e-7 / 5.3e-7
+// Of the lanes' scores this one is smaller for each of nine distributions of ordinary size; for norms spread
+// over four orders of magnitude it is up to 10 % larger at 65 to 80 columns.
 //
 // A workgroup of four wavefronts takes QT queries x 128 base rows per tile.
 // The queries come split, in the order the matrix instruction wants them
@@ -272,18 +290,23 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 // per pass instead of 10, 6 % slower).  From about 340 dimensions on 16 tiles'
 // parts are more than that; other group sizes have not been measured there.
 //
-// 10,112 queries x 1M x 128, a pass without entries: 13.4 ms = 193 TFLOP/s of fp32
+// Three parts, 10,112 queries x 1M x 128, a pass without entries: 13.4 ms = 193 TFLOP/s of fp32
 // work = 1,160 on the matrix cores, at the 1.96 GHz the card runs such work (peak
 // 2,050 there; a large bf16 matrix product reaches 1,420).  Without the query
-// loads it takes 12.1, without the splitting 12.8.
+// loads it takes 12.1, without the splitting 12.8.  Two parts: 10.2, bound by the
+// splitting and the end of a tile (bf_pair_kernel has neither between its products).
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 constexpr int kSK = 32;           // columns per chunk
 constexpr int kSB = 128;          // base rows per tile
 constexpr int kPlane = kSB * kSK * 2;   // bytes of one plane of a chunk
+constexpr uint64_t kPairBytes = 128ull << 20;   // of split rows at a time
 constexpr int kHitList = 96;      // entries a wavefront collects before they go to global memory
+constexpr float kFarNorm2 = 0x1.fp31f;   // two parts: rows of this squared norm and more, scaled, are left out (half precision ends at 2^16)
 constexpr uint32_t kSampleRows = 4096;   // scores one selection workgroup takes; first sample (or twice that, see ann_bruteforce_topk)
 
 // a, b -> their three bf16 parts, a's in the low halves
@@ -297,6 +320,22 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t (&w)[3]) {
       b = __fsub_rn(b, __uint_as_float(w[p] & 0xFFFF0000u));
     }
   }
+}
+
+// a and b times the power of two `scale` -> their two half-precision parts, a's in the low halves
+__device__ __forceinline__ void split2(float a, float b, float scale, uint32_t (&w)[2]) {
+  const halfx2 hi = {(_Float16)__builtin_fmaf(a, scale, 0.0f), (_Float16)__builtin_fmaf(b, scale, 0.0f)};
+  const halfx2 lo = {(_Float16)__builtin_fmaf(a, scale, -(float)hi.x), (_Float16)__builtin_fmaf(b, scale, -(float)hi.y)};
+  w[0] = __builtin_bit_cast(uint32_t, hi);
+  w[1] = __builtin_bit_cast(uint32_t, lo);
+}
+
+// The power of two that brings a vector of squared norm sq to a norm of 2^12 to 2^13
+// (2^-60 to 2^60; 1 for zero).
+__device__ __forceinline__ int half_exponent(float sq) {
+  if (!(sq > 0.0f && sq < INFINITY)) return 0;
+  const int e = 12 - (ilogbf(sq) >> 1);
+  return e < -60 ? -60 : (e > 60 ? 60 : e);
 }
 
 // Queries split and laid out as the second operand of the 32x32x16 matrix
@@ -331,35 +370,6 @@ __global__ __launch_bounds__(256) void bf_split_queries_kernel(const float *__re
   }
 }
 
-// What a call learns on the device and the host reads at its end (or between steps).
-constexpr uint32_t kFarRows = 3840;   // (with 256 results they fit the 4,096 candidates of a rerank)
-struct CallState {
-  uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
-  uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
-  uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
-  uint32_t most_entries;  // of a query in the last pass over uncertain queries
-  uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
-  uint32_t far_row[kFarRows];
-};
-
-struct ScoreArgs {
-  const float *x;
-  const uint4 *qfrag;
-  uint64_t rows;     // rows of this pass: all of them, or a sample
-  double stretch;    // sample: rows of x per row of the sample; 0: all rows
-  uint32_t d, kb_n, nq, metric;
-  uint32_t q_tiles, q_group, slabs, tiles_per_slab;
-  float *scores;     // not NULL: every score goes here, [nq][ld]
-  uint32_t ld;
-  const uint64_t *bound;   // [nq] otherwise: (score, id) pairs up to the bound go to buf
-  uint64_t *buf;     // [nq][cap]
-  uint32_t *count;   // [nq]
-  uint32_t cap;
-  const float *centre;     // [d] subtracted from every row (kernels with CENTRE)
-  CallState *state;        // inner product: norms are noted here (NULL: not in this pass)
-  bool list_far;           // and the rows without one listed
-};
-
 // Row of x that is row j of a sample: a random one of the j-th stretch of rows
 // (the stretches tile the whole set, so the rows are distinct).
 __device__ __forceinline__ uint64_t sample_row(uint64_t j, double stretch) {
@@ -370,13 +380,253 @@ __device__ __forceinline__ uint64_t sample_row(uint64_t j, double stretch) {
   return begin + __umulhi(h, (uint32_t)(end - begin));
 }
 
-template <bool VEC4, int MB, int NQ, bool CENTRE>
+// Largest squared norm (of those that are floats) of each 64th of a sample of
+// kNormSample rows: out[64].  A wavefront per row.
+constexpr uint32_t kNormSample = 1024;
+__global__ __launch_bounds__(1024) void bf_sample_norms_kernel(const float *__restrict__ x, uint32_t d, double stretch, float *__restrict__ out) {
+  __shared__ float sq_s[16];
+  const uint32_t wave = threadIdx.x / kWave;
+  const float *row = x + sample_row(blockIdx.x * 16 + wave, stretch) * d;
+  float sq = 0.0f;
+  for (uint32_t j0 = 0; j0 < d; j0 += 4 * kWave) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t j = j0 + i * kWave + lane_id();
+      v[i] = row[j < d ? j : 0];
+      v[i] = j < d ? v[i] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sq = fmaf(v[i], v[i], sq);
+  }
+#pragma unroll
+  for (int m = 1; m < kWave; m <<= 1) sq += __int_as_float(xor_lane_i32(__float_as_int(sq), m));
+  if (lane_id() == 0) sq_s[wave] = sq < INFINITY ? sq : 0.0f;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) sq_s[0] = fmaxf(sq_s[0], sq_s[w]);
+    out[blockIdx.x] = sq_s[0];
+  }
+}
+__device__ __forceinline__ float rows_sq(const float *sample_sq) { return wave_max_f32(sample_sq[lane_id()]); }
+
+// The same in two half-precision parts, each query times a power of two (2^-60 to
+// 2^60) that brings its norm to 2^12 .. 2^13.  One workgroup per 32 queries and 16 blocks
+// of columns: the norms first.  unscale[q]: what takes a product of parts back, the rows' scale included.
+__global__ __launch_bounds__(1024) void bf_halve_queries_kernel(const float *__restrict__ Q, uint32_t nq, uint32_t d, uint32_t kb_n,
+                                                                const float *__restrict__ sample_sq, uint4 *__restrict__ out,
+                                                                float *__restrict__ unscale, uint64_t *__restrict__ bound,
+                                                                uint32_t *__restrict__ count) {
+  __shared__ float scale_s[32];
+  const uint32_t q32 = blockIdx.x, tid = threadIdx.x;
+  {
+    const uint32_t qi = q32 * 32 + tid / 32;
+    float sq = 0.0f;
+    if (qi < nq)
+      for (uint32_t j = tid % 32; j < d; j += 32) {
+        const float v = Q[(uint64_t)qi * d + j];
+        sq = fmaf(v, v, sq);
+      }
+#pragma unroll
+    for (int m = 1; m < 32; m <<= 1) sq += __int_as_float(xor_lane_i32(__float_as_int(sq), m));
+    const int e = half_exponent(sq), ex = half_exponent(rows_sq(sample_sq));
+    if (tid % 32 == 0) {
+      scale_s[tid / 32] = ldexpf(1.0f, e);
+      if (qi < nq && blockIdx.y == 0) {
+        unscale[qi] = ldexpf(1.0f, -e - ex);
+        bound[qi] = ~0ull;
+        count[qi] = 0;
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t lane = tid % 64, kb = blockIdx.y * 16 + tid / 64;
+  if (kb < kb_n) {
+    const uint32_t qi = q32 * 32 + lane % 32, k0 = kb * 16 + 8 * (lane / 32);
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = qi < nq && k0 + j < d ? Q[(uint64_t)qi * d + k0 + j] : 0.0f;
+    uint32_t w[4][2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], scale_s[lane % 32], w[j]);
+    uint4 *to = out + ((uint64_t)q32 * kb_n + kb) * 128 + lane;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) to[p * 64] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+  }
+}
+
+// What a call learns on the device and the host reads at its end (or between steps).
+constexpr uint32_t kFewFarRows = 64;   // two parts: with more of them the call is repeated with three
+constexpr uint32_t kFarRows = 3840;   // (with 256 results they fit the 4,096 candidates of a rerank)
+struct CallState {
+  uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
+  uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
+  uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
+  uint32_t most_entries;  // of a query in the last pass over uncertain queries
+  uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
+  uint32_t far_row[kFarRows];
+};
+
+// A pass of scores: its rows and queries, and where the scores go.
+struct ScoreArgs {
+  const float *x;
+  const uint4 *qfrag;
+  uint64_t first, rows;    // rows first .. first + rows - 1 of x, or of a sample of it
+  double stretch;    // sample: rows of x per row of the sample; 0: none
+  uint32_t d, kb_n, nq, metric;
+  uint32_t q_tiles, q_group, slabs, tiles_per_slab;
+  float *scores;     // not NULL: every score goes here, [nq][ld]
+  uint32_t ld;
+  const uint64_t *bound;   // [nq] otherwise: (score, id) pairs up to the bound go to buf
+  uint64_t *buf;     // [nq][cap]
+  uint32_t *count;   // [nq]
+  uint32_t cap;
+  const float *centre;     // [d] subtracted from every row (kernels with CENTRE)
+  const float *sample_sq;  // [64] two parts: squared norms that settle the rows' scale
+  const float *unscale;    // [nq] two parts: takes a product back
+  const uint4 *xfrag;      // rows split ahead (bf_pair_kernel) and their squared norms
+  const float *norm;
+  CallState *state;        // inner product: norms are noted here (NULL: not in this pass)
+  bool list_far;           // and the rows without one listed
+};
+
+// v[i], i in 0 .. 15 (selects: an index into registers would take them through memory)
+__device__ __forceinline__ float pick(const floatx16 &v, int i) {
+  const bool b0 = i & 1, b1 = i & 2, b2 = i & 4, b3 = i & 8;
+  const float a0 = b0 ? v[1] : v[0], a1 = b0 ? v[3] : v[2], a2 = b0 ? v[5] : v[4], a3 = b0 ? v[7] : v[6];
+  const float a4 = b0 ? v[9] : v[8], a5 = b0 ? v[11] : v[10], a6 = b0 ? v[13] : v[12], a7 = b0 ? v[15] : v[14];
+  const float c0 = b1 ? a1 : a0, c1 = b1 ? a3 : a2, c2 = b1 ? a5 : a4, c3 = b1 ? a7 : a6;
+  const float e0 = b2 ? c1 : c0, e1 = b2 ? c3 : c2;
+  return b3 ? e1 : e0;
+}
+
+// What a wavefront makes of its products: MB x NQ blocks of 32 rows x 32 queries, the
+// element i of block (m, f) being row m * 32 + 8 (i / 4) + 4 (lane / 32) + i % 4
+// against query f * 32 + lane % 32.  Scores that reach their query's bound collect in
+// LDS (with the row's place in the pass) and go to global memory when that is full: one
+// atomic addition per entry then, far from the matrix instructions.  The walk over a
+// block with hits takes each lane's next hit per turn (a site of code per score made
+// 170 KB of instructions; a pass over 90,000 rows 0.95 -> 0.59 ms).
+template <int MB, int NQ>
+struct TileEnd {
+  const ScoreArgs &a;
+  uint32_t q0;        // the wavefront's first query
+  uint64_t *hits;     // LDS [kHitList]: (score, row of the pass)
+  uint8_t *hits_q;    // LDS [kHitList]: query - q0
+  int n_hits = 0;     // the same in all lanes
+  float top[NQ], scale[NQ];
+
+  __device__ __forceinline__ TileEnd(const ScoreArgs &args, uint32_t q0_, uint64_t *hits_, uint8_t *hits_q_) : a(args), q0(q0_), hits(hits_), hits_q(hits_q_) {
+#pragma unroll
+    for (int f = 0; f < NQ; ++f) {
+      const uint32_t q = q0 + f * 32 + lane_id() % 32;
+      top[f] = a.scores == nullptr && q < a.nq ? unorder_f32((uint32_t)(a.bound[q] >> 32)) : -INFINITY;
+      scale[f] = a.metric == ANN_L2 ? -2.0f : -1.0f;
+      if (a.unscale != nullptr) scale[f] *= q < a.nq ? a.unscale[q] : 0.0f;   // (powers of two)
+    }
+  }
+  __device__ __forceinline__ static void fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  // the collected hits that reach their query's (score, id) bound -> the queries' entries
+  __device__ __forceinline__ void flush() {
+    fence();
+    bool over = false;
+    for (int e = lane_id(); e < n_hits; e += kWave) {
+      const uint32_t q = q0 + hits_q[e];
+      const uint64_t hit = hits[e];
+      const uint64_t row = a.first + (uint32_t)hit, id = a.stretch != 0.0 ? sample_row(row, a.stretch) : row;
+      const uint64_t ent = (hit & 0xFFFFFFFF00000000ull) | (uint32_t)id;
+      if (ent > a.bound[q]) continue;
+      const uint32_t pos = atomicAdd(&a.count[q], 1u);
+      if (pos < a.cap)
+        a.buf[(uint64_t)q * a.cap + pos] = ent;
+      else
+        over = true;
+    }
+    fence();
+    n_hits = 0;
+    // a query with more entries than room has to be treated otherwise: no more of them
+    if (__ballot(over) != 0) {
+#pragma unroll
+      for (int f = 0; f < NQ; ++f) {
+        const uint32_t q = q0 + f * 32 + lane_id() % 32;
+        if (q < a.nq && *(volatile uint32_t *)&a.count[q] > a.cap) top[f] = -INFINITY;
+      }
+    }
+  }
+  // xn: LDS, the rows' squared norms (inner product: 0; +inf: no score); row0: the first row's place in the pass
+  __device__ __forceinline__ void finish(floatx16 (&acc)[MB][NQ], const float *xn, uint32_t row0) {
+    const int half = lane_id() / 32, l32 = lane_id() % 32;
+    float low[MB][NQ];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+#pragma unroll
+      for (int f = 0; f < NQ; ++f) low[m][f] = INFINITY;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 x4 = *reinterpret_cast<const float4 *>(xn + m * 32 + 8 * g + 4 * half);
+        const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+        for (int f = 0; f < NQ; ++f)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            acc[m][f][4 * g + e] = fmaf(scale[f], acc[m][f][4 * g + e], xv[e]);
+            low[m][f] = fminf(low[m][f], acc[m][f][4 * g + e]);   // (never a NaN)
+          }
+      }
+    }
+    if (a.scores) {
+#pragma unroll
+      for (int f = 0; f < NQ; ++f) {
+        const uint32_t q = q0 + f * 32 + l32;
+        if (q >= a.nq) continue;
+        float *to = a.scores + (uint64_t)q * a.ld + row0;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)   // (a NaN becomes +inf: never selected)
+            *reinterpret_cast<float4 *>(to + m * 32 + 8 * g + 4 * half) =
+                make_float4(fminf(acc[m][f][4 * g], INFINITY), fminf(acc[m][f][4 * g + 1], INFINITY), fminf(acc[m][f][4 * g + 2], INFINITY),
+                            fminf(acc[m][f][4 * g + 3], INFINITY));
+      }
+      return;
+    }
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int f = 0; f < NQ; ++f) {
+        if (__ballot(low[m][f] <= top[f]) == 0) continue;
+        uint32_t mine = 0;   // this lane's scores up to the bound, a bit each
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mine |= acc[m][f][i] <= top[f] ? 1u << i : 0u;
+        for (;;) {
+          const uint64_t hm = __ballot(mine != 0);
+          if (hm == 0) break;
+          const int n_new = __popcll(hm);
+          if (n_hits + n_new > kHitList) flush();
+          if (mine != 0) {
+            const int i = __builtin_ctz(mine);
+            const int pos = n_hits + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
+            hits[pos] = ((uint64_t)order_u32(pick(acc[m][f], i)) << 32) | (row0 + (uint32_t)(m * 32 + 8 * (i / 4) + 4 * half + i % 4));
+            hits_q[pos] = (uint8_t)(f * 32 + l32);
+            mine &= mine - 1;
+          }
+          n_hits += n_new;
+        }
+      }
+  }
+};
+
+template <bool VEC4, int MB, int NQ, bool CENTRE, int PARTS>
 __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   constexpr int WB = 4 / MB;                   // wavefronts side by side over the base rows
   constexpr int QT32 = 4 / WB * NQ;            // blocks of 32 queries per tile
   static_assert(WB * MB * 32 == kSB, "tile shape");
   constexpr int NR = kSB / 32;                 // base rows per thread
-  __shared__ __align__(16) unsigned char stage_s[2][3 * kPlane];
+  static_assert(PARTS == 3 || !CENTRE, "centred rows come in three parts");
+  __shared__ __align__(16) unsigned char stage_s[2][PARTS * kPlane];
   __shared__ __align__(16) float xn_s[2][kSB];
   __shared__ uint64_t hit_s[4][kHitList];
   __shared__ uint8_t hit_q_s[4][kHitList];
@@ -397,7 +647,14 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
   const uint32_t n_chunks = a.kb_n / 2;
   const uint4 *qf[NQ];
 #pragma unroll
-  for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wq * NQ + f) * a.kb_n * 192 + lane;
+  for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wq * NQ + f) * a.kb_n * (PARTS * 64) + lane;
+  // two parts: the rows' scale, and the squared norm from which on a row may not fit the format
+  float x_scale = 1.0f, far_from = INFINITY;
+  if constexpr (PARTS == 2) {
+    const int e = __builtin_amdgcn_readfirstlane(half_exponent(rows_sq(a.sample_sq)));
+    x_scale = ldexpf(1.0f, e);
+    far_from = ldexpf(kFarNorm2, -2 * e);
+  }
 
   // ---- base rows: fetch (four floats of four rows per thread), split, stage.
   // Nothing here branches: the steps below are one block of instructions, in
@@ -452,13 +709,18 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
       const float sum = sq_other[i] + t;
       sq_other[i] = sq[i];
       sq[i] = sum;
-      uint32_t w01[3], w23[3];
-      split3(v.x, v.y, w01);
-      split3(v.z, v.w, w23);
+      uint32_t w01[PARTS], w23[PARTS];
+      if constexpr (PARTS == 3) {
+        split3(v.x, v.y, w01);
+        split3(v.z, v.w, w23);
+      } else {
+        split2(v.x, v.y, x_scale, w01);
+        split2(v.z, v.w, x_scale, w23);
+      }
       const int row = s_row + 32 * i;
       const int at = row * 64 + (((s_col >> 3) ^ (row >> 2)) & 3) * 16 + (s_col & 4) * 2;
 #pragma unroll
-      for (int p = 0; p < 3; ++p)
+      for (int p = 0; p < PARTS; ++p)
         *reinterpret_cast<uint2 *>(stage_s[b] + p * kPlane + at) = make_uint2(w01[p], w23[p]);
     }
   };
@@ -475,12 +737,12 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
         // Rows whose squared norm is no float are left out of the scores.  L2: they are infinitely far.  Inner
         // product: with a NaN they have no score; the others may be near, and are listed for the exact stage.
         const uint64_t r = tile * kSB + s_row + 32 * i;
-        const bool in = r < a.rows && t < INFINITY;
+        const bool in = r < a.rows && t < far_from;
         xn_s[tile & 1][s_row + 32 * i] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
         if (a.metric != ANN_L2 && a.state != nullptr) {
           if (in) {
             max_norm = fmaxf(max_norm, t);
-          } else if (r < a.rows && t == INFINITY && qt == 0 && a.list_far) {
+          } else if (r < a.rows && t >= far_from && qt == 0 && a.list_far) {
             const uint32_t at = atomicAdd(&a.state->far_rows, 1u);
             if (at < kFarRows) a.state->far_row[at] = (uint32_t)r;
           }
@@ -489,44 +751,7 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
     }
   };
 
-  // ---- this lane's queries
-  float top[NQ];
-  uint64_t bound[NQ];
-#pragma unroll
-  for (int f = 0; f < NQ; ++f) {
-    const uint32_t q = (qt * QT32 + wq * NQ + f) * 32 + l32;
-    bound[f] = a.scores == nullptr && q < a.nq ? a.bound[q] : 0ull;
-    top[f] = a.scores == nullptr && q < a.nq ? unorder_f32((uint32_t)(bound[f] >> 32)) : -INFINITY;
-  }
-  uint64_t *hits = hit_s[wave];
-  uint8_t *hits_q = hit_q_s[wave];
-  int n_hits = 0;   // the same in all lanes
-  auto fence = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
-  auto flush = [&]() {
-    fence();
-    bool over = false;
-    for (int e = lane; e < n_hits; e += kWave) {
-      const uint32_t q = qt * QT32 * 32 + hits_q[e];
-      const uint32_t pos = atomicAdd(&a.count[q], 1u);
-      if (pos < a.cap)
-        a.buf[(uint64_t)q * a.cap + pos] = hits[e];
-      else
-        over = true;
-    }
-    fence();
-    n_hits = 0;
-    // a query with more entries than room has to be treated otherwise: no more of them
-    if (__ballot(over) != 0) {
-#pragma unroll
-      for (int f = 0; f < NQ; ++f) {
-        const uint32_t q = (qt * QT32 + wq * NQ + f) * 32 + l32;
-        if (q < a.nq && *(volatile uint32_t *)&a.count[q] > a.cap) top[f] = -INFINITY;
-      }
-    }
-  };
+  TileEnd<MB, NQ> end(a, (qt * QT32 + wq * NQ) * 32, hit_s[wave], hit_q_s[wave]);
 
   floatx16 acc[MB][NQ];
   auto clear = [&]() {
@@ -537,99 +762,34 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[m][f][i] = 0.f;
   };
-  const float scale = a.metric == ANN_L2 ? -2.0f : -1.0f;
-  // acc[m][f][i]: base row (wb MB + m) 32 + 8 (i / 4) + 4 half + i % 4 of the tile against query l32 of block f
-  auto finish_tile = [&](uint64_t tile) {
-    const float *xn = xn_s[tile & 1];
-    float low[NQ];
-#pragma unroll
-    for (int f = 0; f < NQ; ++f) low[f] = INFINITY;
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int r0 = (wb * MB + m) * 32 + 8 * g + 4 * half;
-        const float4 x4 = *reinterpret_cast<const float4 *>(xn + r0);
-        const float xv[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-        for (int f = 0; f < NQ; ++f)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            // (a NaN becomes +inf: never selected)
-            acc[m][f][4 * g + e] = fminf(fmaf(scale, acc[m][f][4 * g + e], xv[e]), INFINITY);
-            low[f] = fminf(low[f], acc[m][f][4 * g + e]);
-          }
-      }
-    if (a.scores) {
-#pragma unroll
-      for (int f = 0; f < NQ; ++f) {
-        const uint32_t q = (qt * QT32 + wq * NQ + f) * 32 + l32;
-        if (q >= a.nq) continue;
-        float *to = a.scores + (uint64_t)q * a.ld + tile * kSB;
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<float4 *>(to + (wb * MB + m) * 32 + 8 * g + 4 * half) =
-                make_float4(acc[m][f][4 * g], acc[m][f][4 * g + 1], acc[m][f][4 * g + 2], acc[m][f][4 * g + 3]);
-      }
-      return;
-    }
-#pragma unroll
-    for (int f = 0; f < NQ; ++f) {
-      if (__ballot(low[f] <= top[f]) == 0) continue;
-#pragma unroll
-      for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float low4 = fminf(fminf(acc[m][f][4 * g], acc[m][f][4 * g + 1]), fminf(acc[m][f][4 * g + 2], acc[m][f][4 * g + 3]));
-          if (__ballot(low4 <= top[f]) == 0) continue;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float score = acc[m][f][4 * g + e];
-            if (__ballot(score <= top[f]) == 0) continue;
-            uint64_t id = tile * kSB + (wb * MB + m) * 32 + 8 * g + 4 * half + e;
-            if (a.stretch != 0.0) id = sample_row(id, a.stretch);
-            const uint64_t ent = ((uint64_t)order_u32(score) << 32) | (uint32_t)id;
-            const bool hit = score <= top[f] && ent <= bound[f];
-            const uint64_t hm = __ballot(hit);
-            const int n_new = __popcll(hm);
-            if (n_hits + n_new > kHitList) flush();
-            if (hit) {
-              const int pos = n_hits + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
-              hits[pos] = ent;
-              hits_q[pos] = (uint8_t)((wq * NQ + f) * 32 + l32);
-            }
-            n_hits += n_new;
-          }
-        }
-    }
-  };
-
-  auto load_q = [&](uint4 (&to)[NQ][3], uint32_t kb) {
+  auto load_q = [&](uint4 (&to)[NQ][PARTS], uint32_t kb) {
 #pragma unroll
     for (int f = 0; f < NQ; ++f)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) to[f][p] = qf[f][kb * 192 + p * 64];
+      for (int p = 0; p < PARTS; ++p) to[f][p] = qf[f][kb * (PARTS * 64) + p * 64];
   };
-  auto multiply = [&](const uint4 (&q)[NQ][3], int b, int kbi) {
-    bf16x8 xa[MB][3];
+  auto multiply = [&](const uint4 (&q)[NQ][PARTS], int b, int kbi) {
+    uint4 xa[MB][PARTS];
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
       const int row = (wb * MB + m) * 32 + l32;
       const int at = row * 64 + (((kbi * 2 + half) ^ (row >> 2)) & 3) * 16;
 #pragma unroll
-      for (int p = 0; p < 3; ++p) xa[m][p] = *reinterpret_cast<const bf16x8 *>(stage_s[b] + p * kPlane + at);
+      for (int p = 0; p < PARTS; ++p) xa[m][p] = *reinterpret_cast<const uint4 *>(stage_s[b] + p * kPlane + at);
     }
     // the small products first
-    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int kProducts = PARTS == 3 ? 6 : 3;
+    constexpr int pa[6] = {PARTS == 3 ? 2 : 1, 0, PARTS == 3 ? 1 : 0, 1, 0, 0}, pb[6] = {0, PARTS == 3 ? 2 : 1, PARTS == 3 ? 1 : 0, 0, 1, 0};
 #pragma unroll
-    for (int t = 0; t < 6; ++t)
+    for (int t = 0; t < kProducts; ++t)
 #pragma unroll
       for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int f = 0; f < NQ; ++f)
-          acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[m][pa[t]], __builtin_bit_cast(bf16x8, q[f][pb[t]]), acc[m][f], 0, 0, 0);
+          if constexpr (PARTS == 3)
+            acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[m][pa[t]]), __builtin_bit_cast(bf16x8, q[f][pb[t]]), acc[m][f], 0, 0, 0);
+          else
+            acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, xa[m][pa[t]]), __builtin_bit_cast(halfx8, q[f][pb[t]]), acc[m][f], 0, 0, 0);
   };
 
   // The next (tile, chunk) to stage and the one after it, which is fetched as soon as its registers are free.
@@ -639,7 +799,7 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
       ++tile;
     }
   };
-  uint4 q0[NQ][3], q1[NQ][3];
+  uint4 q0[NQ][PARTS], q1[NQ][PARTS];
   uint64_t tile = tile_begin, f_tile = tile_begin;
   uint32_t c = 0, f_c = 0;
   new_rows(tile);
@@ -663,7 +823,7 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
     // a matrix instruction occupies its unit for eight issue slots: the vector instructions (the
     // splitting, above all) are spread behind them (five each measured best: 13.4 ms, 14.4 with four, 13.8 with seven)
 #pragma unroll
-    for (int i = 0; i < 12 * MB * NQ; ++i) {
+    for (int i = 0; i < (PARTS == 3 ? 12 : 6) * MB * NQ; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x002, MB * NQ == 4 ? 5 : 10, 0);
     }
@@ -672,7 +832,7 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
     if (g_c == 0) new_rows(f_tile);
     fetch(g_c);
     if (c + 1 == n_chunks) {
-      finish_tile(tile);
+      end.finish(acc, xn_s[tile & 1] + wb * MB * 32, (uint32_t)(tile * kSB) + wb * MB * 32);
       clear();
     }
     after(tile, c);
@@ -680,12 +840,206 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
     __syncthreads();
     cur ^= 1;
   }
-  if (n_hits > 0) flush();
+  if (end.n_hits > 0) end.flush();
   if (a.metric != ANN_L2 && a.state != nullptr) {
     max_norm = wave_max_f32(max_norm);
     // (2,000 wavefronts at one address take 8 us; most find a value that is large enough)
     if (lane == 0 && *(volatile uint32_t *)&a.state->max_norm < __float_as_uint(max_norm)) atomicMax(&a.state->max_norm, __float_as_uint(max_norm));
   }
+}
+
+// ---------------------------------------------------------------------------
+// Many queries: the rows are split once, not by every workgroup that meets them.
+//
+// bf_halve_rows_kernel brings the rows of a pass, or of a slab of it, into the order
+// the matrix instruction wants (as the queries: 16-byte unit (((row / 32) * kb_n + kb) * 2
+// + plane) * 64 + lane) and writes their squared norms, summed in fp64 (+inf: left out of
+// the scores).  One workgroup per 32 rows, a wavefront takes every fourth block of 16
+// columns.  Reading and writing 128 MB each way takes 47 us.
+template <bool VEC4>
+__global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *__restrict__ frag, float *__restrict__ norm) {
+  __shared__ double part_s[8][32];
+  const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const uint64_t at = (uint64_t)blockIdx.x * 32 + lane % 32;
+  const int e = __builtin_amdgcn_readfirstlane(half_exponent(rows_sq(a.sample_sq)));
+  const float scale = ldexpf(1.0f, e), far_from = ldexpf(kFarNorm2, -2 * e);
+  uint64_t r = at < a.rows ? at : a.rows - 1;
+  r = a.stretch != 0.0 ? sample_row(a.first + r, a.stretch) : a.first + r;
+  const float *row = a.x + r * a.d;
+  uint4 *to = frag + (uint64_t)blockIdx.x * a.kb_n * 128 + lane;
+  double sq = 0.0;
+#pragma unroll 2
+  for (uint32_t kb = wave; kb < a.kb_n; kb += 4) {
+    const uint32_t k0 = kb * 16 + 8 * (lane / 32);
+    float v[8];
+    if constexpr (VEC4) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t k = k0 + 4 * h;
+        float4 w = *reinterpret_cast<const float4 *>(row + (k < a.d ? k : 0));
+        if (k >= a.d) w = make_float4(0.f, 0.f, 0.f, 0.f);
+        v[4 * h] = w.x, v[4 * h + 1] = w.y, v[4 * h + 2] = w.z, v[4 * h + 3] = w.w;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        v[j] = row[k0 + j < a.d ? k0 + j : 0];
+        v[j] = k0 + j < a.d ? v[j] : 0.0f;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sq = fma((double)v[j], (double)v[j], sq);
+    uint32_t w[4][2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], scale, w[j]);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) to[(uint64_t)kb * 128 + p * 64] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+  }
+  part_s[wave * 2 + lane / 32][lane % 32] = sq;
+  __syncthreads();
+  if (tid >= 32) return;
+  float t = (float)(((part_s[0][tid] + part_s[1][tid]) + (part_s[2][tid] + part_s[3][tid])) + ((part_s[4][tid] + part_s[5][tid]) + (part_s[6][tid] + part_s[7][tid])));
+  const bool in = at < a.rows && t < far_from;
+  norm[at] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
+  if (a.metric == ANN_L2 || a.state == nullptr) return;
+  if (at < a.rows && t >= far_from && a.list_far) {
+    const uint32_t n = atomicAdd(&a.state->far_rows, 1u);
+    if (n < kFarRows) a.state->far_row[n] = (uint32_t)r;
+  }
+  t = in ? t : 0.0f;
+#pragma unroll
+  for (int m = 1; m < 32; m <<= 1) t = fmaxf(t, __int_as_float(xor_lane_i32(__float_as_int(t), m)));
+  if (tid == 0 && *(volatile uint32_t *)&a.state->max_norm < __float_as_uint(t)) atomicMax(&a.state->max_norm, __float_as_uint(t));
+}
+
+// A workgroup of four wavefronts takes 128 rows x 256 queries per tile, a wavefront 128
+// x 64: eight accumulators, 128 registers, so that six products of 16 columns come to two
+// LDS reads of rows and one global read of queries.  No vector instruction
+// stands between the matrix instructions; two wavefronts share a SIMD, and one's
+// end of a tile falls into the other's products.  10,000 x 262,144 x 128: 1.84 ms = 365
+// TFLOP/s of fp32 work = 1,095 on the matrix cores, which are busy 57 % at the
+// 1.84 GHz the card then runs at (bf_score_kernel with two parts: 2.68 ms; with three:
+// 3.7).  128 queries per tile: 7 % slower; first products onto a constant zero instead
+// of cleared registers and the rows' parts requested one block ahead: 1.5 %.
+constexpr int kPairQueries = 256;
+__global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
+  constexpr int MB = 4, NQ = 2, QT32 = 4 * NQ;
+  static_assert(QT32 * 32 == kPairQueries, "tile shape");
+  __shared__ __align__(16) uint4 stage_s[2][4 * 2 * 2 * 64];   // [row / 32][kb][plane][lane]
+  __shared__ __align__(16) float xn_s[2][kSB];
+  __shared__ uint64_t hit_s[4][kHitList];
+  __shared__ uint8_t hit_q_s[4][kHitList];
+
+  // (as bf_score_kernel: a group of query tiles over all of a die's slabs, then the next group)
+  const uint32_t die = blockIdx.x & 7u, nth = blockIdx.x >> 3, die_slabs = (a.slabs + 7) / 8;
+  const uint32_t group = nth / (a.q_group * die_slabs), left = nth % (a.q_group * die_slabs);
+  const uint32_t width = a.q_tiles - group * a.q_group < a.q_group ? a.q_tiles - group * a.q_group : a.q_group;
+  const uint32_t qt = group * a.q_group + left % width, slab = left / width * 8u + die;
+  const uint32_t tiles = (uint32_t)((a.rows + kSB - 1) / kSB);
+  const uint32_t tile_begin = slab * a.tiles_per_slab;
+  const uint32_t tile_end = tile_begin + a.tiles_per_slab < tiles ? tile_begin + a.tiles_per_slab : tiles;
+  if (slab >= a.slabs || tile_begin >= tile_end) return;
+
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const uint32_t n_chunks = a.kb_n / 2;
+  const uint4 *qf[NQ];
+#pragma unroll
+  for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wave * NQ + f) * a.kb_n * 128 + lane;
+
+  // the chunk (two blocks of 16 columns) that is staged next: 32 rows' four units by each wavefront, and the tile's norms
+  uint32_t tile = tile_begin, f_tile = tile_begin, c = 0, f_c = 0;
+  uint4 x0, x1, x2, x3;
+  float xn_reg;
+  const uint4 *xf = a.xfrag + ((uint64_t)tile_begin * 4 + wave) * a.kb_n * 128 + lane;
+  auto fetch = [&]() {
+    const uint4 *p = xf + f_c * 256;
+    x0 = p[0];
+    x1 = p[64];
+    x2 = p[128];
+    x3 = p[192];
+    xn_reg = a.norm[(f_tile < tile_end ? f_tile : tile_end - 1) * kSB + tid % kSB];
+  };
+  auto stage = [&](int b) {
+    uint4 *to = &stage_s[b][wave * 256 + lane];
+    to[0] = x0;
+    to[64] = x1;
+    to[128] = x2;
+    to[192] = x3;
+    xn_s[f_tile & 1][tid % kSB] = xn_reg;   // (the same values with every chunk of a tile)
+  };
+  auto advance = [&]() {
+    if (++f_c == n_chunks) {
+      f_c = 0;
+      if (++f_tile < tile_end) xf += (uint64_t)4 * a.kb_n * 128;   // (past the end: the last tile again)
+    }
+  };
+
+  TileEnd<MB, NQ> end(a, (qt * QT32 + wave * NQ) * 32, hit_s[wave], hit_q_s[wave]);
+  floatx16 acc[MB][NQ];
+  auto load_q = [&](uint4 (&to)[NQ][2], uint32_t kb) {
+#pragma unroll
+    for (int f = 0; f < NQ; ++f)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) to[f][p] = qf[f][kb * 128 + p * 64];
+  };
+  halfx8 xa[2][2];
+  auto read_rows = [&](halfx8 (&to)[2], const uint4 *from) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) to[p] = __builtin_bit_cast(halfx8, from[p * 64]);
+  };
+  // 16 columns: the products of 32 rows at a time while the next 32 rows' parts (after the last: those at `next`) are on their way
+  auto multiply = [&](const uint4 (&q)[NQ][2], const uint4 *from, const uint4 *next, bool first) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      if (m + 1 < MB)
+        read_rows(xa[(m + 1) & 1], from + (m + 1) * 256);
+      else if (next)
+        read_rows(xa[0], next);
+      // the small products first
+      constexpr int pa[3] = {1, 0, 0}, pb[3] = {0, 1, 0};
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int f = 0; f < NQ; ++f) {
+          const floatx16 zero = {};
+          acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[m & 1][pa[t]], __builtin_bit_cast(halfx8, q[f][pb[t]]), first && t == 0 ? zero : acc[m][f], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  uint4 q0[NQ][2], q1[NQ][2];
+  fetch();
+  load_q(q0, 0);
+  stage(0);
+  advance();
+  fetch();
+  __syncthreads();
+  int cur = 0;
+  for (;;) {
+    const uint4 *from = &stage_s[cur][lane];
+    load_q(q1, 2 * c + 1);
+    read_rows(xa[0], from);
+    __builtin_amdgcn_sched_barrier(0);
+    if (c == 0)
+      multiply(q0, from, from + 128, true);
+    else
+      multiply(q0, from, from + 128, false);
+    stage(cur ^ 1);
+    load_q(q0, 2 * f_c);
+    advance();
+    fetch();
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(q1, from + 128, nullptr, false);
+    if (++c == n_chunks) {
+      end.finish(acc, xn_s[tile & 1], tile * kSB);
+      c = 0;
+      if (++tile == tile_end) break;
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+  if (end.n_hits > 0) end.flush();
 }
 
 // How far the score of a row with |x| <= nx may lie from its value, |q| = nq (of
@@ -698,6 +1052,16 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
 __device__ __forceinline__ double score_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric) {
   const double terms = 6.0 * kb_n + 32.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
   return terms * 0x1p-24 * size + 0x1p-124 * (double)d * (1.0 + nq + nx);
+}
+
+// The same for the products of two half-precision parts: three matrix instructions per
+// block of 16 columns; a part left over is below 2^-23 of its value or 2^-25 of the
+// scaled one's unit (x_unit, q_unit: what 1 in the scaled vectors is worth), and the product of
+// two second parts, left out, below 2^-22.
+__device__ __forceinline__ double half_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric, double x_unit, double q_unit) {
+  const double terms = 3.0 * kb_n + 32.0 + 8.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
+  const double lost = sqrt((double)d) * (nq * x_unit + nx * q_unit) + (double)d * x_unit * q_unit;
+  return terms * 0x1p-24 * size + 0x1p-24 * lost * (1.0 + 0x1p-10) + 0x1p-124 * (double)d * (1.0 + nq + nx);
 }
 
 // ---------------------------------------------------------------------------
@@ -854,6 +1218,7 @@ struct CertainArgs {
   const float *centre; // [d] what rows (and, L2, queries) were centred by, or NULL
   uint32_t d, kb_n, metric;
   const CallState *state;
+  const float *sample_sq, *unscale;   // two parts (otherwise NULL): as in ScoreArgs
   float *below;        // [nq] out
 };
 
@@ -924,7 +1289,16 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
     const float more = 1.0f + 0x1p-20f, nq = __fsqrt_rn((float)sq) * more;
     const double value = unorder_f32((uint32_t)(out >> 32)), dist = c.metric == ANN_L2 ? sq + value : value - along;
     const float nx = (c.metric == ANN_L2 ? nq + __fsqrt_rn(fmaxf((float)dist, 0.0f)) : __fsqrt_rn(__uint_as_float(c.state->max_norm))) * more;
-    float below = (float)(dist - score_room(nq, nx, c.d, c.kb_n, c.metric));
+    double room = score_room(nq, nx, c.d, c.kb_n, c.metric);
+    if (c.unscale) {
+      float most = 0.0f;
+      for (int i = 0; i < 64; ++i) most = fmaxf(most, c.sample_sq[i]);
+      const int e = half_exponent(most);
+      room = half_room(nq, nx, c.d, c.kb_n, c.metric, ldexpf(1.0f, -e), ldexpf(c.unscale[q], e));
+      // (L2: a row that was left out for its size may be as near as this one)
+      if (c.metric == ANN_L2 && !(nx * nx < ldexpf(0.99f * kFarNorm2, -2 * e))) room = INFINITY;
+    }
+    float below = (float)(dist - room);
     if (found > cap) below = -INFINITY;   // entries were lost
     if ((uint32_t)(out >> 32) >= kMaxScore || sq != sq) below = INFINITY;
     if (sq == INFINITY) below = -INFINITY;
@@ -993,50 +1367,80 @@ static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const 
   return ANN_OK;
 }
 
-// One pass of the score kernel over a.rows rows: tile shape by the number of
-// queries, slabs so that the last turn of workgroups (two per compute unit) is
-// nearly full.
-static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream_t st) {
-  const uint32_t qt = a.nq > 64 || (a.centre && a.nq > 32) ? 128u : (a.nq > 32 ? 64u : 32u);
-  a.q_tiles = (a.nq + qt - 1) / qt;
-  const uint64_t tiles = (a.rows + kSB - 1) / kSB;
+// Slabs of `tiles` row tiles so that the last turn of workgroups (two per compute unit) is nearly full.
+static void choose_slabs(uint64_t tiles, uint32_t q_tiles, uint32_t n_cu, uint32_t &out_slabs, uint32_t &tiles_per_slab) {
   const uint64_t slots = 2ull * n_cu;
   // a workgroup's time in tiles, with half a tile for its start
   double best = 0.0;
   uint64_t slabs = 1, tps = tiles;
-  const uint64_t most = 8 * slots / a.q_tiles + 8;
+  const uint64_t most = 8 * slots / q_tiles + 8;
   for (uint64_t s = 1; s <= most && s <= tiles; s = s < 8 ? s + 1 : s + 8) {
     const uint64_t t = (tiles + s - 1) / s, used = (tiles + t - 1) / t;
-    const double cost = (double)((used * a.q_tiles + slots - 1) / slots) * ((double)t + 0.5);
+    const double cost = (double)((used * q_tiles + slots - 1) / slots) * ((double)t + 0.5);
     if (s == 1 || cost < best * 0.99) {
       best = cost;
       slabs = used;
       tps = t;
     }
   }
+  out_slabs = (uint32_t)slabs;
+  tiles_per_slab = (uint32_t)tps;
+}
+
+// One pass of the score kernel over a.rows rows: tile shape by the number of
+// queries, slabs so that the last turn of workgroups (two per compute unit) is
+// nearly full.
+static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream_t st) {
+  const uint32_t qt = a.nq > 64 || a.unscale || (a.centre && a.nq > 32) ? 128u : (a.nq > 32 ? 64u : 32u);
+  a.q_tiles = (a.nq + qt - 1) / qt;
+  choose_slabs((a.rows + kSB - 1) / kSB, a.q_tiles, n_cu, a.slabs, a.tiles_per_slab);
   a.q_group = 16;
   if (a.q_group > a.q_tiles) a.q_group = a.q_tiles;
-  a.slabs = (uint32_t)slabs;
-  a.tiles_per_slab = (uint32_t)tps;
-  const uint32_t grid = a.q_tiles * (((uint32_t)slabs + 7) / 8 * 8);
+  const uint32_t grid = a.q_tiles * ((a.slabs + 7) / 8 * 8);
 #define ANN_BS(V)                                                     \
   do {                                                                \
-    if (a.centre && qt == 128)                                        \
-      bf_score_kernel<V, 4, 1, true><<<grid, 256, 0, st>>>(a);        \
+    if (a.unscale)                                                    \
+      bf_score_kernel<V, 4, 1, false, 2><<<grid, 256, 0, st>>>(a);    \
+    else if (a.centre && qt == 128)                                   \
+      bf_score_kernel<V, 4, 1, true, 3><<<grid, 256, 0, st>>>(a);     \
     else if (a.centre)                                                \
-      bf_score_kernel<V, 1, 1, true><<<grid, 256, 0, st>>>(a);        \
+      bf_score_kernel<V, 1, 1, true, 3><<<grid, 256, 0, st>>>(a);     \
     else if (qt == 128)                                               \
-      bf_score_kernel<V, 4, 1, false><<<grid, 256, 0, st>>>(a);       \
+      bf_score_kernel<V, 4, 1, false, 3><<<grid, 256, 0, st>>>(a);    \
     else if (qt == 64)                                                \
-      bf_score_kernel<V, 1, 2, false><<<grid, 256, 0, st>>>(a);       \
+      bf_score_kernel<V, 1, 2, false, 3><<<grid, 256, 0, st>>>(a);    \
     else                                                              \
-      bf_score_kernel<V, 1, 1, false><<<grid, 256, 0, st>>>(a);       \
+      bf_score_kernel<V, 1, 1, false, 3><<<grid, 256, 0, st>>>(a);    \
   } while (0)
   if (vec4)
     ANN_BS(true);
   else
     ANN_BS(false);
 #undef ANN_BS
+  ANN_HIP(hipGetLastError());
+  return ANN_OK;
+}
+
+// The same with the rows split ahead, a slab of at most x_rows at a time.  A die's group
+// of query tiles is a megabyte of parts, four tiles at least (between 4 and 16 tiles within 1 %).
+static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
+  const uint64_t n = a.rows;
+  a.xfrag = xfrag;
+  a.norm = norm;
+  a.q_tiles = (a.nq + kPairQueries - 1) / kPairQueries;
+  a.q_group = 64 / a.kb_n > 4 ? 64 / a.kb_n : 4;
+  if (a.q_group > a.q_tiles) a.q_group = a.q_tiles;
+  for (a.first = 0; a.first < n; a.first += x_rows) {
+    a.rows = n - a.first < x_rows ? n - a.first : x_rows;
+    const uint32_t tiles = (uint32_t)((a.rows + kSB - 1) / kSB);
+    if (vec4)
+      bf_halve_rows_kernel<true><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
+    else
+      bf_halve_rows_kernel<false><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
+    choose_slabs(tiles, a.q_tiles, n_cu, a.slabs, a.tiles_per_slab);
+    const uint32_t grid = a.q_tiles * ((a.slabs + 7) / 8 * 8);
+    bf_pair_kernel<<<grid, 256, 0, st>>>(a);
+  }
   ANN_HIP(hipGetLastError());
   return ANN_OK;
 }
@@ -1218,22 +1622,30 @@ struct Selection {
   uint32_t want, most, most_bound;   // see ann_bruteforce_topk
   uint32_t kb_n, cap, first, samples;
   uint64_t stretches, ld;
-  bool vec4, dense;
+  bool vec4, dense, halves;   // halves: scores from two half-precision parts
   double growth;
   uint4 *qfrag;
   float *scores, *below;
   uint64_t *buf, *bound;
   uint32_t *count, *cand;
   CallState *state;
+  float *sample_sq, *unscale;
+  uint4 *xfrag;        // room for x_rows split rows and their norms
+  float *xnorm;
+  uint64_t x_rows;
 };
 
 // One round: the k nearest rows of the m queries at qr.
 static ann_status select_round(const Truth &t, const Selection &s, const float *qr, uint32_t m, const float *centre, bool list_far,
                                uint32_t *out_ids, float *out_dist, uint32_t *uncertain, uint32_t first_query) {
-  const uint32_t blocks32 = (m + 127) / 128 * 4;
+  const uint32_t blocks32 = (m + 255) / 256 * 8;
   const uint64_t units = (uint64_t)blocks32 * s.kb_n * 64;
-  bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, t.st>>>(
-      qr, m, t.d, s.kb_n, blocks32, t.metric == ANN_L2 ? centre : nullptr, s.qfrag, s.bound, s.count);
+  const bool halves = s.halves && centre == nullptr;
+  if (halves)
+    bf_halve_queries_kernel<<<dim3(blocks32, (s.kb_n + 15) / 16), 1024, 0, t.st>>>(qr, m, t.d, s.kb_n, s.sample_sq, s.qfrag, s.unscale, s.bound, s.count);
+  else
+    bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, t.st>>>(
+        qr, m, t.d, s.kb_n, blocks32, t.metric == ANN_L2 ? centre : nullptr, s.qfrag, s.bound, s.count);
   ScoreArgs a{};
   a.x = t.x;
   a.qfrag = s.qfrag;
@@ -1248,7 +1660,9 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
   a.cap = s.cap;
   a.centre = centre;
   a.list_far = list_far;
-  const CertainArgs certain{qr, centre, t.d, s.kb_n, t.metric, s.state, s.below};
+  a.sample_sq = halves ? s.sample_sq : nullptr;
+  a.unscale = halves ? s.unscale : nullptr;
+  const CertainArgs certain{qr, centre, t.d, s.kb_n, t.metric, s.state, a.sample_sq, a.unscale, s.below};
   auto select_entries = [&](uint32_t *cnt, uint32_t *to, uint32_t up_to) {
     if (s.cap <= 2048)
       bf_select_entries_kernel<8><<<m, kSelThreads, 0, t.st>>>(s.buf, cnt, s.cap, s.want, up_to, s.bound, to, certain);
@@ -1275,7 +1689,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       a.stretch = last ? 0.0 : (double)t.n / (double)a.rows;
       a.scores = p == 0 ? s.scores : nullptr;
       a.state = last ? s.state : nullptr;
-      rc = launch_scores(a, s.vec4, t.n_cu, t.st);
+      rc = halves && s.x_rows ? launch_pairs(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st) : launch_scores(a, s.vec4, t.n_cu, t.st);
       if (rc != ANN_OK) return rc;
       if (p == 0 && s.first == kSampleRows)
         bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
@@ -1505,20 +1919,39 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   uint64_t round = (512ull << 20) / per_query / 128 * 128;
   if (round < 128) round = 128;
   if (round > nq) round = nq;
-  auto parts = [&](uint64_t m, uint64_t (&at)[9]) {
-    const uint64_t size[9] = {(m + 127) / 128 * 4 * kb_n * 192 * 16, m * ld * 4, m * cap * 8, m * 8, m * 4, m * most * 4, m * 4, sizeof(CallState),
-                              (uint64_t)nq * 4};
+  // Two parts where products take the time (up to 64 queries a call reads rows, few rows are a matter of
+  // launches) and where they lose no more than three: from 65 columns on, see bf_score_kernel.  The rows are
+  // split ahead where that costs less than it saves, which is a question of the queries and, since the splitting
+  // moves every row twice, of the columns.  Three parts / two / two, split ahead: 1M x 128, 512 queries 918 /
+  // 685 / 739 us, 768 1,397 / 1,011 / 927, 10,000 15,580 / 10,890 / 7,980; 200,000 x 960, 1,000 queries 2,254 /
+  // 1,590 / 1,801, 1,536 3,537 / 2,450 / 2,354.
+  const bool halves = !dense && nq > 64 && kb_n >= 6;
+  uint64_t x_rows = 0;
+  if (halves && nq >= 512 + kb_n * 16) {
+    x_rows = kPairBytes / (kb_n * 64) / kSB * kSB;
+    if (x_rows > (n + kSB - 1) / kSB * kSB) x_rows = (n + kSB - 1) / kSB * kSB;
+  }
+  auto parts = [&](uint64_t m, uint64_t (&at)[13]) {
+    const uint64_t size[13] = {(m + 255) / 256 * 8 * kb_n * 192 * 16, m * ld * 4, m * cap * 8, m * 8, m * 4, m * most * 4, m * 4, sizeof(CallState),
+                               (uint64_t)nq * 4, 64 * 4, m * 4, x_rows * kb_n * 64, x_rows * 4};
     uint64_t total = 0;
-    for (int i = 0; i < 9; ++i) {
+    for (int i = 0; i < 13; ++i) {
       at[i] = total;
       total += up256(size[i]);
     }
     return total;
   };
-  uint64_t at[9];
+  uint64_t at[13];
   unsigned char *base = nullptr;
-  hipError_t e = alloc_some((void **)&base, round, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
+  uint64_t m_fit = round;
+  hipError_t e = alloc_some((void **)&base, m_fit, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
+  if (e != hipSuccess && x_rows) {   // no room for split rows
+    x_rows = 0;
+    m_fit = round;
+    e = alloc_some((void **)&base, m_fit, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
+  }
   if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+  round = m_fit;
   parts(round, at);
   CallState *const state = reinterpret_cast<CallState *>(base + at[7]);
   uint32_t *const uncertain = reinterpret_cast<uint32_t *>(base + at[8]);
@@ -1543,20 +1976,32 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   s.cand = reinterpret_cast<uint32_t *>(base + at[5]);
   s.below = reinterpret_cast<float *>(base + at[6]);
   s.state = state;
+  s.sample_sq = reinterpret_cast<float *>(base + at[9]);
+  s.unscale = reinterpret_cast<float *>(base + at[10]);
+  s.halves = halves;
+  s.xfrag = reinterpret_cast<uint4 *>(base + at[11]);
+  s.xnorm = reinterpret_cast<float *>(base + at[12]);
+  s.x_rows = x_rows;
   const Truth t{x, n, d, q, k, metric, out_ids, out_dist, (uint32_t)n_cu, st};
 
-  fill_u32_kernel<<<1, 64, 0, st>>>(&state->n_uncertain, 6, 0u);   // (the counters in front of the list of rows)
   ann_status rc = ANN_OK;
-  for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += round) {
-    const uint32_t m = (uint32_t)(nq - q0 < round ? nq - q0 : round);
-    rc = select_round(t, s, q + q0 * d, m, nullptr, q0 == 0, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
-  }
   uint32_t found[2] = {0, 0};   // uncertain queries, far rows
-  e = rc == ANN_OK ? hipMemcpyAsync(found, state, sizeof(found), hipMemcpyDeviceToHost, st) : hipSuccess;
-  const hipError_t e2 = hipStreamSynchronize(st);
-  if (rc == ANN_OK && e != hipSuccess) rc = hip_fail(e, "hipMemcpyAsync");
-  if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipStreamSynchronize");
-  bool idle = e2 == hipSuccess;
+  bool idle = true;
+  for (;;) {
+    fill_u32_kernel<<<1, 64, 0, st>>>(&state->n_uncertain, 6, 0u);   // (the counters in front of the list of rows)
+    if (s.halves) bf_sample_norms_kernel<<<kNormSample / 16, 1024, 0, st>>>(x, d, (double)n / kNormSample, s.sample_sq);
+    for (uint64_t q0 = 0; q0 < nq && rc == ANN_OK; q0 += round) {
+      const uint32_t m = (uint32_t)(nq - q0 < round ? nq - q0 : round);
+      rc = select_round(t, s, q + q0 * d, m, nullptr, q0 == 0, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
+    }
+    e = rc == ANN_OK ? hipMemcpyAsync(found, state, sizeof(found), hipMemcpyDeviceToHost, st) : hipSuccess;
+    const hipError_t e2 = hipStreamSynchronize(st);
+    if (rc == ANN_OK && e != hipSuccess) rc = hip_fail(e, "hipMemcpyAsync");
+    if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipStreamSynchronize");
+    idle = e2 == hipSuccess;
+    if (rc != ANN_OK || !s.halves || found[1] <= kFewFarRows) break;
+    s.halves = false;   // inner product, more than a few rows outside half precision's range: three parts
+  }
   if (rc == ANN_OK && found[1] > kFarRows) {
     rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
   } else if (rc == ANN_OK) {

@@ -233,3 +233,70 @@ def test_one_row_that_is_no_number_costs_little(H, value):
     plain = best()
     X[1234, 5] = value
     assert best() < 2.5 * plain
+
+
+def _check_some(H, X, Q, k, metric, every=13):
+    """_check where the oracle takes some of the queries, the first and the last among them."""
+    gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
+    some = np.unique(np.r_[np.arange(0, len(Q), max(every, len(Q) // 40)), len(Q) - 1])
+    oid, odist = oracle.bruteforce_topk(X, Q[some], k, metric=metric)
+    H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
+
+
+# two half-precision parts (from 65 queries and 65 columns on), split on the way or ahead (from 512 plus the
+# columns on, tiles of 256 queries); samples of both sizes; columns that end inside a block, rows inside a tile and a slab
+@pytest.mark.parametrize("n,d,nq,k,metric", [
+    (16385, 65, 65, 10, oracle.L2), (20011, 100, 129, 17, oracle.IP), (17000, 131, 608, 5, oracle.L2), (17000, 96, 608, 10, oracle.IP),
+    (30001, 72, 641, 10, oracle.L2), (300001, 67, 700, 3, oracle.L2), (140000, 260, 800, 10, oracle.IP), (16640, 2048, 2600, 1, oracle.L2),
+    (50000, 128, 1024, 100, oracle.IP)])
+def test_two_parts(H, n, d, nq, k, metric):
+    _check_some(H, _points(n, d, n + d), _points(nq, d, k), k, metric)
+
+
+@pytest.mark.parametrize("nq", [100, 700])
+@pytest.mark.parametrize("scale", [2.0 ** -40, 1e-6, 3e4, 2.0 ** 40])
+def test_two_parts_of_vectors_of_any_size(H, nq, scale):
+    X, Q = _points(18000, 70, 51) * np.float32(scale), _points(nq, 70, 52) * np.float32(scale)
+    Q[3] *= np.float32(1e-3)
+    Q[5] = 0.0
+    _check_some(H, X, Q, 10, oracle.L2, every=5)
+    Q[5] = X[17]   # (an inner product with zero has no nearest rows)
+    _check_some(H, X, Q, 10, oracle.IP, every=5)
+
+
+@pytest.mark.parametrize("nq", [100, 700])
+@pytest.mark.parametrize("metric,n_large", [(oracle.L2, 5), (oracle.L2, 300), (oracle.IP, 5), (oracle.IP, 64), (oracle.IP, 65), (oracle.IP, 300)])
+def test_two_parts_with_rows_outside_their_range(H, nq, metric, n_large):
+    """Rows a thousand times larger than those of any sample: near to some queries (L2), the nearest of most (inner product)."""
+    n, d = 20_000, 80
+    X, Q = _points(n, d, 61), _points(nq, d, 62)
+    sampled = np.unique(np.concatenate([_sampled_rows(n, 1024), _sampled_rows(n, 4096)]))
+    large = np.setdiff1d(np.arange(n), sampled)[7::11][:n_large]
+    X[large] *= 1000.0
+    if metric == oracle.L2:
+        Q[: nq // 4] = X[large[np.arange(nq // 4) % n_large]] + _points(nq // 4, d, 63)
+    _check_some(H, X, Q, 10, metric, every=4)
+
+
+@pytest.mark.parametrize("nq", [100, 700])
+def test_two_parts_with_rows_that_are_not_finite(H, nq):
+    n, d = 20_000, 80
+    X, Q = _points(n, d, 71), _points(nq, d, 72)
+    X[5, 3], X[9, 70], X[11, 0] = np.nan, np.inf, -np.inf
+    gid, gdist = H.gpu_bruteforce(X, Q, 10, oracle.L2)
+    _check_but(H, X, Q[::7], 10, oracle.L2, [5, 9, 11], [], gid[::7], gdist[::7])
+
+
+@pytest.mark.parametrize("nq", [70, 650])
+def test_two_parts_of_rows_that_are_not_aligned(H, nq):
+    import torch
+    import paper_2503_17911_amd as ann
+    n, d, k = 17000, 96, 10
+    X, Q = _points(n, d, 81), _points(nq, d, 82)
+    buf = torch.empty(n * d + 1, device=H.DEV)
+    buf[1:] = H.dev(X).reshape(-1)
+    ids = torch.empty((nq, k), dtype=torch.int32, device=H.DEV)
+    dist = torch.empty((nq, k), device=H.DEV)
+    ann.ann_bruteforce_topk(buf[1:], n, d, H.dev(Q), nq, k, ann.L2, ids, dist, H.stream_ptr())
+    oid, odist = oracle.bruteforce_topk(X, Q[::7], k, metric=oracle.L2)
+    H.check_rerank(H.as_u32(ids)[::7], dist.cpu().numpy()[::7], oid, odist.astype(np.float32), rel=1e-6)
