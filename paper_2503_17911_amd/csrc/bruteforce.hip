@@ -370,16 +370,6 @@ __global__ __launch_bounds__(256) void bf_split_queries_kernel(const float *__re
   }
 }
 
-// Row of x that is row j of a sample: a random one of the j-th stretch of rows
-// (the stretches tile the whole set, so the rows are distinct).
-__device__ __forceinline__ uint64_t sample_row(uint64_t j, double stretch) {
-  uint32_t h = (uint32_t)j * 0x9E3779B1u;
-  h = (h ^ (h >> 15)) * 0x85EBCA77u;
-  h ^= h >> 13;
-  const uint64_t begin = (uint64_t)((double)j * stretch), end = (uint64_t)((double)(j + 1) * stretch);
-  return begin + __umulhi(h, (uint32_t)(end - begin));
-}
-
 // Largest squared norm (of those that are floats) of each 64th of a sample of
 // kNormSample rows: out[64].  A wavefront per row.
 constexpr uint32_t kNormSample = 1024;

@@ -115,6 +115,16 @@ __device__ __forceinline__ float dot_in_order(const float *a, const float *b, ui
   return (float)acc;
 }
 
+// Row of x that is row j of a sample: a random one of the j-th stretch of rows
+// (the stretches tile the whole set, so the rows are distinct).
+__device__ __forceinline__ uint64_t sample_row(uint64_t j, double stretch) {
+  uint32_t h = (uint32_t)j * 0x9E3779B1u;
+  h = (h ^ (h >> 15)) * 0x85EBCA77u;
+  h ^= h >> 13;
+  const uint64_t begin = (uint64_t)((double)j * stretch), end = (uint64_t)((double)(j + 1) * stretch);
+  return begin + __umulhi(h, (uint32_t)(end - begin));
+}
+
 // fp32 -> uint32 such that unsigned order equals numeric order (no NaN).
 __device__ __forceinline__ uint32_t order_u32(float f) {
   uint32_t u = __float_as_uint(f);

@@ -221,6 +221,322 @@ __global__ void truncated_range_kernel(const uint32_t *__restrict__ prefix, uint
   delta[j] = (mx > mn) ? __fdiv_rn(__fsub_rn(mx, mn), levels) : 1.0f;
 }
 
+// The same in one read of x where a sample says between which two values an order
+// statistic must lie.  Per column and end of the range, from a stratified random sample of
+// m rows: `a` and `b`, kBracketWidth standard deviations of the sample's order statistic (and a
+// little) to either side of it.  One pass over x then counts what lies outside of
+// the two brackets and what equals an end of one, and lists what lies strictly inside (1 % of
+// the values); the wanted one is picked from the list by its rank.  Any order of the
+// rows and any distribution: a bracket that does not hold the wanted rank or has more values
+// inside than there is room for (many equal ones) is noticed, and the call takes
+// the four radix passes.  Bound: the pass' read of x (a third of its time beyond that is
+// the walk over the values inside).  200,000 x 960, coverage 0.99: four passes and
+// picks 738 us; sample 20, brackets 52, pass 210, picks 24: 303 with the host's wait.
+// 1M x 128 521 / 252, 33,000 x 100 145 / 75.
+constexpr double kBracketWidth = 5.5;
+constexpr uint32_t kBracketMost = 1u << 18;   // values of a list at most
+constexpr int kBracketKeys = 32;              // keys of the sample per thread
+
+// What the pass finds out about an end (0: low, 1: high) of column j, at [end * d + j].
+struct BracketArgs {
+  const float *x;
+  uint64_t n;
+  uint32_t d, k;          // rank of the low end; of the high one, from above
+  uint32_t m, room;       // rows of the sample; values a list has room for
+  double below, beyond, slack;   // ranks in the sample between which the bracket reaches, and how much further it may
+  uint32_t *sample;       // [d][m] ordered keys
+  uint32_t *a, *b;        // brackets
+  uint32_t *outside;      // values below a (low end), above b (high end)
+  uint32_t *at_a, *at_b, *inside;
+  uint32_t *list;         // [2 * d][room]
+  uint32_t *failed;
+};
+
+// Rows of the sample, column by column: a workgroup turns 64 rows x 64 columns in LDS.
+__global__ __launch_bounds__(256) void bracket_sample_kernel(BracketArgs g) {
+  __shared__ uint32_t tile[64][65];
+  const uint32_t lane = threadIdx.x % 64, w = threadIdx.x / 64, j = blockIdx.y * 64 + lane;
+  const double stretch = (double)g.n / g.m;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint64_t r = sample_row(blockIdx.x * 64 + w * 16 + i, stretch);
+    tile[w * 16 + i][lane] = j < g.d ? order_u32(g.x[r * g.d + j]) : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t c = blockIdx.y * 64 + w * 16 + i;
+    if (c < g.d) g.sample[(uint64_t)c * g.m + blockIdx.x * 64 + lane] = tile[lane][w * 16 + i];
+  }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *g.failed = 0;
+}
+
+// Keys in registers, EPT per thread of THREADS; a step of a bisection counts those up to the middle.
+template <int EPT, int THREADS>
+struct KeyCounter {
+  static constexpr int kWaves = THREADS / kWave;
+  uint32_t key[EPT];
+  uint32_t *red;   // LDS [2][kWaves]
+  int parity = 0;
+  __device__ __forceinline__ uint32_t up_to(uint32_t v) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) c += (uint32_t)__popcll(__ballot(key[e] <= v));
+    return total(c);
+  }
+  __device__ __forceinline__ uint32_t total(uint32_t c) {   // of the wavefronts' counts
+    if (threadIdx.x % kWave == 0) red[parity * kWaves + threadIdx.x / kWave] = c;
+    __syncthreads();
+    c = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) c += red[parity * kWaves + w];
+    parity ^= 1;
+    return c;
+  }
+};
+
+// One workgroup per column: the brackets of both ends.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void bracket_bounds_kernel(BracketArgs g) {
+  constexpr int EPT = kBracketKeys, kWaves = THREADS / kWave;
+  __shared__ uint32_t red[2 * kWaves], ends[kWaves];
+  const uint32_t j = blockIdx.x, tid = threadIdx.x;
+  KeyCounter<EPT, THREADS> s;
+  s.red = red;
+  uint32_t mn = 0xFFFFFFFFu, mx = 0;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    s.key[e] = g.sample[(uint64_t)j * g.m + e * THREADS + tid];
+    mn = s.key[e] < mn ? s.key[e] : mn;
+    mx = s.key[e] > mx ? s.key[e] : mx;
+  }
+  auto least = [&](uint32_t v) {   // of all threads' values
+#pragma unroll
+    for (int x = 1; x < kWave; x <<= 1) {
+      const uint32_t o = (uint32_t)xor_lane_i32((int)v, x);
+      v = o < v ? o : v;
+    }
+    __syncthreads();
+    if (tid % kWave == 0) ends[tid / kWave] = v;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v = ends[w] < v ? ends[w] : v;
+    return v;
+  };
+  mn = least(mn);
+  mx = ~least(~mx);
+  for (int end = 0; end < 2; ++end) {
+    // the high end is the low end of the complements
+    if (end == 1) {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) s.key[e] = ~s.key[e];
+      const uint32_t t = ~mx;
+      mx = ~mn;
+      mn = t;
+    }
+    uint32_t a = 0, b = 0xFFFFFFFFu;
+    const uint32_t under = mn > 0 ? mn - 1 : 0;
+    // a: the smallest key above a value that few enough keys reach (no bound if the wanted rank is among the first)
+    if (g.below >= 1.0) {
+      uint32_t lo = under, hi = mx;   // count(lo) <= below < count(hi)
+      while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        const double n = s.up_to(mid);
+        if (n <= g.below) {
+          lo = mid;
+          if (n >= g.below - g.slack) break;
+        } else {
+          hi = mid;
+        }
+      }
+      uint32_t next = 0xFFFFFFFFu;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) next = s.key[e] > lo && s.key[e] < next ? s.key[e] : next;
+      a = least(next);
+    }
+    // b: the first value that enough keys reach, or one not far above it
+    if (g.beyond <= (double)g.m) {
+      uint32_t lo = under, hi = mx;   // count(lo) < beyond <= count(hi)
+      while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        const double n = s.up_to(mid);
+        if (n >= g.beyond) {
+          hi = mid;
+          if (n <= g.beyond + g.slack) break;
+        } else {
+          lo = mid;
+        }
+      }
+      b = hi;
+    }
+    const uint32_t between = a < b ? s.up_to(b - 1) - s.up_to(a) : 0u;
+    if (tid == 0) {
+      const uint64_t at = (uint64_t)end * g.d + j;
+      g.a[at] = end ? ~b : a;
+      g.b[at] = end ? ~a : b;
+      g.outside[at] = g.at_a[at] = g.at_b[at] = g.inside[at] = 0;
+      if ((double)between * ((double)g.n / g.m) > 0.75 * g.room) atomicOr(g.failed, 1u);
+    }
+  }
+}
+
+// The pass over x.  A thread stays in its column (32 columns x 16 rows at a time),
+// carries kSelUnroll values and then walks those of them that lie in a bracket; these
+// collect in LDS and go to their lists when the workgroup's rows are done.  A workgroup
+// takes every gridDim.x-th group of 16 rows: rows in an order that puts a bracket's
+// values side by side spread over the workgroups.
+constexpr int kBracketLocal = 128;   // values of a column and end collected in LDS
+__global__ __launch_bounds__(kSelBlock) void bracket_collect_kernel(BracketArgs g) {
+  __shared__ uint32_t local[2 * kSelCols][kBracketLocal], n_local[2 * kSelCols], tally[6][kSelCols], base_s[2 * kSelCols];
+  if (*(volatile uint32_t *)g.failed) return;   // (set by an earlier kernel only)
+  const uint32_t tid = threadIdx.x, c = tid % kSelCols, col = blockIdx.y * kSelCols + c;
+  if (tid < 2 * kSelCols) n_local[tid] = 0;
+  for (uint32_t e = tid; e < 6 * kSelCols; e += kSelBlock) (&tally[0][0])[e] = 0;
+  __syncthreads();
+  constexpr uint32_t side = kSelBlock / kSelCols;
+  if (col < g.d) {
+    const uint32_t a0 = g.a[col], b0 = g.b[col], a1 = g.a[g.d + col], b1 = g.b[g.d + col];
+    uint32_t below = 0, above = 0, eq[4] = {0, 0, 0, 0};
+    auto put = [&](uint32_t key, uint32_t end) {
+      const uint32_t at = end * kSelCols + c, pos = atomicAdd(&n_local[at], 1u);
+      if (pos < kBracketLocal) {
+        local[at][pos] = key;
+      } else {
+        const uint64_t l = (uint64_t)end * g.d + col;
+        const uint32_t to = atomicAdd(&g.inside[l], 1u);
+        if (to < g.room) g.list[l * g.room + to] = key;
+      }
+    };
+    auto take = [&](const float (&v)[kSelUnroll], uint32_t valid) {
+      uint32_t key[kSelUnroll], mine = 0;
+#pragma unroll
+      for (int u = 0; u < kSelUnroll; ++u) {
+        key[u] = order_u32(v[u]);
+        const bool in = (valid >> u) & 1u;
+        below += in && key[u] < a0 ? 1u : 0u;
+        above += in && key[u] > b1 ? 1u : 0u;
+        mine |= key[u] - a0 <= b0 - a0 ? 1u << u : 0u;
+        mine |= key[u] - a1 <= b1 - a1 ? 256u << u : 0u;
+      }
+      mine &= valid * 257u;
+      while (mine) {
+        const int i = __builtin_ctz(mine), u = i & 7;
+        mine &= mine - 1;
+        static_assert(kSelUnroll == 8, "three selects");
+        const uint32_t s0 = u & 1 ? key[1] : key[0], s1 = u & 1 ? key[3] : key[2], s2 = u & 1 ? key[5] : key[4], s3 = u & 1 ? key[7] : key[6];
+        const uint32_t t0 = u & 2 ? s1 : s0, t1 = u & 2 ? s3 : s2, v_ = u & 4 ? t1 : t0;
+        const bool high = i >= 8;
+        const uint32_t a = high ? a1 : a0, b = high ? b1 : b0;
+        eq[0] += !high && v_ == a ? 1u : 0u;
+        eq[1] += !high && v_ == b ? 1u : 0u;
+        eq[2] += high && v_ == a ? 1u : 0u;
+        eq[3] += high && v_ == b ? 1u : 0u;
+        if (v_ != a && v_ != b) put(v_, high ? 1u : 0u);
+      }
+    };
+    const float *at = g.x + col;
+    const uint64_t step = (uint64_t)gridDim.x * side;
+    for (uint64_t i = (uint64_t)blockIdx.x * side + tid / kSelCols; i < g.n; i += kSelUnroll * step) {
+      float v[kSelUnroll];
+      uint32_t valid = 0;
+#pragma unroll
+      for (int u = 0; u < kSelUnroll; ++u) {
+        const uint64_t r = i + (uint64_t)u * step;
+        v[u] = at[(r < g.n ? r : g.n - 1) * g.d];
+        valid |= r < g.n ? 1u << u : 0u;
+      }
+      take(v, valid);
+    }
+    if (below) atomicAdd(&tally[0][c], below);
+    if (above) atomicAdd(&tally[1][c], above);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (eq[e]) atomicAdd(&tally[2 + e][c], eq[e]);
+  }
+  __syncthreads();
+  if (tid < 2 * kSelCols) {
+    const uint32_t end = tid / kSelCols, gc = blockIdx.y * kSelCols + tid % kSelCols;
+    if (gc < g.d) {
+      const uint64_t l = (uint64_t)end * g.d + gc;
+      const uint32_t out = tally[end][tid % kSelCols], ea = tally[2 + 2 * end][tid % kSelCols], eb = tally[3 + 2 * end][tid % kSelCols];
+      const uint32_t n_l = n_local[tid] < kBracketLocal ? n_local[tid] : kBracketLocal;
+      if (out) atomicAdd(&g.outside[l], out);
+      if (ea) atomicAdd(&g.at_a[l], ea);
+      if (eb) atomicAdd(&g.at_b[l], eb);
+      base_s[tid] = n_l ? atomicAdd(&g.inside[l], n_l) : 0u;
+      n_local[tid] = n_l;
+    } else {
+      n_local[tid] = 0;
+    }
+  }
+  __syncthreads();
+  for (uint32_t e = tid; e < 2 * kSelCols * kBracketLocal; e += kSelBlock) {
+    const uint32_t at = e / kBracketLocal, i = e % kBracketLocal;
+    if (i >= n_local[at]) continue;
+    const uint64_t l = (uint64_t)(at / kSelCols) * g.d + blockIdx.y * kSelCols + at % kSelCols;
+    const uint32_t to = base_s[at] + i;
+    if (to < g.room) g.list[l * g.room + to] = local[at][i];
+  }
+}
+
+// One workgroup per column and end: the wanted value, as radix_pick_kernel leaves it.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void bracket_pick_kernel(BracketArgs g, uint32_t *__restrict__ prefix) {
+  __shared__ uint32_t red[2 * THREADS / kWave];
+  if (*(volatile uint32_t *)g.failed & 1u) return;   // (by bracket_bounds_kernel; the other bit may be set meanwhile)
+  const uint32_t end = blockIdx.x / g.d, tid = threadIdx.x;
+  const uint64_t l = blockIdx.x;
+  // from the end inwards: outside, equal to the outer end, inside, equal to the inner end
+  const uint32_t out = g.outside[l], ea = g.at_a[l], eb = g.at_b[l], n_l = g.inside[l], a = g.a[l], b = g.b[l];
+  const uint32_t outer = end ? eb : ea, inner = end ? ea : eb, want = g.k - out;   // (wraps below)
+  if (g.k < out || n_l > g.room || (uint64_t)want >= (uint64_t)outer + n_l + (a < b ? inner : 0u)) {
+    if (tid == 0) atomicOr(g.failed, 2u);
+    return;
+  }
+  if (want < outer || want - outer >= n_l) {
+    if (tid == 0) prefix[l] = (want < outer) == (end == 0) ? a : b;
+    return;
+  }
+  const uint32_t from_low = end ? n_l - 1 - (want - outer) : want - outer;
+  const uint32_t *list = g.list + l * g.room;
+  auto bisect = [&](auto &&count) {
+    uint32_t lo = a, hi = b;   // count(lo) <= from_low < count(hi)
+    while (hi - lo > 1) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      if (count(mid) > from_low)
+        hi = mid;
+      else
+        lo = mid;
+    }
+    if (tid == 0) prefix[l] = hi;
+  };
+  auto in_registers = [&](auto &s) {
+    s.red = red;
+    constexpr int kEach = sizeof(s.key) / sizeof(s.key[0]);
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) {
+      const uint32_t i = (uint32_t)e * THREADS + tid;
+      s.key[e] = i < n_l ? list[i] : 0xFFFFFFFFu;   // (none inside a bracket is that large)
+    }
+    bisect([&](uint32_t mid) { return s.up_to(mid); });
+  };
+  if (n_l <= 16u * THREADS) {
+    KeyCounter<16, THREADS> s;
+    in_registers(s);
+  } else if (n_l <= 64u * THREADS) {
+    KeyCounter<64, THREADS> s;
+    in_registers(s);
+  } else {   // (millions of rows: the list is read again for every step)
+    KeyCounter<1, THREADS> s;
+    s.red = red;
+    bisect([&](uint32_t mid) {
+      uint32_t c = 0;
+      for (uint32_t i = tid; i < n_l; i += THREADS) c += list[i] <= mid ? 1u : 0u;
+      return s.total((uint32_t)group_sum_i32<kWave>((int)c));
+    });
+  }
+}
+
 // ------------------------------------------------------------- encoder
 // Bound: one read of x, one write of the codes (vector instructions are close
 // behind).  A group of LPR lanes takes a row, VEC dimensions per lane and piece
@@ -523,6 +839,78 @@ ann_status launch_query_prep(ann_index *ix, uint32_t level, const float *q, uint
   return ANN_OK;
 }
 
+// Workgroups of 256 to 4,096 rows, about a thousand (two and more fit a compute unit).
+static dim3 select_grid(uint64_t n, uint32_t d, uint64_t &rows_per_block) {
+  const uint32_t groups = (d + kSelCols - 1) / kSelCols;
+  rows_per_block = n * groups / 1024;
+  rows_per_block = rows_per_block < 256 ? 256 : (rows_per_block > 4096 ? 4096 : rows_per_block);
+  return dim3((uint32_t)((n + rows_per_block - 1) / rows_per_block), groups);
+}
+
+// The truncated range by brackets from a sample, if that is to be expected to work (`done`: it did).
+static ann_status train_bracketed(const float *x, uint64_t n, uint32_t d, uint32_t k, float levels, float *lo, float *delta,
+                                  hipStream_t st, bool &done) {
+  // the smallest sample whose brackets hold few values
+  const double p = ((double)k + 0.5) / (double)n;
+  BracketArgs g{};
+  double expected = 0.0, deviation = 0.0;
+  for (uint32_t m = 8192; m <= 32768 && n >= 4ull * m && (g.m == 0 || expected > 6000.0); m *= 2) {
+    g.m = m;
+    deviation = sqrt((double)m * p * (1.0 - p)) + 1.0;
+    expected = (2.0 * (kBracketWidth + 0.5) * deviation + 4.0) / m * (double)n;
+  }
+  // (with more values in the brackets the lists cost more than three passes: 1M x 128, coverage 0.9, 2 %: 524 us / 290, 0.6, 3.3 %: 527 / 900)
+  if (g.m == 0 || expected > 0.3 * kBracketMost || expected > 0.022 * (double)n) return ANN_OK;
+  g.x = x;
+  g.n = n;
+  g.d = d;
+  g.k = k;
+  g.below = p * g.m - kBracketWidth * deviation - 1.0;
+  g.beyond = p * g.m + kBracketWidth * deviation + 2.0;
+  g.slack = deviation;
+  g.room = 3.0 * expected + 256.0 < kBracketMost ? (uint32_t)(3.0 * expected) + 256 : kBracketMost;
+  const uint64_t ends = 2ull * d, words = (uint64_t)d * g.m + ends * g.room + 7 * ends + 1;
+  uint32_t *base = nullptr;
+  if (device_alloc((void **)&base, words * sizeof(uint32_t)) != hipSuccess) {
+    (void)hipGetLastError();
+    return ANN_OK;   // (the radix passes need less)
+  }
+  g.sample = base;
+  g.list = g.sample + (uint64_t)d * g.m;
+  g.a = g.list + ends * g.room;
+  g.b = g.a + ends;
+  g.outside = g.b + ends;
+  g.at_a = g.outside + ends;
+  g.at_b = g.at_a + ends;
+  g.inside = g.at_b + ends;
+  uint32_t *prefix = g.inside + ends;
+  g.failed = prefix + ends;
+  bracket_sample_kernel<<<dim3(g.m / 64, (d + 63) / 64), 256, 0, st>>>(g);
+  static_assert(kBracketKeys * 1024 == 32768, "keys per thread");
+  if (g.m == 8192)
+    bracket_bounds_kernel<256><<<d, 256, 0, st>>>(g);
+  else if (g.m == 16384)
+    bracket_bounds_kernel<512><<<d, 512, 0, st>>>(g);
+  else
+    bracket_bounds_kernel<1024><<<d, 1024, 0, st>>>(g);
+  uint64_t rows_per_block;
+  bracket_collect_kernel<<<select_grid(n, d, rows_per_block), kSelBlock, 0, st>>>(g);
+  if (expected <= 8192.0)
+    bracket_pick_kernel<256><<<(uint32_t)ends, 256, 0, st>>>(g, prefix);
+  else
+    bracket_pick_kernel<1024><<<(uint32_t)ends, 1024, 0, st>>>(g, prefix);
+  truncated_range_kernel<<<(d + 255) / 256, 256, 0, st>>>(prefix, d, levels, lo, delta);
+  uint32_t failed = 1;
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(&failed, g.failed, sizeof(failed), hipMemcpyDeviceToHost, st);
+  const hipError_t e2 = hipStreamSynchronize(st);
+  device_free(base, e2 == hipSuccess);
+  if (e != hipSuccess) return hip_fail(e, "ann_sq_train_truncated");
+  if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
+  done = failed == 0;
+  return ANN_OK;
+}
+
 }  // namespace ann
 
 using namespace ann;
@@ -567,15 +955,15 @@ ann_status ann_sq_train_truncated(const float *x, uint64_t n, uint32_t d, uint32
   if (bits != 8 && bits != 4) return fail(ANN_EINVAL, "ann_sq_train_truncated: bits must be 4 or 8");
   if (!(coverage > 0.5 && coverage <= 1.0)) return fail(ANN_EINVAL, "ann_sq_train_truncated: coverage must be in (0.5, 1]");
   const uint64_t k = (uint64_t)floor((1.0 - coverage) * (double)(n - 1));
+  bool done = false;
+  ann_status rc = train_bracketed(x, n, d, (uint32_t)k, (float)((1u << bits) - 1u), lo, delta, st, done);
+  if (rc != ANN_OK || done) return rc;
   uint32_t *hist = nullptr;  // [2][d][256], then prefix[2][d] and rank[2][d]
   const size_t n_hist = (size_t)512 * d;
   ANN_HIP(device_alloc((void **)&hist, (n_hist + (size_t)4 * d) * sizeof(uint32_t)));
   uint32_t *prefix = hist + n_hist, *rank = prefix + (size_t)2 * d;
-  // about a thousand workgroups (two fit a compute unit), of 256 to 4,096 rows
-  const uint32_t groups = (d + kSelCols - 1) / kSelCols;
-  uint64_t rows_per_block = n * groups / 1024;
-  rows_per_block = rows_per_block < 256 ? 256 : (rows_per_block > 4096 ? 4096 : rows_per_block);
-  const dim3 grid((uint32_t)((n + rows_per_block - 1) / rows_per_block), groups);
+  uint64_t rows_per_block;
+  const dim3 grid = select_grid(n, d, rows_per_block);
   radix_init_kernel<<<(uint32_t)((n_hist + 255) / 256), 256, 0, st>>>(d, (uint32_t)k, (uint32_t)(n - 1 - k), prefix, rank, hist);
   for (int shift = 24; shift >= 0; shift -= 8) {
     radix_hist_kernel<<<grid, kSelBlock, 0, st>>>(x, n, d, (uint32_t)rows_per_block, shift, prefix, hist);

@@ -82,6 +82,38 @@ def test_truncated_edges(H, n, d, bits, coverage):
     assert (lo == lo_o).all() and _same(delta, delta_o)
 
 
+# ranges from one pass over brackets (from 32,768 rows on): its smallest size, columns and rows that do not fill a group,
+# lists of several sizes, ranks among the first values, rows in an order, few distinct values, infinities and NaN,
+# more equal values than a list holds
+@pytest.mark.parametrize("n,d,coverage,kind", [
+    (32768, 1, 0.99, "values"), (32769, 33, 0.99, "values"), (40003, 70, 0.9999, "values"), (50000, 5, 0.99997, "values"), (33000, 31, 0.97, "values"),
+    (400001, 4, 0.95, "values"), (1200003, 2, 0.97, "values"), (60000, 40, 0.99, "sorted"), (60000, 40, 0.99, "whole"), (60000, 24, 0.99, "mostly zero"),
+    (50000, 12, 0.98, "not finite"), (70000, 9, 0.995, "one value"), (60000, 7, 0.8, "values")])
+def test_truncated_by_brackets(H, n, d, coverage, kind):
+    X = _values(n, d, n + d)
+    if kind == "sorted":
+        X.sort(axis=0)
+        X[:, ::2] = X[::-1, ::2]
+    elif kind == "whole":
+        X = np.round(X)
+    elif kind == "mostly zero":
+        X[np.random.default_rng(1).random(X.shape) < 0.97] = 0.0
+    elif kind == "not finite":
+        X[::37], X[::41], X[5::1009, :4] = np.inf, -np.inf, np.nan
+    elif kind == "one value":
+        X[:, ::2], X[:, 1] = -2.5, 0.0
+        X[::3, 1] = -0.0
+    lo, delta, _, _ = H.gpu_sq_fit(X, 8, coverage=coverage)
+    # the definition: order statistics of the ordered bit patterns
+    u = np.ascontiguousarray(X).view(np.uint32)
+    key = np.sort(np.where(u >> 31, ~u, u | 0x80000000), axis=0)
+    k = int(np.floor((1.0 - coverage) * (n - 1)))
+    mn, mx = (np.where(v >> 31, v & 0x7FFFFFFF, ~v).astype(np.uint32).view(np.float32) for v in (key[k], key[n - 1 - k]))
+    assert (lo.view(np.uint32) == mn.view(np.uint32)).all()
+    with np.errstate(invalid="ignore"):
+        assert _same(delta, np.where(mx > mn, (mx - mn) / np.float32(255), np.float32(1)).astype(np.float32))
+
+
 @pytest.mark.parametrize("degree", [1, 2, 7, 8, 9, 16, 31, 33, 64])
 def test_adjacency_checks(H, degree):
     """Every pair of slots of a row is compared, every id is checked, and rows in order are taken."""
