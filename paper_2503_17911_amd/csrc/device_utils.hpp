@@ -36,6 +36,12 @@ __device__ __forceinline__ int group_sum_i32(int v) {
   return v;
 }
 
+// Sum of a lane's value and that of the lane 32 further on (or back).
+__device__ __forceinline__ int half_sum_i32(int v) {
+  const auto halves = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  return (int)(halves[0] + halves[1]);
+}
+
 // Inclusive prefix sum over the 64 lanes (row shifts inside each row of 16
 // lanes, then the row totals are broadcast to the rows that follow).
 __device__ __forceinline__ int wave_inclusive_scan_i32(int v) {

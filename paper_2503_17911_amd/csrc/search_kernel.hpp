@@ -128,14 +128,14 @@ __host__ __device__ constexpr int stage_entries(int m, int pmax, bool fast) {
   return pmax == 1 ? 64 : (fast && 32 * pmax > 64 * m ? 32 * pmax : 64 * m);
 }
 // During a merge the area holds 64 m integer counters (32 m entries).  The
-// list of the batch's candidates (64 and 4 of padding) lies in the merge
+// list of the batch's candidates (64 and 16 of padding) lies in the merge
 // buffer itself when that has 128 entries or more: the buffer's old contents
 // are not read again once the candidates are ranked, and the scatter that
 // ends the merge rewrites every slot of it.  With 64 entries the list follows
 // the counters.
 __host__ __device__ constexpr int merge_list_at(int m) { return 32 * m; }
 __host__ __device__ constexpr int stage_area_entries(int m, int pmax, bool fast) {
-  const int need = m >= 2 ? merge_list_at(m) : merge_list_at(m) + 68;
+  const int need = m >= 2 ? merge_list_at(m) : merge_list_at(m) + 80;
   return stage_entries(m, pmax, fast) > need ? stage_entries(m, pmax, fast) : need;
 }
 
@@ -478,27 +478,43 @@ struct SearchWave {
     worst = pack64(__builtin_amdgcn_readlane(k_, rl), __builtin_amdgcn_readlane(v_, rl));
   }
 
-  // Merge up to 64 candidates (one per lane where `have`) into the pool.
+  // Merge up to 64 candidates (one per lane where `have`) into the pool.  With
+  // width = 32 the upper half of the wavefront holds the lower half's candidates
+  // once more.
   //
   // mbuf[0 .. 64 M) is the pool in order as the last merge left it (expanded
   // marks may be out of date, which no comparison below depends on); slots
   // behind the pool hold all-ones or entries that were pushed out, all of them
   // above any candidate that beats the pool's last entry.
-  __device__ __forceinline__ void merge(bool have, uint32_t ck, uint32_t cv) {
+  //
+  // Bound: a chain of LDS round trips (about 130 cycles each) and of dependent
+  // instructions, so each round asks for as much as it can: 8 rounds for up to 16
+  // candidates and a pool of 128, 13 with a probe, a level or four list entries at a
+  // time.  1M x 128, ef = 128: one query 139 -> 132 us, 100 queries 273 -> 260; 1,000
+  // queries x 960 4-bit, ef = 256: 400 -> 396; full batches are not bound by it (745 -> 743).
+  __device__ __forceinline__ void merge(bool have, uint32_t ck, uint32_t cv, int width) {
     const uint64_t c64 = pack64(ck, cv);
     bool mine = have && c64 < worst;
     if (__ballot(mine) == 0) return;
     // number of pool entries below the candidate: lower bound over slots
     // 0 .. 64 M - 2 (a candidate that beats the last entry ranks below 64 M).
-    // Two levels of the bisection per round: the probe of the first level and
-    // both possible probes of the second are read together, so a round costs
-    // one LDS latency instead of two.
+    // The first two levels of the bisection probe entries that are the same for
+    // all lanes (from registers); then two levels per round, the second's both
+    // possible probes read with the first's; the last three levels and the entry
+    // at the rank found are one read of eight entries in a row.
     uint32_t pos = 0;  // byte offset into mbuf
-    {
+    uint32_t at_id = 0;
+    if (mine) {
       const char *mb = reinterpret_cast<const char *>(mbuf);
-      int step = 32 * M;
 #pragma unroll
-      for (; step >= 2; step >>= 2) {
+      for (int i = 16 * M - 1; i < 64 * M - 1; i += 16 * M) {
+        const uint64_t e = pack64((uint32_t)__builtin_amdgcn_readlane((int)pk[i / kWave], i % kWave),
+                                  (uint32_t)__builtin_amdgcn_readlane((int)pv[i / kWave], i % kWave));
+        pos += e < c64 ? 128u * M : 0u;
+      }
+      int step = 8 * M;
+#pragma unroll
+      for (; step >= 16; step >>= 2) {
         const uint64_t ea = *reinterpret_cast<const uint64_t *>(mb + pos + (step - 1) * 8);
         const uint64_t eb = *reinterpret_cast<const uint64_t *>(mb + pos + (step / 2 - 1) * 8);
         const uint64_t ec = *reinterpret_cast<const uint64_t *>(mb + pos + (step + step / 2 - 1) * 8);
@@ -506,79 +522,103 @@ struct SearchWave {
         const uint64_t second = up ? ec : eb;
         pos += (up ? (uint32_t)step * 8u : 0u) + (second < c64 ? (uint32_t)(step / 2) * 8u : 0u);
       }
-      if (step == 1) {
-        const uint64_t e = *reinterpret_cast<const uint64_t *>(mb + pos);
-        pos += e < c64 ? 8u : 0u;
+      if (step == 8) {
+        const uint64_t e = *reinterpret_cast<const uint64_t *>(mb + pos + 7 * 8);
+        pos += e < c64 ? 64u : 0u;
+      }
+      uint64_t e[8];
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        const uint4 two = *reinterpret_cast<const uint4 *>(mb + pos + i * 8);
+        e[i] = pack64(two.y, two.x);
+        e[i + 1] = pack64(two.w, two.z);
+      }
+      at_id = (uint32_t)e[7];
+#pragma unroll
+      for (int i = 6; i >= 0; --i) {
+        const bool below = e[i] < c64;
+        pos += below ? 8u : 0u;
+        at_id = below ? at_id : (uint32_t)e[i];
       }
     }
     // A node the visited set has forgotten can come back.  If it is in the
     // pool, the entry found is that node (ids are unique in the pool): dropped.
-    const uint32_t at_id = (uint32_t)*reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(mbuf) + pos);
-    mine = mine && (at_id | 1u) != (cv | 1u);
+    mine = mine && (at_id | 1u) != (cv | 1u) && lane < width;
     uint64_t km = __ballot(mine);
     if (km == 0) return;
     const int rank_p = (int)(pos >> 3);
     int *cnt = reinterpret_cast<int *>(stage);
     uint64_t *lst = M >= 2 ? mbuf : stage + merge_list_at(M);
-    int shift[M];
-    int dest;
+    uint64_t merged[M];
     for (;;) {
       // pool entry i moves up by the number of candidates with rank <= i
 #pragma unroll
       for (int r = 0; r < M; ++r) cnt[r * kWave + lane] = 0;
-      // the batch's candidates side by side, padded to a multiple of four with
+      // the batch's candidates side by side, padded to a multiple of sixteen with
       // values above every candidate
       const int n_l = __popcll(km);
       if (mine) lst[lanes_below(km)] = c64;
-      if (lane < 4) lst[n_l + lane] = ~0ull;
+      if (lane < 16) lst[n_l + lane] = ~0ull;
       wave_sync();
       if (mine) atomicAdd(&cnt[rank_p], 1);
       wave_sync();
+      int shift[M];
+#pragma unroll
+      for (int r = 0; r < M; ++r) shift[r] = cnt[r * kWave + lane];
+      // candidates below this lane's candidate: every lane walks the list (eight
+      // entries in flight, the same for all lanes), with width = 32 each half of
+      // the wavefront every other eight
+      int below_c = 0;
+      const uint4 *walk = reinterpret_cast<const uint4 *>(lst + (lane < width ? 0 : 8));
+      const int stride = width < kWave ? 16 : 8;
+#pragma nounroll
+      for (int i = 0; i < n_l; i += stride) {
+        uint4 two[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) two[t] = walk[t];
+        walk += stride / 2;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          below_c += (pack64(two[t].y, two[t].x) < c64 ? 1 : 0) + (pack64(two[t].w, two[t].z) < c64 ? 1 : 0);
+      }
+      if (width < kWave) below_c = half_sum_i32(below_c);
       int carry = 0;
 #pragma unroll
       for (int r = 0; r < M; ++r) {
-        shift[r] = wave_inclusive_scan_i32(cnt[r * kWave + lane]) + carry;
+        shift[r] = wave_inclusive_scan_i32(shift[r]) + carry;
         carry = __builtin_amdgcn_readlane(shift[r], kWave - 1);
       }
-      // candidates below this lane's candidate: every lane walks the list
-      // (all lanes read the same entry: one LDS access each, four in flight)
-      int below_c = 0;
-      for (int i = 0; i < n_l; i += 4) {
-        const uint64_t e0 = lst[i], e1 = lst[i + 1], e2 = lst[i + 2], e3 = lst[i + 3];
-        below_c += (e0 < c64 ? 1 : 0) + (e1 < c64 ? 1 : 0) + (e2 < c64 ? 1 : 0) + (e3 < c64 ? 1 : 0);
-      }
-      dest = rank_p + below_c;
+      const int dest = rank_p + below_c;
       // The same forgotten node twice among the candidates: equal values get
-      // equal destinations.  One of them stays, the count starts over (rare).
+      // equal destinations.  One of them stays, all of it starts over (rare; the
+      // old pool is still in the registers).
       // (candidates ranked past the buffer are dropped anyway)
       const bool lands = mine && dest < 64 * M;
       wave_sync();
       if (lands) cnt[dest] = lane;
+      // no two other (key, id) pairs are equal: the destinations are a permutation
+#pragma unroll
+      for (int r = 0; r < M; ++r) {
+        const int to = r * kWave + lane + shift[r];
+        if (to < 64 * M) mbuf[to] = pack64(pk[r], pv[r]);
+      }
+      if (lands) mbuf[dest] = c64;
       wave_sync();
-      const uint64_t lose = __ballot(lands && cnt[dest] != lane);
+      const int winner = cnt[lands ? dest : 0];
+#pragma unroll
+      for (int r = 0; r < M; ++r) merged[r] = mbuf[r * kWave + lane];
+      const uint64_t lose = __ballot(lands && winner != lane);
+      wave_sync();
       if (lose == 0) break;
       km &= ~lose;
       mine = mine && ((lose >> lane) & 1ull) == 0;
-      wave_sync();
     }
-    const int n_m = __popcll(km);
-    // no two (key, id) pairs are equal: the destinations are a permutation
 #pragma unroll
     for (int r = 0; r < M; ++r) {
-      const int to = r * kWave + lane + shift[r];
-      if (to < 64 * M) mbuf[to] = pack64(pk[r], pv[r]);
-    }
-    if (mine && dest < 64 * M) mbuf[dest] = c64;
-    wave_sync();
-#pragma unroll
-    for (int r = 0; r < M; ++r) {
-      const uint64_t v = mbuf[r * kWave + lane];
       const bool beyond = r * kWave + lane >= ef_q;  // entries pushed past the pool size are dropped
-      pk[r] = beyond ? kEmpty : (uint32_t)(v >> 32);
-      pv[r] = beyond ? kEmpty : (uint32_t)v;
+      pk[r] = beyond ? kEmpty : (uint32_t)(merged[r] >> 32);
+      pv[r] = beyond ? kEmpty : (uint32_t)merged[r];
     }
-    wave_sync();
-    (void)n_m;
     refresh_worst();
   }
 
@@ -694,10 +734,11 @@ struct SearchWave {
       n_q = 0;
       return;
     }
+    const int width = n_q <= kWave / 2 ? kWave / 2 : kWave, at = lane & (width - 1);
     constexpr int kBatches = kStage / kWave;
     uint64_t batch[kBatches];
 #pragma unroll
-    for (int b = 0; b < kBatches; ++b) batch[b] = b * kWave + lane < n_q ? stage[b * kWave + lane] : 0;
+    for (int b = 0; b < kBatches; ++b) batch[b] = b * kWave + at < n_q ? stage[b * kWave + at] : 0;
     wave_sync();
     // one copy of the merge code, however many batches: the batch is picked by selects
 #pragma nounroll
@@ -705,7 +746,7 @@ struct SearchWave {
       uint64_t c = batch[0];
 #pragma unroll
       for (int t = 1; t < kBatches; ++t) c = b == t ? batch[t] : c;
-      merge(b * kWave + lane < n_q, (uint32_t)(c >> 32), (uint32_t)c);
+      merge(b * kWave + at < n_q, (uint32_t)(c >> 32), (uint32_t)c, width);
     }
     n_q = 0;
   }
