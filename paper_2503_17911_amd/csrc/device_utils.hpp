@@ -23,23 +23,37 @@ __device__ __forceinline__ int xor_lane_i32(int v, int mask) {
   return __builtin_amdgcn_ds_bpermute((lane_id() ^ mask) << 2, v);
 }
 
+// A lane's own value and that of the lane 16 (ROWS) or 32 lanes away, the lower lane's first.
+struct LanePair {
+  uint32_t low, high;
+};
+template <bool ROWS>
+__device__ __forceinline__ LanePair lane_pair(uint32_t v) {
+  const auto p = ROWS ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return {p[0], p[1]};
+}
+__device__ __forceinline__ int half_sum_i32(int v) {
+  const LanePair p = lane_pair<false>((uint32_t)v);
+  return (int)(p.low + p.high);
+}
+
 // Sum over aligned groups of W consecutive lanes; every lane of the group
-// ends with the group's total.  W in {1,2,4,8,16,32,64}.
+// ends with the group's total.  W in {1,2,4,8,16,32,64}.  No LDS round trips
+// (about 130 cycles each): exchanges inside a row of 16 lanes by DPP - once a
+// quad's lanes hold one value, the mirrored lane's is that of the lane 4 or 8 away -
+// and between rows by lane swaps.
 template <int W>
 __device__ __forceinline__ int group_sum_i32(int v) {
   if constexpr (W >= 2) v += dpp_i32<kDppQuadXor1>(v);
   if constexpr (W >= 4) v += dpp_i32<kDppQuadXor2>(v);
   if constexpr (W >= 8) v += dpp_i32<kDppRowHalfMirror>(v);
   if constexpr (W >= 16) v += dpp_i32<kDppRowMirror>(v);
-  if constexpr (W >= 32) v += xor_lane_i32(v, 16);
-  if constexpr (W >= 64) v += xor_lane_i32(v, 32);
+  if constexpr (W >= 32) {
+    const LanePair p = lane_pair<true>((uint32_t)v);
+    v = (int)(p.low + p.high);
+  }
+  if constexpr (W >= 64) v = half_sum_i32(v);
   return v;
-}
-
-// Sum of a lane's value and that of the lane 32 further on (or back).
-__device__ __forceinline__ int half_sum_i32(int v) {
-  const auto halves = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-  return (int)(halves[0] + halves[1]);
 }
 
 // Inclusive prefix sum over the 64 lanes (row shifts inside each row of 16
@@ -61,17 +75,35 @@ __device__ __forceinline__ double xor_lane_f64(double v, int mask) {
   return __hiloint2double(hi, lo);
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  return __hiloint2double(dpp_i32<CTRL>(__double2hiint(v)), dpp_i32<CTRL>(__double2loint(v)));
+}
+template <bool ROWS>
+__device__ __forceinline__ double pair_sum_f64(double v) {
+  const LanePair lo = lane_pair<ROWS>((uint32_t)__double2loint(v)), hi = lane_pair<ROWS>((uint32_t)__double2hiint(v));
+  return __hiloint2double((int)hi.low, (int)lo.low) + __hiloint2double((int)hi.high, (int)lo.high);
+}
 template <int W>
 __device__ __forceinline__ double group_sum_f64(double v) {
-#pragma unroll
-  for (int m = 1; m < W; m <<= 1) v += xor_lane_f64(v, m);
+  if constexpr (W >= 2) v += dpp_f64<kDppQuadXor1>(v);
+  if constexpr (W >= 4) v += dpp_f64<kDppQuadXor2>(v);
+  if constexpr (W >= 8) v += dpp_f64<kDppRowHalfMirror>(v);
+  if constexpr (W >= 16) v += dpp_f64<kDppRowMirror>(v);
+  if constexpr (W >= 32) v = pair_sum_f64<true>(v);
+  if constexpr (W >= 64) v = pair_sum_f64<false>(v);
   return v;
 }
 
 __device__ __forceinline__ float wave_max_f32(float v) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) v = fmaxf(v, __int_as_float(xor_lane_i32(__float_as_int(v), m)));
-  return v;
+  v = fmaxf(v, __int_as_float(dpp_i32<kDppQuadXor1>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp_i32<kDppQuadXor2>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp_i32<kDppRowHalfMirror>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp_i32<kDppRowMirror>(__float_as_int(v))));
+  LanePair p = lane_pair<true>(__float_as_uint(v));
+  v = fmaxf(__uint_as_float(p.low), __uint_as_float(p.high));
+  p = lane_pair<false>(__float_as_uint(v));
+  return fmaxf(__uint_as_float(p.low), __uint_as_float(p.high));
 }
 
 // Where a result is defined as an fp64 sum of `count` terms in a given order,
@@ -202,6 +234,12 @@ __device__ __forceinline__ int chunk_dot(const uint4 &c, const int *tq) {
     acc = __builtin_amdgcn_sdot4(tq[7], (int)((c.w >> 4) & m), acc, false);
   }
   return acc;
+}
+
+// Dimension that byte e of word w of a folded query holds (the words in the order chunk_dot takes them).
+template <int BITS>
+__device__ __forceinline__ uint32_t folded_dim(uint32_t w, uint32_t e) {
+  return BITS == 8 ? 4 * w + e : w / 8 * 32 + w % 4 * 8 + e * 2 + w % 8 / 4;
 }
 
 template <int BITS>

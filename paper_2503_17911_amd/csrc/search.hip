@@ -75,8 +75,16 @@ ann_status check_search_args(const char *fn, const ann_index *index, const float
   return ANN_OK;
 }
 
-// Launch of the search kernel for a batch whose folded queries are in `w`.
-ann_status launch_search_with(const ann_index *index, uint32_t nq, const ann_search_params *params,
+// Whether the search kernels can fold their queries themselves: not the 15-bit query's two
+// planes, and not with an order, which need not name every query (all of a batch are folded,
+// also those).
+bool search_folds(const ann_index *index, const ann_search_params *params, const Workspace &w) {
+  const LevelDev &L = index->level[0];
+  return index->query_bits != 15 && !params->query_order && w.tq_plane == L.search_lanes * 4 * (L.bits == 8 ? 16u : 32u);
+}
+
+// Launch of the search kernel for a batch whose folded queries are in `w`, or (q given) are put there by it.
+ann_status launch_search_with(const ann_index *index, const float *q, uint32_t nq, const ann_search_params *params,
                               const SearchPlan &plan, const uint32_t *entry_ids, uint32_t n_entry, uint32_t *out_ids,
                               float *out_keys, int32_t *out_idot, uint32_t *out_counts, const Workspace &w,
                               hipStream_t st) {
@@ -91,11 +99,15 @@ ann_status launch_search_with(const ann_index *index, uint32_t nq, const ann_sea
   a.adj_norms = params->layout == 2 ? 1u : 0u;
   a.adjacency = a.adj_norms ? index->adjacency_norms : index->adjacency;
   a.adj_stride = a.adj_norms ? 2 * index->degree : index->degree;
+  a.q = q;
+  a.lo = L.lo;
+  a.delta = L.delta;
+  a.d = index->d;
   a.tq = w.tq;
   a.s = w.s;
   a.qlo = w.qlo;
   a.sum_t = w.sum_t;
-  a.sum_t_lo = index->query_bits == 15 ? w.sum_t + w.nq_cap : nullptr;
+  a.sum_t_lo = w.sum_t + w.nq_cap;
   a.tq_plane = w.tq_plane;
   a.q15 = index->query_bits == 15 ? 1u : 0u;
   a.entry_ids = entry_ids;
@@ -186,17 +198,23 @@ extern "C" ann_status ann_search_batch(ann_index *index, const float *q, uint32_
   ann_status rc = check_search_args("ann_search_batch", index, q, nq, params, entry_ids, n_entry, out_ids, plan);
   if (rc != ANN_OK) return rc;
   WorkspaceLease lease;  // held until the search kernel is enqueued
+  rc = workspace_for(index, 0, nq, st, lease);
+  if (rc != ANN_OK) return rc;
+  const bool folds = !params->reuse_folded_queries && search_folds(index, params, *lease.ws);
   if (params->reuse_folded_queries) {
-    rc = workspace_for(index, 0, nq, st, lease);
-    if (rc != ANN_OK) return rc;
     if (lease.ws->folded_q != q || lease.ws->folded_nq != nq)
       return fail(ANN_EINVAL, "ann_search_batch: reuse_folded_queries, but the last folding for this index on this stream was of another batch");
-  } else {
-    rc = launch_query_prep(index, 0, q, nq, nullptr, nullptr, nullptr, st, lease);
+  } else if (!folds) {
+    rc = launch_query_prep_into(index, 0, q, nq, *lease.ws, nullptr, nullptr, nullptr, st);
     if (rc != ANN_OK) return rc;
   }
-  return launch_search_with(index, nq, params, plan, entry_ids, n_entry, out_ids, out_keys, out_idot, out_counts,
-                            *lease.ws, st);
+  rc = launch_search_with(index, folds ? q : nullptr, nq, params, plan, entry_ids, n_entry, out_ids, out_keys, out_idot, out_counts,
+                          *lease.ws, st);
+  if (rc == ANN_OK || !folds) {
+    lease.ws->folded_q = q;
+    lease.ws->folded_nq = nq;
+  }
+  return rc;
 }
 
 // ---------------------------------------------------------------- no allocation
@@ -260,8 +278,11 @@ extern "C" ann_status ann_search_batch_static(ann_index *index, const float *q, 
   w.sum_t = reinterpret_cast<int32_t *>(base + tq_bytes + 2 * word_bytes);  // two planes of nq sums
   // the folding writes every byte the search reads (rows are written whole,
   // zero padding included), so nothing of an earlier call has to be cleared
-  rc = launch_query_prep_into(index, 0, q, nq, w, nullptr, nullptr, nullptr, st);
-  if (rc != ANN_OK) return rc;
-  return launch_search_with(index, nq, params, plan, entry_ids, n_entry, out_ids, out_keys, out_idot, out_counts, w,
+  const bool folds = search_folds(index, params, w);
+  if (!folds) {
+    rc = launch_query_prep_into(index, 0, q, nq, w, nullptr, nullptr, nullptr, st);
+    if (rc != ANN_OK) return rc;
+  }
+  return launch_search_with(index, folds ? q : nullptr, nq, params, plan, entry_ids, n_entry, out_ids, out_keys, out_idot, out_counts, w,
                             st);
 }

@@ -67,11 +67,13 @@ struct SearchArgs {
   const uint8_t *codes;
   const float *norm_term;
   const uint32_t *adjacency;
-  const uint8_t *tq;
-  const float *s;
-  const float *qlo;
-  const int32_t *sum_t;
-  const int32_t *sum_t_lo;  // second plane's sums (15-bit query) or nullptr
+  const float *q;  // [nq][d]: the kernel folds its query itself and leaves the result in the next four; or nullptr: they hold it
+  const float *lo, *delta;  // [d] the level's codebook (with q)
+  uint8_t *tq;
+  float *s;
+  float *qlo;
+  int32_t *sum_t;
+  int32_t *sum_t_lo;  // second plane's sums (zero but for the 15-bit query)
   const uint32_t *entry_ids;
   const uint32_t *order;  // processing order (workgroup -> query) or nullptr
   const uint32_t *ef_per_query;  // [nq] pool size of each query (<= ef) or nullptr
@@ -83,6 +85,7 @@ struct SearchArgs {
   int32_t *out_idot;
   uint32_t *out_counts;
   uint64_t n;
+  uint32_t d;
   uint32_t row_stride, n_chunks, degree, metric, tq_stride, n_entry, entry_point, ef, vis_log2, nq, p;
   uint32_t filtered;  // the label test and/or the per-expansion cap m_s is active
   uint32_t vis_cache;  // visited set is the two-way cache
@@ -181,7 +184,7 @@ struct SearchWave {
   // candidates, so two are requested together (1M x 960 4-bit: 6 % faster;
   // four groups, or four in the multi-expansion kernels, cost more in
   // registers than they gain)
-  static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? ANN_U : (LPR >= 8 ? 2 : 1));
+    static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? ANN_U : (LPR >= 8 ? 2 : 1));
   static constexpr int TQW = TqRegs<BITS>::kWords;
 
   // the i-th unvisited neighbour of the current step: id in the upper word,
@@ -214,7 +217,7 @@ struct SearchWave {
   const int *tql;  // LDS: the folded query, TQW words per 16-byte code chunk
   int qreg[QREG ? CPL : 1][TQW];
   uint64_t *res;   // LDS (TEAM > 1): the step's candidates as (key, id) pairs, in list order
-  int *step_n;     // LDS (TEAM > 1): candidates of the step; negative: the search has ended
+  int *step_n;     // LDS (TEAM > 1), four words: candidates of the step (negative: the search has ended); scale, offset and bias of a query folded here
   int lane, sub, grp;
   uint32_t coff[CPL];  // byte offsets of this lane's chunks inside a code row
   uint32_t vis_mask, vis_shift, vis_limit;
@@ -790,7 +793,16 @@ struct SearchWave {
 
   // TEAM > 1: what the wavefronts but the first do.
   __device__ __forceinline__ void help(uint32_t qi, int wave) {
-    load_query_terms(qi);
+    if (a.q) {
+      team_barrier();   // the first wavefront has folded the query
+      s = __int_as_float(step_n[1]);
+      qlo = __int_as_float(step_n[2]);
+      bias = step_n[3];
+      bias_lo = 0;
+      load_query_part(tql);
+    } else {
+      load_query_terms(qi);
+    }
     for (;;) {
       team_barrier();
       const int n_cand = *step_n;
@@ -897,12 +909,12 @@ struct SearchWave {
     }
   }
 
-  // What of the folded query a wavefront keeps in registers.
-  __device__ __forceinline__ void load_query_terms(uint32_t qi) {
+  // QREG: this lane's part of the folded query, from memory or from LDS.
+  __device__ __forceinline__ void load_query_part(const int *folded) {
     if constexpr (QREG) {
 #pragma unroll
       for (int j = 0; j < CPL; ++j) {
-        const int4 *src = reinterpret_cast<const int4 *>(a.tq + (uint64_t)qi * a.tq_stride + (uint32_t)(sub + j * LPR) * (TQW * 4u));
+        const int4 *src = reinterpret_cast<const int4 *>(folded + (uint32_t)(sub + j * LPR) * TQW);
 #pragma unroll
         for (int w = 0; w < TQW / 4; ++w) {
           const int4 v = src[w];
@@ -913,24 +925,114 @@ struct SearchWave {
         }
       }
     }
+  }
+
+  // What of an already folded query a wavefront keeps in registers.
+  __device__ __forceinline__ void load_query_terms(uint32_t qi) {
+    load_query_part(reinterpret_cast<const int *>(a.tq + (uint64_t)qi * a.tq_stride));
     s = a.s[qi];
     qlo = a.qlo[qi];
     bias = BITS == 8 ? 128 * a.sum_t[qi] : 0;
-    bias_lo = BITS == 8 && a.sum_t_lo ? 128 * a.sum_t_lo[qi] : 0;
+    bias_lo = BITS == 8 ? 128 * a.sum_t_lo[qi] : 0;
+  }
+
+  // Folds the query as query_prep_kernel does (the same values: the sum in fp64 is
+  // in another order, which certain_f32 allows for), into LDS for this search and
+  // to memory for calls that reuse the folding.  A launch less (4.6 us), for about 3 us
+  // at the start of a search: 100 queries on 10,000 x 128, one expansion per step 142.6 -> 139.2 us,
+  // 1,000 x 960 4-bit 412.8 -> 404.9, one query 124.4 -> 123.3, 10,000 x 96 649.9 -> 644.4.
+  __device__ __forceinline__ void fold(uint32_t qi) {
+    constexpr int kWords = CPL * LPR * TQW, kRounds = (kWords + kWave - 1) / kWave;
+    const float *qr = a.q + (uint64_t)qi * a.d;
+    float prod[kRounds][4];
+    float amax = 0.0f;
+    double part = 0.0, mag = 0.0;
+#pragma unroll
+    for (int t = 0; t < kRounds; ++t) {
+      const uint32_t w = (uint32_t)(t * kWave + lane);
+      float qv[4], dv[4], lv[4];
+      uint32_t dim[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        dim[e] = folded_dim<BITS>(w, (uint32_t)e);
+        const uint32_t j = dim[e] < a.d ? dim[e] : a.d - 1;
+        qv[e] = qr[j];
+        dv[e] = a.delta[j];
+        lv[e] = a.lo[j];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = dim[e] < a.d;
+        prod[t][e] = in ? __fmul_rn(dv[e], qv[e]) : 0.0f;
+        amax = fmaxf(amax, fabsf(prod[t][e]));
+        const double term = in ? (double)qv[e] * (double)lv[e] : 0.0;
+        part += term;
+        mag += fabs(term);
+      }
+    }
+    amax = wave_max_f32(amax);
+    s = 1.0f;
+    float r = 0.0f;
+    if (amax > 0.0f) {
+      s = __fdiv_rn(amax, 127.0f);
+      r = __fdiv_rn(127.0f, amax);
+    }
+    int *to_lds = const_cast<int *>(tql), *to_memory = reinterpret_cast<int *>(a.tq + (uint64_t)qi * a.tq_stride);
+    int sum = 0;
+#pragma unroll
+    for (int t = 0; t < kRounds; ++t) {
+      const int w = t * kWave + lane;
+      uint32_t word = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int ti = __float2int_rn(__fmul_rn(prod[t][e], r));  // round half to even
+        ti = ti > 127 ? 127 : (ti < -127 ? -127 : ti);
+        word |= (uint32_t)(uint8_t)(int8_t)ti << (8 * e);
+        sum += ti;
+      }
+      if (w < kWords) {
+        to_lds[w] = (int)word;
+        to_memory[w] = (int)word;
+      }
+    }
+    sum = group_sum_i32<kWave>(sum);
+    part = group_sum_f64<kWave>(part);
+    mag = group_sum_f64<kWave>(mag);
+    if (!certain_f32(part, mag, a.d, qlo)) qlo = dot_in_order(qr, a.lo, a.d, reinterpret_cast<double *>(mbuf));
+    bias = BITS == 8 ? 128 * sum : 0;
+    bias_lo = 0;
+    if (lane == 0) {
+      a.s[qi] = s;
+      a.qlo[qi] = qlo;
+      a.sum_t[qi] = sum;
+      a.sum_t_lo[qi] = 0;
+      if constexpr (TEAM > 1) {
+        step_n[1] = __float_as_int(s);
+        step_n[2] = __float_as_int(qlo);
+        step_n[3] = bias;
+      }
+    }
+    wave_sync();
+    load_query_part(tql);
   }
 
   __device__ __forceinline__ void run(uint32_t qi) {
-    if constexpr (!QREG) {   // the folded query goes to LDS: it is read again for every group of rows
-      const int *src = reinterpret_cast<const int *>(a.tq + (uint64_t)qi * a.tq_stride);
-      int *dst = const_cast<int *>(tql);
-      for (uint32_t i = lane; i < a.tq_stride / 4; i += kWave) dst[i] = src[i];
+    if (a.q) {
+      fold(qi);
+      if constexpr (TEAM > 1) team_barrier();
+    } else {
+      if constexpr (!QREG) {   // the folded query goes to LDS: it is read again for every group of rows
+        const int *src = reinterpret_cast<const int *>(a.tq + (uint64_t)qi * a.tq_stride);
+        int *dst = const_cast<int *>(tql);
+        for (uint32_t i = lane; i < a.tq_stride / 4; i += kWave) dst[i] = src[i];
+      }
+      load_query_terms(qi);
     }
     ef_q = (int)a.ef;
     if (a.ef_per_query) {
       const uint32_t e = a.ef_per_query[qi];
       ef_q = e == 0 ? 1 : (e < a.ef ? (int)e : (int)a.ef);
     }
-    load_query_terms(qi);
 #pragma unroll
     for (int r = 0; r < M; ++r) {
       pk[r] = kEmpty;

@@ -767,12 +767,7 @@ __global__ __launch_bounds__(64) void query_prep_kernel(const float *__restrict_
     uint32_t word = 0, word_lo = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      // byte 4 w + e holds dimension dim
-      uint32_t dim;
-      if constexpr (BITS == 8)
-        dim = 4 * w + e;
-      else
-        dim = w / 8 * 32 + w % 4 * 8 + e * 2 + w % 8 / 4;
+      const uint32_t dim = folded_dim<BITS>(w, (uint32_t)e);
       int ti = 0;
       if (dim < d) {
         ti = __float2int_rn(__fmul_rn(a_s[dim], r));  // round half to even
