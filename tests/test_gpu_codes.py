@@ -138,3 +138,16 @@ def test_adjacency_checks(H, degree):
     with pytest.raises(ann.AnnError) as e:
         H.GpuIndex(X, adj, 0, [lv], oracle.L2)
     assert e.value.status == ann.EINVAL and ">= n" in str(e.value)
+
+
+@pytest.mark.parametrize("n", [1, 9, 31, 33, 255, 257, 8191, 8193, 70_001])
+@pytest.mark.parametrize("d,bits", [(4, 8), (6, 4), (33, 8), (128, 8)])
+def test_rows_at_the_edges_of_the_passes(n, d, bits):
+    """Row counts around the groups of rows that a thread and a workgroup take."""
+    import gpu_harness as H
+    X = np.random.default_rng(n + d).standard_normal((n, d)).astype(np.float32)
+    X[-1] *= 9.0  # the last row holds an end of most ranges
+    lv = oracle.sq_fit(X, bits)
+    lo, delta, codes, norm = H.gpu_sq_fit(X, bits)
+    assert (lo == lv.lo).all() and (delta == lv.delta).all() and (codes == lv.codes).all()
+    assert (norm.view(np.uint32) == lv.norm_term.view(np.uint32)).all()
