@@ -300,3 +300,10 @@ def test_two_parts_of_rows_that_are_not_aligned(H, nq):
     ann.ann_bruteforce_topk(buf[1:], n, d, H.dev(Q), nq, k, ann.L2, ids, dist, H.stream_ptr())
     oid, odist = oracle.bruteforce_topk(X, Q[::7], k, metric=oracle.L2)
     H.check_rerank(H.as_u32(ids)[::7], dist.cpu().numpy()[::7], oid, odist.astype(np.float32), rel=1e-6)
+
+
+@pytest.mark.parametrize("n,nq", [(100, 33), (3000, 65), (12_000, 100), (16_000, 64), (20_000, 128), (20_003, 129), (33_000, 70)])
+@pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
+def test_query_tiles_by_the_number_of_rows(H, n, nq, metric):
+    """On both sides of the lines where tiles of 128, 64 and 32 queries are taken."""
+    _check(H, _points(n, 50, n), _points(nq, 50, n + 1), 10, metric)
