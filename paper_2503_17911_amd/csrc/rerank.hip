@@ -268,8 +268,13 @@ __global__ __launch_bounds__(64 * W) void rerank_kernel(const float *__restrict_
 }
 
 // ------------------------------------------------------------------ rescore
-// Keys of the candidates under another code level, then a full sort.
-template <int BITS, int LPR>
+// Keys of the candidates under another code level, then a full sort.  Rows are
+// shared out as in the search kernels: LPR lanes to a row, four 16-byte chunks to a
+// lane, so that the sum over the lanes and the key are formed for 64 / LPR rows at a
+// time; the query stays in registers, two planes of it with Q15 (15 bits).  With one
+// chunk to a lane (and one 768-byte row at a time) the kernel was bound by vector instructions:
+// 4,000 queries x 512 rows of 768 bytes 377 us (4.2 TB/s) -> 326.
+template <int BITS, int LPR, bool Q15>
 __global__ __launch_bounds__(64) void rescore_kernel(const uint8_t *__restrict__ codes, uint32_t row_stride,
                                                      uint32_t n_chunks, const float *__restrict__ norm_term,
                                                      uint32_t metric, uint64_t n, const uint8_t *__restrict__ tq,
@@ -286,21 +291,25 @@ __global__ __launch_bounds__(64) void rescore_kernel(const uint8_t *__restrict__
   int32_t *dots = reinterpret_cast<int32_t *>(smem64 + n_cand);  // [n_cand]
   const uint32_t qi = blockIdx.x;
   if (qi >= nq) return;
-  const int lane = threadIdx.x, chunk = lane % LPR, grp = lane / LPR;
-  constexpr int G = kWave / LPR;
+  const int lane = threadIdx.x, sub = lane % LPR, grp = lane / LPR;
+  constexpr int G = kWave / LPR, CPL = 4;
   constexpr int TQW = TqRegs<BITS>::kWords;
-  // sum_t_lo given: the query has 15 bits, its low bytes are a second plane
-  const bool q15 = sum_t_lo != nullptr;
-  int tqr[TQW], tqr_lo[TQW];
-  const int *tqp = reinterpret_cast<const int *>(tq + (uint64_t)qi * tq_stride + (uint32_t)chunk * (TQW * 4u));
+  int tqr[CPL][TQW], tqr_lo[Q15 ? CPL : 1][TQW];
+  uint32_t coff[CPL];   // chunks past the end of the row: the last one (their share of the query is zero)
 #pragma unroll
-  for (int w = 0; w < TQW; ++w) {
-    tqr[w] = tqp[w];
-    tqr_lo[w] = q15 ? tqp[tq_plane / 4 + w] : 0;
+  for (int j = 0; j < CPL; ++j) {
+    const uint32_t c = (uint32_t)(sub + j * LPR);
+    const int *tqp = reinterpret_cast<const int *>(tq + (uint64_t)qi * tq_stride) + c * TQW;
+#pragma unroll
+    for (int w = 0; w < TQW; ++w) {
+      tqr[j][w] = tqp[w];
+      if (Q15) tqr_lo[j][w] = tqp[tq_plane / 4 + w];
+    }
+    coff[j] = (c < n_chunks ? c : n_chunks - 1) * 16u;
   }
   const float s = s_arr[qi], qlo = qlo_arr[qi];
   const int bias = BITS == 8 ? 128 * sum_t[qi] : 0;
-  const int bias_lo = BITS == 8 && q15 ? 128 * sum_t_lo[qi] : 0;
+  const int bias_lo = BITS == 8 && Q15 ? 128 * sum_t_lo[qi] : 0;
   const uint32_t *cand = cand_ids + (uint64_t)qi * cand_stride;
   // the candidate ids go to LDS first (they share the words of `dots`: entry i
   // is read before dot product i is written), so that the rows of several
@@ -311,34 +320,36 @@ __global__ __launch_bounds__(64) void rescore_kernel(const uint8_t *__restrict__
     ids_s[i] = v != kNone && v >= n ? kNone : v;
   }
   __syncthreads();
-  constexpr int UNR = 8;  // groups of G rows in flight
+  constexpr int UNR = LPR >= 8 ? 4 : 2;  // groups of G rows in flight (2 / 3 / 4: 352 / 333 / 326 us)
   for (uint32_t base = 0; base < n_cand; base += G * UNR) {
     uint32_t vs[UNR];
-    uint4 rows[UNR];
+    uint4 rows[UNR][CPL];
     float nrms[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       const uint32_t ci = base + u * G + grp;
       vs[u] = ci < n_cand ? ids_s[ci] : kNone;
-      rows[u] = make_uint4(0, 0, 0, 0);
-      nrms[u] = 0.0f;
-      if (vs[u] != kNone) {
-        if (chunk < (int)n_chunks)
-          rows[u] = *reinterpret_cast<const uint4 *>(codes + (uint64_t)vs[u] * row_stride + (uint32_t)chunk * 16u);
-        if (norm_term && chunk == 0) nrms[u] = norm_term[vs[u]];
-      }
+      const uint64_t v = vs[u] != kNone ? vs[u] : 0u;   // (no branch around the loads)
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) rows[u][j] = *reinterpret_cast<const uint4 *>(codes + v * row_stride + coff[j]);
+      nrms[u] = norm_term ? norm_term[v] : 0.0f;
     }
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       const uint32_t ci = base + u * G + grp;
       const uint32_t v = vs[u];
-      const int dot = group_sum_i32<LPR>(chunk_dot<BITS>(rows[u], tqr)) + bias;
-      int dot_lo = 0;
-      if (q15) dot_lo = group_sum_i32<LPR>(chunk_dot<BITS>(rows[u], tqr_lo)) + bias_lo;
-      if (chunk == 0 && ci < n_cand) {
-        const float key = q15 ? key_from_idot15(metric, s, qlo, dot, dot_lo, nrms[u]) : key_from_idot(metric, s, qlo, dot, nrms[u]);
+      int dot = 0, dot_lo = 0;
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        dot += chunk_dot<BITS>(rows[u][j], tqr[j]);
+        if (Q15) dot_lo += chunk_dot<BITS>(rows[u][j], tqr_lo[j]);
+      }
+      dot = group_sum_i32<LPR>(dot) + bias;
+      if (Q15) dot_lo = group_sum_i32<LPR>(dot_lo) + bias_lo;
+      if (sub == 0 && ci < n_cand) {
+        const float key = Q15 ? key_from_idot15(metric, s, qlo, dot, dot_lo, nrms[u]) : key_from_idot(metric, s, qlo, dot, nrms[u]);
         list[ci] = v == kNone ? ~0ull : pack_vi(order_u32(key), v);
-        dots[ci] = v == kNone || q15 ? 0 : dot;
+        dots[ci] = v == kNone || Q15 ? 0 : dot;
       }
     }
   }
@@ -446,27 +457,29 @@ ann_status ann_rescore(ann_index *index, uint32_t level, const float *q, uint32_
   const Workspace &w = *lease.ws;
   const float *norm = index->key_metric == ANN_L2 ? L.norm_term : nullptr;
   const size_t smem = (size_t)n_cand * (sizeof(uint64_t) + sizeof(int32_t));
-#define ANN_RS(B, P)                                                                                              \
-  rescore_kernel<B, P><<<nq, 64, smem, st>>>(L.codes, L.row_stride, L.row_stride / 16, norm, index->key_metric,   \
-                                             index->n, w.tq, w.tq_stride, w.tq_plane,                             \
-                                             index->query_bits == 15 ? w.sum_t + w.nq_cap : nullptr, w.s, w.qlo,  \
-                                             w.sum_t, nq, cand_ids,                                               \
-                                             n_cand, cand_stride, out_ids, out_keys, out_idot)
-  if (L.bits == 8) {
-    switch (L.lanes_per_row) {
-      case 8: ANN_RS(8, 8); break;
-      case 16: ANN_RS(8, 16); break;
-      case 32: ANN_RS(8, 32); break;
-      default: ANN_RS(8, 64); break;
-    }
-  } else {
-    switch (L.lanes_per_row) {
-      case 8: ANN_RS(4, 8); break;
-      case 16: ANN_RS(4, 16); break;
-      case 32: ANN_RS(4, 32); break;
-      default: ANN_RS(4, 64); break;
-    }
+#define ANN_RS(B, P, F)                                                                                           \
+  rescore_kernel<B, P, F><<<nq, 64, smem, st>>>(L.codes, L.row_stride, L.row_stride / 16, norm, index->key_metric, \
+                                                index->n, w.tq, w.tq_stride, w.tq_plane, w.sum_t + w.nq_cap, w.s, \
+                                                w.qlo, w.sum_t, nq, cand_ids, n_cand, cand_stride, out_ids,       \
+                                                out_keys, out_idot)
+#define ANN_RS_LANES(B, F)           \
+  switch (L.search_lanes) {          \
+    case 1: ANN_RS(B, 1, F); break;  \
+    case 2: ANN_RS(B, 2, F); break;  \
+    case 4: ANN_RS(B, 4, F); break;  \
+    case 8: ANN_RS(B, 8, F); break;  \
+    default: ANN_RS(B, 16, F); break; \
   }
+  const bool q15 = index->query_bits == 15;
+  if (L.bits == 8 && q15)
+    ANN_RS_LANES(8, true)
+  else if (L.bits == 8)
+    ANN_RS_LANES(8, false)
+  else if (q15)
+    ANN_RS_LANES(4, true)
+  else
+    ANN_RS_LANES(4, false)
+#undef ANN_RS_LANES
 #undef ANN_RS
   ANN_HIP(hipGetLastError());
   return ANN_OK;
