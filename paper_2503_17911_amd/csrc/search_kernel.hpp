@@ -179,12 +179,17 @@ template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1, bool QREG
 struct SearchWave {
   static constexpr int G = kWave / LPR;      // code rows evaluated side by side
   static constexpr int CPL = 4;              // 16-byte chunks of a row per lane
-  // groups of G rows in flight.  With one expansion per step and wide rows
+  // groups of G rows in flight.  Multi-expansion kernels of large pools and wide rows have
+  // few wavefronts per SIMD, so registers for more: 8-bit codes 2 / 3 / 4 groups: 6,000 queries x 768,
+  // ef = 256: 2,715 / 2,630 / 2,614 us, 4,000 x 768, ef = 512: 2,936 / 2,917 / 2,833, 6,000 x 512, degree 48,
+  // ef = 500: 3,385 / 3,368 / 3,339.  4-bit codes (part of the query is in registers, too): 4,000 x 768, degree
+  // 48, ef = 512 3,187 / 3,110 / 3,147, with four pool registers they spill (8,000 x 960, ef = 256: 2,638 / 2,748 / 4,352).
+  static constexpr int kGroupsLong = BITS == 8 ? 4 : (M >= 8 ? 3 : ANN_U);
+  // With one expansion per step and wide rows
   // (eight or more lanes to a row) a group is fewer rows than a step has
   // candidates, so two are requested together (1M x 960 4-bit: 6 % faster;
-  // four groups, or four in the multi-expansion kernels, cost more in
-  // registers than they gain)
-    static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? ANN_U : (LPR >= 8 ? 2 : 1));
+  // four groups cost more in registers than they gain)
+      static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? (FAST && M >= 4 && LPR >= 8 ? kGroupsLong : ANN_U) : (LPR >= 8 ? 2 : 1));
   static constexpr int TQW = TqRegs<BITS>::kWords;
 
   // the i-th unvisited neighbour of the current step: id in the upper word,
