@@ -230,9 +230,9 @@ __global__ void truncated_range_kernel(const uint32_t *__restrict__ prefix, uint
 // the values); the wanted one is picked from the list by its rank.  Any order of the
 // rows and any distribution: a bracket that does not hold the wanted rank or has more values
 // inside than there is room for (many equal ones) is noticed, and the call takes
-// the four radix passes.  Bound: the pass' read of x (a third of its time beyond that is
+// the four radix passes.  Bound: the pass' read of x (4 TB/s of it: the rest of its time is
 // the walk over the values inside).  200,000 x 960, coverage 0.99: four passes and
-// picks 738 us; sample 20, brackets 52, pass 210, picks 24: 303 with the host's wait.
+// picks 738 us; sample 19, brackets 33, pass 190, picks 24: 270 with the host's wait.
 // 1M x 128 521 / 252, 33,000 x 100 145 / 75.
 constexpr double kBracketWidth = 5.5;
 constexpr uint32_t kBracketMost = 1u << 18;   // values of a list at most
@@ -296,11 +296,14 @@ struct KeyCounter {
   }
 };
 
-// One workgroup per column: the brackets of both ends.
+// One workgroup per column: the brackets of both ends.  A few steps over the whole
+// sample find a value that the keys of interest do not reach and at most four keys per thread do;
+// the bracket's ends are then searched among those (a step over 32 keys per thread is bound by
+// vector instructions; 960 columns: 50 us with all steps over all keys -> 33).
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void bracket_bounds_kernel(BracketArgs g) {
-  constexpr int EPT = kBracketKeys, kWaves = THREADS / kWave;
-  __shared__ uint32_t red[2 * kWaves], ends[kWaves];
+  constexpr int EPT = kBracketKeys, kWaves = THREADS / kWave, kFew = 4;
+  __shared__ uint32_t red[2 * kWaves], ends[kWaves], few_s[kFew * THREADS], n_few;
   const uint32_t j = blockIdx.x, tid = threadIdx.x;
   KeyCounter<EPT, THREADS> s;
   s.red = red;
@@ -335,11 +338,13 @@ __global__ __launch_bounds__(THREADS) void bracket_bounds_kernel(BracketArgs g) 
       mx = ~mn;
       mn = t;
     }
-    uint32_t a = 0, b = 0xFFFFFFFFu;
+    uint32_t a = 0, b = 0xFFFFFFFFu, between = 0;
     const uint32_t under = mn > 0 ? mn - 1 : 0;
+    auto bracket = [&](auto &s, uint32_t most) {
+    constexpr int kEach = sizeof(s.key) / sizeof(s.key[0]);
     // a: the smallest key above a value that few enough keys reach (no bound if the wanted rank is among the first)
     if (g.below >= 1.0) {
-      uint32_t lo = under, hi = mx;   // count(lo) <= below < count(hi)
+      uint32_t lo = under, hi = most;   // count(lo) <= below < count(hi)
       while (hi - lo > 1) {
         const uint32_t mid = lo + (hi - lo) / 2;
         const double n = s.up_to(mid);
@@ -352,12 +357,12 @@ __global__ __launch_bounds__(THREADS) void bracket_bounds_kernel(BracketArgs g) 
       }
       uint32_t next = 0xFFFFFFFFu;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) next = s.key[e] > lo && s.key[e] < next ? s.key[e] : next;
+      for (int e = 0; e < kEach; ++e) next = s.key[e] > lo && s.key[e] < next ? s.key[e] : next;
       a = least(next);
     }
     // b: the first value that enough keys reach, or one not far above it
     if (g.beyond <= (double)g.m) {
-      uint32_t lo = under, hi = mx;   // count(lo) < beyond <= count(hi)
+      uint32_t lo = under, hi = most;   // count(lo) < beyond <= count(hi)
       while (hi - lo > 1) {
         const uint32_t mid = lo + (hi - lo) / 2;
         const double n = s.up_to(mid);
@@ -370,7 +375,51 @@ __global__ __launch_bounds__(THREADS) void bracket_bounds_kernel(BracketArgs g) 
       }
       b = hi;
     }
-    const uint32_t between = a < b ? s.up_to(b - 1) - s.up_to(a) : 0u;
+    between = a < b ? s.up_to(b - 1) - s.up_to(a) : 0u;
+    };
+    // the few: keys up to `most`, which at least `beyond` and at most kFew * THREADS keys reach
+    uint32_t most = mx;
+    bool some = false;
+    if (g.beyond <= (double)(kFew * THREADS)) {
+      uint32_t lo = under, hi = mx;   // count(lo) < beyond <= count(hi)
+      while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        const double n = s.up_to(mid);
+        if (n >= g.beyond) {
+          hi = mid;
+          if (n <= (double)(kFew * THREADS)) break;
+        } else {
+          lo = mid;
+        }
+      }
+      most = hi;
+      some = s.up_to(most) <= (uint32_t)(kFew * THREADS);
+    }
+    if (some) {
+      if (tid == 0) n_few = 0;
+      __syncthreads();
+      uint32_t mine = 0, to = 0;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) mine += (uint32_t)__popcll(__ballot(s.key[e] <= most));
+      if (tid % kWave == 0) to = atomicAdd(&n_few, mine);
+      to = (uint32_t)__builtin_amdgcn_readfirstlane((int)to);
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const uint64_t m = __ballot(s.key[e] <= most);
+        if (s.key[e] <= most) few_s[to + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = s.key[e];
+        to += (uint32_t)__popcll(m);
+      }
+      __syncthreads();
+      KeyCounter<kFew, THREADS> few;
+      few.red = red;
+      few.parity = s.parity;
+#pragma unroll
+      for (int e = 0; e < kFew; ++e) few.key[e] = e * THREADS + tid < n_few ? few_s[e * THREADS + tid] : 0xFFFFFFFFu;
+      bracket(few, most);
+      s.parity = few.parity;
+    } else {
+      bracket(s, mx);
+    }
     if (tid == 0) {
       const uint64_t at = (uint64_t)end * g.d + j;
       g.a[at] = end ? ~b : a;
@@ -408,31 +457,30 @@ __global__ __launch_bounds__(kSelBlock) void bracket_collect_kernel(BracketArgs 
         if (to < g.room) g.list[l * g.room + to] = key;
       }
     };
+    // nearly all values lie between the brackets: for those a subtraction and a comparison
+    const uint32_t after = b0 + 1u, gap = a1 > b0 ? a1 - after : 0u;
     auto take = [&](const float (&v)[kSelUnroll], uint32_t valid) {
       uint32_t key[kSelUnroll], mine = 0;
 #pragma unroll
       for (int u = 0; u < kSelUnroll; ++u) {
         key[u] = order_u32(v[u]);
-        const bool in = (valid >> u) & 1u;
-        below += in && key[u] < a0 ? 1u : 0u;
-        above += in && key[u] > b1 ? 1u : 0u;
-        mine |= key[u] - a0 <= b0 - a0 ? 1u << u : 0u;
-        mine |= key[u] - a1 <= b1 - a1 ? 256u << u : 0u;
+        mine |= key[u] - after < gap ? 0u : 1u << u;
       }
-      mine &= valid * 257u;
+      mine &= valid;
       while (mine) {
-        const int i = __builtin_ctz(mine), u = i & 7;
+        const int u = __builtin_ctz(mine);
         mine &= mine - 1;
         static_assert(kSelUnroll == 8, "three selects");
         const uint32_t s0 = u & 1 ? key[1] : key[0], s1 = u & 1 ? key[3] : key[2], s2 = u & 1 ? key[5] : key[4], s3 = u & 1 ? key[7] : key[6];
         const uint32_t t0 = u & 2 ? s1 : s0, t1 = u & 2 ? s3 : s2, v_ = u & 4 ? t1 : t0;
-        const bool high = i >= 8;
-        const uint32_t a = high ? a1 : a0, b = high ? b1 : b0;
-        eq[0] += !high && v_ == a ? 1u : 0u;
-        eq[1] += !high && v_ == b ? 1u : 0u;
-        eq[2] += high && v_ == a ? 1u : 0u;
-        eq[3] += high && v_ == b ? 1u : 0u;
-        if (v_ != a && v_ != b) put(v_, high ? 1u : 0u);
+        below += v_ < a0 ? 1u : 0u;
+        above += v_ > b1 ? 1u : 0u;
+        eq[0] += v_ == a0 ? 1u : 0u;
+        eq[1] += v_ == b0 ? 1u : 0u;
+        eq[2] += v_ == a1 ? 1u : 0u;
+        eq[3] += v_ == b1 ? 1u : 0u;
+        if (v_ > a0 && v_ < b0) put(v_, 0u);
+        if (v_ > a1 && v_ < b1) put(v_, 1u);
       }
     };
     const float *at = g.x + col;
@@ -844,6 +892,16 @@ static dim3 select_grid(uint64_t n, uint32_t d, uint64_t &rows_per_block) {
   return dim3((uint32_t)((n + rows_per_block - 1) / rows_per_block), groups);
 }
 
+// For bracket_collect_kernel: whole turns of workgroups (four to each of 256 compute units) of at most
+// 6,144 rows, of which about 1.4 % lie in a bracket and find room in LDS.  200,000 x 960: 1,470 workgroups
+// of 4,096 rows, a second turn less than half full, 207 us; 1,020 of 5,883 190.
+static dim3 collect_grid(uint64_t n, uint32_t d) {
+  const uint32_t groups = (d + kSelCols - 1) / kSelCols, side = groups < 1024 ? 1024 / groups : 1;
+  uint64_t blocks = (n + 6144ull * side - 1) / (6144ull * side) * side;
+  if (blocks > (n + 255) / 256) blocks = (n + 255) / 256;
+  return dim3((uint32_t)blocks, groups);
+}
+
 // The truncated range by brackets from a sample, if that is to be expected to work (`done`: it did).
 static ann_status train_bracketed(const float *x, uint64_t n, uint32_t d, uint32_t k, float levels, float *lo, float *delta,
                                   hipStream_t st, bool &done) {
@@ -890,8 +948,7 @@ static ann_status train_bracketed(const float *x, uint64_t n, uint32_t d, uint32
     bracket_bounds_kernel<512><<<d, 512, 0, st>>>(g);
   else
     bracket_bounds_kernel<1024><<<d, 1024, 0, st>>>(g);
-  uint64_t rows_per_block;
-  bracket_collect_kernel<<<select_grid(n, d, rows_per_block), kSelBlock, 0, st>>>(g);
+  bracket_collect_kernel<<<collect_grid(n, d), kSelBlock, 0, st>>>(g);
   if (expected <= 8192.0)
     bracket_pick_kernel<256><<<(uint32_t)ends, 256, 0, st>>>(g, prefix);
   else

@@ -151,3 +151,14 @@ def test_rows_at_the_edges_of_the_passes(n, d, bits):
     lo, delta, codes, norm = H.gpu_sq_fit(X, bits)
     assert (lo == lv.lo).all() and (delta == lv.delta).all() and (codes == lv.codes).all()
     assert (norm.view(np.uint32) == lv.norm_term.view(np.uint32)).all()
+
+
+@pytest.mark.parametrize("n,d", [(32_768, 1000), (33_000, 33), (40_000, 32), (210_000, 30), (98_305, 8)])
+def test_truncated_range_of_one_and_several_turns_of_workgroups(H, n, d):
+    X = _values(n, d, n)
+    X[:, 0] = np.maximum(X[:, 0], 0.0)  # half of a column equal: more than the few keys its bracket is searched among
+    lo, delta, _, _ = H.gpu_sq_fit(X, 8, coverage=0.99)
+    k = int(np.floor((1.0 - 0.99) * (n - 1)))
+    S = np.sort(X, axis=0)
+    mn, mx = S[k], S[n - 1 - k]
+    assert (lo == mn).all() and _same(delta, ((mx - mn) / np.float32(255)).astype(np.float32))
