@@ -38,6 +38,10 @@ namespace {
 std::mutex g_kept_mutex;
 KeptBlocks g_kept;
 
+std::mutex g_words_mutex;
+uint32_t *g_words[kKeptHostWords];
+int g_n_words = 0;
+
 void give_back_kept() {
   for (;;) {
     KeptBlock b;
@@ -50,6 +54,29 @@ void give_back_kept() {
 }
 
 }  // namespace
+
+uint32_t *host_words_take() {
+  {
+    std::lock_guard<std::mutex> lock(g_words_mutex);
+    if (g_n_words > 0) return g_words[--g_n_words];
+  }
+  void *p = nullptr;
+  if (hipHostMalloc(&p, kHostWords * sizeof(uint32_t), hipHostMallocPortable) == hipSuccess) return static_cast<uint32_t *>(p);
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+void host_words_give(uint32_t *words) {
+  if (!words) return;
+  {
+    std::lock_guard<std::mutex> lock(g_words_mutex);
+    if (g_n_words < kKeptHostWords) {
+      g_words[g_n_words++] = words;
+      return;
+    }
+  }
+  (void)hipHostFree(words);
+}
 
 hipError_t device_alloc(void **ptr, size_t bytes) {
   *ptr = nullptr;
@@ -569,7 +596,15 @@ ann_status ann_free_index(ann_index *index) {
 
 ann_status ann_trim_memory(void) {
   give_back_kept();
-  return ANN_OK;
+  for (;;) {
+    uint32_t *words = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(g_words_mutex);
+      if (g_n_words > 0) words = g_words[--g_n_words];
+    }
+    if (!words) return ANN_OK;
+    (void)hipHostFree(words);
+  }
 }
 
 }  // extern "C"
