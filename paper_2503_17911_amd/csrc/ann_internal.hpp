@@ -92,12 +92,12 @@ ann_status hip_fail(hipError_t e, const char *what);
 // a no-op.)
 hipError_t device_alloc(void **ptr, size_t bytes);
 void device_free(void *ptr, bool idle);
-// A few words of pinned host memory that kernels write and the host reads after a
-// synchronisation (nullptr: none to be had), and back.  From any thread; up to
-// kKeptHostWords of them are kept, and given back by ann_trim_memory.
+// `count` (up to kHostWords) words of device memory to the host, and the wait for the
+// stream: by a kernel into pinned memory, where a copy to the stack would go through the
+// runtime's staging buffer (8 us more).  From any thread; up to kKeptHostWords pieces of
+// pinned memory are kept, and given back by ann_trim_memory.
 constexpr int kHostWords = 16, kKeptHostWords = 16;
-uint32_t *host_words_take();
-void host_words_give(uint32_t *words);
+hipError_t read_words(const uint32_t *src, uint32_t *dst, int count, hipStream_t st);
 
 // Exhaustive search: what the rerank kernel needs to list the queries whose k-th
 // distance does not lie below every row that is no candidate.

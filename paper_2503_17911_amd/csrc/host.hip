@@ -55,7 +55,11 @@ void give_back_kept() {
 
 }  // namespace
 
-uint32_t *host_words_take() {
+static __global__ void copy_words_kernel(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst, int count) {
+  if ((int)threadIdx.x < count) dst[threadIdx.x] = src[threadIdx.x];
+}
+
+static uint32_t *host_words_take() {
   {
     std::lock_guard<std::mutex> lock(g_words_mutex);
     if (g_n_words > 0) return g_words[--g_n_words];
@@ -66,8 +70,7 @@ uint32_t *host_words_take() {
   return nullptr;
 }
 
-void host_words_give(uint32_t *words) {
-  if (!words) return;
+static void host_words_give(uint32_t *words) {
   {
     std::lock_guard<std::mutex> lock(g_words_mutex);
     if (g_n_words < kKeptHostWords) {
@@ -76,6 +79,23 @@ void host_words_give(uint32_t *words) {
     }
   }
   (void)hipHostFree(words);
+}
+
+hipError_t read_words(const uint32_t *src, uint32_t *dst, int count, hipStream_t st) {
+  uint32_t *const words = host_words_take();
+  hipError_t e;
+  if (words) {
+    copy_words_kernel<<<1, 64, 0, st>>>(src, words, count);
+    e = hipGetLastError();
+  } else {
+    e = hipMemcpyAsync(dst, src, (size_t)count * sizeof(uint32_t), hipMemcpyDeviceToHost, st);
+  }
+  const hipError_t e2 = hipStreamSynchronize(st);
+  if (!words) return e != hipSuccess ? e : e2;
+  if (e == hipSuccess && e2 == hipSuccess)
+    for (int i = 0; i < count; ++i) dst[i] = reinterpret_cast<volatile uint32_t *>(words)[i];
+  if (e2 == hipSuccess) host_words_give(words);   // (a stream that failed may still write to them)
+  return e != hipSuccess ? e : e2;
 }
 
 hipError_t device_alloc(void **ptr, size_t bytes) {
@@ -498,8 +518,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
   }
   ANN_TRY_HIP(hipGetLastError());
   uint32_t bad = 0;
-  ANN_TRY_HIP(hipMemcpyAsync(&bad, bad_dev, sizeof(bad), hipMemcpyDeviceToHost, st));
-  ANN_TRY_HIP(hipStreamSynchronize(st));
+  ANN_TRY_HIP(read_words(bad_dev, &bad, 1, st));
   if (bad & 1u) return cleanup(fail(ANN_EINVAL, "a CSR row has more than degree = %u neighbours", desc->degree));
   if (bad & 2u) return cleanup(fail(ANN_EINVAL, "adjacency holds a neighbour id >= n"));
   if (bad & 4u) return cleanup(fail(ANN_EINVAL, "an adjacency row names the same neighbour twice"));

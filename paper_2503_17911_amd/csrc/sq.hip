@@ -955,9 +955,8 @@ static ann_status train_bracketed(const float *x, uint64_t n, uint32_t d, uint32
     bracket_pick_kernel<1024><<<(uint32_t)ends, 1024, 0, st>>>(g, prefix);
   truncated_range_kernel<<<(d + 255) / 256, 256, 0, st>>>(prefix, d, levels, lo, delta);
   uint32_t failed = 1;
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(&failed, g.failed, sizeof(failed), hipMemcpyDeviceToHost, st);
-  const hipError_t e2 = hipStreamSynchronize(st);
+  const hipError_t e = hipGetLastError();
+  const hipError_t e2 = e == hipSuccess ? read_words(g.failed, &failed, 1, st) : hipStreamSynchronize(st);
   device_free(base, e2 == hipSuccess);
   if (e != hipSuccess) return hip_fail(e, "ann_sq_train_truncated");
   if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
