@@ -75,15 +75,15 @@ ann_status check_search_args(const char *fn, const ann_index *index, const float
   return ANN_OK;
 }
 
-// Whether the search kernels can fold their queries themselves: not the 15-bit query's two
-// planes, and not with an order, which need not name every query (all of a batch are folded,
-// also those).
+// Whether a search kernel may fold its queries itself: not the 15-bit query's two planes, and not
+// with an order, which need not name every query (all of a batch are folded, also those).
 bool search_folds(const ann_index *index, const ann_search_params *params, const Workspace &w) {
   const LevelDev &L = index->level[0];
   return index->query_bits != 15 && !params->query_order && w.tq_plane == L.search_lanes * 4 * (L.bits == 8 ? 16u : 32u);
 }
 
-// Launch of the search kernel for a batch whose folded queries are in `w`, or (q given) are put there by it.
+// Launch of the search kernel for a batch whose folded queries are in `w`, or (q given) are put there by it
+// (the kernels for small batches) or by a launch ahead of it.
 ann_status launch_search_with(const ann_index *index, const float *q, uint32_t nq, const ann_search_params *params,
                               const SearchPlan &plan, const uint32_t *entry_ids, uint32_t n_entry, uint32_t *out_ids,
                               float *out_keys, int32_t *out_idot, uint32_t *out_counts, const Workspace &w,
@@ -99,7 +99,6 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
   a.adj_norms = params->layout == 2 ? 1u : 0u;
   a.adjacency = a.adj_norms ? index->adjacency_norms : index->adjacency;
   a.adj_stride = a.adj_norms ? 2 * index->degree : index->degree;
-  a.q = q;
   a.lo = L.lo;
   a.delta = L.delta;
   a.d = index->d;
@@ -162,6 +161,7 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
       const size_t smem = search_smem_bytes(m, (int)p_built, true, vis_log2, index->degree, w.tq_stride, team);
       const uint32_t by_lds = (uint32_t)(128 / ((smem + 1279) / 1280)), by_waves = 4u * kTeamWaves / (uint32_t)team;
       if (nq > (uint32_t)index->n_cu * (by_lds < by_waves ? by_lds : by_waves)) continue;
+      a.q = q;
       return team == 4 ? launch_search_team4(a, L.bits, L.search_lanes, m, wide_step, st)
                        : launch_search_team2(a, L.bits, L.search_lanes, m, wide_step, st);
     }
@@ -169,7 +169,14 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
   // One expansion per step: with 16 queries or fewer to a compute unit the kernel
   // with 128 registers, which keeps the folded query in them.  100 queries x 128 8-bit,
   // ef = 64: 138 -> 134 us, 4,000: 192 -> 188; x 960 4-bit: 335 -> 281, 768 -> 583.
-  if (fast && !multi && nq <= (uint32_t)index->n_cu * 4u * kTeamWaves) return launch_search_small(a, L.bits, L.search_lanes, m, st);
+  const bool small = fast && !multi && nq <= (uint32_t)index->n_cu * 4u * kTeamWaves;
+  if (small && small_kernel_folds((int)L.bits, m)) {
+    a.q = q;
+  } else if (q) {
+    const ann_status rc = launch_query_prep_into(index, 0, q, nq, w, nullptr, nullptr, nullptr, st);
+    if (rc != ANN_OK) return rc;
+  }
+  if (small) return launch_search_small(a, L.bits, L.search_lanes, m, st);
   if (a.filtered)
     return wide_step ? launch_search_filtered_wide(a, L.bits, L.search_lanes, m, st)
                      : launch_search_filtered(a, L.bits, L.search_lanes, m, multi, st);
@@ -210,10 +217,9 @@ extern "C" ann_status ann_search_batch(ann_index *index, const float *q, uint32_
   }
   rc = launch_search_with(index, folds ? q : nullptr, nq, params, plan, entry_ids, n_entry, out_ids, out_keys, out_idot, out_counts,
                           *lease.ws, st);
-  if (rc == ANN_OK || !folds) {
-    lease.ws->folded_q = q;
-    lease.ws->folded_nq = nq;
-  }
+  const bool folded = rc == ANN_OK || !folds;   // (a launch that failed may have left anything)
+  lease.ws->folded_q = folded ? q : nullptr;
+  lease.ws->folded_nq = folded ? nq : 0;
   return rc;
 }
 

@@ -67,7 +67,7 @@ struct SearchArgs {
   const uint8_t *codes;
   const float *norm_term;
   const uint32_t *adjacency;
-  const float *q;  // [nq][d]: the kernel folds its query itself and leaves the result in the next four; or nullptr: they hold it
+  const float *q;  // [nq][d]: the kernel (FOLDS) folds its query itself and leaves the result in the next four; or nullptr: they hold it
   const float *lo, *delta;  // [d] the level's codebook (with q)
   uint8_t *tq;
   float *s;
@@ -175,7 +175,10 @@ __host__ __device__ inline size_t search_smem_bytes(int m, int pmax, bool fast, 
 // With two pool registers and 8-bit codes a wavefront per SIMD is lost (10,000
 // queries on 1M x 128: 733 -> 864 us), with eight and several wavefronts per query it
 // spills (754 -> 767).
-template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1, bool QREG = false, bool FILTER = false>
+//
+// FOLDS: the kernel can fold its query itself (SearchArgs::q).  Those with 128 registers: with fewer, what
+// that adds spills (10,000 queries on 1M x 128, ef = 128: three registers, 746 -> 812 us).
+template <int BITS, int LPR, int M, int PMAX, bool FAST, int TEAM = 1, bool QREG = false, bool FILTER = false, bool FOLDS = false>
 struct SearchWave {
   static constexpr int G = kWave / LPR;      // code rows evaluated side by side
   static constexpr int CPL = 4;              // 16-byte chunks of a row per lane
@@ -557,7 +560,7 @@ struct SearchWave {
     const int rank_p = (int)(pos >> 3);
     int *cnt = reinterpret_cast<int *>(stage);
     uint64_t *lst = M >= 2 ? mbuf : stage + merge_list_at(M);
-    uint64_t merged[M];
+    uint64_t merged[M <= 2 ? M : 1];
     for (;;) {
       // pool entry i moves up by the number of candidates with rank <= i
 #pragma unroll
@@ -571,29 +574,32 @@ struct SearchWave {
       if (mine) atomicAdd(&cnt[rank_p], 1);
       wave_sync();
       int shift[M];
+      if (M <= 2) {   // (on their way during the walk)
 #pragma unroll
-      for (int r = 0; r < M; ++r) shift[r] = cnt[r * kWave + lane];
-      // candidates below this lane's candidate: every lane walks the list (eight
+        for (int r = 0; r < M; ++r) shift[r] = cnt[r * kWave + lane];
+      }
+      // candidates below this lane's candidate: every lane walks the list (kWalk
       // entries in flight, the same for all lanes), with width = 32 each half of
-      // the wavefront every other eight
+      // the wavefront every other kWalk
+      constexpr int kWalk = M <= 2 ? 8 : 4;
       int below_c = 0;
-      const uint4 *walk = reinterpret_cast<const uint4 *>(lst + (lane < width ? 0 : 8));
-      const int stride = width < kWave ? 16 : 8;
+      const uint4 *walk = reinterpret_cast<const uint4 *>(lst + (lane < width ? 0 : kWalk));
+      const int stride = width < kWave ? 2 * kWalk : kWalk;
 #pragma nounroll
       for (int i = 0; i < n_l; i += stride) {
-        uint4 two[4];
+        uint4 two[kWalk / 2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) two[t] = walk[t];
+        for (int t = 0; t < kWalk / 2; ++t) two[t] = walk[t];
         walk += stride / 2;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < kWalk / 2; ++t)
           below_c += (pack64(two[t].y, two[t].x) < c64 ? 1 : 0) + (pack64(two[t].w, two[t].z) < c64 ? 1 : 0);
       }
       if (width < kWave) below_c = half_sum_i32(below_c);
       int carry = 0;
 #pragma unroll
       for (int r = 0; r < M; ++r) {
-        shift[r] = wave_inclusive_scan_i32(shift[r]) + carry;
+        shift[r] = wave_inclusive_scan_i32(M <= 2 ? shift[r] : cnt[r * kWave + lane]) + carry;
         carry = __builtin_amdgcn_readlane(shift[r], kWave - 1);
       }
       const int dest = rank_p + below_c;
@@ -613,8 +619,11 @@ struct SearchWave {
       if (lands) mbuf[dest] = c64;
       wave_sync();
       const int winner = cnt[lands ? dest : 0];
+      // (with four registers and more the old pool and the new one are not held together)
+      if (M <= 2) {
 #pragma unroll
-      for (int r = 0; r < M; ++r) merged[r] = mbuf[r * kWave + lane];
+        for (int r = 0; r < M; ++r) merged[M <= 2 ? r : 0] = mbuf[r * kWave + lane];
+      }
       const uint64_t lose = __ballot(lands && winner != lane);
       wave_sync();
       if (lose == 0) break;
@@ -623,10 +632,12 @@ struct SearchWave {
     }
 #pragma unroll
     for (int r = 0; r < M; ++r) {
+      const uint64_t v = M <= 2 ? merged[M <= 2 ? r : 0] : mbuf[r * kWave + lane];
       const bool beyond = r * kWave + lane >= ef_q;  // entries pushed past the pool size are dropped
-      pk[r] = beyond ? kEmpty : (uint32_t)(merged[r] >> 32);
-      pv[r] = beyond ? kEmpty : (uint32_t)merged[r];
+      pk[r] = beyond ? kEmpty : (uint32_t)(v >> 32);
+      pv[r] = beyond ? kEmpty : (uint32_t)v;
     }
+    if (M > 2) wave_sync();
     refresh_worst();
   }
 
@@ -798,7 +809,7 @@ struct SearchWave {
 
   // TEAM > 1: what the wavefronts but the first do.
   __device__ __forceinline__ void help(uint32_t qi, int wave) {
-    if (a.q) {
+    if (FOLDS && a.q) {
       team_barrier();   // the first wavefront has folded the query
       s = __int_as_float(step_n[1]);
       qlo = __int_as_float(step_n[2]);
@@ -945,7 +956,7 @@ struct SearchWave {
   // in another order, which certain_f32 allows for), into LDS for this search and
   // to memory for calls that reuse the folding.  A launch less (4.6 us), for about 3 us
   // at the start of a search: 100 queries on 10,000 x 128, one expansion per step 142.6 -> 139.2 us,
-  // 1,000 x 960 4-bit 412.8 -> 404.9, one query 124.4 -> 123.3, 10,000 x 96 649.9 -> 644.4.
+  // 1,000 x 960 4-bit 412.8 -> 404.9, one query 124.4 -> 123.3.
   __device__ __forceinline__ void fold(uint32_t qi) {
     constexpr int kWords = CPL * LPR * TQW, kRounds = (kWords + kWave - 1) / kWave;
     const float *qr = a.q + (uint64_t)qi * a.d;
@@ -1022,7 +1033,7 @@ struct SearchWave {
   }
 
   __device__ __forceinline__ void run(uint32_t qi) {
-    if (a.q) {
+    if (FOLDS && a.q) {
       fold(qi);
       if constexpr (TEAM > 1) team_barrier();
     } else {
@@ -1318,13 +1329,16 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(kTeam
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
   if (qi >= args.nq) return;
-  SearchWave<BITS, LPR, M, PMAX, true, TEAM, BITS == 4 && M <= 4> w(args, smem);
+  SearchWave<BITS, LPR, M, PMAX, true, TEAM, BITS == 4 && M <= 4, false, true> w(args, smem);
   const int wave = (int)threadIdx.x / kWave;
   if (wave == 0)
     w.run(qi);
   else
     w.help(qi, wave);
 }
+
+// (4-bit codes with eight pool registers have none left for the folding)
+constexpr bool small_kernel_folds(int bits, int m) { return bits == 8 || m < 8; }
 
 // One expansion per step for batches that fit the chip at 128 registers (16
 // queries to a compute unit): the folded query in registers.
@@ -1334,7 +1348,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kTeamWaves))
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
   if (qi >= args.nq) return;
-  SearchWave<BITS, LPR, M, 1, true, 1, true> w(args, smem);
+  SearchWave<BITS, LPR, M, 1, true, 1, true, false, small_kernel_folds(BITS, M)> w(args, smem);
   w.run(qi);
 }
 
