@@ -489,6 +489,9 @@ struct SearchWave {
     worst = pack64(__builtin_amdgcn_readlane(k_, rl), __builtin_amdgcn_readlane(v_, rl));
   }
 
+  // Registers for more in flight during a merge (kernels of large pools would spill; 1,000 queries x 960 4-bit on
+  // the kernel with four wavefronts per query: 399 -> 392 us).
+  static constexpr bool kRoomy = M <= 2 || (FOLDS && M <= 4);
   // Merge up to 64 candidates (one per lane where `have`) into the pool.  With
   // width = 32 the upper half of the wavefront holds the lower half's candidates
   // once more.
@@ -560,7 +563,7 @@ struct SearchWave {
     const int rank_p = (int)(pos >> 3);
     int *cnt = reinterpret_cast<int *>(stage);
     uint64_t *lst = M >= 2 ? mbuf : stage + merge_list_at(M);
-    uint64_t merged[M <= 2 ? M : 1];
+    uint64_t merged[kRoomy ? M : 1];
     for (;;) {
       // pool entry i moves up by the number of candidates with rank <= i
 #pragma unroll
@@ -574,14 +577,14 @@ struct SearchWave {
       if (mine) atomicAdd(&cnt[rank_p], 1);
       wave_sync();
       int shift[M];
-      if (M <= 2) {   // (on their way during the walk)
+      if (kRoomy) {   // (on their way during the walk)
 #pragma unroll
         for (int r = 0; r < M; ++r) shift[r] = cnt[r * kWave + lane];
       }
       // candidates below this lane's candidate: every lane walks the list (kWalk
       // entries in flight, the same for all lanes), with width = 32 each half of
       // the wavefront every other kWalk
-      constexpr int kWalk = M <= 2 ? 8 : 4;
+      constexpr int kWalk = kRoomy ? 8 : 4;
       int below_c = 0;
       const uint4 *walk = reinterpret_cast<const uint4 *>(lst + (lane < width ? 0 : kWalk));
       const int stride = width < kWave ? 2 * kWalk : kWalk;
@@ -599,7 +602,7 @@ struct SearchWave {
       int carry = 0;
 #pragma unroll
       for (int r = 0; r < M; ++r) {
-        shift[r] = wave_inclusive_scan_i32(M <= 2 ? shift[r] : cnt[r * kWave + lane]) + carry;
+        shift[r] = wave_inclusive_scan_i32(kRoomy ? shift[r] : cnt[r * kWave + lane]) + carry;
         carry = __builtin_amdgcn_readlane(shift[r], kWave - 1);
       }
       const int dest = rank_p + below_c;
@@ -619,10 +622,10 @@ struct SearchWave {
       if (lands) mbuf[dest] = c64;
       wave_sync();
       const int winner = cnt[lands ? dest : 0];
-      // (with four registers and more the old pool and the new one are not held together)
-      if (M <= 2) {
+      // (without room the old pool and the new one are not held together)
+      if (kRoomy) {
 #pragma unroll
-        for (int r = 0; r < M; ++r) merged[M <= 2 ? r : 0] = mbuf[r * kWave + lane];
+        for (int r = 0; r < M; ++r) merged[kRoomy ? r : 0] = mbuf[r * kWave + lane];
       }
       const uint64_t lose = __ballot(lands && winner != lane);
       wave_sync();
@@ -632,12 +635,12 @@ struct SearchWave {
     }
 #pragma unroll
     for (int r = 0; r < M; ++r) {
-      const uint64_t v = M <= 2 ? merged[M <= 2 ? r : 0] : mbuf[r * kWave + lane];
+      const uint64_t v = kRoomy ? merged[kRoomy ? r : 0] : mbuf[r * kWave + lane];
       const bool beyond = r * kWave + lane >= ef_q;  // entries pushed past the pool size are dropped
       pk[r] = beyond ? kEmpty : (uint32_t)(v >> 32);
       pv[r] = beyond ? kEmpty : (uint32_t)v;
     }
-    if (M > 2) wave_sync();
+    if (!kRoomy) wave_sync();
     refresh_worst();
   }
 
