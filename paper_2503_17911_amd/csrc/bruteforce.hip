@@ -1297,7 +1297,11 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
     }
     float below = (float)(dist - room);
     if (found > cap) below = -INFINITY;   // entries were lost
-    if ((uint32_t)(out >> 32) >= kMaxScore || sq != sq) below = INFINITY;
+    // (two parts, L2: rows left out for their size were not counted)
+    if ((uint32_t)(out >> 32) >= kMaxScore) below = c.unscale && c.metric == ANN_L2 ? -INFINITY : INFINITY;
+    // (two parts: from here on the query's squared norm in fp32, which its scale comes from, may be infinite and its scores no numbers)
+    if (c.unscale && sq >= 0x1p127) below = -INFINITY;
+    if (sq != sq) below = INFINITY;
     if (sq == INFINITY) below = -INFINITY;
     c.below[q] = below;
   }

@@ -243,20 +243,26 @@ def _check_some(H, X, Q, k, metric, every=13):
     H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
 
 
-# two half-precision parts (from 65 queries and 65 columns on), split on the way or ahead (from 512 plus the
-# columns on, tiles of 256 queries); samples of both sizes; columns that end inside a block, rows inside a tile and a slab
+# Two half-precision parts: more than 64 queries and 64 columns, more than 16,384 rows and than 2^24 scores.  The rows are split on
+# the way (below 512 queries and as many more as columns) or ahead (tiles of 256 queries): 100 and 700 queries in most tests below.
+PARTS = [(100, 170_000), (700, 30_000)]
+DENSE = [(100, 18_000), (700, 18_000)]   # (three parts)
+
+
+# neither way (the first four: few enough scores) and both; samples of both sizes; columns that end inside a block, rows inside a tile and a slab
 @pytest.mark.parametrize("n,d,nq,k,metric", [
     (16385, 65, 65, 10, oracle.L2), (20011, 100, 129, 17, oracle.IP), (17000, 131, 608, 5, oracle.L2), (17000, 96, 608, 10, oracle.IP),
-    (30001, 72, 641, 10, oracle.L2), (300001, 67, 700, 3, oracle.L2), (140000, 260, 800, 10, oracle.IP), (16640, 2048, 2600, 1, oracle.L2),
-    (50000, 128, 1024, 100, oracle.IP)])
+    (262_145, 65, 65, 10, oracle.L2), (140_011, 100, 129, 17, oracle.IP), (40_000, 300, 600, 10, oracle.IP), (1_000_001, 66, 70, 5, oracle.L2),
+    (28_000, 131, 639, 5, oracle.L2), (28_000, 131, 656, 5, oracle.L2), (28_000, 96, 608, 10, oracle.IP), (30001, 72, 641, 10, oracle.L2),
+    (300001, 67, 700, 3, oracle.L2), (140000, 260, 800, 10, oracle.IP), (16640, 2048, 2600, 1, oracle.L2), (50000, 128, 1024, 100, oracle.IP)])
 def test_two_parts(H, n, d, nq, k, metric):
     _check_some(H, _points(n, d, n + d), _points(nq, d, k), k, metric)
 
 
-@pytest.mark.parametrize("nq", [100, 700])
+@pytest.mark.parametrize("nq,n", PARTS + DENSE)
 @pytest.mark.parametrize("scale", [2.0 ** -40, 1e-6, 3e4, 2.0 ** 40])
-def test_two_parts_of_vectors_of_any_size(H, nq, scale):
-    X, Q = _points(18000, 70, 51) * np.float32(scale), _points(nq, 70, 52) * np.float32(scale)
+def test_two_parts_of_vectors_of_any_size(H, nq, n, scale):
+    X, Q = _points(n, 70, 51) * np.float32(scale), _points(nq, 70, 52) * np.float32(scale)
     Q[3] *= np.float32(1e-3)
     Q[5] = 0.0
     _check_some(H, X, Q, 10, oracle.L2, every=5)
@@ -264,11 +270,11 @@ def test_two_parts_of_vectors_of_any_size(H, nq, scale):
     _check_some(H, X, Q, 10, oracle.IP, every=5)
 
 
-@pytest.mark.parametrize("nq", [100, 700])
+@pytest.mark.parametrize("nq,n", PARTS + DENSE)
 @pytest.mark.parametrize("metric,n_large", [(oracle.L2, 5), (oracle.L2, 300), (oracle.IP, 5), (oracle.IP, 64), (oracle.IP, 65), (oracle.IP, 300)])
-def test_two_parts_with_rows_outside_their_range(H, nq, metric, n_large):
+def test_two_parts_with_rows_outside_their_range(H, nq, n, metric, n_large):
     """Rows a thousand times larger than those of any sample: near to some queries (L2), the nearest of most (inner product)."""
-    n, d = 20_000, 80
+    d = 80
     X, Q = _points(n, d, 61), _points(nq, d, 62)
     sampled = np.unique(np.concatenate([_sampled_rows(n, 1024), _sampled_rows(n, 4096)]))
     large = np.setdiff1d(np.arange(n), sampled)[7::11][:n_large]
@@ -278,20 +284,68 @@ def test_two_parts_with_rows_outside_their_range(H, nq, metric, n_large):
     _check_some(H, X, Q, 10, metric, every=4)
 
 
-@pytest.mark.parametrize("nq", [100, 700])
-def test_two_parts_with_rows_that_are_not_finite(H, nq):
-    n, d = 20_000, 80
+@pytest.mark.parametrize("nq,n", PARTS)
+def test_two_parts_where_only_left_out_rows_are_near(H, nq, n):
+    """L2: hardly a row has a finite norm, none of those in the sample does, and the finite ones are outside the range
+    that their scale leaves: fewer rows in range than results, and the others count all the same."""
+    d, k = 80, 10
+    X, Q = np.full((n, d), 1e30, np.float32), _points(nq, d, 64)
+    outside = np.setdiff1d(np.arange(n), _sampled_rows(n, 1024))
+    rows = outside[np.linspace(0, len(outside) - 1, 12).astype(int)]
+    X[rows[:4]] = _points(4, d, 65)
+    X[rows[4:]] = _points(8, d, 66) * 1e6
+    gid, gdist = H.gpu_bruteforce(X, Q, k, oracle.L2)
+    oid, odist = oracle.bruteforce_topk(X[rows], Q, k, metric=oracle.L2)
+    H.check_rerank(gid, gdist, rows[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
+
+
+@pytest.mark.parametrize("nq,n", PARTS + DENSE)
+@pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
+def test_two_parts_with_rows_and_queries_that_are_not_finite(H, nq, n, metric):
+    """As the tests of the same with fewer columns; and finite queries whose squares are not: ordinary neighbours by inner
+    product, in L2 infinitely far from every row."""
+    d, k = 80, 10
     X, Q = _points(n, d, 71), _points(nq, d, 72)
-    X[5, 3], X[9, 70], X[11, 0] = np.nan, np.inf, -np.inf
-    gid, gdist = H.gpu_bruteforce(X, Q, 10, oracle.L2)
-    _check_but(H, X, Q[::7], 10, oracle.L2, [5, 9, 11], [], gid[::7], gdist[::7])
+    X[5, 3] = X[11, 0] = np.nan
+    Q[11, 2], Q[17, 4], Q[20, 19] = np.nan, np.inf, 3.4e38
+    Q[[23, 50], [5, 7]] = 2e19, 1e25
+    Q[30] *= 1e19
+    Q[31] = np.abs(Q[31]) * 1e19
+    gid, gdist = H.gpu_bruteforce(X, Q, k, metric)
+    large = [20, 23, 30, 31, 50]
+    some = np.unique(np.r_[0:nq:7, 30, 31, 23, 50, nq - 1])
+    some = some[~np.isin(some, [11, 17, 20] + (large if metric == oracle.L2 else []))]
+    _check_but(H, X, Q[some], k, metric, [5, 11], [], gid[some], gdist[some])
+    assert (gid[11] == 0xFFFFFFFF).all() and np.isposinf(gdist[11]).all()
+    if metric == oracle.IP:
+        near = np.flatnonzero(X[:, 4] > 0)
+        assert (gid[17] == near[~np.isin(near, [5, 11])][:k]).all() and np.isneginf(gdist[17]).all()
+    else:
+        for q in large:   # (all distances are infinite in fp32: any rows but those with a NaN, each once)
+            assert np.isposinf(gdist[q]).all() and (gid[q] < n).all() and len(set(gid[q])) == k and not np.isin(gid[q], [5, 11]).any()
 
 
-@pytest.mark.parametrize("nq", [70, 650])
-def test_two_parts_of_rows_that_are_not_aligned(H, nq):
+@pytest.mark.parametrize("nq,n", PARTS)
+@pytest.mark.parametrize("n_far", [3, 64, 65, 300])
+def test_two_parts_with_rows_without_a_finite_norm(H, nq, n, n_far):
+    """Inner product: infinite coordinates and finite ones whose squares are not, up to as many as are listed and more."""
+    d, k = 80, 12
+    X, Q = np.abs(_points(n, d, 73)) + 0.1, np.abs(_points(nq, d, 74)) + 0.1
+    far = np.sort(np.random.default_rng(75).permutation(n)[:n_far])
+    X[far[0::3], 3], X[far[1::3], 5], X[far[2::3], 7] = -np.inf, 2e25, np.inf
+    gid, gdist = H.gpu_bruteforce(X, Q, k, oracle.IP)
+    keep = np.ones(n, bool)
+    keep[far[0::3]] = False   # (infinitely far)
+    some = np.unique(np.r_[0:nq:9, nq - 1])
+    oid, odist = oracle.bruteforce_topk(X[keep], Q[some], k, metric=oracle.IP)
+    H.check_rerank(gid[some], gdist[some], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
+
+
+@pytest.mark.parametrize("nq,n", PARTS + DENSE)
+def test_two_parts_of_rows_that_are_not_aligned(H, nq, n):
     import torch
     import paper_2503_17911_amd as ann
-    n, d, k = 17000, 96, 10
+    d, k = 96, 10
     X, Q = _points(n, d, 81), _points(nq, d, 82)
     buf = torch.empty(n * d + 1, device=H.DEV)
     buf[1:] = H.dev(X).reshape(-1)
