@@ -244,9 +244,9 @@ def _check_some(H, X, Q, k, metric, every=13):
 
 
 # Two half-precision parts: more than 64 queries and 64 columns, more than 16,384 rows and than 2^24 scores.  The rows are split on
-# the way (below 512 queries and as many more as columns) or ahead (tiles of 256 queries): 100 and 700 queries in most tests below.
+# the way (below 512 queries and as many more as columns) or ahead (tiles of 256 queries): 100 and 700 queries in most tests below,
+# which also have sizes with fewer scores than that (three parts).
 PARTS = [(100, 170_000), (700, 30_000)]
-DENSE = [(100, 18_000), (700, 18_000)]   # (three parts)
 
 
 # neither way (the first four: few enough scores) and both; samples of both sizes; columns that end inside a block, rows inside a tile and a slab
@@ -259,7 +259,7 @@ def test_two_parts(H, n, d, nq, k, metric):
     _check_some(H, _points(n, d, n + d), _points(nq, d, k), k, metric)
 
 
-@pytest.mark.parametrize("nq,n", PARTS + DENSE)
+@pytest.mark.parametrize("nq,n", PARTS + [(100, 18_000), (700, 18_000)])
 @pytest.mark.parametrize("scale", [2.0 ** -40, 1e-6, 3e4, 2.0 ** 40])
 def test_two_parts_of_vectors_of_any_size(H, nq, n, scale):
     X, Q = _points(n, 70, 51) * np.float32(scale), _points(nq, 70, 52) * np.float32(scale)
@@ -270,7 +270,7 @@ def test_two_parts_of_vectors_of_any_size(H, nq, n, scale):
     _check_some(H, X, Q, 10, oracle.IP, every=5)
 
 
-@pytest.mark.parametrize("nq,n", PARTS + DENSE)
+@pytest.mark.parametrize("nq,n", PARTS + [(100, 20_000), (700, 20_000)])
 @pytest.mark.parametrize("metric,n_large", [(oracle.L2, 5), (oracle.L2, 300), (oracle.IP, 5), (oracle.IP, 64), (oracle.IP, 65), (oracle.IP, 300)])
 def test_two_parts_with_rows_outside_their_range(H, nq, n, metric, n_large):
     """Rows a thousand times larger than those of any sample: near to some queries (L2), the nearest of most (inner product)."""
@@ -299,7 +299,16 @@ def test_two_parts_where_only_left_out_rows_are_near(H, nq, n):
     H.check_rerank(gid, gdist, rows[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
 
 
-@pytest.mark.parametrize("nq,n", PARTS + DENSE)
+@pytest.mark.parametrize("nq,n", PARTS + [(100, 20_000), (700, 20_000)])
+def test_two_parts_with_rows_that_are_not_finite(H, nq, n):
+    d = 80
+    X, Q = _points(n, d, 71), _points(nq, d, 72)
+    X[5, 3], X[9, 70], X[11, 0] = np.nan, np.inf, -np.inf
+    gid, gdist = H.gpu_bruteforce(X, Q, 10, oracle.L2)
+    _check_but(H, X, Q[::7], 10, oracle.L2, [5, 9, 11], [], gid[::7], gdist[::7])
+
+
+@pytest.mark.parametrize("nq,n", PARTS)
 @pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
 def test_two_parts_with_rows_and_queries_that_are_not_finite(H, nq, n, metric):
     """As the tests of the same with fewer columns; and finite queries whose squares are not: ordinary neighbours by inner
@@ -341,7 +350,7 @@ def test_two_parts_with_rows_without_a_finite_norm(H, nq, n, n_far):
     H.check_rerank(gid[some], gdist[some], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
 
 
-@pytest.mark.parametrize("nq,n", PARTS + DENSE)
+@pytest.mark.parametrize("nq,n", PARTS + [(70, 17_000), (650, 17_000)])
 def test_two_parts_of_rows_that_are_not_aligned(H, nq, n):
     import torch
     import paper_2503_17911_amd as ann
