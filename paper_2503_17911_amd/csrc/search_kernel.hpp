@@ -67,8 +67,6 @@ struct SearchArgs {
   const uint8_t *codes;
   const float *norm_term;
   const uint32_t *adjacency;
-  const float *q;  // [nq][d]: the kernel (FOLDS) folds its query itself and leaves the result in the next four; or nullptr: they hold it
-  const float *lo, *delta;  // [d] the level's codebook (with q)
   uint8_t *tq;
   float *s;
   float *qlo;
@@ -85,7 +83,6 @@ struct SearchArgs {
   int32_t *out_idot;
   uint32_t *out_counts;
   uint64_t n;
-  uint32_t d;
   uint32_t row_stride, n_chunks, degree, metric, tq_stride, n_entry, entry_point, ef, vis_log2, nq, p;
   uint32_t filtered;  // the label test and/or the per-expansion cap m_s is active
   uint32_t vis_cache;  // visited set is the two-way cache
@@ -97,6 +94,11 @@ struct SearchArgs {
   uint32_t adj_stride;  // words from one adjacency row to the next: degree, or 2 * degree with adj_norms
   uint32_t adj_norms;   // every adjacency row is followed by the norm terms of its neighbours, in slot order
   float alpha_s;
+  // (last: kernels that do not read these keep the argument loads and registers they have without them; with
+  // them further up 10,000 queries on 100,000 x 480 4-bit, one expansion, ef = 64 took 970 us instead of 839)
+  uint32_t d;
+  const float *q;  // [nq][d]: the kernel (FOLDS) folds its query itself and leaves the result in tq, s, qlo, sum_t; or nullptr: they hold it
+  const float *lo, *delta;  // [d] the level's codebook (with q)
 };
 
 // All but the evaluation of a step is one wavefront's work (with several to a
@@ -192,7 +194,7 @@ struct SearchWave {
   // (eight or more lanes to a row) a group is fewer rows than a step has
   // candidates, so two are requested together (1M x 960 4-bit: 6 % faster;
   // four groups cost more in registers than they gain)
-      static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? (FAST && M >= 4 && LPR >= 8 ? kGroupsLong : ANN_U) : (LPR >= 8 ? 2 : 1));
+  static constexpr int U = TEAM > 1 ? ANN_U_TEAM : (PMAX > 1 ? (FAST && M >= 4 && LPR >= 8 ? kGroupsLong : ANN_U) : (LPR >= 8 ? 2 : 1));
   static constexpr int TQW = TqRegs<BITS>::kWords;
 
   // the i-th unvisited neighbour of the current step: id in the upper word,
@@ -473,7 +475,12 @@ struct SearchWave {
         test_and_set(pv[r] >> 1);
         ++kept;
       }
-    n_vis = (uint32_t)group_sum_i32<64>(kept);
+    // (By LDS from row to row: the general kernels' registers fall out otherwise with the other sums.  10,000 queries, one
+    // expansion, ef = 128, wide cache, 100,000 x 200 4-bit: 1,055 us, with lane swaps 1,218; four expansions, 50,000 x 768
+    // 8-bit, degree 48: 2,305, with a count of ballots 2,726.)
+    kept = group_sum_i32<16>(kept);
+    kept += xor_lane_i32(kept, 16);
+    n_vis = (uint32_t)(kept + xor_lane_i32(kept, 32));
     ++n_rebuild;
     wave_sync();
   }
@@ -489,6 +496,15 @@ struct SearchWave {
     worst = pack64(__builtin_amdgcn_readlane(k_, rl), __builtin_amdgcn_readlane(v_, rl));
   }
 
+  // Kernels that take merge_narrow(): those whose registers do not hold what merge() has in flight.  The line
+  // follows both sides' times over rows of 1 to 16 lanes (merge() / merge_narrow(), 10,000 queries): 8-bit, degree
+  // 48, ef = 128, four expansions 50,000 x 768 4,340 / 2,300 us, 100,000 x 256 1,612 / 968, 200,000 x 128 930 / 730;
+  // labels, ef = 256, eight expansions, 100,000 x 200 4-bit 2,084 / 1,845; one expansion, ef = 64, 100,000 x 480 4-bit
+  // 970 / 850.  With the filter and pools of up to 128 merge() is 1 to 3 % the faster, with eight pool registers and
+  // rows of one or two lanes 3 to 5 %, with one expansion, ef = 128 and 100,000 x 200 4-bit 1,070 / 1,150.
+  static constexpr bool kNarrow =
+      FAST ? BITS == 4 && PMAX == 1 && !FOLDS && M <= 2 && !(M == 2 && LPR == 2)
+           : (FILTER ? (M >= 4 && LPR >= 2) || (BITS == 4 && PMAX == 1 && M == 1) : M <= 4 || LPR >= 4 || PMAX == 4);
   // Registers for more in flight during a merge (kernels of large pools would spill; 1,000 queries x 960 4-bit on
   // the kernel with four wavefronts per query: 399 -> 392 us).
   static constexpr bool kRoomy = M <= 2 || (FOLDS && M <= 4);
@@ -644,6 +660,86 @@ struct SearchWave {
     refresh_worst();
   }
 
+  // The same with few registers: two levels of the bisection and four list entries at a time, and candidates
+  // with equal destinations told before the scatter.
+  __device__ __forceinline__ void merge_narrow(bool have, uint32_t ck, uint32_t cv) {
+    const uint64_t c64 = pack64(ck, cv);
+    bool mine = have && c64 < worst;
+    if (__ballot(mine) == 0) return;
+    const char *mb = reinterpret_cast<const char *>(mbuf);
+    uint32_t pos = 0;  // byte offset into mbuf
+    int step = 32 * M;
+#pragma unroll
+    for (; step >= 2; step >>= 2) {
+      const uint64_t ea = *reinterpret_cast<const uint64_t *>(mb + pos + (step - 1) * 8);
+      const uint64_t eb = *reinterpret_cast<const uint64_t *>(mb + pos + (step / 2 - 1) * 8);
+      const uint64_t ec = *reinterpret_cast<const uint64_t *>(mb + pos + (step + step / 2 - 1) * 8);
+      const bool up = ea < c64;
+      const uint64_t second = up ? ec : eb;
+      pos += (up ? (uint32_t)step * 8u : 0u) + (second < c64 ? (uint32_t)(step / 2) * 8u : 0u);
+    }
+    if (step == 1) {
+      const uint64_t e = *reinterpret_cast<const uint64_t *>(mb + pos);
+      pos += e < c64 ? 8u : 0u;
+    }
+    const uint32_t at_id = (uint32_t)*reinterpret_cast<const uint64_t *>(mb + pos);
+    mine = mine && (at_id | 1u) != (cv | 1u);
+    uint64_t km = __ballot(mine);
+    if (km == 0) return;
+    const int rank_p = (int)(pos >> 3);
+    int *cnt = reinterpret_cast<int *>(stage);
+    uint64_t *lst = M >= 2 ? mbuf : stage + merge_list_at(M);
+    int shift[M];
+    int dest;
+    for (;;) {
+#pragma unroll
+      for (int r = 0; r < M; ++r) cnt[r * kWave + lane] = 0;
+      const int n_l = __popcll(km);   // (the list: padded to a multiple of four)
+      if (mine) lst[lanes_below(km)] = c64;
+      if (lane < 4) lst[n_l + lane] = ~0ull;
+      wave_sync();
+      if (mine) atomicAdd(&cnt[rank_p], 1);
+      wave_sync();
+      int carry = 0;
+#pragma unroll
+      for (int r = 0; r < M; ++r) {
+        shift[r] = wave_inclusive_scan_i32(cnt[r * kWave + lane]) + carry;
+        carry = __builtin_amdgcn_readlane(shift[r], kWave - 1);
+      }
+      int below_c = 0;
+      for (int i = 0; i < n_l; i += 4) {
+        const uint64_t e0 = lst[i], e1 = lst[i + 1], e2 = lst[i + 2], e3 = lst[i + 3];
+        below_c += (e0 < c64 ? 1 : 0) + (e1 < c64 ? 1 : 0) + (e2 < c64 ? 1 : 0) + (e3 < c64 ? 1 : 0);
+      }
+      dest = rank_p + below_c;
+      const bool lands = mine && dest < 64 * M;
+      wave_sync();
+      if (lands) cnt[dest] = lane;
+      wave_sync();
+      const uint64_t lose = __ballot(lands && cnt[dest] != lane);
+      if (lose == 0) break;
+      km &= ~lose;
+      mine = mine && ((lose >> lane) & 1ull) == 0;
+      wave_sync();
+    }
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+      const int to = r * kWave + lane + shift[r];
+      if (to < 64 * M) mbuf[to] = pack64(pk[r], pv[r]);
+    }
+    if (mine && dest < 64 * M) mbuf[dest] = c64;
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+      const uint64_t v = mbuf[r * kWave + lane];
+      const bool beyond = r * kWave + lane >= ef_q;
+      pk[r] = beyond ? kEmpty : (uint32_t)(v >> 32);
+      pv[r] = beyond ? kEmpty : (uint32_t)v;
+    }
+    wave_sync();
+    refresh_worst();
+  }
+
   // Merge of a few candidates (lanes 0 .. n-1 hold them, all below the pool's
   // last entry): one pass per candidate, its value broadcast to all lanes.
   // Every pool entry counts the candidates below it (it moves up by that
@@ -756,7 +852,7 @@ struct SearchWave {
       n_q = 0;
       return;
     }
-    const int width = n_q <= kWave / 2 ? kWave / 2 : kWave, at = lane & (width - 1);
+    const int width = !kNarrow && n_q <= kWave / 2 ? kWave / 2 : kWave, at = kNarrow ? lane : lane & (width - 1);   // (a mask in the general kernels costs registers: 26 instead of 14 spilled)
     constexpr int kBatches = kStage / kWave;
     uint64_t batch[kBatches];
 #pragma unroll
@@ -768,7 +864,10 @@ struct SearchWave {
       uint64_t c = batch[0];
 #pragma unroll
       for (int t = 1; t < kBatches; ++t) c = b == t ? batch[t] : c;
-      merge(b * kWave + at < n_q, (uint32_t)(c >> 32), (uint32_t)c, width);
+      if constexpr (kNarrow)
+        merge_narrow(b * kWave + at < n_q, (uint32_t)(c >> 32), (uint32_t)c);
+      else
+        merge(b * kWave + at < n_q, (uint32_t)(c >> 32), (uint32_t)c, width);
     }
     n_q = 0;
   }
