@@ -1453,7 +1453,11 @@ static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm
 // ---------------------------------------------------------------------------
 // Queries whose result is not certain (see bf_select_entries_kernel): vectors far
 // from the origin, where the squares cancel, or many rows at the same distance.
-// First the whole selection again with centred rows and queries (distances do not
+// After two parts, unless the rows lie around another point than the origin, the
+// selection again with three parts: rows much smaller or larger than the sample's
+// largest lose in half precision, not in bf16.  (300,000 x 128, norms spread like exp(3 z), 2,000 queries:
+// 12.0 ms with centred rows at once, in which the small ones lose, too; 0.93 so; 1.12 with three parts only.)
+// Then the whole selection with centred rows and queries (distances do not
 // change, nor does the order of inner products), which brings the scores' error
 // down to that of the spread.  What is still uncertain then: the k-th distance
 // found so far bounds the score of every row that can be among the k nearest, so
@@ -1488,6 +1492,19 @@ __global__ __launch_bounds__(1024) void bf_centre_kernel(const float *__restrict
     for (int k = 1; k < 16; ++k) sum += sum_s[k][c], n += n_s[k][c];
     centre[j] = n ? (float)(sum / n) : 0.0f;
   }
+}
+
+// One wavefront: whether rows lie around the centre rather than around the origin, told by its squared norm and the median
+// of the sample's 64 (each the largest of 16 rows).
+__global__ __launch_bounds__(64) void bf_off_centre_kernel(const float *__restrict__ centre, uint32_t d, const float *__restrict__ sample_sq,
+                                                           uint32_t *__restrict__ out) {
+  double sq = 0.0;
+  for (uint32_t j = lane_id(); j < d; j += kWave) sq += (double)centre[j] * centre[j];
+  sq = group_sum_f64<kWave>(sq);
+  const float mine = sample_sq[lane_id()];
+  int below = 0;
+  for (int i = 0; i < kWave; ++i) below += sample_sq[i] < mine || (sample_sq[i] == mine && i < lane_id()) ? 1 : 0;
+  if (below == kWave / 2) *out = sq > 0.25 * (double)mine ? 1u : 0u;
 }
 
 // One wavefront per uncertain query: its coordinates side by side with the
@@ -1771,9 +1788,11 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_uncertain, 1, 0u);
   fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->max_norm, 1, 0u);   // (each selection finds that of the centred rows)
 
-  auto select_chunk = [&](uint32_t i0, uint32_t c) -> ann_status {
+  Selection three = s;
+  three.halves = false;
+  auto select_chunk = [&](uint32_t i0, uint32_t c, const float *around) -> ann_status {
     bf_gather_uncertain_kernel<<<c, 64, 0, t.st>>>(t.q, t.d, s.kb_n, t.k, t.metric, nullptr, list + i0, t.out_dist, nullptr, qg, nullptr, nullptr);
-    const ann_status rc = select_round(t, s, qg, c, centre, false, ids, dist, places, 0);
+    const ann_status rc = select_round(t, three, qg, c, around, false, ids, dist, places, 0);
     if (rc != ANN_OK) return rc;
     bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, nullptr, nullptr, ids, dist, t.out_ids, t.out_dist, nullptr, nullptr, nullptr);
     bf_next_list_kernel<<<1, 1024, 0, t.st>>>(places, list + i0, state, other);
@@ -1813,14 +1832,24 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   };
   ann_status rc = ANN_OK;
   uint32_t n_fp32 = 0;
-  for (uint32_t pass = 0; n_list > 0 && rc == ANN_OK; ++pass) {
-    if (pass > kMaxPasses) {
+  // pass -1: three parts; 0: centred rows; then the passes with a bound
+  int pass = 0;
+  if (s.halves) {
+    uint32_t off_centre = 1;
+    bf_off_centre_kernel<<<1, 64, 0, t.st>>>(centre, t.d, s.sample_sq, &state->most_entries);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = read_words(&state->most_entries, &off_centre, 1, t.st);
+    if (e != hipSuccess) rc = hip_fail(e, "the wait for a call's centre");
+    if (off_centre == 0) pass = -1;
+  }
+  for (; n_list > 0 && rc == ANN_OK; ++pass) {
+    if (pass > (int)kMaxPasses) {
       rc = fp32_for(t, list, n_list);
       break;
     }
     for (uint64_t i0 = 0; i0 < n_list && rc == ANN_OK; i0 += m) {
       const uint32_t c = (uint32_t)(n_list - i0 < m ? n_list - i0 : m);
-      rc = pass == 0 ? select_chunk((uint32_t)i0, c) : pass_chunk((uint32_t)i0, c);
+      rc = pass <= 0 ? select_chunk((uint32_t)i0, c, pass < 0 ? nullptr : centre) : pass_chunk((uint32_t)i0, c);
     }
     if (rc != ANN_OK) break;
     uint32_t left[2] = {0, 0};
@@ -1832,6 +1861,7 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
     n_list = left[0];
     n_fp32 = left[1];
     fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_next, 1, 0u);
+    if (pass < 0) fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->max_norm, 1, 0u);
     uint32_t *was = list;
     list = other;
     other = was;

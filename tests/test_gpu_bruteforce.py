@@ -350,6 +350,38 @@ def test_two_parts_with_rows_without_a_finite_norm(H, nq, n, n_far):
     H.check_rerank(gid[some], gdist[some], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
 
 
+@pytest.mark.parametrize("spread,offset", [(3.0, 0.0), (0.0, 300.0)])
+def test_two_parts_with_norms_of_many_sizes(H, spread, offset):
+    """Most queries are uncertain with two parts: with norms spread over many orders three parts settle them, far from the
+    origin centred rows do; both cost a few times a call without such queries (20 times the centred way alone)."""
+    import time
+    import torch
+    import paper_2503_17911_amd as ann
+    n, d, nq, k = 200_000, 96, 1000, 10
+    g = torch.Generator(device=H.DEV).manual_seed(1)
+    X, Q = torch.randn(n, d, generator=g, device=H.DEV), torch.randn(nq, d, generator=g, device=H.DEV)
+    sizes = [torch.exp(spread * torch.randn(m, 1, generator=g, device=H.DEV)) for m in (n, nq)]
+    ids, dist = torch.empty((nq, k), dtype=torch.int32, device=H.DEV), torch.empty((nq, k), device=H.DEV)
+
+    def best(x, q):
+        took = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ann.ann_bruteforce_topk(x, n, d, q, nq, k, ann.L2, ids, dist, H.stream_ptr())
+            took.append(time.perf_counter() - t)
+        return min(took)
+
+    plain = best(X, Q)
+    X, Q = X * sizes[0] + offset, Q * sizes[1] + offset
+    took = best(X, Q)
+    oid, odist = oracle.bruteforce_topk(X.cpu().numpy(), Q[::40].cpu().numpy(), k, metric=oracle.L2)
+    H.check_rerank(H.as_u32(ids)[::40], dist.cpu().numpy()[::40], oid, odist.astype(np.float32), rel=1e-6)
+    if offset == 0.0:
+        assert took < 6 * plain, (took, plain)
+    print(f"plain {plain * 1e6:.0f} us, with sizes {took * 1e6:.0f} us")
+
+
 @pytest.mark.parametrize("nq,n", PARTS + [(70, 17_000), (650, 17_000)])
 def test_two_parts_of_rows_that_are_not_aligned(H, nq, n):
     import torch
