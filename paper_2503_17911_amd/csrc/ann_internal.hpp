@@ -16,8 +16,7 @@ struct LevelDev {
   uint32_t bits = 0;
   uint32_t row_bytes = 0;    // d or d/2: the bytes that carry codes
   uint32_t row_stride = 0;   // row_bytes rounded up to 16
-  uint32_t lanes_per_row = 0;  // rescore kernel: one 16-byte chunk per lane; power of two >= row_stride/16, in {8,..,64}
-  uint32_t search_lanes = 0;   // search kernel: four chunks per lane; power of two >= row_stride/64, in {1,..,16}
+  uint32_t search_lanes = 0;   // lanes to a row, four 16-byte chunks each; power of two >= row_stride/64, in {1,..,16}
   uint8_t *codes = nullptr;  // [n][row_stride]; 8-bit codes stored as (c ^ 0x80), 4-bit codes as given
   float *lo = nullptr;       // [d]
   float *delta = nullptr;    // [d]
@@ -115,9 +114,11 @@ ann_status rerank_device(const float *X, uint64_t n, uint32_t d, uint32_t metric
 
 // Kernel-layout length of one byte plane of a folded query for a level: every 16-byte chunk of
 // codes needs 16 (8-bit) or 32 (4-bit) query bytes; zero-padded to the number
-// of chunks the kernels' lanes cover.
+// of chunks the kernels' lanes cover, and to eight (rows of up to 64 bytes: four would do, but how many
+// queries ann_search_batch_static takes follows from this).
+constexpr uint32_t kMinPlaneChunks = 8;
 inline uint32_t tq_plane_for(const LevelDev &L) {
-  uint32_t chunks = L.search_lanes * 4 > L.lanes_per_row ? L.search_lanes * 4 : L.lanes_per_row;
+  const uint32_t chunks = L.search_lanes * 4 > kMinPlaneChunks ? L.search_lanes * 4 : kMinPlaneChunks;
   return chunks * (L.bits == 8 ? 16u : 32u);
 }
 

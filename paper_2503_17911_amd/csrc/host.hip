@@ -441,10 +441,8 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
       uint32_t aligned = L.row_bytes <= 16 ? 16u : L.row_bytes <= 32 ? 32u : L.row_bytes <= 64 ? 64u : (L.row_bytes + 127u) & ~127u;
       if ((aligned - L.row_bytes) * 3u <= L.row_bytes) L.row_stride = aligned;
     }
-    uint32_t chunks = L.row_stride / 16u, lpr = 8;
-    while (lpr < chunks) lpr <<= 1;
-    if (lpr > 64) return cleanup(fail(ANN_ECAPACITY, "level %u: code rows of %u bytes exceed 1024", l, L.row_bytes));
-    L.lanes_per_row = lpr;
+    const uint32_t chunks = L.row_stride / 16u;
+    if (chunks > 64) return cleanup(fail(ANN_ECAPACITY, "level %u: code rows of %u bytes exceed 1024", l, L.row_bytes));
     uint32_t sl = 1;
     while (sl * 4 < chunks) sl <<= 1;
     L.search_lanes = sl;

@@ -77,9 +77,8 @@ ann_status check_search_args(const char *fn, const ann_index *index, const float
 
 // Whether a search kernel may fold its queries itself: not the 15-bit query's two planes, and not
 // with an order, which need not name every query (all of a batch are folded, also those).
-bool search_folds(const ann_index *index, const ann_search_params *params, const Workspace &w) {
-  const LevelDev &L = index->level[0];
-  return index->query_bits != 15 && !params->query_order && w.tq_plane == L.search_lanes * 4 * (L.bits == 8 ? 16u : 32u);
+bool search_folds(const ann_index *index, const ann_search_params *params) {
+  return index->query_bits != 15 && !params->query_order;
 }
 
 // Launch of the search kernel for a batch whose folded queries are in `w`, or (q given) are put there by it
@@ -207,7 +206,7 @@ extern "C" ann_status ann_search_batch(ann_index *index, const float *q, uint32_
   WorkspaceLease lease;  // held until the search kernel is enqueued
   rc = workspace_for(index, 0, nq, st, lease);
   if (rc != ANN_OK) return rc;
-  const bool folds = !params->reuse_folded_queries && search_folds(index, params, *lease.ws);
+  const bool folds = !params->reuse_folded_queries && search_folds(index, params);
   if (params->reuse_folded_queries) {
     if (lease.ws->folded_q != q || lease.ws->folded_nq != nq)
       return fail(ANN_EINVAL, "ann_search_batch: reuse_folded_queries, but the last folding for this index on this stream was of another batch");
@@ -284,7 +283,7 @@ extern "C" ann_status ann_search_batch_static(ann_index *index, const float *q, 
   w.sum_t = reinterpret_cast<int32_t *>(base + tq_bytes + 2 * word_bytes);  // two planes of nq sums
   // the folding writes every byte the search reads (rows are written whole,
   // zero padding included), so nothing of an earlier call has to be cleared
-  const bool folds = search_folds(index, params, w);
+  const bool folds = search_folds(index, params);
   if (!folds) {
     rc = launch_query_prep_into(index, 0, q, nq, w, nullptr, nullptr, nullptr, st);
     if (rc != ANN_OK) return rc;

@@ -1060,7 +1060,7 @@ struct SearchWave {
   // at the start of a search: 100 queries on 10,000 x 128, one expansion per step 142.6 -> 139.2 us,
   // 1,000 x 960 4-bit 412.8 -> 404.9, one query 124.4 -> 123.3.
   __device__ __forceinline__ void fold(uint32_t qi) {
-    constexpr int kWords = CPL * LPR * TQW, kRounds = (kWords + kWave - 1) / kWave;
+    constexpr int kWords = (CPL * LPR > (int)kMinPlaneChunks ? CPL * LPR : (int)kMinPlaneChunks) * TQW, kRounds = (kWords + kWave - 1) / kWave;
     const float *qr = a.q + (uint64_t)qi * a.d;
     float prod[kRounds][4];
     float amax = 0.0f;

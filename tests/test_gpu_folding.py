@@ -38,6 +38,18 @@ def test_cancelling_terms(d):
     ix.close()
 
 
+def _check_launches(H, ix, Q):
+    """The search kernel alone is launched (no folding ahead of it) for small batches."""
+    import torch
+    kw = dict(mode=0, visited_kind=H.ann.VISITED_CACHE)
+    ix.search(Q, 20, **kw)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        ix.search(Q, 20, **kw)
+    names = [e.name for e in prof.events()]
+    assert any("search_small_kernel" in s for s in names), names
+    assert not any("query_prep_kernel" in s for s in names), names
+
+
 @pytest.mark.parametrize("d,bits", [(2, 8), (30, 4), (63, 8), (66, 8), (130, 4), (256, 8), (258, 8), (960, 4), (1024, 8), (2046, 4)])
 def test_folding_inside_the_search(d, bits):
     """The search kernels' own folding: rows of one to sixteen lanes, cancelling terms, a zero query, with one and
@@ -54,6 +66,7 @@ def test_folding_inside_the_search(d, bits):
     Q = (Q - (Q @ lo)[:, None] * lo / (lo @ lo)).astype(np.float32)
     Q[5] = 0.0
     ix = H.GpuIndex(X, adj, 0, [lv], oracle.L2)
+    _check_launches(H, ix, Q)
     for p in (1, 4):
         kw = dict(mode=0 if p == 1 else 1, expansions_per_step=p)
         oi, ok, od, _ = oracle.search_batch(lv, d, adj, 0, Q, 20, expansions_per_step=p)
