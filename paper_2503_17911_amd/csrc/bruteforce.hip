@@ -305,7 +305,7 @@ constexpr int kSK = 32;           // columns per chunk
 constexpr int kSB = 128;          // base rows per tile
 constexpr int kPlane = kSB * kSK * 2;   // bytes of one plane of a chunk
 constexpr uint64_t kPairBytes = 128ull << 20;   // of split rows at a time
-constexpr uint32_t kCallCounters = 6;   // of CallState
+constexpr uint32_t kCallCounters = 7;   // of CallState
 constexpr int kHitList = 96;      // entries a wavefront collects before they go to global memory
 constexpr float kFarNorm2 = 0x1.fp31f;   // two parts: rows of this squared norm and more, scaled, are left out (half precision ends at 2^16)
 constexpr uint32_t kSampleRows = 4096;   // scores one selection workgroup takes; first sample (or twice that, see ann_bruteforce_topk)
@@ -458,6 +458,7 @@ constexpr uint32_t kFarRows = 3840;   // (with 256 results they fit the 4,096 ca
 struct CallState {
   uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
   uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
+  uint32_t n_wide;        // two parts: queries whose scores would be nearer to their value with three
   uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
   uint32_t most_entries;  // of a query in the last pass over uncertain queries
   uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
@@ -1214,7 +1215,7 @@ struct CertainArgs {
   const float *q;      // [nq][d]
   const float *centre; // [d] what rows (and, L2, queries) were centred by, or NULL
   uint32_t d, kb_n, metric;
-  const CallState *state;
+  CallState *state;
   const float *sample_sq, *unscale;   // two parts (otherwise NULL): as in ScoreArgs
   float *below;        // [nq] out
 };
@@ -1288,12 +1289,14 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
     const float nx = (c.metric == ANN_L2 ? nq + __fsqrt_rn(fmaxf((float)dist, 0.0f)) : __fsqrt_rn(__uint_as_float(c.state->max_norm))) * more;
     double room = score_room(nq, nx, c.d, c.kb_n, c.metric);
     if (c.unscale) {
+      const double room3 = room;
       float most = 0.0f;
       for (int i = 0; i < 64; ++i) most = fmaxf(most, c.sample_sq[i]);
       const int e = half_exponent(most);
       room = half_room(nq, nx, c.d, c.kb_n, c.metric, ldexpf(1.0f, -e), ldexpf(c.unscale[q], e));
       // (L2: a row that was left out for its size may be as near as this one)
       if (c.metric == ANN_L2 && !(nx * nx < ldexpf(0.99f * kFarNorm2, -2 * e))) room = INFINITY;
+      if (room > room3) atomicAdd(&c.state->n_wide, 1u);
     }
     float below = (float)(dist - room);
     if (found > cap) below = -INFINITY;   // entries were lost
@@ -1453,10 +1456,12 @@ static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm
 // ---------------------------------------------------------------------------
 // Queries whose result is not certain (see bf_select_entries_kernel): vectors far
 // from the origin, where the squares cancel, or many rows at the same distance.
-// After two parts, unless the rows lie around another point than the origin, the
-// selection again with three parts: rows much smaller or larger than the sample's
-// largest lose in half precision, not in bf16.  (300,000 x 128, norms spread like exp(3 z), 2,000 queries:
-// 12.0 ms with centred rows at once, in which the small ones lose, too; 0.93 so; 1.12 with three parts only.)
+// After two parts, where these left more room than three for a quarter as many queries as are
+// uncertain, the selection again with three parts: rows much smaller or larger than the sample's
+// largest lose in half precision, not in bf16.  (300,000 x 128, norms spread like exp(3 z), 2,000
+// queries: 12.0 ms with centred rows at once, in which the small ones lose, too; 0.93 so; 1.12 with three parts
+// only.  Rows that occur 50 times are uncertain with any scores: 1M x 128, 700 queries 5.0 ms with
+// three parts first, 3.57 without; four calls of three parts 4.15.)
 // Then the whole selection with centred rows and queries (distances do not
 // change, nor does the order of inner products), which brings the scores' error
 // down to that of the spread.  What is still uncertain then: the k-th distance
@@ -1492,19 +1497,6 @@ __global__ __launch_bounds__(1024) void bf_centre_kernel(const float *__restrict
     for (int k = 1; k < 16; ++k) sum += sum_s[k][c], n += n_s[k][c];
     centre[j] = n ? (float)(sum / n) : 0.0f;
   }
-}
-
-// One wavefront: whether rows lie around the centre rather than around the origin, told by its squared norm and the median
-// of the sample's 64 (each the largest of 16 rows).
-__global__ __launch_bounds__(64) void bf_off_centre_kernel(const float *__restrict__ centre, uint32_t d, const float *__restrict__ sample_sq,
-                                                           uint32_t *__restrict__ out) {
-  double sq = 0.0;
-  for (uint32_t j = lane_id(); j < d; j += kWave) sq += (double)centre[j] * centre[j];
-  sq = group_sum_f64<kWave>(sq);
-  const float mine = sample_sq[lane_id()];
-  int below = 0;
-  for (int i = 0; i < kWave; ++i) below += sample_sq[i] < mine || (sample_sq[i] == mine && i < lane_id()) ? 1 : 0;
-  if (below == kWave / 2) *out = sq > 0.25 * (double)mine ? 1u : 0u;
 }
 
 // One wavefront per uncertain query: its coordinates side by side with the
@@ -1758,7 +1750,7 @@ static ann_status fp32_for(const Truth &t, const uint32_t *list, uint32_t m_all)
 // The uncertain queries list[0 .. n_list), `round` of them at a time in s: the
 // selection with centred rows, passes over what that leaves, and the fp32 kernel
 // for what these do.
-static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uint32_t *list, uint32_t n_list) {
+static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uint32_t *list, uint32_t n_list, uint32_t n_wide) {
   CallState *const state = s.state;
   // buffers for m queries at a time, the other lists and the centre
   uint64_t m = n_list < 2048 ? n_list : 2048;
@@ -1833,15 +1825,7 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   ann_status rc = ANN_OK;
   uint32_t n_fp32 = 0;
   // pass -1: three parts; 0: centred rows; then the passes with a bound
-  int pass = 0;
-  if (s.halves) {
-    uint32_t off_centre = 1;
-    bf_off_centre_kernel<<<1, 64, 0, t.st>>>(centre, t.d, s.sample_sq, &state->most_entries);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = read_words(&state->most_entries, &off_centre, 1, t.st);
-    if (e != hipSuccess) rc = hip_fail(e, "the wait for a call's centre");
-    if (off_centre == 0) pass = -1;
-  }
+  int pass = s.halves && n_wide >= (n_list + 3) / 4 ? -1 : 0;
   for (; n_list > 0 && rc == ANN_OK; ++pass) {
     if (pass > (int)kMaxPasses) {
       rc = fp32_for(t, list, n_list);
@@ -2019,7 +2003,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   const Truth t{x, n, d, q, k, metric, out_ids, out_dist, (uint32_t)n_cu, st};
 
   ann_status rc = ANN_OK;
-  uint32_t found[2] = {0, 0};   // uncertain queries, far rows
+  uint32_t found[3] = {0, 0, 0};   // uncertain queries, far rows, queries that three parts would leave less uncertain
   bool idle = true;
   for (;;) {
     // the counters are cleared by the first kernel of either path
@@ -2029,7 +2013,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
       rc = select_round(t, s, q + q0 * d, m, nullptr, q0 == 0, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
     }
     // (100 queries x 10,000 rows x 128, read through pinned memory and with one launch less at the start: 65.9 -> 55.9 us)
-    const hipError_t e2 = rc == ANN_OK ? read_words(&state->n_uncertain, found, 2, st) : hipStreamSynchronize(st);
+    const hipError_t e2 = rc == ANN_OK ? read_words(&state->n_uncertain, found, 3, st) : hipStreamSynchronize(st);
     if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "the wait for a call's counters");
     idle = e2 == hipSuccess;
     if (rc != ANN_OK || !s.halves || found[1] <= kFewFarRows) break;
@@ -2038,7 +2022,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   if (rc == ANN_OK && found[1] > kFarRows) {
     rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
   } else if (rc == ANN_OK) {
-    if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0]);
+    if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0], found[2]);
     if (rc == ANN_OK && found[1] > 0) rc = add_far_rows(t, nq, found[1], state);
     if (rc != ANN_OK) idle = hipStreamSynchronize(st) == hipSuccess;
   }

@@ -350,7 +350,7 @@ def test_two_parts_with_rows_without_a_finite_norm(H, nq, n, n_far):
     H.check_rerank(gid[some], gdist[some], np.flatnonzero(keep)[oid].astype(np.uint32), odist.astype(np.float32), rel=1e-6)
 
 
-@pytest.mark.parametrize("spread,offset", [(3.0, 0.0), (0.0, 300.0)])
+@pytest.mark.parametrize("spread,offset", [(3.0, 0.0), (4.0, 0.0), (0.0, 300.0)])
 def test_two_parts_with_norms_of_many_sizes(H, spread, offset):
     """Most queries are uncertain with two parts: with norms spread over many orders three parts settle them, far from the
     origin centred rows do; both cost a few times a call without such queries (20 times the centred way alone)."""
@@ -380,6 +380,25 @@ def test_two_parts_with_norms_of_many_sizes(H, spread, offset):
     if offset == 0.0:
         assert took < 6 * plain, (took, plain)
     print(f"plain {plain * 1e6:.0f} us, with sizes {took * 1e6:.0f} us")
+
+
+@pytest.mark.parametrize("nq,n", PARTS)
+@pytest.mark.parametrize("spread", [0.0, 3.0])
+def test_two_parts_with_rows_that_occur_often(H, nq, n, spread):
+    """Every row 50 times: uncertain with any scores, so that three parts are not tried (but where norms are spread as well)."""
+    import torch
+    d, k = 96, 10
+    rng = np.random.default_rng(93)
+    rows, Q = (_points(m, d, 91 + m) * np.exp(spread * rng.standard_normal((m, 1))).astype(np.float32) for m in (n // 50, nq))
+    X = np.tile(rows, (50, 1))
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        gid, gdist = H.gpu_bruteforce(X, Q, k, oracle.L2)
+    assert any("bf_score_kernel<true, 4, 1, true, 3>" in e.name for e in prof.events())   # centred
+    assert any("bf_score_kernel<true, 4, 1, false, 3>" in e.name for e in prof.events()) == (spread > 0)
+    some = np.arange(0, nq, 9)
+    oid, odist = oracle.bruteforce_topk(X, Q[some], k, metric=oracle.L2)
+    H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
+    assert (gid[some] == oid).all()   # (equal distances: the smallest ids)
 
 
 @pytest.mark.parametrize("nq,n", PARTS + [(70, 17_000), (650, 17_000)])
