@@ -305,7 +305,7 @@ constexpr int kSK = 32;           // columns per chunk
 constexpr int kSB = 128;          // base rows per tile
 constexpr int kPlane = kSB * kSK * 2;   // bytes of one plane of a chunk
 constexpr uint64_t kPairBytes = 128ull << 20;   // of split rows at a time
-constexpr uint32_t kCallCounters = 7;   // of CallState
+constexpr uint32_t kCallCounters = 8;   // of CallState
 constexpr int kHitList = 96;      // entries a wavefront collects before they go to global memory
 constexpr float kFarNorm2 = 0x1.fp31f;   // two parts: rows of this squared norm and more, scaled, are left out (half precision ends at 2^16)
 constexpr uint32_t kSampleRows = 4096;   // scores one selection workgroup takes; first sample (or twice that, see ann_bruteforce_topk)
@@ -459,6 +459,7 @@ struct CallState {
   uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
   uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
   uint32_t n_wide;        // two parts: queries whose scores would be nearer to their value with three
+  uint32_t left_out;      // two parts, L2: not 0: rows were left out for their size
   uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
   uint32_t most_entries;  // of a query in the last pass over uncertain queries
   uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
@@ -744,6 +745,8 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
             const uint32_t at = atomicAdd(&a.state->far_rows, 1u);
             if (at < kFarRows) a.state->far_row[at] = (uint32_t)r;
           }
+        } else if (PARTS == 2 && a.state != nullptr && r < a.rows && t >= far_from && t < INFINITY) {
+          a.state->left_out = 1u;
         }
       }
     }
@@ -899,7 +902,11 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
   float t = (float)(((part_s[0][tid] + part_s[1][tid]) + (part_s[2][tid] + part_s[3][tid])) + ((part_s[4][tid] + part_s[5][tid]) + (part_s[6][tid] + part_s[7][tid])));
   const bool in = at < a.rows && t < far_from;
   norm[at] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
-  if (a.metric == ANN_L2 || a.state == nullptr) return;
+  if (a.state == nullptr) return;
+  if (a.metric == ANN_L2) {
+    if (at < a.rows && t >= far_from && t < INFINITY) a.state->left_out = 1u;
+    return;
+  }
   if (at < a.rows && t >= far_from && a.list_far) {
     const uint32_t n = atomicAdd(&a.state->far_rows, 1u);
     if (n < kFarRows) a.state->far_row[n] = (uint32_t)r;
@@ -1286,22 +1293,24 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
     // (norms in fp32, rounded up: one thread computes this while the others are done)
     const float more = 1.0f + 0x1p-20f, nq = __fsqrt_rn((float)sq) * more;
     const double value = unorder_f32((uint32_t)(out >> 32)), dist = c.metric == ANN_L2 ? sq + value : value - along;
-    const float nx = (c.metric == ANN_L2 ? nq + __fsqrt_rn(fmaxf((float)dist, 0.0f)) : __fsqrt_rn(__uint_as_float(c.state->max_norm))) * more;
+    float nx = (c.metric == ANN_L2 ? nq + __fsqrt_rn(fmaxf((float)dist, 0.0f)) : __fsqrt_rn(__uint_as_float(c.state->max_norm))) * more;
     double room = score_room(nq, nx, c.d, c.kb_n, c.metric);
     if (c.unscale) {
       const double room3 = room;
       float most = 0.0f;
       for (int i = 0; i < 64; ++i) most = fmaxf(most, c.sample_sq[i]);
       const int e = half_exponent(most);
+      // (L2: rows that were left out for their size may be as near as this one; where there are none, no row is larger than that)
+      const bool beyond = c.metric == ANN_L2 && !(nx * nx < ldexpf(0.99f * kFarNorm2, -2 * e));
+      if (beyond && !c.state->left_out) nx = __fsqrt_rn(ldexpf(1.01f * kFarNorm2, -2 * e));
       room = half_room(nq, nx, c.d, c.kb_n, c.metric, ldexpf(1.0f, -e), ldexpf(c.unscale[q], e));
-      // (L2: a row that was left out for its size may be as near as this one)
-      if (c.metric == ANN_L2 && !(nx * nx < ldexpf(0.99f * kFarNorm2, -2 * e))) room = INFINITY;
+      if (beyond && c.state->left_out) room = INFINITY;
       if (room > room3) atomicAdd(&c.state->n_wide, 1u);
     }
     float below = (float)(dist - room);
     if (found > cap) below = -INFINITY;   // entries were lost
-    // (two parts, L2: rows left out for their size were not counted)
-    if ((uint32_t)(out >> 32) >= kMaxScore) below = c.unscale && c.metric == ANN_L2 ? -INFINITY : INFINITY;
+    // (rows left out for their size were not counted)
+    if ((uint32_t)(out >> 32) >= kMaxScore) below = c.unscale && c.state->left_out ? -INFINITY : INFINITY;
     // (two parts: from here on the query's squared norm in fp32, which its scale comes from, may be infinite and its scores no numbers)
     if (c.unscale && sq >= 0x1p127) below = -INFINITY;
     if (sq != sq) below = INFINITY;
@@ -1461,7 +1470,7 @@ static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm
 // largest lose in half precision, not in bf16.  (300,000 x 128, norms spread like exp(3 z), 2,000
 // queries: 12.0 ms with centred rows at once, in which the small ones lose, too; 0.93 so; 1.12 with three parts
 // only.  Rows that occur 50 times are uncertain with any scores: 1M x 128, 700 queries 5.0 ms with
-// three parts first, 3.57 without; four calls of three parts 4.15.)
+// three parts first, 3.57 without.)
 // Then the whole selection with centred rows and queries (distances do not
 // change, nor does the order of inner products), which brings the scores' error
 // down to that of the spread.  What is still uncertain then: the k-th distance

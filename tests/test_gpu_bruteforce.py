@@ -401,6 +401,23 @@ def test_two_parts_with_rows_that_occur_often(H, nq, n, spread):
     assert (gid[some] == oid).all()   # (equal distances: the smallest ids)
 
 
+@pytest.mark.parametrize("nq,n", PARTS)
+def test_two_parts_with_queries_larger_than_the_rows(H, nq, n):
+    """L2: certain at once where no row is left out for its size, however large the bound on a near row's norm is."""
+    import torch
+    d, k = 80, 10
+    X, Q = _points(n, d, 94), _points(nq, d, 95) * np.float32(100.0)
+    for far in (False, True):
+        if far:   # one row near some of the queries
+            X[np.setdiff1d(np.arange(n), _sampled_rows(n, 1024))[n // 3]] = Q[0]
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+            gid, gdist = H.gpu_bruteforce(X, Q, k, oracle.L2)
+        assert any("bf_gather_uncertain_kernel" in e.name for e in prof.events()) == far
+        some = np.arange(0, nq, 9)
+        oid, odist = oracle.bruteforce_topk(X, Q[some], k, metric=oracle.L2)
+        H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
+
+
 @pytest.mark.parametrize("nq,n", PARTS + [(70, 17_000), (650, 17_000)])
 def test_two_parts_of_rows_that_are_not_aligned(H, nq, n):
     import torch
