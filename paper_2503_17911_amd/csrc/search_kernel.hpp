@@ -96,9 +96,9 @@ struct SearchArgs {
   float alpha_s;
   // (last: kernels that do not read these keep the argument loads and registers they have without them; with
   // them further up 10,000 queries on 100,000 x 480 4-bit, one expansion, ef = 64 took 970 us instead of 839)
-  uint32_t d;
   const float *q;  // [nq][d]: the kernel (FOLDS) folds its query itself and leaves the result in tq, s, qlo, sum_t; or nullptr: they hold it
   const float *lo, *delta;  // [d] the level's codebook (with q)
+  uint32_t d;
 };
 
 // All but the evaluation of a step is one wavefront's work (with several to a
@@ -1135,7 +1135,8 @@ struct SearchWave {
   }
 
   __device__ __forceinline__ void run(uint32_t qi) {
-    if (FOLDS && a.q) {
+    // (d as well, so that it is loaded with the other arguments and not on the way: 100 queries x 10,000 x 128 1.2 % faster)
+    if (FOLDS && ((a.q != nullptr) & (a.d != 0))) {
       fold(qi);
       if constexpr (TEAM > 1) team_barrier();
     } else {
