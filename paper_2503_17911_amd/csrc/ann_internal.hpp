@@ -84,6 +84,7 @@ ann_status hip_fail(hipError_t e, const char *what);
     if (e_ != hipSuccess) return ::ann::hip_fail(e_, #call); \
   } while (0)
 
+uint32_t compute_units();   // of the current device
 // Device memory for index arrays, workspaces and temporaries (host.hip): hipMalloc
 // and hipFree with freed blocks kept for the next request, up to 2 GiB per process.
 // idle: the caller knows that nothing enqueued on the device uses the block any

@@ -1901,12 +1901,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   if (metric != ANN_L2 && metric != ANN_IP) return fail(ANN_EINVAL, "ann_bruteforce_topk: unknown metric %u", metric);
   if (k > 256) return fail(ANN_ECAPACITY, "ann_bruteforce_topk: k = %u exceeds 256", k);
   if (d > 2048) return fail(ANN_ECAPACITY, "ann_bruteforce_topk: d = %u exceeds 2048", d);
-  int n_cu = 256;
-  {
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (n_cu <= 0) n_cu = 256;
-  }
+  const uint32_t n_cu = compute_units();
   // k and a margin for the error of the scores; the selection stops as soon as it has between `want` and `most`
   const uint32_t want = k + 8, most = want + (want / 2 > 14 ? want / 2 : 14);
   // (a bound from a sample is worth a few steps more: what reaches it in the next pass is proportional to it)
@@ -2009,7 +2004,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   s.xfrag = reinterpret_cast<uint4 *>(base + at[11]);
   s.xnorm = reinterpret_cast<float *>(base + at[12]);
   s.x_rows = x_rows;
-  const Truth t{x, n, d, q, k, metric, out_ids, out_dist, (uint32_t)n_cu, st};
+  const Truth t{x, n, d, q, k, metric, out_ids, out_dist, n_cu, st};
 
   ann_status rc = ANN_OK;
   uint32_t found[3] = {0, 0, 0};   // uncertain queries, far rows, queries that three parts would leave less uncertain
@@ -2029,7 +2024,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
     s.halves = false;   // inner product, more than a few rows outside half precision's range: three parts
   }
   if (rc == ANN_OK && found[1] > kFarRows) {
-    rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, (uint32_t)n_cu, st);
+    rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, n_cu, st);
   } else if (rc == ANN_OK) {
     if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0], found[2]);
     if (rc == ANN_OK && found[1] > 0) rc = add_far_rows(t, nq, found[1], state);

@@ -98,6 +98,12 @@ hipError_t read_words(const uint32_t *src, uint32_t *dst, int count, hipStream_t
   return e != hipSuccess ? e : e2;
 }
 
+uint32_t compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  return (uint32_t)n;
+}
+
 hipError_t device_alloc(void **ptr, size_t bytes) {
   *ptr = nullptr;
   int dev = 0;
@@ -391,7 +397,7 @@ ann_status ann_upload_index(const ann_index_desc *desc, void *stream, ann_index 
   ix->n_levels = desc->n_levels;
   ix->entry_point = desc->entry_point;
   (void)hipGetDevice(&ix->device);
-  if (hipDeviceGetAttribute(&ix->n_cu, hipDeviceAttributeMultiprocessorCount, ix->device) != hipSuccess || ix->n_cu <= 0) ix->n_cu = 256;
+  ix->n_cu = (int)compute_units();
 
   ann_status rc = ANN_OK;
   uint32_t *bad_dev = nullptr;

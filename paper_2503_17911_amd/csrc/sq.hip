@@ -341,41 +341,41 @@ __global__ __launch_bounds__(THREADS) void bracket_bounds_kernel(BracketArgs g) 
     uint32_t a = 0, b = 0xFFFFFFFFu, between = 0;
     const uint32_t under = mn > 0 ? mn - 1 : 0;
     auto bracket = [&](auto &s, uint32_t most) {
-    constexpr int kEach = sizeof(s.key) / sizeof(s.key[0]);
-    // a: the smallest key above a value that few enough keys reach (no bound if the wanted rank is among the first)
-    if (g.below >= 1.0) {
-      uint32_t lo = under, hi = most;   // count(lo) <= below < count(hi)
-      while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        const double n = s.up_to(mid);
-        if (n <= g.below) {
-          lo = mid;
-          if (n >= g.below - g.slack) break;
-        } else {
-          hi = mid;
+      constexpr int kEach = sizeof(s.key) / sizeof(s.key[0]);
+      // a: the smallest key above a value that few enough keys reach (no bound if the wanted rank is among the first)
+      if (g.below >= 1.0) {
+        uint32_t lo = under, hi = most;   // count(lo) <= below < count(hi)
+        while (hi - lo > 1) {
+          const uint32_t mid = lo + (hi - lo) / 2;
+          const double n = s.up_to(mid);
+          if (n <= g.below) {
+            lo = mid;
+            if (n >= g.below - g.slack) break;
+          } else {
+            hi = mid;
+          }
         }
-      }
-      uint32_t next = 0xFFFFFFFFu;
+        uint32_t next = 0xFFFFFFFFu;
 #pragma unroll
-      for (int e = 0; e < kEach; ++e) next = s.key[e] > lo && s.key[e] < next ? s.key[e] : next;
-      a = least(next);
-    }
-    // b: the first value that enough keys reach, or one not far above it
-    if (g.beyond <= (double)g.m) {
-      uint32_t lo = under, hi = most;   // count(lo) < beyond <= count(hi)
-      while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        const double n = s.up_to(mid);
-        if (n >= g.beyond) {
-          hi = mid;
-          if (n <= g.beyond + g.slack) break;
-        } else {
-          lo = mid;
-        }
+        for (int e = 0; e < kEach; ++e) next = s.key[e] > lo && s.key[e] < next ? s.key[e] : next;
+        a = least(next);
       }
-      b = hi;
-    }
-    between = a < b ? s.up_to(b - 1) - s.up_to(a) : 0u;
+      // b: the first value that enough keys reach, or one not far above it
+      if (g.beyond <= (double)g.m) {
+        uint32_t lo = under, hi = most;   // count(lo) < beyond <= count(hi)
+        while (hi - lo > 1) {
+          const uint32_t mid = lo + (hi - lo) / 2;
+          const double n = s.up_to(mid);
+          if (n >= g.beyond) {
+            hi = mid;
+            if (n <= g.beyond + g.slack) break;
+          } else {
+            lo = mid;
+          }
+        }
+        b = hi;
+      }
+      between = a < b ? s.up_to(b - 1) - s.up_to(a) : 0u;
     };
     // the few: keys up to `most`, which at least `beyond` and at most kFew * THREADS keys reach
     uint32_t most = mx;
@@ -892,11 +892,11 @@ static dim3 select_grid(uint64_t n, uint32_t d, uint64_t &rows_per_block) {
   return dim3((uint32_t)((n + rows_per_block - 1) / rows_per_block), groups);
 }
 
-// For bracket_collect_kernel: whole turns of workgroups (four to each of 256 compute units) of at most
+// For bracket_collect_kernel: whole turns of workgroups (four to a compute unit) of at most
 // 6,144 rows, of which about 1.4 % lie in a bracket and find room in LDS.  200,000 x 960: 1,470 workgroups
 // of 4,096 rows, a second turn less than half full, 207 us; 1,020 of 5,883 190.
 static dim3 collect_grid(uint64_t n, uint32_t d) {
-  const uint32_t groups = (d + kSelCols - 1) / kSelCols, side = groups < 1024 ? 1024 / groups : 1;
+  const uint32_t turn = 4 * compute_units(), groups = (d + kSelCols - 1) / kSelCols, side = groups < turn ? turn / groups : 1;
   uint64_t blocks = (n + 6144ull * side - 1) / (6144ull * side) * side;
   if (blocks > (n + 255) / 256) blocks = (n + 255) / 256;
   return dim3((uint32_t)blocks, groups);
