@@ -246,6 +246,9 @@ ann_status ann_sq_train(const float *x, uint64_t n, uint32_t d, uint32_t bits, f
  * and the upper end its element of rank n - 1 - k (exact order statistics);
  * coverage in (0.5, 1], 0.99 being the paper's choice, 1 the same as
  * ann_sq_train.  ann_sq_encode clamps values outside the range.
+ *   From 32,768 rows on the temporary holds a sample of the rows and lists of
+ * values: 100 MB at 200,000 x 960, 290 MB at 1M x 960 (without room for it
+ * the call takes four passes over x and a small one).
  */
 ann_status ann_sq_train_truncated(const float *x, uint64_t n, uint32_t d, uint32_t bits, double coverage,
                                   float *lo, float *delta, void *stream);
@@ -269,8 +272,9 @@ ann_status ann_free_index(ann_index *index); /* synchronises the device; NULL is
  * request of this library (the driver clears freed memory before it hands it out
  * again, which takes longer than building an index): up to 2 GiB and 64 blocks
  * per process, given back oldest first beyond that and altogether when an
- * allocation of this library fails.  ann_trim_memory gives all of it back now,
- * for other allocators in the process.  From any thread; never fails.
+ * allocation of this library fails; and up to 16 pieces of 64 bytes of pinned
+ * host memory, through which counters are read.  ann_trim_memory gives all of it
+ * back now, for other allocators in the process.  From any thread; never fails.
  */
 ann_status ann_trim_memory(void);
 
@@ -397,7 +401,7 @@ ann_status ann_search_batch(ann_index *index, const float *q, uint32_t nq, const
  *   Limit: 256-byte rounded nq * folded_row + 4 * (4 * nq) bytes must fit, where
  *   folded_row is 16 bytes (8-bit codes) or 32 bytes (4-bit codes) per 16-byte
  *   chunk of a code row, for at least the chunks the search kernel's lanes
- *   cover (twice that with ANN_DESC_QUERY_15BIT): 128 bytes for d = 128 at 8
+ *   cover and at least eight (twice that with ANN_DESC_QUERY_15BIT): 128 bytes for d = 128 at 8
  *   bits (about 58,000 queries), 1,024 bytes for d = 960 at 4 bits (about
  *   8,000).  Beyond it: ANN_ECAPACITY,
  *   nothing launched.

@@ -4,8 +4,8 @@
 // Scores that only select candidates: -2 q.x + |x|^2 (or -q.x) from a dense
 // contraction on the matrix cores, every fp32 value split into three bf16
 // parts and six of the nine partial products accumulated in fp32, or into two
-// half-precision parts and three of the four products; neither loses more than
-// fp32 products do (see bf_score_kernel).  Between `want` = k + 8 and
+// half-precision parts and three of the four products; for vectors of like
+// sizes neither loses more than fp32 products do (see bf_score_kernel).  Between `want` = k + 8 and
 // `most`, half as many again, of a query's best rows are re-evaluated in fp64 by
 // the rerank kernel and sorted by (distance, id).
 //
@@ -30,8 +30,8 @@
 //
 // Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
 // kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
-// k = 10: 25.8 -> 8.0 ms (15.5 with three parts); 2,000 x 200,000 x 768, k = 100:
-// 13.9 -> 2.45 ms (3.8); 100 x 10,000 x 128, k = 10: 2.56 -> 0.07 ms.
+// k = 10: 25.8 -> 7.7 to 8.3 ms, by the card (15.5 with three parts); 2,000 x 200,000
+// x 768, k = 100: 13.9 -> 2.27 to 2.41 (3.8); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
 #include <math.h>
 
 #include "ann_internal.hpp"
@@ -269,8 +269,13 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 //   inner products   128 1.4e-7 / 1.0e-7, 960 3.1e-7 / 2.6e-7; centred normal 128 1.6e-7 /
 //                    1.4e-7, 48 9.1e-8 / 1.04e-7, 24 6.0e-8 / 9.2e-8 (there three are taken)
 //   offset of 1,000 spreads, L2   128 2.2e-7 / 1.8e-7, 960 8.7e-7 / 5.3e-7
-// Of the lanes' scores this one is smaller for each of nine distributions of ordinary size; for norms spread
-// over four orders of magnitude it is up to 10 % larger at 65 to 80 columns.
+// The format holds 22 to 23 bits of a float's 24, so two parts are not the more exact ones everywhere: of
+// mixtures with 8 to 100 centres and 65 to 128 columns the scores of a query's 50 nearest rows err 15 to 28 %
+// less than with three, all scores together between 25 % less and (65 columns, inner product) 4 % more; inner
+// products of centred normal vectors 10 % more at 65 columns, 5 % at 96 and less from 128 on; of norms spread
+// over four orders of magnitude 6 to 28 % more up to 256 columns, rows below 2^-14 of the largest far more
+// (the arithmetic in numpy, a rounding per instruction).  Scores only select; what an error could
+// change is found out from half_room() and settled.
 //
 // A workgroup of four wavefronts takes QT queries x 128 base rows per tile.
 // The queries come split, in the order the matrix instruction wants them
@@ -921,10 +926,11 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
 // x 64: eight accumulators, 128 registers, so that six products of 16 columns come to two
 // LDS reads of rows and one global read of queries.  No vector instruction
 // stands between the matrix instructions; two wavefronts share a SIMD, and one's
-// end of a tile falls into the other's products.  10,000 x 262,144 x 128: 1.84 ms = 365
-// TFLOP/s of fp32 work = 1,095 on the matrix cores, which are busy 57 % at the
-// 1.84 GHz the card then runs at (bf_score_kernel with two parts: 2.68 ms; with three:
-// 3.7).  128 queries per tile: 7 % slower; first products onto a constant zero instead
+// end of a tile falls into the other's products.  10,000 x 262,144 x 128: 1.75 to 2.0
+// ms, by the clock: 3.27 M cycles each time, at 1.86 down to 1.63 GHz as the card warms up,
+// the matrix cores busy in 60 % of them = 383 to 336 TFLOP/s of fp32 work (bf_score_kernel with two parts: 2.68
+// ms; with three: 3.7).  The rate is the same at 768 columns, so the loop over chunks is what leaves the
+// rest idle, not the end of a tile.  128 queries per tile: 7 % slower; first products onto a constant zero instead
 // of cleared registers and the rows' parts requested one block ahead: 1.5 %.
 constexpr int kPairQueries = 256;
 __global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
@@ -1942,7 +1948,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   if (round < 128) round = 128;
   if (round > nq) round = nq;
   // Two parts where products take the time (up to 64 queries a call reads rows, few rows are a matter of
-  // launches) and where they lose no more than three: from 65 columns on, see bf_score_kernel.  The rows are
+  // launches) and where near rows' scores lose no more than with three: from 65 columns on, see bf_score_kernel.  The rows are
   // split ahead where that costs less than it saves, which is a question of the queries and, since the splitting
   // moves every row twice, of the columns.  Three parts / two / two, split ahead: 1M x 128, 512 queries 918 /
   // 685 / 739 us, 768 1,397 / 1,011 / 927, 10,000 15,580 / 10,890 / 7,980; 200,000 x 960, 1,000 queries 2,254 /
