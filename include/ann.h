@@ -178,7 +178,10 @@ typedef struct {
  *                 on V itself: with m_s below the degree the table is used and
  *                 the result is the sequential one only for queries that report
  *                 0 rebuilds in out_counts.  ANN_VISITED_AUTO: the cache, or the
- *                 table (8192 slots by default) when m_s is active.
+ *                 table (8192 slots by default) when m_s is active; with one
+ *                 expansion per step and visited_slots = 0 a bit per node
+ *                 (complete, never rebuilt) where that is faster: base sets whose
+ *                 bits fit in LDS, for batches that are then resident at once.
  *   alpha_s, m_s  the search-time edge filter of Algorithm 1 (Section 4.3): an
  *                 edge is followed only if its label <= alpha_s, and at most
  *                 m_s unvisited neighbours are taken per expansion, in stored

@@ -1,6 +1,6 @@
 // Host entry point of the batched graph search: argument checks, choice of the
 // visited set and of the kernel family, launch (kernels: search_kernel.hpp).
-#include "search_kernel.hpp"
+#include "search_chain.hpp"
 
 
 #include <mutex>
@@ -9,10 +9,13 @@ using namespace ann;
 
 namespace {
 
+constexpr size_t kChainLds = 160 << 10;   // a compute unit's
+
 // What the argument checks settle before anything is launched.
 struct SearchPlan {
   uint32_t p = 1, vis_log2 = 0;
   bool cache = false, wide = false;
+  bool any_set = false;   // how the visited set is kept is the library's choice
 };
 
 ann_status check_search_args(const char *fn, const ann_index *index, const float *q, uint32_t nq,
@@ -72,6 +75,7 @@ ann_status check_search_args(const char *fn, const ann_index *index, const float
   plan.vis_log2 = vis_log2;
   plan.cache = cache;
   plan.wide = wide;
+  plan.any_set = params->visited_kind == ANN_VISITED_AUTO && params->visited_slots == 0;
   return ANN_OK;
 }
 
@@ -163,6 +167,27 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
       a.q = q;
       return team == 4 ? launch_search_team4(a, L.bits, L.search_lanes, m, wide_step, st)
                        : launch_search_team2(a, L.bits, L.search_lanes, m, wide_step, st);
+    }
+  }
+  if (!multi && plan.any_set && index->n <= kChainNodes && !a.prs_codes && !a.q15) {
+    // One expansion per step, the visited set a bit per node: if all queries are then resident at once.  Beyond that
+    // the kernels with a cache of the visited nodes hold more queries (before / this one, 128-byte rows, ef = 128: 100,000
+    // nodes (10 queries to a compute unit) 2,500 queries 356 / 254 us, 6,000 459 / 539; 300,000 (4) 1,000 492 / 300, 2,500
+    // 500 / 619; 480-byte rows, 60,000 nodes 2,000 327 / 303, 2,500 340 / 351).  Rows of 16 lanes: four to a compute
+    // unit (960 bytes: 1,000 448 / 373, 1,500 463 / 496: half of what a wrong guess requests is never used, and rows
+    // that long are bound by what is read).
+    a.vis_words = (uint32_t)((index->n + 127) / 128) * 4;
+    const size_t smem = chain_smem_bytes(m, a.vis_words, w.tq_stride);
+    const uint32_t by_lds = smem <= kChainLds ? (uint32_t)(128 / ((smem + 1279) / 1280)) : 0u, n_cu = (uint32_t)index->n_cu;
+    const uint32_t by_waves = L.search_lanes <= 8 ? 4u * (uint32_t)chain_waves((int)L.search_lanes, m) : 4u;
+    uint32_t most = n_cu * (by_lds < by_waves ? by_lds : by_waves);
+    // With the cap the other choice is a complete table of 32 KB, slower for every batch (10,000 queries, 300,000 x 128,
+    // ef = 100: 3,160 / 1,831 us, 600,000 x 96: 2,296 / 2,221) unless a query's bits fill the compute unit (1M x 64: 500
+    // queries 410 / 330, 1,000 446 / 535).
+    if (a.m_s < a.degree) most = by_lds >= 2 ? nq : 2 * n_cu * by_lds;
+    if (nq <= most) {
+      a.q = q;
+      return a.filtered ? launch_search_chain_filtered(a, L.bits, L.search_lanes, m, st) : launch_search_chain(a, L.bits, L.search_lanes, m, st);
     }
   }
   // One expansion per step: with 16 queries or fewer to a compute unit the kernel

@@ -1,0 +1,8 @@
+// One-expansion search kernels for small batches (see search_chain.hpp).
+#include "search_chain.hpp"
+
+namespace ann {
+ann_status launch_search_chain(const SearchArgs &a, uint32_t bits, uint32_t lpr, int m, hipStream_t st) {
+  return bits == 8 ? launch_chain<8, false>(a, lpr, m, st) : launch_chain<4, false>(a, lpr, m, st);
+}
+}  // namespace ann

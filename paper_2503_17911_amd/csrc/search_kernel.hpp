@@ -99,6 +99,7 @@ struct SearchArgs {
   const float *q;  // [nq][d]: the kernel (FOLDS) folds its query itself and leaves the result in tq, s, qlo, sum_t; or nullptr: they hold it
   const float *lo, *delta;  // [d] the level's codebook (with q)
   uint32_t d;
+  uint32_t vis_words;  // search_chain_kernel: words of the visited set
 };
 
 // All but the evaluation of a step is one wavefront's work (with several to a
@@ -1134,19 +1135,8 @@ struct SearchWave {
     load_query_part(tql);
   }
 
-  __device__ __forceinline__ void run(uint32_t qi) {
-    // (d as well, so that it is loaded with the other arguments and not on the way: 100 queries x 10,000 x 128 1.2 % faster)
-    if (FOLDS && ((a.q != nullptr) & (a.d != 0))) {
-      fold(qi);
-      if constexpr (TEAM > 1) team_barrier();
-    } else {
-      if constexpr (!QREG) {   // the folded query goes to LDS: it is read again for every group of rows
-        const int *src = reinterpret_cast<const int *>(a.tq + (uint64_t)qi * a.tq_stride);
-        int *dst = const_cast<int *>(tql);
-        for (uint32_t i = lane; i < a.tq_stride / 4; i += kWave) dst[i] = src[i];
-      }
-      load_query_terms(qi);
-    }
+  // The query's pool size; the empty pool.
+  __device__ __forceinline__ void start_pool(uint32_t qi) {
     ef_q = (int)a.ef;
     if (a.ef_per_query) {
       const uint32_t e = a.ef_per_query[qi];
@@ -1160,6 +1150,22 @@ struct SearchWave {
     worst = ~0ull;
 #pragma unroll
     for (int r = 0; r < M; ++r) mbuf[r * kWave + lane] = ~0ull;  // the empty pool, in order
+  }
+
+  __device__ __forceinline__ void run(uint32_t qi) {
+    // (d as well, so that it is loaded with the other arguments and not on the way: 100 queries x 10,000 x 128 1.2 % faster)
+    if (FOLDS && ((a.q != nullptr) & (a.d != 0))) {
+      fold(qi);
+      if constexpr (TEAM > 1) team_barrier();
+    } else {
+      if constexpr (!QREG) {   // the folded query goes to LDS: it is read again for every group of rows
+        const int *src = reinterpret_cast<const int *>(a.tq + (uint64_t)qi * a.tq_stride);
+        int *dst = const_cast<int *>(tql);
+        for (uint32_t i = lane; i < a.tq_stride / 4; i += kWave) dst[i] = src[i];
+      }
+      load_query_terms(qi);
+    }
+    start_pool(qi);
     clear_table();
     wave_sync();
 
@@ -1352,6 +1358,11 @@ struct SearchWave {
       team_barrier();
     }
 
+    write_results(qi);
+  }
+
+  // The pool and the counts of a finished search.
+  __device__ __forceinline__ void write_results(uint32_t qi) {
     // results (pool index r*64 + lane: coalesced)
     int kept = 0;
 #pragma unroll
