@@ -12,7 +12,7 @@ CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 LIBDIR = PKG / "lib"
 LIB = LIBDIR / "libann_gfx950.so"
-SOURCES = ["host.hip", "sq.hip", "search.hip", "search_fast.hip", "search_general.hip", "search_fast_wide.hip", "search_general_wide.hip", "search_filtered.hip", "search_filtered_wide.hip", "search_small.hip", "search_chain.hip", "search_chain_filtered.hip", "search_team4.hip", "search_team2.hip", "rerank.hip", "bruteforce.hip", "entry.hip", "schedule.hip"]
+SOURCES = ["host.hip", "sq.hip", "search.hip", "search_fast.hip", "search_general.hip", "search_fast_wide.hip", "search_general_wide.hip", "search_filtered.hip", "search_filtered_wide.hip", "search_small.hip", "search_chain.hip", "search_chain_filtered.hip", "search_relay.hip", "search_relay_wide.hip", "search_team4.hip", "search_team2.hip", "rerank.hip", "bruteforce.hip", "entry.hip", "schedule.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -ffp-contract=off: roundings are part of the results that must match a
 # reference bit for bit; fused multiply-adds are written explicitly (fmaf).

@@ -1,6 +1,7 @@
 // Host entry point of the batched graph search: argument checks, choice of the
 // visited set and of the kernel family, launch (kernels: search_kernel.hpp).
 #include "search_chain.hpp"
+#include "search_relay.hpp"
 
 
 #include <mutex>
@@ -151,6 +152,26 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
   // FAST multi-expansion kernels: the staging area (64 m entries, at least 32 per expansion) must hold a step's ids
   const bool ids_fit = index->degree <= 32 || 64 * m >= (int)(64 * p_built);
   const bool fast = packed && !a.filtered && !a.prs_codes && !a.q15 && (!multi || (ids_fit && p == p_built));
+  // (offsets of code rows are 32-bit in this kernel)
+  if (fast && multi && index->n * L.row_stride < (1ull << 32)) {
+    // Up to two queries to a compute unit: five wavefronts per query, one of which keeps the pool.  512 queries, four
+    // wavefronts of search_team_kernel / this one: 1M x 128, ef = 128 (the cache: a query's bits take a compute unit) 328 / 272
+    // us; 100,000 x 100, ef = 200 (bits) 163 / 108; 100,000 x 960 4-bit, ef = 256 249 / 218; 60,000 x 960 8-bit 168 / 153.
+    const bool by_slot = relay_by_slot(L.search_lanes, a.degree);
+    auto resident = [&](uint32_t words) {
+      const size_t smem = relay_smem_bytes(m, (int)p_built, by_slot, words, w.tq_stride);
+      const uint32_t by_lds = smem <= kChainLds ? (uint32_t)(128 / ((smem + 1279) / 1280)) : 0u, most = by_lds < kRelayQueries ? by_lds : kRelayQueries;
+      return nq <= (uint32_t)index->n_cu * most;
+    };
+    const uint64_t bit_words = ((index->n + 127) / 128) * 4;
+    const bool bits = plan.any_set && bit_words * 4 < kChainLds && resident((uint32_t)bit_words);
+    a.vis_words = bits ? (uint32_t)bit_words : 1u << vis_log2;
+    if (resident(a.vis_words)) {
+      a.vis_cache = bits ? 0u : 1u;
+      a.q = q;
+      return launch_search_relay(a, L.bits, L.search_lanes, m, wide_step, st);
+    }
+  }
   if (fast && multi) {
     // Small batches: four or two wavefronts per query as long as all queries are
     // then resident at once (registers and LDS blocks of 1,280 bytes, 128 to a
