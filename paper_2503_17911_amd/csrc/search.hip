@@ -154,14 +154,15 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
   const bool fast = packed && !a.filtered && !a.prs_codes && !a.q15 && (!multi || (ids_fit && p == p_built));
   // (offsets of code rows are 32-bit in this kernel)
   if (fast && multi && index->n * L.row_stride < (1ull << 32)) {
-    // Up to two queries to a compute unit: five wavefronts per query, one of which keeps the pool.  512 queries, four
-    // wavefronts of search_team_kernel / this one: 1M x 128, ef = 128 (the cache: a query's bits take a compute unit) 328 / 272
-    // us; 100,000 x 100, ef = 200 (bits) 163 / 108; 100,000 x 960 4-bit, ef = 256 249 / 218; 60,000 x 960 8-bit 168 / 153.
+    // Up to two or three queries to a compute unit: five wavefronts per query, one of which keeps the pool.  Four wavefronts
+    // of search_team_kernel / this one: 768 queries on 1M x 128, ef = 128 (the cache: a query's bits take a compute unit) 331 / 274
+    // us, 100,000 x 100, ef = 200 (bits) 181 / 123, 60,000 x 480, ef = 256 224 / 204; 512 on 100,000 x 960 4-bit, ef = 256
+    // 249 / 218, on 60,000 x 960 8-bit 168 / 153.
     const bool by_slot = relay_by_slot(L.search_lanes, a.degree);
     auto resident = [&](uint32_t words) {
       const size_t smem = relay_smem_bytes(m, (int)p_built, by_slot, words, w.tq_stride);
-      const uint32_t by_lds = smem <= kChainLds ? (uint32_t)(128 / ((smem + 1279) / 1280)) : 0u, most = by_lds < kRelayQueries ? by_lds : kRelayQueries;
-      return nq <= (uint32_t)index->n_cu * most;
+      const uint32_t by_lds = smem <= kChainLds ? (uint32_t)(128 / ((smem + 1279) / 1280)) : 0u, by_waves = relay_queries((int)L.bits, (int)L.search_lanes, m);
+      return nq <= (uint32_t)index->n_cu * (by_lds < by_waves ? by_lds : by_waves);
     };
     const uint64_t bit_words = ((index->n + 127) / 128) * 4;
     const bool bits = plan.any_set && bit_words * 4 < kChainLds && resident((uint32_t)bit_words);

@@ -30,10 +30,11 @@
 namespace ann {
 
 constexpr int kRelayWorkers = 4;
-// Wavefronts per SIMD the kernels are compiled for (128 registers).  Two queries to a compute unit: of a query's five
-// wavefronts two are on the first SIMD.
-constexpr int kRelayWaves = 4;
-constexpr uint32_t kRelayQueries = 2;
+// Wavefronts per SIMD a kernel is compiled for (five: 96 registers; four: 128), and queries to a compute unit: of a
+// query's five wavefronts two are on the first SIMD.  Long 4-bit rows and rows of sixteen lanes spill with 96 (1,000 x
+// 960 4-bit, ef = 256: 256 queries 184 -> 319 us).
+__host__ __device__ constexpr int relay_waves(int bits, int lpr, int m) { return (bits == 8 ? lpr <= 8 : lpr <= 4 && m < 8) ? 5 : 4; }
+__host__ __device__ constexpr uint32_t relay_queries(int bits, int lpr, int m) { return relay_waves(bits, lpr, m) == 5 ? 3u : 2u; }
 
 // Whether every slot of an adjacency row has lanes of its own: no list of the unvisited neighbours then.
 __host__ __device__ constexpr bool relay_by_slot(uint32_t lpr, uint32_t degree) { return degree * lpr <= 64u; }
@@ -457,7 +458,7 @@ struct SearchRelay : SearchWave<BITS, LPR, M, 1, true, 1, true, false, true> {
 };
 
 template <int BITS, int LPR, int M, int P, bool BY_SLOT>
-__global__ __launch_bounds__(64 * (1 + kRelayWorkers)) __attribute__((amdgpu_waves_per_eu(kRelayWaves))) void search_relay_kernel(SearchArgs args) {
+__global__ __launch_bounds__(64 * (1 + kRelayWorkers)) __attribute__((amdgpu_waves_per_eu(relay_waves(BITS, LPR, M)))) void search_relay_kernel(SearchArgs args) {
   extern __shared__ uint64_t smem[];
   if (blockIdx.x >= args.nq) return;
   const uint32_t qi = args.order ? args.order[blockIdx.x] : blockIdx.x;
