@@ -5,7 +5,9 @@
 // contraction on the matrix cores, every fp32 value split into three bf16
 // parts and six of the nine partial products accumulated in fp32, or into two
 // half-precision parts and three of the four products; for vectors of like
-// sizes neither loses more than fp32 products do (see bf_score_kernel).  Between `want` = k + 8 and
+// sizes neither loses more than fp32 products do (see bf_score_kernel).  With many queries only the product of the first
+// half-precision parts is taken, and every row that this product, less the most it can err, leaves among the best is
+// re-evaluated in fp64 before it is selected (see screen_room).  Between `want` = k + 8 and
 // `most`, half as many again, of a query's best rows are re-evaluated in fp64 by
 // the rerank kernel and sorted by (distance, id).
 //
@@ -30,8 +32,8 @@
 //
 // Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
 // kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
-// k = 10: 25.8 -> 7.7 to 8.3 ms, by the card (15.5 with three parts); 2,000 x 200,000
-// x 768, k = 100: 13.9 -> 2.27 to 2.41 (3.8); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
+// k = 10: 25.8 -> 4.77 to 4.95 ms (15.5 with three parts, 7.6 to 8.3 with two); 2,000 x 200,000
+// x 768, k = 100: 13.9 -> 1.79 to 1.84 (3.8, 2.27 to 2.41); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
 #include <math.h>
 
 #include "ann_internal.hpp"
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 // they are listed, and the call is repeated with three parts if they are many).  The product of the
 // two second parts, below 2^-22 of the product, is left out.  That is half the products, and
 // half the roundings of the accumulators, which are the larger error from 65 columns on.
-// Error as above, three parts / two (two and norms in fp64, bf_pair_kernel):
+// Error as above, three parts / two (norms in fp64):
 //   L2 of mixtures   d = 72 7.3e-8 / 6.8e-8, 128 1.04e-7 / 8.5e-8, 960 2.1e-7 / 1.8e-7,
 //                    2,048 3.0e-7 / 2.7e-7
 //   inner products   128 1.4e-7 / 1.0e-7, 960 3.1e-7 / 2.6e-7; centred normal 128 1.6e-7 /
@@ -299,7 +301,7 @@ __global__ __launch_bounds__(256) void bf_tile_kernel(const float *__restrict__ 
 // work = 1,160 on the matrix cores, at the 1.96 GHz the card runs such work (peak
 // 2,050 there; a large bf16 matrix product reaches 1,420).  Without the query
 // loads it takes 12.1, without the splitting 12.8.  Two parts: 10.2, bound by the
-// splitting and the end of a tile (bf_pair_kernel has neither between its products).
+// splitting and the end of a tile.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -309,8 +311,8 @@ typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 constexpr int kSK = 32;           // columns per chunk
 constexpr int kSB = 128;          // base rows per tile
 constexpr int kPlane = kSB * kSK * 2;   // bytes of one plane of a chunk
-constexpr uint64_t kPairBytes = 128ull << 20;   // of split rows at a time
-constexpr uint32_t kCallCounters = 8;   // of CallState
+constexpr uint64_t kScreenBytes = 128ull << 20;   // of rows' first parts at a time
+constexpr uint32_t kCallCounters = 9;   // of CallState
 constexpr int kHitList = 96;      // entries a wavefront collects before they go to global memory
 constexpr float kFarNorm2 = 0x1.fp31f;   // two parts: rows of this squared norm and more, scaled, are left out (half precision ends at 2^16)
 constexpr uint32_t kSampleRows = 4096;   // scores one selection workgroup takes; first sample (or twice that, see ann_bruteforce_topk)
@@ -413,11 +415,12 @@ __device__ __forceinline__ float rows_sq(const float *sample_sq) { return wave_m
 
 // The same in two half-precision parts, each query times a power of two (2^-60 to
 // 2^60) that brings its norm to 2^12 .. 2^13.  One workgroup per 32 queries and 16 blocks
-// of columns: the norms first.  unscale[q]: what takes a product of parts back, the rows' scale included.
+// of columns: the norms first.  unscale[q]: what takes a product of parts back, the rows' scale included; norm[q]: at
+// least |q|; rest[q]: at least the norm of what the first part leaves of it.
 __global__ __launch_bounds__(1024) void bf_halve_queries_kernel(const float *__restrict__ Q, uint32_t nq, uint32_t d, uint32_t kb_n,
                                                                 const float *__restrict__ sample_sq, uint4 *__restrict__ out,
-                                                                float *__restrict__ unscale, uint64_t *__restrict__ bound,
-                                                                uint32_t *__restrict__ count) {
+                                                                float *__restrict__ unscale, float *__restrict__ norm, float *__restrict__ rest,
+                                                                uint64_t *__restrict__ bound, uint32_t *__restrict__ count) {
   __shared__ float scale_s[32];
   const uint32_t q32 = blockIdx.x, tid = threadIdx.x;
   {
@@ -431,10 +434,21 @@ __global__ __launch_bounds__(1024) void bf_halve_queries_kernel(const float *__r
 #pragma unroll
     for (int m = 1; m < 32; m <<= 1) sq += __int_as_float(xor_lane_i32(__float_as_int(sq), m));
     const int e = half_exponent(sq), ex = half_exponent(rows_sq(sample_sq));
+    const float scale = ldexpf(1.0f, e);
+    float left = 0.0f;
+    if (qi < nq && blockIdx.y == 0)
+      for (uint32_t j = tid % 32; j < d; j += 32) {
+        const float v = Q[(uint64_t)qi * d + j] * scale, lo = v - (float)(_Float16)v;
+        left = fmaf(lo, lo, left);
+      }
+#pragma unroll
+    for (int m = 1; m < 32; m <<= 1) left += __int_as_float(xor_lane_i32(__float_as_int(left), m));
     if (tid % 32 == 0) {
-      scale_s[tid / 32] = ldexpf(1.0f, e);
+      scale_s[tid / 32] = scale;
       if (qi < nq && blockIdx.y == 0) {
+        rest[qi] = __fsqrt_rn(left) * (1.0f + 0x1p-10f) * ldexpf(1.0f, -e);
         unscale[qi] = ldexpf(1.0f, -e - ex);
+        norm[qi] = __fsqrt_rn(sq) * (1.0f + 0x1p-10f);   // (rounded up; infinite where the square is no float)
         bound[qi] = ~0ull;
         count[qi] = 0;
       }
@@ -465,9 +479,10 @@ struct CallState {
   uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
   uint32_t n_wide;        // two parts: queries whose scores would be nearer to their value with three
   uint32_t left_out;      // two parts, L2: not 0: rows were left out for their size
-  uint32_t max_norm;      // inner product: bits of the largest squared norm of the others
+  uint32_t max_norm;      // inner product, or first parts: bits of the largest squared norm of the others
   uint32_t most_entries;  // of a query in the last pass over uncertain queries
   uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
+  uint32_t max_rest;      // first parts: bits of the largest squared norm of what they leave of a scaled row
   uint32_t far_row[kFarRows];
 };
 
@@ -477,6 +492,8 @@ struct ScoreArgs {
   const uint4 *qfrag;
   uint64_t first, rows;    // rows first .. first + rows - 1 of x, or of a sample of it
   double stretch;    // sample: rows of x per row of the sample; 0: none
+  uint64_t n;        // part_w != 0: rows of x; the pass takes part_w of every 2^part_log2 rows, see part_row()
+  uint32_t part_log2, part_from, part_w;
   uint32_t d, kb_n, nq, metric;
   uint32_t q_tiles, q_group, slabs, tiles_per_slab;
   float *scores;     // not NULL: every score goes here, [nq][ld]
@@ -488,11 +505,23 @@ struct ScoreArgs {
   const float *centre;     // [d] subtracted from every row (kernels with CENTRE)
   const float *sample_sq;  // [64] two parts: squared norms that settle the rows' scale
   const float *unscale;    // [nq] two parts: takes a product back
-  const uint4 *xfrag;      // rows split ahead (bf_pair_kernel) and their squared norms
+  const uint4 *xfrag;      // rows' first parts (bf_screen_kernel) and their squared norms
   const float *norm;
+  const float *q_norm, *q_rest;   // bf_screen_kernel: [nq] at least |q|, and the norm of what its first part leaves
   CallState *state;        // inner product: norms are noted here (NULL: not in this pass)
   bool list_far;           // and the rows without one listed
 };
+
+// Row of x that row v of a pass over a part of the rows is: of each stretch of 2^part_log2 rows the pass takes
+// places part_from .. part_from + part_w - 1 of a random order (places exchanged by a random mask), so
+// that passes over disjoint places share out all rows and each is a stratified random sample.  n or more: no row.
+__device__ __forceinline__ uint64_t part_row(const ScoreArgs &a, uint64_t v) {
+  const uint32_t stretch = (uint32_t)v / a.part_w, place = a.part_from + ((uint32_t)v - stretch * a.part_w);
+  uint32_t h = stretch * 0x9E3779B1u;
+  h = (h ^ (h >> 15)) * 0x85EBCA77u;
+  h ^= h >> 13;
+  return ((uint64_t)stretch << a.part_log2) + (place ^ (h & ((1u << a.part_log2) - 1u)));
+}
 
 // v[i], i in 0 .. 15 (selects: an index into registers would take them through memory)
 __device__ __forceinline__ float pick(const floatx16 &v, int i) {
@@ -504,6 +533,47 @@ __device__ __forceinline__ float pick(const floatx16 &v, int i) {
   return b3 ? e1 : e0;
 }
 
+// How far the score of a row with |x| <= nx may lie from its value, |q| = nq (of
+// the centred vectors where they are).  Each of the kb_n blocks of 16 columns
+// takes six matrix instructions, each of which rounds an accumulator that never
+// exceeds |q| |x|; 32 roundings more stand for the products left out, the norm,
+// the subtraction of the centre and the last addition.  The second term: what
+// the instruction may drop of values below the smallest normal number.  The
+// largest error seen is 0.13 of it (seven distributions, d = 24 to 2,048).
+__device__ __forceinline__ double score_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric) {
+  const double terms = 6.0 * kb_n + 32.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
+  return terms * 0x1p-24 * size + 0x1p-124 * (double)d * (1.0 + nq + nx);
+}
+
+// The same for the products of two half-precision parts: three matrix instructions per
+// block of 16 columns; a part left over is below 2^-23 of its value or 2^-25 of the
+// scaled one's unit (x_unit, q_unit: what 1 in the scaled vectors is worth), and the product of
+// two second parts, left out, below 2^-22.
+__device__ __forceinline__ double half_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric, double x_unit, double q_unit) {
+  const double terms = 3.0 * kb_n + 32.0 + 8.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
+  const double lost = sqrt((double)d) * (nq * x_unit + nx * q_unit) + (double)d * x_unit * q_unit;
+  return terms * 0x1p-24 * size + 0x1p-24 * lost * (1.0 + 0x1p-10) + 0x1p-124 * (double)d * (1.0 + nq + nx);
+}
+
+// How far a product of first parts only (bf_screen_kernel) may put the score of a row that can matter from its value,
+// where `value` bounds the score of the row in question: |q| times what the row's first part leaves, and the other way
+// round (both norms are known: 0.4 of the 2^-11 |x| that a rounding may leave), and what half_room() allows for.  No row
+// of the passes so far is larger than max_norm (its square), or leaves more than max_rest (the scaled one's square); L2:
+// a row whose score is at most `value` has |x| <= |q| + sqrt(distance) as well (a little more, so that it also
+// holds for rows whose score only seems to be that).
+__device__ __forceinline__ float screen_room(float nq, float q_rest, float value, uint32_t d, uint32_t kb_n, uint32_t metric, float x_unit, float unscale,
+                                             uint32_t max_norm, uint32_t max_rest) {
+  const double more = 1.0 + 0x1p-10, x_rest = (double)__fsqrt_rn(__uint_as_float(max_rest)) * (double)x_unit * more;
+  double nx = (double)__fsqrt_rn(__uint_as_float(max_norm)) * more;
+  if (metric == ANN_L2) {
+    const double dist = (double)nq * nq + (double)value;
+    nx = fmin(nx, 1.0625 * (double)nq + (double)__fsqrt_rn(fmaxf((float)dist, 0.0f)) * more);
+  }
+  const double room = half_room((double)nq, nx, d, kb_n, metric, (double)x_unit, (double)unscale / (double)x_unit);
+  const double rest = x_rest * (double)nq + (nx + x_rest) * (double)q_rest;
+  return (float)((room + (metric == ANN_L2 ? 2.0 : 1.0) * rest) * more);
+}
+
 // What a wavefront makes of its products: MB x NQ blocks of 32 rows x 32 queries, the
 // element i of block (m, f) being row m * 32 + 8 (i / 4) + 4 (lane / 32) + i % 4
 // against query f * 32 + lane % 32.  Scores that reach their query's bound collect in
@@ -511,7 +581,8 @@ __device__ __forceinline__ float pick(const floatx16 &v, int i) {
 // atomic addition per entry then, far from the matrix instructions.  The walk over a
 // block with hits takes each lane's next hit per turn (a site of code per score made
 // 170 KB of instructions; a pass over 90,000 rows 0.95 -> 0.59 ms).
-template <int MB, int NQ>
+// SCREEN: the products are of first parts only, and what may reach the bound is written.
+template <int MB, int NQ, bool SCREEN = false>
 struct TileEnd {
   const ScoreArgs &a;
   uint32_t q0;        // the wavefront's first query
@@ -521,10 +592,18 @@ struct TileEnd {
   float top[NQ], scale[NQ];
 
   __device__ __forceinline__ TileEnd(const ScoreArgs &args, uint32_t q0_, uint64_t *hits_, uint8_t *hits_q_) : a(args), q0(q0_), hits(hits_), hits_q(hits_q_) {
+    const float x_unit = SCREEN ? ldexpf(1.0f, -half_exponent(rows_sq(a.sample_sq))) : 1.0f;
+    const uint32_t max_norm = SCREEN ? *(volatile uint32_t *)&a.state->max_norm : 0u, max_rest = SCREEN ? *(volatile uint32_t *)&a.state->max_rest : 0u;
 #pragma unroll
     for (int f = 0; f < NQ; ++f) {
       const uint32_t q = q0 + f * 32 + lane_id() % 32;
       top[f] = a.scores == nullptr && q < a.nq ? unorder_f32((uint32_t)(a.bound[q] >> 32)) : -INFINITY;
+      // (no bound, FLT_MAX: everything; a query whose norm is no float: nothing, its result is found to be uncertain)
+      if (SCREEN && top[f] > -INFINITY && top[f] < 0x1.fffffep127f) {
+        float room = screen_room(a.q_norm[q], a.q_rest[q], top[f], a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
+        room = screen_room(a.q_norm[q], a.q_rest[q], top[f] + room, a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
+        top[f] = room < INFINITY ? top[f] + 2.0f * room * (1.0f + 0x1p-20f) : -INFINITY;   // (a room for the bound, one for the score)
+      }
       scale[f] = a.metric == ANN_L2 ? -2.0f : -1.0f;
       if (a.unscale != nullptr) scale[f] *= q < a.nq ? a.unscale[q] : 0.0f;   // (powers of two)
     }
@@ -540,9 +619,9 @@ struct TileEnd {
     for (int e = lane_id(); e < n_hits; e += kWave) {
       const uint32_t q = q0 + hits_q[e];
       const uint64_t hit = hits[e];
-      const uint64_t row = a.first + (uint32_t)hit, id = a.stretch != 0.0 ? sample_row(row, a.stretch) : row;
+      const uint64_t row = a.first + (uint32_t)hit, id = a.part_w ? part_row(a, row) : (a.stretch != 0.0 ? sample_row(row, a.stretch) : row);
       const uint64_t ent = (hit & 0xFFFFFFFF00000000ull) | (uint32_t)id;
-      if (ent > a.bound[q]) continue;
+      if (!SCREEN && ent > a.bound[q]) continue;
       const uint32_t pos = atomicAdd(&a.count[q], 1u);
       if (pos < a.cap)
         a.buf[(uint64_t)q * a.cap + pos] = ent;
@@ -855,25 +934,30 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Many queries: the rows are split once, not by every workgroup that meets them.
+// Many queries: most scores only have to be shown to be too large, which takes the product of the
+// first parts alone, a third of the work.  What that leaves is re-evaluated in fp64 before anything is
+// selected or bounded by it (bf_range_kernel).
 //
-// bf_halve_rows_kernel brings the rows of a pass, or of a slab of it, into the order
-// the matrix instruction wants (as the queries: 16-byte unit (((row / 32) * kb_n + kb) * 2
-// + plane) * 64 + lane) and writes their squared norms, summed in fp64 (+inf: left out of
-// the scores).  One workgroup per 32 rows, a wavefront takes every fourth block of 16
-// columns.  Reading and writing 128 MB each way takes 47 us.
+// bf_halve_rows_kernel brings the first parts of a pass' rows, or of a slab of it, into the order
+// the matrix instruction wants (16-byte unit ((row / 32) * kb_n + kb) * 64 + lane) and writes
+// the rows' squared norms, summed in fp64 (+inf: left out of the scores).  One workgroup per 32 rows, a wavefront
+// takes every fourth block of 16 columns.
 template <bool VEC4>
 __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *__restrict__ frag, float *__restrict__ norm) {
   __shared__ double part_s[8][32];
+  __shared__ float rest_s[8][32];
   const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const uint64_t at = (uint64_t)blockIdx.x * 32 + lane % 32;
   const int e = __builtin_amdgcn_readfirstlane(half_exponent(rows_sq(a.sample_sq)));
   const float scale = ldexpf(1.0f, e), far_from = ldexpf(kFarNorm2, -2 * e);
   uint64_t r = at < a.rows ? at : a.rows - 1;
-  r = a.stretch != 0.0 ? sample_row(a.first + r, a.stretch) : a.first + r;
+  r = a.part_w ? part_row(a, a.first + r) : (a.stretch != 0.0 ? sample_row(a.first + r, a.stretch) : a.first + r);
+  const bool real = at < a.rows && (a.part_w == 0 || r < a.n);
+  if (!real && a.part_w) r = a.n - 1;
   const float *row = a.x + r * a.d;
-  uint4 *to = frag + (uint64_t)blockIdx.x * a.kb_n * 128 + lane;
+  uint4 *to = frag + (uint64_t)blockIdx.x * a.kb_n * 64 + lane;
   double sq = 0.0;
+  float rest = 0.0f;
 #pragma unroll 2
   for (uint32_t kb = wave; kb < a.kb_n; kb += 4) {
     const uint32_t k0 = kb * 16 + 8 * (lane / 32);
@@ -898,45 +982,55 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
     uint32_t w[4][2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], scale, w[j]);
+    to[(uint64_t)kb * 64] = make_uint4(w[0][0], w[1][0], w[2][0], w[3][0]);
 #pragma unroll
-    for (int p = 0; p < 2; ++p) to[(uint64_t)kb * 128 + p * 64] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+    for (int j = 0; j < 4; ++j) {
+      const halfx2 hi = __builtin_bit_cast(halfx2, w[j][0]);
+      const float l0 = __builtin_fmaf(v[2 * j], scale, -(float)hi.x), l1 = __builtin_fmaf(v[2 * j + 1], scale, -(float)hi.y);
+      rest = fmaf(l0, l0, fmaf(l1, l1, rest));
+    }
   }
   part_s[wave * 2 + lane / 32][lane % 32] = sq;
+  rest_s[wave * 2 + lane / 32][lane % 32] = rest;
   __syncthreads();
   if (tid >= 32) return;
   float t = (float)(((part_s[0][tid] + part_s[1][tid]) + (part_s[2][tid] + part_s[3][tid])) + ((part_s[4][tid] + part_s[5][tid]) + (part_s[6][tid] + part_s[7][tid])));
-  const bool in = at < a.rows && t < far_from;
+  const bool in = real && t < far_from;
   norm[at] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
-  if (a.state == nullptr) return;
   if (a.metric == ANN_L2) {
-    if (at < a.rows && t >= far_from && t < INFINITY) a.state->left_out = 1u;
-    return;
-  }
-  if (at < a.rows && t >= far_from && a.list_far) {
+    if (real && t >= far_from && t < INFINITY) a.state->left_out = 1u;
+  } else if (real && t >= far_from && a.list_far) {
     const uint32_t n = atomicAdd(&a.state->far_rows, 1u);
     if (n < kFarRows) a.state->far_row[n] = (uint32_t)r;
   }
   t = in ? t : 0.0f;
+  rest = 0.0f;
 #pragma unroll
-  for (int m = 1; m < 32; m <<= 1) t = fmaxf(t, __int_as_float(xor_lane_i32(__float_as_int(t), m)));
+  for (int i = 0; i < 8; ++i) rest += rest_s[i][tid];
+  rest = in ? rest : 0.0f;
+#pragma unroll
+  for (int m = 1; m < 32; m <<= 1) {
+    t = fmaxf(t, __int_as_float(xor_lane_i32(__float_as_int(t), m)));
+    rest = fmaxf(rest, __int_as_float(xor_lane_i32(__float_as_int(rest), m)));
+  }
   if (tid == 0 && *(volatile uint32_t *)&a.state->max_norm < __float_as_uint(t)) atomicMax(&a.state->max_norm, __float_as_uint(t));
+  if (tid == 0 && *(volatile uint32_t *)&a.state->max_rest < __float_as_uint(rest)) atomicMax(&a.state->max_rest, __float_as_uint(rest));
 }
 
 // A workgroup of four wavefronts takes 128 rows x 256 queries per tile, a wavefront 128
-// x 64: eight accumulators, 128 registers, so that six products of 16 columns come to two
-// LDS reads of rows and one global read of queries.  No vector instruction
-// stands between the matrix instructions; two wavefronts share a SIMD, and one's
-// end of a tile falls into the other's products.  10,000 x 262,144 x 128: 1.75 to 2.0
-// ms, by the clock: 3.27 M cycles each time, at 1.86 down to 1.63 GHz as the card warms up,
-// the matrix cores busy in 60 % of them = 383 to 336 TFLOP/s of fp32 work (bf_score_kernel with two parts: 2.68
-// ms; with three: 3.7).  The rate is the same at 768 columns, so the loop over chunks is what leaves the
-// rest idle, not the end of a tile.  128 queries per tile: 7 % slower; first products onto a constant zero instead
-// of cleared registers and the rows' parts requested one block ahead: 1.5 %.
-constexpr int kPairQueries = 256;
-__global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
+// x 64: eight accumulators, 128 registers.  64 columns of rows are staged through LDS at a time; queries
+// come from the L2, 32 columns ahead of the products.  No vector instruction stands between the matrix
+// instructions; two wavefronts share a SIMD, and one's end of a tile falls into the other's products.
+// Three of the four products of two parts, 32 columns at a time, took 3.4 times as long and was bound by the power that the
+// matrix cores may draw; one of them, 524,000 rows x 128 against 10,000 queries, takes 2.38 ms = 564 TFLOP/s of fp32 work with
+// the matrix cores busy 27 % of the cycles, and is bound by how long the rows' parts take to come (none fetched: 1.53 ms;
+// tiles without an end: 2.0).
+constexpr int kScreenQueries = 256;
+constexpr int kScreenKb = 4;   // blocks of 16 columns staged at a time
+__global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
   constexpr int MB = 4, NQ = 2, QT32 = 4 * NQ;
-  static_assert(QT32 * 32 == kPairQueries, "tile shape");
-  __shared__ __align__(16) uint4 stage_s[2][4 * 2 * 2 * 64];   // [row / 32][kb][plane][lane]
+  static_assert(QT32 * 32 == kScreenQueries, "tile shape");
+  __shared__ __align__(16) uint4 stage_s[2][4 * kScreenKb * 64];   // [row / 32][kb][lane]
   __shared__ __align__(16) float xn_s[2][kSB];
   __shared__ uint64_t hit_s[4][kHitList];
   __shared__ uint8_t hit_q_s[4][kHitList];
@@ -952,74 +1046,70 @@ __global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
   if (slab >= a.slabs || tile_begin >= tile_end) return;
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
-  const uint32_t n_chunks = a.kb_n / 2;
+  const uint32_t n_chunks = (a.kb_n + kScreenKb - 1) / kScreenKb;
   const uint4 *qf[NQ];
 #pragma unroll
   for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wave * NQ + f) * a.kb_n * 128 + lane;
 
-  // the chunk (two blocks of 16 columns) that is staged next: 32 rows' four units by each wavefront, and the tile's norms
+  // the chunk that is staged next: 32 rows' units by each wavefront, and the tile's norms
   uint32_t tile = tile_begin, f_tile = tile_begin, c = 0, f_c = 0;
-  uint4 x0, x1, x2, x3;
+  uint4 x[kScreenKb];
   float xn_reg;
-  const uint4 *xf = a.xfrag + ((uint64_t)tile_begin * 4 + wave) * a.kb_n * 128 + lane;
+  const uint4 *xf = a.xfrag + ((uint64_t)tile_begin * 4 + wave) * a.kb_n * 64 + lane;
   auto fetch = [&]() {
-    const uint4 *p = xf + f_c * 256;
-    x0 = p[0];
-    x1 = p[64];
-    x2 = p[128];
-    x3 = p[192];
+#pragma unroll
+    for (uint32_t j = 0; j < kScreenKb; ++j) {   // (past the last block: that one again, never used)
+      const uint32_t kb = f_c * kScreenKb + j < a.kb_n ? f_c * kScreenKb + j : a.kb_n - 1;
+      x[j] = xf[kb * 64];
+    }
     xn_reg = a.norm[(f_tile < tile_end ? f_tile : tile_end - 1) * kSB + tid % kSB];
   };
   auto stage = [&](int b) {
-    uint4 *to = &stage_s[b][wave * 256 + lane];
-    to[0] = x0;
-    to[64] = x1;
-    to[128] = x2;
-    to[192] = x3;
+#pragma unroll
+    for (int j = 0; j < kScreenKb; ++j) stage_s[b][(wave * kScreenKb + j) * 64 + lane] = x[j];
     xn_s[f_tile & 1][tid % kSB] = xn_reg;   // (the same values with every chunk of a tile)
   };
   auto advance = [&]() {
     if (++f_c == n_chunks) {
       f_c = 0;
-      if (++f_tile < tile_end) xf += (uint64_t)4 * a.kb_n * 128;   // (past the end: the last tile again)
+      if (++f_tile < tile_end) xf += (uint64_t)4 * a.kb_n * 64;   // (past the end: the last tile again)
     }
   };
 
-  TileEnd<MB, NQ> end(a, (qt * QT32 + wave * NQ) * 32, hit_s[wave], hit_q_s[wave]);
+  TileEnd<MB, NQ, true> end(a, (qt * QT32 + wave * NQ) * 32, hit_s[wave], hit_q_s[wave]);
   floatx16 acc[MB][NQ];
-  auto load_q = [&](uint4 (&to)[NQ][2], uint32_t kb) {
+  // queries: two blocks of 16 columns
+  auto load_q = [&](uint4 (&to)[2][NQ], uint32_t kb) {
 #pragma unroll
-    for (int f = 0; f < NQ; ++f)
+    for (uint32_t j = 0; j < 2; ++j)
 #pragma unroll
-      for (int p = 0; p < 2; ++p) to[f][p] = qf[f][kb * 128 + p * 64];
+      for (int f = 0; f < NQ; ++f) to[j][f] = qf[f][(kb + j < a.kb_n ? kb + j : a.kb_n - 1) * 128];
   };
-  halfx8 xa[2][2];
-  auto read_rows = [&](halfx8 (&to)[2], const uint4 *from) {
+  halfx8 xa[2][MB];
+  auto read_rows = [&](halfx8 (&to)[MB], const uint4 *from) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p) to[p] = __builtin_bit_cast(halfx8, from[p * 64]);
+    for (int m = 0; m < MB; ++m) to[m] = __builtin_bit_cast(halfx8, from[m * kScreenKb * 64]);
   };
-  // 16 columns: the products of 32 rows at a time while the next 32 rows' parts (after the last: those at `next`) are on their way
-  auto multiply = [&](const uint4 (&q)[NQ][2], const uint4 *from, const uint4 *next, bool first) {
+  // two blocks of 16 columns at `from`, the first one's rows in xa[0]; the second's, and those at `next` (if any), are read meanwhile
+  auto multiply = [&](const uint4 (&q)[2][NQ], const uint4 *from, const uint4 *next, bool first) {
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
-      if (m + 1 < MB)
-        read_rows(xa[(m + 1) & 1], from + (m + 1) * 256);
+    for (int j = 0; j < 2; ++j) {
+      if (j == 0)
+        read_rows(xa[1], from + 64);
       else if (next)
         read_rows(xa[0], next);
-      // the small products first
-      constexpr int pa[3] = {1, 0, 0}, pb[3] = {0, 1, 0};
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int f = 0; f < NQ; ++f) {
           const floatx16 zero = {};
-          acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[m & 1][pa[t]], __builtin_bit_cast(halfx8, q[f][pb[t]]), first && t == 0 ? zero : acc[m][f], 0, 0, 0);
+          acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[j][m], __builtin_bit_cast(halfx8, q[j][f]), first && j == 0 ? zero : acc[m][f], 0, 0, 0);
         }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 
-  uint4 q0[NQ][2], q1[NQ][2];
+  uint4 q0[2][NQ], q1[2][NQ];
   fetch();
   load_q(q0, 0);
   stage(0);
@@ -1029,7 +1119,8 @@ __global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
   int cur = 0;
   for (;;) {
     const uint4 *from = &stage_s[cur][lane];
-    load_q(q1, 2 * c + 1);
+    const bool whole = c * kScreenKb + 2 < a.kb_n;   // (kb_n is even: a last chunk may be half)
+    load_q(q1, whole ? c * kScreenKb + 2 : 0);
     read_rows(xa[0], from);
     __builtin_amdgcn_sched_barrier(0);
     if (c == 0)
@@ -1037,11 +1128,11 @@ __global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
     else
       multiply(q0, from, from + 128, false);
     stage(cur ^ 1);
-    load_q(q0, 2 * f_c);
+    load_q(q0, f_c * kScreenKb);
     advance();
     fetch();
     __builtin_amdgcn_sched_barrier(0);
-    multiply(q1, from + 128, nullptr, false);
+    if (whole) multiply(q1, from + 128, nullptr, false);
     if (++c == n_chunks) {
       end.finish(acc, xn_s[tile & 1], tile * kSB);
       c = 0;
@@ -1051,28 +1142,6 @@ __global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
     cur ^= 1;
   }
   if (end.n_hits > 0) end.flush();
-}
-
-// How far the score of a row with |x| <= nx may lie from its value, |q| = nq (of
-// the centred vectors where they are).  Each of the kb_n blocks of 16 columns
-// takes six matrix instructions, each of which rounds an accumulator that never
-// exceeds |q| |x|; 32 roundings more stand for the products left out, the norm,
-// the subtraction of the centre and the last addition.  The second term: what
-// the instruction may drop of values below the smallest normal number.  The
-// largest error seen is 0.13 of it (seven distributions, d = 24 to 2,048).
-__device__ __forceinline__ double score_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric) {
-  const double terms = 6.0 * kb_n + 32.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
-  return terms * 0x1p-24 * size + 0x1p-124 * (double)d * (1.0 + nq + nx);
-}
-
-// The same for the products of two half-precision parts: three matrix instructions per
-// block of 16 columns; a part left over is below 2^-23 of its value or 2^-25 of the
-// scaled one's unit (x_unit, q_unit: what 1 in the scaled vectors is worth), and the product of
-// two second parts, left out, below 2^-22.
-__device__ __forceinline__ double half_room(double nq, double nx, uint32_t d, uint32_t kb_n, uint32_t metric, double x_unit, double q_unit) {
-  const double terms = 3.0 * kb_n + 32.0 + 8.0, size = metric == ANN_L2 ? 2.0 * nq * nx + nx * nx : nq * nx;
-  const double lost = sqrt((double)d) * (nq * x_unit + nx * q_unit) + (double)d * x_unit * q_unit;
-  return terms * 0x1p-24 * size + 0x1p-24 * lost * (1.0 + 0x1p-10) + 0x1p-124 * (double)d * (1.0 + nq + nx);
 }
 
 // ---------------------------------------------------------------------------
@@ -1085,13 +1154,15 @@ __device__ __forceinline__ double half_room(double nq, double nx, uint32_t d, ui
 constexpr uint32_t kMaxScore = 0xFF7FFFFFu;   // FLT_MAX in score order
 constexpr int kSelThreads = 256;
 
-template <int EPT>
+// THREADS: of the workgroup; one wavefront needs no LDS and no barriers.
+template <int EPT, int THREADS = kSelThreads>
 struct Selector {
   uint32_t key[EPT], id[EPT];
   uint32_t *red;   // LDS [2][4]
   int parity = 0;
 
   __device__ __forceinline__ uint32_t total(uint32_t wave_count) {
+    if constexpr (THREADS == kWave) return wave_count;
     if (threadIdx.x % kWave == 0) red[parity * 4 + threadIdx.x / kWave] = wave_count;
     __syncthreads();
     const uint32_t t = red[parity * 4] + red[parity * 4 + 1] + red[parity * 4 + 2] + red[parity * 4 + 3];
@@ -1121,19 +1192,21 @@ struct Selector {
         mn = o < mn ? o : mn;
         mx = p > mx ? p : mx;
       }
-      if (threadIdx.x % kWave == 0) {
-        red[parity * 4 + threadIdx.x / kWave] = mn;
-        red[8 + threadIdx.x / kWave] = mx;
-      }
-      __syncthreads();
+      if constexpr (THREADS > kWave) {
+        if (threadIdx.x % kWave == 0) {
+          red[parity * 4 + threadIdx.x / kWave] = mn;
+          red[8 + threadIdx.x / kWave] = mx;
+        }
+        __syncthreads();
 #pragma unroll
-      for (int w = 0; w < kSelThreads / kWave; ++w) {
-        mn = red[parity * 4 + w] < mn ? red[parity * 4 + w] : mn;
-        mx = red[8 + w] > mx ? red[8 + w] : mx;
+        for (int w = 0; w < THREADS / kWave; ++w) {
+          mn = red[parity * 4 + w] < mn ? red[parity * 4 + w] : mn;
+          mx = red[8 + w] > mx ? red[8 + w] : mx;
+        }
+        parity ^= 1;
       }
-      parity ^= 1;
       if (mn > 0) lo = mn - 1;
-      if (most < (uint32_t)kSelThreads && mx < hi) hi = mx;
+      if (most < (uint32_t)THREADS && mx < hi) hi = mx;
     }
     while (hi - lo > 1) {
       const uint32_t mid = lo + (hi - lo) / 2;
@@ -1331,6 +1404,155 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
   for (uint32_t e = n_kept + tid; e < most; e += kSelThreads) cand[(uint64_t)q * most + e] = ANN_PAD_ID;
 }
 
+// A query's entries after a pass of bf_screen_kernel, whose scores may be a room (screen_room) off: the score that `want` to
+// `most` of them reach bounds the next pass, and what is more than two rooms beyond it goes (one for the bound, one for the
+// entry: it is not among the `want` best).  After the last pass what is left is re-evaluated in fp64, the score rounded
+// once, and the best `want` to `most` of that stay.  More than there is room for: the count says so to the last selection.
+// (Re-evaluating each pass's new entries made the bounds a room tighter and cost more: 200,000 rows, d = 768, k = 100,
+// 2,000 queries: these kernels 263 instead of 660 us.)
+// A wavefront takes a query with up to 512 entries, a workgroup one with more, in a launch of its own: 10,000 queries with
+// about a hundred each, k = 10, d = 128, by workgroups 130 to 205 us a pass, by wavefronts 16 to 57.  After the last pass a workgroup takes every query where there is much
+// to read again, want d >= 32,768 elements: d = 768, k = 100 by both kinds 442 us, by workgroups 222 (d = 300, k = 10, 3,000
+// queries, whole call: 658 by workgroups, 620 by wavefronts; d = 960, k = 10: no difference).
+struct RangeArgs {
+  const float *x, *q;
+  const float *sample_sq, *unscale, *q_norm, *q_rest;
+  const CallState *state;
+  uint32_t d, kb_n, metric, want, most;
+  bool last;   // pass
+  uint32_t few;   // entries that a wavefront takes
+  uint64_t *buf;
+  uint32_t *count;
+  uint32_t cap;
+  uint64_t *bound;
+};
+constexpr uint32_t kFewEntries = 8 * kWave;
+constexpr uint32_t range_room(int threads) { return threads == kWave ? kFewEntries : 4 * kSelThreads; }   // entries that may be among the best
+
+// Those that may be among the best to best[]; the score that `want` to `most` reach.
+template <int EPT, int THREADS>
+__device__ __forceinline__ uint64_t range_entries(const RangeArgs &a, uint32_t q, uint32_t n_ent, float room, uint64_t *best, uint32_t *n_best, uint32_t *red) {
+  const uint32_t tid = threadIdx.x;
+  Selector<EPT, THREADS> s;
+  s.red = red;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const uint32_t i = (uint32_t)(e * THREADS) + tid;
+    const uint64_t ent = i < n_ent ? a.buf[(uint64_t)q * a.cap + i] : ~0ull;
+    s.key[e] = (uint32_t)(ent >> 32);
+    s.id[e] = (uint32_t)ent;
+  }
+  uint32_t n_kept;
+  const uint64_t b = s.run(a.want, a.most, n_kept);
+  const float last = n_ent <= a.most ? INFINITY : unorder_f32((uint32_t)(b >> 32)) + 2.0f * room * (1.0f + 0x1p-20f);
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    if (s.key[e] > kMaxScore || unorder_f32(s.key[e]) > last) continue;
+    const uint32_t at = atomicAdd(n_best, 1u);
+    if (at < range_room(THREADS)) best[at] = ((uint64_t)s.key[e] << 32) | s.id[e];
+  }
+  __syncthreads();
+  return b;
+}
+template <bool VEC4, int THREADS>
+__global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
+  constexpr uint32_t kRoomHere = range_room(THREADS), kLanes = THREADS == kWave ? 4 : 8;   // lanes to a row
+  __shared__ uint32_t red[16], n_best[2];
+  __shared__ unsigned long long last_s;
+  __shared__ uint64_t best[kRoomHere];
+  const uint32_t q = blockIdx.x, tid = threadIdx.x;
+  const uint32_t found = a.count[q];
+  // (none, or taken by the other launch, which may only leave few of many; more than cap: entries were lost)
+  if (found == 0 || found > a.cap || (found <= a.few) != (THREADS == kWave)) return;
+  const uint64_t old_bound = a.bound[q];
+  if (tid < 2) n_best[tid] = 0;
+  if (tid == 0) last_s = 0;
+  __syncthreads();
+  const float x_unit = ldexpf(1.0f, -half_exponent(rows_sq(a.sample_sq))), q_norm = a.q_norm[q], unscale = a.unscale[q];
+  const float value = unorder_f32((uint32_t)(old_bound >> 32)), q_rest = a.q_rest[q];
+  const uint32_t max_norm = a.state->max_norm, max_rest = a.state->max_rest;
+  float room = screen_room(q_norm, q_rest, value, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);
+  room = screen_room(q_norm, q_rest, value + 3.0f * room, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);   // (of entries up to two rooms beyond the bound)
+  uint64_t b;
+  if constexpr (THREADS == kWave)
+    b = range_entries<8, THREADS>(a, q, found, room, best, n_best, red);
+  else if (found <= 8 * kSelThreads)
+    b = range_entries<8, THREADS>(a, q, found, room, best, n_best, red);
+  else
+    b = range_entries<32, THREADS>(a, q, found, room, best, n_best, red);
+  const uint32_t n = n_best[0];
+  const bool bounds = found > a.most && b < old_bound;   // (else the selection took all of them)
+  if (!a.last) {
+    if (n <= kRoomHere && n < found)
+      for (uint32_t i = tid; i < n; i += THREADS) a.buf[(uint64_t)q * a.cap + i] = best[i];
+    if (tid == 0) {
+      if (n <= kRoomHere) a.count[q] = n;
+      if (bounds) a.bound[q] = b;
+    }
+    return;
+  }
+  if (n > kRoomHere) {
+    if (tid == 0) a.count[q] = a.cap + 1;
+    return;
+  }
+  const float *qr = a.q + (uint64_t)q * a.d;
+  for (uint32_t i = tid / kLanes; i < n; i += THREADS / kLanes) {
+    const uint32_t id = (uint32_t)best[i];
+    const float *row = a.x + (uint64_t)id * a.d;
+    double dot = 0.0, sq = 0.0;
+    if constexpr (VEC4) {
+#pragma unroll 8
+      for (uint32_t j = tid % kLanes * 4; j < a.d; j += kLanes * 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(row + j);
+        const float4 w = *reinterpret_cast<const float4 *>(qr + j);
+        dot = fma((double)v.x, (double)w.x, dot), dot = fma((double)v.y, (double)w.y, dot);
+        dot = fma((double)v.z, (double)w.z, dot), dot = fma((double)v.w, (double)w.w, dot);
+        sq = fma((double)v.x, (double)v.x, sq), sq = fma((double)v.y, (double)v.y, sq);
+        sq = fma((double)v.z, (double)v.z, sq), sq = fma((double)v.w, (double)v.w, sq);
+      }
+    } else {
+#pragma unroll 8
+      for (uint32_t j = tid % kLanes; j < a.d; j += kLanes) {
+        const double v = row[j];
+        dot = fma(v, (double)qr[j], dot);
+        sq = fma(v, v, sq);
+      }
+    }
+    dot = group_sum_f64<kLanes>(dot);
+    sq = group_sum_f64<kLanes>(sq);
+    if (tid % kLanes == 0) best[i] = ((uint64_t)order_u32((float)(a.metric == ANN_L2 ? sq - 2.0 * dot : -dot)) << 32) | id;
+  }
+  __syncthreads();
+  Selector<(int)kRoomHere / THREADS, THREADS> s;
+  s.red = red;
+#pragma unroll
+  for (int e = 0; e < (int)kRoomHere / THREADS; ++e) {
+    const uint32_t i = (uint32_t)(e * THREADS) + tid;
+    const uint64_t ent = i < n ? best[i] : ~0ull;
+    s.key[e] = (uint32_t)(ent >> 32);
+    s.id[e] = (uint32_t)ent;
+  }
+  uint32_t n_kept;
+  const uint64_t kept = s.run(a.want, a.most, n_kept);
+#pragma unroll
+  for (int e = 0; e < (int)kRoomHere / THREADS; ++e) {
+    const uint64_t ent = ((uint64_t)s.key[e] << 32) | s.id[e];
+    if (s.key[e] <= kMaxScore && ent <= kept) {
+      a.buf[(uint64_t)q * a.cap + atomicAdd(&n_best[1], 1u)] = ent;
+      atomicMax(&last_s, (unsigned long long)ent);
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    // (The last that stays: where no more than `most` were left the selection takes all and gives no bound.  What went or was
+    // never noted lies more than a room beyond `from`.)
+    const float from = unorder_f32((uint32_t)((bounds ? b : old_bound) >> 32)) + room;
+    const uint64_t beyond = from < INFINITY ? (uint64_t)order_u32(from) << 32 : ~0ull;
+    if (n_kept >= a.want) a.bound[q] = last_s < beyond ? last_s : beyond;
+    a.count[q] = n_kept;
+  }
+}
+
 // The whole search with fp32 products and a top-k per (query, slab): for batches
 // that the split products cannot serve.
 static ann_status bruteforce_fp32(const float *x, uint64_t n, uint32_t d, const float *q, uint32_t nq, uint32_t k, uint32_t metric,
@@ -1444,14 +1666,14 @@ static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream
   return ANN_OK;
 }
 
-// The same with the rows split ahead, a slab of at most x_rows at a time.  A die's group
+// One pass of first parts, a slab of at most x_rows rows at a time.  A die's group
 // of query tiles is a megabyte of parts, four tiles at least (between 4 and 16 tiles within 1 %).
-static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
+static ann_status launch_screen(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
   const uint64_t n = a.rows;
   a.xfrag = xfrag;
   a.norm = norm;
-  a.q_tiles = (a.nq + kPairQueries - 1) / kPairQueries;
-  a.q_group = 64 / a.kb_n > 4 ? 64 / a.kb_n : 4;
+  a.q_tiles = (a.nq + kScreenQueries - 1) / kScreenQueries;
+  a.q_group = 128 / a.kb_n > 4 ? 128 / a.kb_n : 4;
   if (a.q_group > a.q_tiles) a.q_group = a.q_tiles;
   for (a.first = 0; a.first < n; a.first += x_rows) {
     a.rows = n - a.first < x_rows ? n - a.first : x_rows;
@@ -1462,7 +1684,7 @@ static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm
       bf_halve_rows_kernel<false><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
     choose_slabs(tiles, a.q_tiles, n_cu, a.slabs, a.tiles_per_slab);
     const uint32_t grid = a.q_tiles * ((a.slabs + 7) / 8 * 8);
-    bf_pair_kernel<<<grid, 256, 0, st>>>(a);
+    bf_screen_kernel<<<grid, 256, 0, st>>>(a);
   }
   ANN_HIP(hipGetLastError());
   return ANN_OK;
@@ -1650,6 +1872,7 @@ static uint64_t up256(uint64_t v) { return (v + 255) & ~255ull; }
 struct Selection {
   uint32_t want, most, most_bound;   // see ann_bruteforce_topk
   uint32_t kb_n, cap, first, samples;
+  uint32_t part_log2, part_cap;   // first parts: passes over 1 / 2^part_log2 of the rows, entries per query
   uint64_t stretches, ld;
   bool vec4, dense, halves;   // halves: scores from two half-precision parts
   double growth;
@@ -1658,8 +1881,8 @@ struct Selection {
   uint64_t *buf, *bound;
   uint32_t *count, *cand;
   CallState *state;
-  float *sample_sq, *unscale;
-  uint4 *xfrag;        // room for x_rows split rows and their norms
+  float *sample_sq, *unscale, *q_norm, *q_rest;
+  uint4 *xfrag;        // room for x_rows rows' first parts and their norms
   float *xnorm;
   uint64_t x_rows;
 };
@@ -1671,7 +1894,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
   const uint64_t units = (uint64_t)blocks32 * s.kb_n * 64;
   const bool halves = s.halves && centre == nullptr;
   if (halves)
-    bf_halve_queries_kernel<<<dim3(blocks32, (s.kb_n + 15) / 16), 1024, 0, t.st>>>(qr, m, t.d, s.kb_n, s.sample_sq, s.qfrag, s.unscale, s.bound, s.count);
+    bf_halve_queries_kernel<<<dim3(blocks32, (s.kb_n + 15) / 16), 1024, 0, t.st>>>(qr, m, t.d, s.kb_n, s.sample_sq, s.qfrag, s.unscale, s.q_norm, s.q_rest, s.bound, s.count);
   else
     bf_split_queries_kernel<<<(uint32_t)(units / 256 < 4096 ? (units + 255) / 256 : 4096), 256, 0, t.st>>>(
         qr, m, t.d, s.kb_n, blocks32, t.metric == ANN_L2 ? centre : nullptr, s.qfrag, s.bound, s.count,
@@ -1711,6 +1934,49 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
     bf_select_scores_kernel<kSampleRows / kSelThreads><<<dim3(m, (uint32_t)s.stretches), kSelThreads, 0, t.st>>>(s.scores, a.ld, t.n, 0, s.want, s.most,
                                                                                                                  s.bound, s.buf);
     select_entries(nullptr, s.cand, s.most);
+  } else if (halves && s.x_rows) {
+    // First parts: a sample, all of whose scores are written, gives the first bounds.  Then all rows in passes over a
+    // 2^part_log2-th of them, three times that, four times what there was so far, and so on, each a random sample: what may reach
+    // the bounds is a few times a bound's rank per pass, and the best of it gives the next bounds.
+    // (A sample of 4,096 rows, one of 64,000 and then all rows in order, three products each: 1M x 128, 10,000 queries 7,640 to
+    // 7,940 us, with passes over parts 7,554, with first products only 4,770 to 4,950.)
+    a.rows = kSampleRows;
+    a.stretch = (double)t.n / kSampleRows;
+    a.scores = s.scores;
+    a.state = s.state;   // (the largest norm; the sample's rows come again)
+    a.list_far = false;
+    a.q_norm = s.q_norm;
+    a.q_rest = s.q_rest;
+    rc = launch_screen(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
+    if (rc != ANN_OK) return rc;
+    bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
+                                                                                    nullptr);
+    a.scores = nullptr;
+    a.stretch = 0.0;
+    a.list_far = list_far;
+    a.cap = s.part_cap;
+    a.n = t.n;
+    a.part_log2 = s.part_log2;
+    RangeArgs range{t.x, qr, s.sample_sq, s.unscale, s.q_norm, s.q_rest, s.state, t.d, s.kb_n, t.metric, s.want, s.most_bound, false, kFewEntries, s.buf, s.count, a.cap, s.bound};
+    const uint32_t parts = 1u << s.part_log2;
+    for (uint32_t from = 0, to = 1; from < parts; from = to, to *= 4) {
+      a.part_from = from;
+      a.part_w = to - from;
+      a.rows = ((t.n + parts - 1) >> s.part_log2) * a.part_w;
+      rc = launch_screen(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
+      if (rc != ANN_OK) return rc;
+      range.last = to == parts;
+      if (range.last && (uint64_t)s.want * t.d >= 32768) range.few = 0;   // (see bf_range_kernel)
+      if (s.vec4) {
+        if (range.few) bf_range_kernel<true, kWave><<<m, kWave, 0, t.st>>>(range);
+        bf_range_kernel<true, kSelThreads><<<m, kSelThreads, 0, t.st>>>(range);
+      } else {
+        if (range.few) bf_range_kernel<false, kWave><<<m, kWave, 0, t.st>>>(range);
+        bf_range_kernel<false, kSelThreads><<<m, kSelThreads, 0, t.st>>>(range);
+      }
+    }
+    // (at most most_bound entries now, unless there was no room for them)
+    bf_select_entries_kernel<2><<<m, kSelThreads, 0, t.st>>>(s.buf, s.count, a.cap, s.want, s.most, s.bound, s.cand, certain);
   } else {
     double rows = (double)s.first;
     for (uint32_t p = 0; p <= s.samples; ++p, rows *= s.growth) {
@@ -1719,7 +1985,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       a.stretch = last ? 0.0 : (double)t.n / (double)a.rows;
       a.scores = p == 0 ? s.scores : nullptr;
       a.state = last ? s.state : nullptr;
-      rc = halves && s.x_rows ? launch_pairs(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st) : launch_scores(a, s.vec4, t.n_cu, t.st);
+      rc = launch_scores(a, s.vec4, t.n_cu, t.st);
       if (rc != ANN_OK) return rc;
       if (p == 0 && s.first == kSampleRows)
         bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
@@ -1942,38 +2208,44 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
     while ((double)cap < growth * spread && cap < 8192) cap <<= 1;
   }
   const uint64_t ld = dense ? (n + kSB - 1) / kSB * kSB : first;
+  // With first parts: passes over a 4^i-th of the rows, at most eight times the first sample, and so on (see select_round).
+  uint32_t part_log2 = 0, part_cap = 2048;
+  while ((double)(n >> part_log2) > 8.0 * kSampleRows) part_log2 += 2;
+  const double part_growth = (double)n / (1u << part_log2) / kSampleRows;
+  while ((double)part_cap < (part_growth > 3.0 ? part_growth : 3.0) * spread + most_bound && part_cap < 8192) part_cap <<= 1;
+  const uint32_t room = cap > part_cap ? cap : part_cap;
   // queries per round: at most half a GiB of scores and entries, less if the card has no room
-  const uint64_t per_query = ld * 4 + (uint64_t)cap * 8;
+  const uint64_t per_query = ld * 4 + (uint64_t)room * 8;
   uint64_t round = (512ull << 20) / per_query / 128 * 128;
   if (round < 128) round = 128;
   if (round > nq) round = nq;
   // Two parts where products take the time (up to 64 queries a call reads rows, few rows are a matter of
-  // launches) and where near rows' scores lose no more than with three: from 65 columns on, see bf_score_kernel.  The rows are
-  // split ahead where that costs less than it saves, which is a question of the queries and, since the splitting
-  // moves every row twice, of the columns.  Three parts / two / two, split ahead: 1M x 128, 512 queries 918 /
-  // 685 / 739 us, 768 1,397 / 1,011 / 927, 10,000 15,580 / 10,890 / 7,980; 200,000 x 960, 1,000 queries 2,254 /
-  // 1,590 / 1,801, 1,536 3,537 / 2,450 / 2,354.
+  // launches) and where near rows' scores lose no more than with three: from 65 columns on, see bf_score_kernel.  First parts
+  // only where that costs less than it saves, which is a question of the queries and, since every row is read once more to be
+  // rounded, of the columns.  Two parts / first parts: 1M x 128, 512 queries 656 / 561 us, 700 737 / 670; 100,000 x 300, 700 274 /
+  // 292, 1,000 (above the line) 312; 200,000 x 768, k = 100, 700 1,038 / 1,010, 1,000 1,298 / 1,138; 200,000 x 960, 700 1,132 /
+  // 1,107, 512 803 / 1,009; 50,000 x 400, 700 235 / 325, 1,000 319 / 355.
   const bool halves = !dense && nq > 64 && kb_n >= 6;
   uint64_t x_rows = 0;
   if (halves && nq >= 512 + kb_n * 16) {
-    x_rows = kPairBytes / (kb_n * 64) / kSB * kSB;
+    x_rows = kScreenBytes / (kb_n * 32) / kSB * kSB;
     if (x_rows > (n + kSB - 1) / kSB * kSB) x_rows = (n + kSB - 1) / kSB * kSB;
   }
-  auto parts = [&](uint64_t m, uint64_t (&at)[13]) {
-    const uint64_t size[13] = {(m + 255) / 256 * 8 * kb_n * 192 * 16, m * ld * 4, m * cap * 8, m * 8, m * 4, m * most * 4, m * 4, sizeof(CallState),
-                               (uint64_t)nq * 4, 64 * 4, m * 4, x_rows * kb_n * 64, x_rows * 4};
+  auto parts = [&](uint64_t m, uint64_t (&at)[15]) {
+    const uint64_t size[15] = {(m + 255) / 256 * 8 * kb_n * 192 * 16, m * ld * 4, m * room * 8, m * 8, m * 4, m * most * 4, m * 4, sizeof(CallState),
+                               (uint64_t)nq * 4, 64 * 4, m * 4, x_rows * kb_n * 32, x_rows * 4, m * 4, m * 4};
     uint64_t total = 0;
-    for (int i = 0; i < 13; ++i) {
+    for (int i = 0; i < 15; ++i) {
       at[i] = total;
       total += up256(size[i]);
     }
     return total;
   };
-  uint64_t at[13];
+  uint64_t at[15];
   unsigned char *base = nullptr;
   uint64_t m_fit = round;
   hipError_t e = alloc_some((void **)&base, m_fit, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
-  if (e != hipSuccess && x_rows) {   // no room for split rows
+  if (e != hipSuccess && x_rows) {   // no room for the rows' first parts
     x_rows = 0;
     m_fit = round;
     e = alloc_some((void **)&base, m_fit, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
@@ -1991,6 +2263,8 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   s.cap = cap;
   s.first = first;
   s.samples = samples;
+  s.part_log2 = part_log2;
+  s.part_cap = part_cap;
   s.stretches = stretches;
   s.ld = ld;
   s.vec4 = vec4;
@@ -2010,6 +2284,8 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   s.xfrag = reinterpret_cast<uint4 *>(base + at[11]);
   s.xnorm = reinterpret_cast<float *>(base + at[12]);
   s.x_rows = x_rows;
+  s.q_norm = reinterpret_cast<float *>(base + at[13]);
+  s.q_rest = reinterpret_cast<float *>(base + at[14]);
   const Truth t{x, n, d, q, k, metric, out_ids, out_dist, n_cu, st};
 
   ann_status rc = ANN_OK;

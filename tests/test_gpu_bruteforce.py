@@ -243,8 +243,8 @@ def _check_some(H, X, Q, k, metric, every=13):
     H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
 
 
-# Two half-precision parts: more than 64 queries and 64 columns, more than 16,384 rows and than 2^24 scores.  The rows are split on
-# the way (below 512 queries and as many more as columns) or ahead (tiles of 256 queries): 100 and 700 queries in most tests below,
+# Two half-precision parts: more than 64 queries and 64 columns, more than 16,384 rows and than 2^24 scores.  All products
+# (below 512 queries and as many more as columns) or those of first parts (tiles of 256 queries): 100 and 700 queries in most tests below,
 # which also have sizes with fewer scores than that (three parts).
 PARTS = [(100, 170_000), (700, 30_000)]
 
@@ -257,6 +257,19 @@ PARTS = [(100, 170_000), (700, 30_000)]
     (300001, 67, 700, 3, oracle.L2), (140000, 260, 800, 10, oracle.IP), (16640, 2048, 2600, 1, oracle.L2), (50000, 128, 1024, 100, oracle.IP)])
 def test_two_parts(H, n, d, nq, k, metric):
     _check_some(H, _points(n, d, n + d), _points(nq, d, k), k, metric)
+
+
+# One pass, four, three and two; columns in and out of groups of four; wavefronts and workgroups; clusters no wider than what first parts lose
+@pytest.mark.parametrize("n,d,nq,k,metric,spread", [
+    (32_768, 80, 640, 10, oracle.L2, 1.0), (32_769, 82, 640, 10, oracle.IP, 1.0), (524_289, 66, 600, 10, oracle.L2, 1.0),
+    (131_073, 130, 700, 256, oracle.L2, 1.0), (60_001, 132, 700, 256, oracle.IP, 1.0), (60_000, 96, 650, 10, oracle.L2, 0.05),
+    (140_000, 96, 650, 100, oracle.IP, 0.05), (60_000, 99, 650, 100, oracle.L2, 0.01)])
+def test_first_parts(H, n, d, nq, k, metric, spread):
+    X, Q = _points(n, d, n + d), _points(nq, d, k)
+    if spread < 1.0:
+        centres = _points(100, d, 91)
+        X, Q = X * np.float32(spread) + centres[np.arange(n) % 100], Q * np.float32(spread) + centres[np.arange(nq) % 100]
+    _check_some(H, X, Q, k, metric)
 
 
 @pytest.mark.parametrize("nq,n", PARTS + [(100, 18_000), (700, 18_000)])
