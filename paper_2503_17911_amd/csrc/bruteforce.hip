@@ -32,8 +32,8 @@
 //
 // Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
 // kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
-// k = 10: 25.8 -> 4.77 to 4.95 ms (15.5 with three parts, 7.6 to 8.3 with two); 2,000 x 200,000
-// x 768, k = 100: 13.9 -> 1.79 to 1.84 (3.8, 2.27 to 2.41); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
+// k = 10: 25.8 -> 3.51 to 3.66 ms (15.5 with three parts, 7.6 to 8.3 with two); 2,000 x 200,000
+// x 768, k = 100: 13.9 -> 1.39 to 1.43 (3.8, 2.27 to 2.41); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
 #include <math.h>
 
 #include "ann_internal.hpp"
@@ -1021,10 +1021,9 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
 // x 64: eight accumulators, 128 registers.  64 columns of rows are staged through LDS at a time; queries
 // come from the L2, 32 columns ahead of the products.  No vector instruction stands between the matrix
 // instructions; two wavefronts share a SIMD, and one's end of a tile falls into the other's products.
-// Three of the four products of two parts, 32 columns at a time, took 3.4 times as long and was bound by the power that the
-// matrix cores may draw; one of them, 524,000 rows x 128 against 10,000 queries, takes 2.38 ms = 564 TFLOP/s of fp32 work with
-// the matrix cores busy 27 % of the cycles, and is bound by how long the rows' parts take to come (none fetched: 1.53 ms;
-// tiles without an end: 2.0).
+// 524,000 rows x 128 against 10,000 queries: 1.53 ms = 900 TFLOP/s of fp32 work, matrix cores busy 46 % of the cycles
+// at 1.89 GHz (three of the four products of two parts 5.1 ms, bound by the power that the matrix cores may draw).  With the chunk
+// on its way in an array, which the compiler kept in scratch memory, 2.38; with 64-bit addresses 1.6.
 constexpr int kScreenQueries = 256;
 constexpr int kScreenKb = 4;   // blocks of 16 columns staged at a time
 __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
@@ -1047,32 +1046,38 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const uint32_t n_chunks = (a.kb_n + kScreenKb - 1) / kScreenKb;
-  const uint4 *qf[NQ];
-#pragma unroll
-  for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wave * NQ + f) * a.kb_n * 128 + lane;
+  // Loads through buffer descriptors: an offset of the lane, the rest in scalar registers (64-bit addresses take 20 vector
+  // registers, which go to scratch memory, and reading them back at a tile's end waits for every load on its way).
+  const uint32_t lane16 = lane * 16, block_bytes = a.kb_n * 1024;   // of 32 rows' first parts; queries have two parts
+  const auto q_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.qfrag + (uint64_t)(qt * QT32 + wave * NQ) * a.kb_n * 128), 0, NQ * 2 * block_bytes, 0x00027000);
+  const auto x_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a.xfrag), 0, tiles * 4 * block_bytes, 0x00027000);
+  const auto norm_buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.norm), 0, tiles * kSB * 4, 0x00027000);
+  auto load16 = [&](auto buf, uint32_t at) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(buf, lane16, at, 0));
+  };
 
   // the chunk that is staged next: 32 rows' units by each wavefront, and the tile's norms
   uint32_t tile = tile_begin, f_tile = tile_begin, c = 0, f_c = 0;
-  uint4 x[kScreenKb];
+  uint4 x0, x1, x2, x3;   // (an array goes to scratch memory, and every load is waited for at once)
+  static_assert(kScreenKb == 4, "registers of a chunk");
   float xn_reg;
-  const uint4 *xf = a.xfrag + ((uint64_t)tile_begin * 4 + wave) * a.kb_n * 64 + lane;
+  uint32_t xf = (tile_begin * 4 + wave) * block_bytes;
   auto fetch = [&]() {
-#pragma unroll
-    for (uint32_t j = 0; j < kScreenKb; ++j) {   // (past the last block: that one again, never used)
-      const uint32_t kb = f_c * kScreenKb + j < a.kb_n ? f_c * kScreenKb + j : a.kb_n - 1;
-      x[j] = xf[kb * 64];
-    }
-    xn_reg = a.norm[(f_tile < tile_end ? f_tile : tile_end - 1) * kSB + tid % kSB];
+    auto unit = [&](uint32_t j) {   // (past the last block: that one again, never used)
+      return load16(x_buf, xf + (f_c * kScreenKb + j < a.kb_n ? f_c * kScreenKb + j : a.kb_n - 1) * 1024);
+    };
+    x0 = unit(0), x1 = unit(1), x2 = unit(2), x3 = unit(3);
+    xn_reg = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(norm_buf, tid % kSB * 4, (f_tile < tile_end ? f_tile : tile_end - 1) * kSB * 4, 0));
   };
   auto stage = [&](int b) {
-#pragma unroll
-    for (int j = 0; j < kScreenKb; ++j) stage_s[b][(wave * kScreenKb + j) * 64 + lane] = x[j];
+    uint4 *to = &stage_s[b][wave * kScreenKb * 64 + lane];
+    to[0] = x0, to[64] = x1, to[128] = x2, to[192] = x3;
     xn_s[f_tile & 1][tid % kSB] = xn_reg;   // (the same values with every chunk of a tile)
   };
   auto advance = [&]() {
     if (++f_c == n_chunks) {
       f_c = 0;
-      if (++f_tile < tile_end) xf += (uint64_t)4 * a.kb_n * 64;   // (past the end: the last tile again)
+      if (++f_tile < tile_end) xf += 4 * block_bytes;   // (past the end: the last tile again)
     }
   };
 
@@ -1083,7 +1088,7 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
 #pragma unroll
     for (uint32_t j = 0; j < 2; ++j)
 #pragma unroll
-      for (int f = 0; f < NQ; ++f) to[j][f] = qf[f][(kb + j < a.kb_n ? kb + j : a.kb_n - 1) * 128];
+      for (int f = 0; f < NQ; ++f) to[j][f] = load16(q_buf, f * 2 * block_bytes + (kb + j < a.kb_n ? kb + j : a.kb_n - 1) * 2048);
   };
   halfx8 xa[2][MB];
   auto read_rows = [&](halfx8 (&to)[MB], const uint4 *from) {
@@ -1939,7 +1944,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
     // 2^part_log2-th of them, three times that, four times what there was so far, and so on, each a random sample: what may reach
     // the bounds is a few times a bound's rank per pass, and the best of it gives the next bounds.
     // (A sample of 4,096 rows, one of 64,000 and then all rows in order, three products each: 1M x 128, 10,000 queries 7,640 to
-    // 7,940 us, with passes over parts 7,554, with first products only 4,770 to 4,950.)
+    // 7,940 us, with passes over parts 7,554, with first products only 3,510 to 3,660.)
     a.rows = kSampleRows;
     a.stretch = (double)t.n / kSampleRows;
     a.scores = s.scores;
@@ -2221,13 +2226,14 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   if (round > nq) round = nq;
   // Two parts where products take the time (up to 64 queries a call reads rows, few rows are a matter of
   // launches) and where near rows' scores lose no more than with three: from 65 columns on, see bf_score_kernel.  First parts
-  // only where that costs less than it saves, which is a question of the queries and, since every row is read once more to be
-  // rounded, of the columns.  Two parts / first parts: 1M x 128, 512 queries 656 / 561 us, 700 737 / 670; 100,000 x 300, 700 274 /
-  // 292, 1,000 (above the line) 312; 200,000 x 768, k = 100, 700 1,038 / 1,010, 1,000 1,298 / 1,138; 200,000 x 960, 700 1,132 /
-  // 1,107, 512 803 / 1,009; 50,000 x 400, 700 235 / 325, 1,000 319 / 355.
+  // only where that costs less than it saves: every row is read once more to be rounded, and there are more passes.  That is a
+  // question of the queries and, since a pass has a least time, of all scores.  Two parts / first parts, us: 1M x 128, 256 queries
+  // 410 / 430, 512 656 / 491; 200,000 x 128, 512 207 / 224, 700 255 / 243; 200,000 x 768, k = 100, 400 743 / 743, 700 1,038 / 852;
+  // 200,000 x 960, 512 803 / 795, 1,000 1,452 / 974; 100,000 x 300, 512 224 / 236, 700 274 / 255; 50,000 x 400, 700 235 / 291, 1,000
+  // 319 / 317; 30,000 x 96, 700 133 / 132, 2,500 192 / 177.
   const bool halves = !dense && nq > 64 && kb_n >= 6;
   uint64_t x_rows = 0;
-  if (halves && nq >= 512 + kb_n * 16) {
+  if (halves && nq > 512 && ((uint64_t)nq * n >= 50'000'000 || nq >= 512 + kb_n * 16)) {
     x_rows = kScreenBytes / (kb_n * 32) / kSB * kSB;
     if (x_rows > (n + kSB - 1) / kSB * kSB) x_rows = (n + kSB - 1) / kSB * kSB;
   }

@@ -244,7 +244,7 @@ def _check_some(H, X, Q, k, metric, every=13):
 
 
 # Two half-precision parts: more than 64 queries and 64 columns, more than 16,384 rows and than 2^24 scores.  All products
-# (below 512 queries and as many more as columns) or those of first parts (tiles of 256 queries): 100 and 700 queries in most tests below,
+# (up to 512 queries; with fewer than 50 million scores below 512 and as many more as columns) or those of first parts (tiles of 256 queries): 100 and 700 queries in most tests below,
 # which also have sizes with fewer scores than that (three parts).
 PARTS = [(100, 170_000), (700, 30_000)]
 
@@ -263,7 +263,7 @@ def test_two_parts(H, n, d, nq, k, metric):
 @pytest.mark.parametrize("n,d,nq,k,metric,spread", [
     (32_768, 80, 640, 10, oracle.L2, 1.0), (32_769, 82, 640, 10, oracle.IP, 1.0), (524_289, 66, 600, 10, oracle.L2, 1.0),
     (131_073, 130, 700, 256, oracle.L2, 1.0), (60_001, 132, 700, 256, oracle.IP, 1.0), (60_000, 96, 650, 10, oracle.L2, 0.05),
-    (140_000, 96, 650, 100, oracle.IP, 0.05), (60_000, 99, 650, 100, oracle.L2, 0.01)])
+    (100_000, 230, 513, 10, oracle.L2, 1.0), (140_000, 96, 650, 100, oracle.IP, 0.05), (60_000, 99, 650, 100, oracle.L2, 0.01)])
 def test_first_parts(H, n, d, nq, k, metric, spread):
     X, Q = _points(n, d, n + d), _points(nq, d, k)
     if spread < 1.0:
