@@ -37,8 +37,8 @@ KERNEL_SOURCES = ("paper_2503_17911_amd/csrc/search_kernel.hpp", "paper_2503_179
                   "paper_2503_17911_amd/csrc/entry.hip")
 MEASURED_TRAFFIC = {
     # sha256 of KERNEL_SOURCES -> bytes per launch on c2, ef=128, multi-expansion, 10,000 queries scheduled by 256 pivots
-    # (medians over the 174 launches of that grid in one run of this script under rocprofv3 --pmc, profiles/)
-    "1e281538e03328ab46c9558d54e05211697300895f10e3a521ecd073ebe20ab5": 837321.0 * 1024 * 2.0 + 5000.0 * 1024 * 1.0,
+    # (medians over the 323 launches of that pool in one run of this script under rocprofv3 --pmc, profiles/)
+    "0c7041e1ec31760f98bf3b06c3501babecb6da6a2a5c566b0ca7fdd591fd4260": 842263.0 * 1024 * 2.0 + 5000.0 * 1024 * 1.0,
 }
 
 
