@@ -36,8 +36,10 @@ constexpr int kRelayWorkers = 4;
 __host__ __device__ constexpr int relay_waves(int bits, int lpr, int m) { return (bits == 8 ? lpr <= 8 : lpr <= 4 && m < 8) ? 5 : 4; }
 __host__ __device__ constexpr uint32_t relay_queries(int bits, int lpr, int m) { return relay_waves(bits, lpr, m) == 5 ? 3u : 2u; }
 
-// Whether every slot of an adjacency row has lanes of its own: no list of the unvisited neighbours then.
-__host__ __device__ constexpr bool relay_by_slot(uint32_t lpr, uint32_t degree) { return degree * lpr <= 64u; }
+// Whether every slot of an adjacency row has lanes of its own: no list of the unvisited neighbours then.  (Built for rows of one
+// and two lanes; both the LDS that a launch is granted and the kernel that is launched follow from this.)
+__host__ __device__ constexpr bool relay_by_slot(uint32_t lpr, uint32_t degree) { return lpr <= 2 && degree * lpr <= 64u; }
+static_assert(relay_by_slot(1, ANN_MAX_DEGREE), "rows of one lane have no kernel with a list");
 
 constexpr int kNear = 32;   // un-expanded pool entries and candidates that the next step's nodes are picked from
 

@@ -74,3 +74,24 @@ def test_batches_and_base_sets_on_both_sides_of_what_is_resident(n, degree):
         assert all((g == np.tile(w, (rep, 1))[:nq]).all() for g, w in zip(got[:3], want))
         assert (got[3][:, 0] == np.tile(want[3], (rep, 1))[:nq, 0]).all()
     ix.close()
+
+
+def test_longer_rows_on_both_sides_of_what_fits():
+    """Rows of four lanes and few neighbours: the kernel lists them, and its LDS holds the lists beside a query's bits.  (Bits with
+    lists in 160 KB: up to 1,261,952 nodes with four expansions and one pool register per lane, 1,215,872 with eight and four.)"""
+    import gpu_harness as H
+    d, degree, most = 130, 16, 1_270_000
+    rng = np.random.default_rng(4)
+    X = rng.standard_normal((most, d), dtype=np.float32)
+    lv = oracle.sq_fit(X, 8)
+    Q = rng.standard_normal((3, d)).astype(np.float32)
+    for n in (1_210_000, 1_230_000, 1_255_000, most):
+        adj = (np.arange(n, dtype=np.int64)[:, None] + rng.integers(1, n // degree, (n, degree)) + np.arange(degree) * (n // degree)) % n
+        adj = adj.astype(np.uint32)
+        part = oracle.SQLevel(8, lv.lo, lv.delta, lv.codes[:n], lv.norm_term[:n])
+        ix = H.GpuIndex(X[:n], adj, 11, [part], oracle.L2)
+        for ef, p in ((40, 4), (200, 8)):
+            got = ix.search(Q, ef, mode=1, expansions_per_step=p, visited_slots=0)
+            want = oracle.search_batch(part, d, adj, 11, Q, ef, expansions_per_step=p)
+            assert all((g == w).all() for g, w in zip(got[:3], want)) and (got[3][:, 0] == want[3][:, 0]).all()
+        ix.close()
