@@ -1459,6 +1459,7 @@ __device__ __forceinline__ uint64_t range_entries(const RangeArgs &a, uint32_t q
   __syncthreads();
   return b;
 }
+// VEC4: rows and queries are read 16 bytes at a time (both aligned to that).
 template <bool VEC4, int THREADS>
 __global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
   constexpr uint32_t kRoomHere = range_room(THREADS), kLanes = THREADS == kWave ? 4 : 8;   // lanes to a row
@@ -1972,7 +1973,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       if (rc != ANN_OK) return rc;
       range.last = to == parts;
       if (range.last && (uint64_t)s.want * t.d >= 32768) range.few = 0;   // (see bf_range_kernel)
-      if (s.vec4) {
+      if (s.vec4 && reinterpret_cast<uintptr_t>(qr) % 16 == 0) {
         if (range.few) bf_range_kernel<true, kWave><<<m, kWave, 0, t.st>>>(range);
         bf_range_kernel<true, kSelThreads><<<m, kSelThreads, 0, t.st>>>(range);
       } else {

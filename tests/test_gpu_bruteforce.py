@@ -446,6 +446,26 @@ def test_two_parts_of_rows_that_are_not_aligned(H, nq, n):
     H.check_rerank(H.as_u32(ids)[::7], dist.cpu().numpy()[::7], oid, odist.astype(np.float32), rel=1e-6)
 
 
+@pytest.mark.parametrize("nq,n", PARTS)
+def test_two_parts_of_queries_that_are_not_aligned(H, nq, n):
+    """Rows on 16-byte boundaries, queries not: no kernel reads these 16 bytes at a time."""
+    import torch
+    import paper_2503_17911_amd as ann
+    d, k = 96, 10
+    X, Q = _points(n, d, 81), _points(nq, d, 82)
+    buf = torch.empty(nq * d + 1, device=H.DEV)
+    buf[1:] = H.dev(Q).reshape(-1)
+    x = H.dev(X)
+    ids = torch.empty((nq, k), dtype=torch.int32, device=H.DEV)
+    dist = torch.empty((nq, k), device=H.DEV)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        ann.ann_bruteforce_topk(x, n, d, buf[1:], nq, k, ann.L2, ids, dist, H.stream_ptr())
+        torch.cuda.synchronize()
+    assert not any("bf_range_kernel<true" in e.name for e in prof.events())
+    oid, odist = oracle.bruteforce_topk(X, Q[::7], k, metric=oracle.L2)
+    H.check_rerank(H.as_u32(ids)[::7], dist.cpu().numpy()[::7], oid, odist.astype(np.float32), rel=1e-6)
+
+
 @pytest.mark.parametrize("n,nq", [(100, 33), (3000, 65), (12_000, 100), (16_000, 64), (20_000, 128), (20_003, 129), (33_000, 70)])
 @pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
 def test_query_tiles_by_the_number_of_rows(H, n, nq, metric):
