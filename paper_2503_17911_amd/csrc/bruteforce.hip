@@ -312,7 +312,10 @@ constexpr int kSK = 32;           // columns per chunk
 constexpr int kSB = 128;          // base rows per tile
 constexpr int kPlane = kSB * kSK * 2;   // bytes of one plane of a chunk
 constexpr uint64_t kScreenBytes = 128ull << 20;   // of rows' first parts at a time
-constexpr uint32_t kCallCounters = 9;   // of CallState
+constexpr uint32_t kCallCounters = 12;   // of CallState
+// One query in kVoters votes (additions to one counter, one after the other: by all of 10,000 queries 110 us; an odd number, so that
+// workgroups that do are on all dies: 9,000 queries x 20,000 rows, one in sixteen 15 us, in seventeen 3).
+constexpr uint32_t kVoters = 17;
 constexpr int kHitList = 96;      // entries a wavefront collects before they go to global memory
 constexpr float kFarNorm2 = 0x1.fp31f;   // two parts: rows of this squared norm and more, scaled, are left out (half precision ends at 2^16)
 constexpr uint32_t kSampleRows = 4096;   // scores one selection workgroup takes; first sample (or twice that, see ann_bruteforce_topk)
@@ -478,11 +481,14 @@ struct CallState {
   uint32_t n_uncertain;   // queries whose k-th distance is not certain (listed by the rerank kernel)
   uint32_t far_rows;      // inner product: rows whose squared norm is no float; the first kFarRows are listed
   uint32_t n_wide;        // two parts: queries whose scores would be nearer to their value with three
+  uint32_t n_lost;        // first parts: queries for whose entries there was no room
+  uint32_t abandoned;     // first parts: not 0: the passes were given up, all queries of the round and of those after it are lost
   uint32_t left_out;      // two parts, L2: not 0: rows were left out for their size
   uint32_t max_norm;      // inner product, or first parts: bits of the largest squared norm of the others
   uint32_t most_entries;  // of a query in the last pass over uncertain queries
   uint32_t n_next, n_fp32;   // uncertain queries for another pass; for the fp32 kernel
   uint32_t max_rest;      // first parts: bits of the largest squared norm of what they leave of a scaled row
+  uint32_t n_hopeless;    // first parts: queries of which the pass before this one tells that they will be lost, see vote()
   uint32_t far_row[kFarRows];
 };
 
@@ -559,17 +565,21 @@ __device__ __forceinline__ double half_room(double nq, double nx, uint32_t d, ui
 // where `value` bounds the score of the row in question: |q| times what the row's first part leaves, and the other way
 // round (both norms are known: 0.4 of the 2^-11 |x| that a rounding may leave), and what half_room() allows for.  No row
 // of the passes so far is larger than max_norm (its square), or leaves more than max_rest (the scaled one's square); L2:
-// a row whose score is at most `value` has |x| <= |q| + sqrt(distance) as well (a little more, so that it also
-// holds for rows whose score only seems to be that).
+// a row whose score is at most `value` has |x| <= |q| + sqrt(distance) as well, and a rounding leaves it at most 2^-11 |x| and
+// 2^-25 per column, scaled, whatever larger rows leave.  (A little more, so that no other row's score seems to be that:
+// with |x| = 17/16 |q| + sqrt(distance) + u it is too large by |q|^2 / 256 + |q| sqrt(distance) / 8 + |q| u / 8 at least, and first
+// parts take 2^-9 |q| |x| off at most.)  1M x 128, 10,000 queries, norms like exp(z): by the largest row's rest three queries
+// in four are lost, so none.
 __device__ __forceinline__ float screen_room(float nq, float q_rest, float value, uint32_t d, uint32_t kb_n, uint32_t metric, float x_unit, float unscale,
                                              uint32_t max_norm, uint32_t max_rest) {
-  const double more = 1.0 + 0x1p-10, x_rest = (double)__fsqrt_rn(__uint_as_float(max_rest)) * (double)x_unit * more;
+  const double more = 1.0 + 0x1p-10;
   double nx = (double)__fsqrt_rn(__uint_as_float(max_norm)) * more;
   if (metric == ANN_L2) {
     const double dist = (double)nq * nq + (double)value;
     nx = fmin(nx, 1.0625 * (double)nq + (double)__fsqrt_rn(fmaxf((float)dist, 0.0f)) * more);
   }
   const double room = half_room((double)nq, nx, d, kb_n, metric, (double)x_unit, (double)unscale / (double)x_unit);
+  const double x_rest = fmin((double)__fsqrt_rn(__uint_as_float(max_rest)) * (double)x_unit, 0x1p-11 * nx + 0x1p-25 * (double)__fsqrt_rn((float)d) * (double)x_unit) * more;
   const double rest = x_rest * (double)nq + (nx + x_rest) * (double)q_rest;
   return (float)((room + (metric == ANN_L2 ? 2.0 : 1.0) * rest) * more);
 }
@@ -598,7 +608,7 @@ struct TileEnd {
     for (int f = 0; f < NQ; ++f) {
       const uint32_t q = q0 + f * 32 + lane_id() % 32;
       top[f] = a.scores == nullptr && q < a.nq ? unorder_f32((uint32_t)(a.bound[q] >> 32)) : -INFINITY;
-      // (no bound, FLT_MAX: everything; a query whose norm is no float: nothing, its result is found to be uncertain)
+      // (no bound, FLT_MAX: everything; a lost query, NaN: nothing; a query whose norm is no float: nothing, its result is found to be uncertain)
       if (SCREEN && top[f] > -INFINITY && top[f] < 0x1.fffffep127f) {
         float room = screen_room(a.q_norm[q], a.q_rest[q], top[f], a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
         room = screen_room(a.q_norm[q], a.q_rest[q], top[f] + room, a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
@@ -938,24 +948,35 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
 // first parts alone, a third of the work.  What that leaves is re-evaluated in fp64 before anything is
 // selected or bounded by it (bf_range_kernel).
 //
-// bf_halve_rows_kernel brings the first parts of a pass' rows, or of a slab of it, into the order
-// the matrix instruction wants (16-byte unit ((row / 32) * kb_n + kb) * 64 + lane) and writes
+// Where that leaves too much (see bf_range_kernel) the call is repeated with both parts of all rows, bf_pair_kernel.
+//
+// bf_halve_rows_kernel brings the first parts (PLANES 1) or both of a pass' rows, or of a slab of it, into the order
+// the matrix instruction wants (16-byte unit (((row / 32) * kb_n + kb) * PLANES + plane) * 64 + lane) and writes
 // the rows' squared norms, summed in fp64 (+inf: left out of the scores).  One workgroup per 32 rows, a wavefront
-// takes every fourth block of 16 columns.
-template <bool VEC4>
+// takes every fourth block of 16 columns.  Both parts: reading and writing 128 MB each way takes 47 us.
+template <bool VEC4, int PLANES>
 __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *__restrict__ frag, float *__restrict__ norm) {
   __shared__ double part_s[8][32];
   __shared__ float rest_s[8][32];
   const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  uint32_t abandoned = 0, n_hopeless = 0;
+  if constexpr (PLANES == 1) {   // (both parts: no state but in the last pass)
+    abandoned = a.state->abandoned;
+    n_hopeless = a.state->n_hopeless;
+  }
   const uint64_t at = (uint64_t)blockIdx.x * 32 + lane % 32;
   const int e = __builtin_amdgcn_readfirstlane(half_exponent(rows_sq(a.sample_sq)));
   const float scale = ldexpf(1.0f, e), far_from = ldexpf(kFarNorm2, -2 * e);
+  if (abandoned || n_hopeless * (4 * kVoters) > a.nq) {   // (see bf_range_kernel; read with the sample's norms)
+    if (blockIdx.x == 0 && tid == 0) a.state->abandoned = 1u;
+    return;
+  }
   uint64_t r = at < a.rows ? at : a.rows - 1;
   r = a.part_w ? part_row(a, a.first + r) : (a.stretch != 0.0 ? sample_row(a.first + r, a.stretch) : a.first + r);
   const bool real = at < a.rows && (a.part_w == 0 || r < a.n);
   if (!real && a.part_w) r = a.n - 1;
   const float *row = a.x + r * a.d;
-  uint4 *to = frag + (uint64_t)blockIdx.x * a.kb_n * 64 + lane;
+  uint4 *to = frag + (uint64_t)blockIdx.x * a.kb_n * (64 * PLANES) + lane;
   double sq = 0.0;
   float rest = 0.0f;
 #pragma unroll 2
@@ -982,7 +1003,9 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
     uint32_t w[4][2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) split2(v[2 * j], v[2 * j + 1], scale, w[j]);
-    to[(uint64_t)kb * 64] = make_uint4(w[0][0], w[1][0], w[2][0], w[3][0]);
+#pragma unroll
+    for (int p = 0; p < PLANES; ++p) to[(uint64_t)kb * (64 * PLANES) + p * 64] = make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]);
+    if constexpr (PLANES == 2) continue;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const halfx2 hi = __builtin_bit_cast(halfx2, w[j][0]);
@@ -997,8 +1020,10 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
   float t = (float)(((part_s[0][tid] + part_s[1][tid]) + (part_s[2][tid] + part_s[3][tid])) + ((part_s[4][tid] + part_s[5][tid]) + (part_s[6][tid] + part_s[7][tid])));
   const bool in = real && t < far_from;
   norm[at] = in ? (a.metric == ANN_L2 ? t : 0.f) : INFINITY;
+  if (PLANES == 2 && a.state == nullptr) return;
   if (a.metric == ANN_L2) {
     if (real && t >= far_from && t < INFINITY) a.state->left_out = 1u;
+    if (PLANES == 2) return;
   } else if (real && t >= far_from && a.list_far) {
     const uint32_t n = atomicAdd(&a.state->far_rows, 1u);
     if (n < kFarRows) a.state->far_row[n] = (uint32_t)r;
@@ -1014,10 +1039,141 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
     rest = fmaxf(rest, __int_as_float(xor_lane_i32(__float_as_int(rest), m)));
   }
   if (tid == 0 && *(volatile uint32_t *)&a.state->max_norm < __float_as_uint(t)) atomicMax(&a.state->max_norm, __float_as_uint(t));
-  if (tid == 0 && *(volatile uint32_t *)&a.state->max_rest < __float_as_uint(rest)) atomicMax(&a.state->max_rest, __float_as_uint(rest));
+  if (PLANES == 1 && tid == 0 && *(volatile uint32_t *)&a.state->max_rest < __float_as_uint(rest)) atomicMax(&a.state->max_rest, __float_as_uint(rest));
 }
 
-// A workgroup of four wavefronts takes 128 rows x 256 queries per tile, a wavefront 128
+// Both parts.  A workgroup of four wavefronts takes 128 rows x 256 queries per tile, a wavefront 128
+// x 64: eight accumulators, 128 registers, so that six products of 16 columns come to two
+// LDS reads of rows and one global read of queries.  No vector instruction
+// stands between the matrix instructions; two wavefronts share a SIMD, and one's
+// end of a tile falls into the other's products.  10,000 x 262,144 x 128: 1.75 to 2.0
+// ms, by the clock: 3.27 M cycles each time, at 1.86 down to 1.63 GHz as the card warms up,
+// the matrix cores busy in 60 % of them = 383 to 336 TFLOP/s of fp32 work (bf_score_kernel with two parts: 2.68
+// ms; with three: 3.7).  The rate is the same at 768 columns, so the loop over chunks is what leaves the
+// rest idle, not the end of a tile.  128 queries per tile: 7 % slower; first products onto a constant zero instead
+// of cleared registers and the rows' parts requested one block ahead: 1.5 %.
+constexpr int kPairQueries = 256;
+__global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
+  constexpr int MB = 4, NQ = 2, QT32 = 4 * NQ;
+  static_assert(QT32 * 32 == kPairQueries, "tile shape");
+  __shared__ __align__(16) uint4 stage_s[2][4 * 2 * 2 * 64];   // [row / 32][kb][plane][lane]
+  __shared__ __align__(16) float xn_s[2][kSB];
+  __shared__ uint64_t hit_s[4][kHitList];
+  __shared__ uint8_t hit_q_s[4][kHitList];
+
+  // (as bf_score_kernel: a group of query tiles over all of a die's slabs, then the next group)
+  const uint32_t die = blockIdx.x & 7u, nth = blockIdx.x >> 3, die_slabs = (a.slabs + 7) / 8;
+  const uint32_t group = nth / (a.q_group * die_slabs), left = nth % (a.q_group * die_slabs);
+  const uint32_t width = a.q_tiles - group * a.q_group < a.q_group ? a.q_tiles - group * a.q_group : a.q_group;
+  const uint32_t qt = group * a.q_group + left % width, slab = left / width * 8u + die;
+  const uint32_t tiles = (uint32_t)((a.rows + kSB - 1) / kSB);
+  const uint32_t tile_begin = slab * a.tiles_per_slab;
+  const uint32_t tile_end = tile_begin + a.tiles_per_slab < tiles ? tile_begin + a.tiles_per_slab : tiles;
+  if (slab >= a.slabs || tile_begin >= tile_end) return;
+
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const uint32_t n_chunks = a.kb_n / 2;
+  const uint4 *qf[NQ];
+#pragma unroll
+  for (int f = 0; f < NQ; ++f) qf[f] = a.qfrag + (uint64_t)(qt * QT32 + wave * NQ + f) * a.kb_n * 128 + lane;
+
+  // the chunk (two blocks of 16 columns) that is staged next: 32 rows' four units by each wavefront, and the tile's norms
+  uint32_t tile = tile_begin, f_tile = tile_begin, c = 0, f_c = 0;
+  uint4 x0, x1, x2, x3;
+  float xn_reg;
+  const uint4 *xf = a.xfrag + ((uint64_t)tile_begin * 4 + wave) * a.kb_n * 128 + lane;
+  auto fetch = [&]() {
+    const uint4 *p = xf + f_c * 256;
+    x0 = p[0];
+    x1 = p[64];
+    x2 = p[128];
+    x3 = p[192];
+    xn_reg = a.norm[(f_tile < tile_end ? f_tile : tile_end - 1) * kSB + tid % kSB];
+  };
+  auto stage = [&](int b) {
+    uint4 *to = &stage_s[b][wave * 256 + lane];
+    to[0] = x0;
+    to[64] = x1;
+    to[128] = x2;
+    to[192] = x3;
+    xn_s[f_tile & 1][tid % kSB] = xn_reg;   // (the same values with every chunk of a tile)
+  };
+  auto advance = [&]() {
+    if (++f_c == n_chunks) {
+      f_c = 0;
+      if (++f_tile < tile_end) xf += (uint64_t)4 * a.kb_n * 128;   // (past the end: the last tile again)
+    }
+  };
+
+  TileEnd<MB, NQ> end(a, (qt * QT32 + wave * NQ) * 32, hit_s[wave], hit_q_s[wave]);
+  floatx16 acc[MB][NQ];
+  auto load_q = [&](uint4 (&to)[NQ][2], uint32_t kb) {
+#pragma unroll
+    for (int f = 0; f < NQ; ++f)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) to[f][p] = qf[f][kb * 128 + p * 64];
+  };
+  halfx8 xa[2][2];
+  auto read_rows = [&](halfx8 (&to)[2], const uint4 *from) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) to[p] = __builtin_bit_cast(halfx8, from[p * 64]);
+  };
+  // 16 columns: the products of 32 rows at a time while the next 32 rows' parts (after the last: those at `next`) are on their way
+  auto multiply = [&](const uint4 (&q)[NQ][2], const uint4 *from, const uint4 *next, bool first) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      if (m + 1 < MB)
+        read_rows(xa[(m + 1) & 1], from + (m + 1) * 256);
+      else if (next)
+        read_rows(xa[0], next);
+      // the small products first
+      constexpr int pa[3] = {1, 0, 0}, pb[3] = {0, 1, 0};
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int f = 0; f < NQ; ++f) {
+          const floatx16 zero = {};
+          acc[m][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[m & 1][pa[t]], __builtin_bit_cast(halfx8, q[f][pb[t]]), first && t == 0 ? zero : acc[m][f], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  uint4 q0[NQ][2], q1[NQ][2];
+  fetch();
+  load_q(q0, 0);
+  stage(0);
+  advance();
+  fetch();
+  __syncthreads();
+  int cur = 0;
+  for (;;) {
+    const uint4 *from = &stage_s[cur][lane];
+    load_q(q1, 2 * c + 1);
+    read_rows(xa[0], from);
+    __builtin_amdgcn_sched_barrier(0);
+    if (c == 0)
+      multiply(q0, from, from + 128, true);
+    else
+      multiply(q0, from, from + 128, false);
+    stage(cur ^ 1);
+    load_q(q0, 2 * f_c);
+    advance();
+    fetch();
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(q1, from + 128, nullptr, false);
+    if (++c == n_chunks) {
+      end.finish(acc, xn_s[tile & 1], tile * kSB);
+      c = 0;
+      if (++tile == tile_end) break;
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+  if (end.n_hits > 0) end.flush();
+}
+
+// First parts.  A workgroup of four wavefronts takes 128 rows x 256 queries per tile, a wavefront 128
 // x 64: eight accumulators, 128 registers.  64 columns of rows are staged through LDS at a time; queries
 // come from the L2, 32 columns ahead of the products.  No vector instruction stands between the matrix
 // instructions; two wavefronts share a SIMD, and one's end of a tile falls into the other's products.
@@ -1034,6 +1190,7 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
   __shared__ uint64_t hit_s[4][kHitList];
   __shared__ uint8_t hit_q_s[4][kHitList];
 
+  const uint32_t abandoned = a.state->abandoned;
   // (as bf_score_kernel: a group of query tiles over all of a die's slabs, then the next group)
   const uint32_t die = blockIdx.x & 7u, nth = blockIdx.x >> 3, die_slabs = (a.slabs + 7) / 8;
   const uint32_t group = nth / (a.q_group * die_slabs), left = nth % (a.q_group * die_slabs);
@@ -1117,6 +1274,8 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
   uint4 q0[2][NQ], q1[2][NQ];
   fetch();
   load_q(q0, 0);
+  if (abandoned) return;
+  if (blockIdx.x == 0 && tid == 0) a.state->n_hopeless = 0u;
   stage(0);
   advance();
   fetch();
@@ -1149,6 +1308,39 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
   if (end.n_hits > 0) end.flush();
 }
 
+// What bf_range_kernel, and the selection from the sample before it, need (see there).
+struct RangeArgs {
+  const float *x, *q;
+  const float *sample_sq, *unscale, *q_norm, *q_rest;
+  CallState *state;
+  uint32_t d, kb_n, metric, want, most;
+  bool last;   // pass
+  // what a pass tells of the last: entries up to two rooms beyond the one of rank `rank`, each of which stands for `weight`; more
+  // than `limit`, and the query will be lost
+  uint32_t rank;
+  float weight, limit;
+  uint32_t few;   // entries that a wavefront takes
+  uint64_t *buf;
+  uint32_t *count;
+  uint32_t cap;
+  uint64_t *bound;
+};
+constexpr int kSelThreads = 256;
+constexpr uint32_t kFewEntries = 8 * kWave;
+constexpr uint32_t range_room(int threads) { return threads == kWave ? kFewEntries : 4 * kSelThreads; }   // entries that may be among the best
+
+// How far the score of an entry up to two rooms beyond a bound may lie from its value.
+__device__ __forceinline__ float entry_room(const RangeArgs &a, uint32_t q, float bound) {
+  const float x_unit = ldexpf(1.0f, -half_exponent(rows_sq(a.sample_sq))), q_norm = a.q_norm[q], q_rest = a.q_rest[q], unscale = a.unscale[q];
+  const uint32_t max_norm = a.state->max_norm, max_rest = a.state->max_rest;
+  const float room = screen_room(q_norm, q_rest, bound, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);
+  return screen_room(q_norm, q_rest, bound + 3.0f * room, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);
+}
+// A voting query tells whether the last pass will lose it.
+__device__ __forceinline__ void vote(const RangeArgs &a, uint32_t q, uint32_t n_near) {
+  if (q % kVoters == 0 && (float)n_near * a.weight > a.limit) atomicAdd(&a.state->n_hopeless, 1u);
+}
+
 // ---------------------------------------------------------------------------
 // Selection by bisection on the order-preserving bits of the scores: a bound
 // that at least `want` and at most `most` of the workgroup's entries reach.
@@ -1157,7 +1349,6 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
 // With more than `most` equal scores at the bound the ids decide (ascending).
 // Entries with an ordered score above kMaxScore (+inf) are none.
 constexpr uint32_t kMaxScore = 0xFF7FFFFFu;   // FLT_MAX in score order
-constexpr int kSelThreads = 256;
 
 // THREADS: of the workgroup; one wavefront needs no LDS and no barriers.
 template <int EPT, int THREADS = kSelThreads>
@@ -1244,15 +1435,42 @@ struct Selector {
         ihi = mid;
     }
   }
+  // The smallest score.
+  __device__ __forceinline__ uint32_t lowest() {
+    uint32_t mn = 0xFFFFFFFFu;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) mn = key[e] < mn ? key[e] : mn;
+#pragma unroll
+    for (int x = 1; x < kWave; x <<= 1) {
+      const uint32_t o = (uint32_t)xor_lane_i32((int)mn, x);
+      mn = o < mn ? o : mn;
+    }
+    if constexpr (THREADS > kWave) {
+      if (threadIdx.x % kWave == 0) red[parity * 4 + threadIdx.x / kWave] = mn;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < THREADS / kWave; ++w) mn = red[parity * 4 + w] < mn ? red[parity * 4 + w] : mn;
+      parity ^= 1;
+    }
+    return mn;
+  }
+  // How many entries lie up to two rooms beyond the one of that rank, give or take a few places (a step of the bisection
+  // takes a microsecond in all: the smallest score for ranks up to four).
+  __device__ __forceinline__ uint32_t near_rank(uint32_t rank, float room) {
+    uint32_t n;
+    const uint32_t from = rank <= 4 ? lowest() : (uint32_t)(run(rank, rank + rank / 4 + 1, n) >> 32);
+    const float last = unorder_f32(from) + 2.0f * room;
+    return count_up_to(last < INFINITY ? order_u32(last) : kMaxScore);
+  }
 };
 
 // The best of one stretch of a query's scores.  Sample (stretch != 0): the bound
-// is all that is wanted.  Otherwise the entries go to out[q][blockIdx.y][most],
+// is all that is wanted (vote, with first parts: and what it tells of the passes to come).  Otherwise the entries go to out[q][blockIdx.y][most],
 // padded with all-ones, and the bound is the smallest of the stretches'.
-template <int EPT>
+template <int EPT, typename... Vote>
 __global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const float *__restrict__ scores, uint32_t ld, uint64_t rows,
                                                                        double stretch, uint32_t want, uint32_t most,
-                                                                       uint64_t *__restrict__ bound, uint64_t *__restrict__ out) {
+                                                                       uint64_t *__restrict__ bound, uint64_t *__restrict__ out, Vote... range) {
   __shared__ uint32_t red[16], wave_at[4];
   const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const uint64_t r0 = (uint64_t)blockIdx.y * (EPT * kSelThreads);
@@ -1275,6 +1493,12 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const flo
   const uint64_t b = s.run(want, most, n_kept);
   if (out == nullptr) {
     if (tid == 0) bound[q] = b;
+    auto tell = [&](const RangeArgs &a) {
+      if (q % kVoters != 0 || (uint32_t)(b >> 32) >= kMaxScore) return;
+      const uint32_t n_near = s.near_rank(a.rank, entry_room(a, q, unorder_f32((uint32_t)(b >> 32))));
+      if (tid == 0) vote(a, q, n_near);
+    };
+    (tell(range), ...);
     return;
   }
   if (tid == 0) atomicMin(reinterpret_cast<unsigned long long *>(&bound[q]), (unsigned long long)b);
@@ -1309,6 +1533,7 @@ struct CertainArgs {
   CallState *state;
   const float *sample_sq, *unscale;   // two parts (otherwise NULL): as in ScoreArgs
   float *below;        // [nq] out
+  bool screened;       // entries are those of bf_range_kernel: none of a query that is lost
 };
 
 // The best of a query's entries.  count == NULL: all `cap` of them (all-ones:
@@ -1347,7 +1572,8 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
     }
   }
   const uint32_t found = count ? count[q] : cap;
-  const uint32_t n_ent = found < cap ? found : cap;
+  const bool repeated = c.screened && c.state->abandoned, lost = repeated || (c.screened && found > cap);   // (repeated: the whole call)
+  const uint32_t n_ent = lost ? 0u : (found < cap ? found : cap);
   Selector<EPT> s;
   s.red = red;
 #pragma unroll
@@ -1396,9 +1622,11 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
     // (rows left out for their size were not counted)
     if ((uint32_t)(out >> 32) >= kMaxScore) below = c.unscale && c.state->left_out ? -INFINITY : INFINITY;
     // (two parts: from here on the query's squared norm in fp32, which its scale comes from, may be infinite and its scores no numbers)
-    if (c.unscale && sq >= 0x1p127) below = -INFINITY;
+    if (lost || (c.unscale && sq >= 0x1p127)) below = -INFINITY;
     if (sq != sq) below = INFINITY;
     if (sq == INFINITY) below = -INFINITY;
+    if (repeated) below = INFINITY;
+    if (lost && below == -INFINITY) atomicAdd(&c.state->n_lost, 1u);
     c.below[q] = below;
   }
 #pragma unroll
@@ -1412,31 +1640,27 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
 // A query's entries after a pass of bf_screen_kernel, whose scores may be a room (screen_room) off: the score that `want` to
 // `most` of them reach bounds the next pass, and what is more than two rooms beyond it goes (one for the bound, one for the
 // entry: it is not among the `want` best).  After the last pass what is left is re-evaluated in fp64, the score rounded
-// once, and the best `want` to `most` of that stay.  More than there is room for: the count says so to the last selection.
+// once, and the best `want` to `most` of that stay.  More than there is room for: the query is lost, and the count says so to the
+// last selection.
+// Where vectors lie far from the origin for their spread, or in narrow clusters, thousands of rows lie within the room, and
+// first parts settle nothing.  A query in kVoters tells, from the sample and each pass, what the last pass will find (see
+// select_round).  Once one voter in four will be lost the passes after it do nothing and the call is repeated with two
+// parts; below that the lost queries are taken up again by themselves.  10,000 queries x 1M x 128, two parts alone / first
+// parts, and centred rows for what these lost / this: 7 spreads from the origin 7.3 / 4.4 / 4.5 ms, 10 7.4 / 21.4 / 7.5, 20
+// 7.8 / 21.4 / 8.0; 100 clusters of spread 0.1 7.7 / 5.3 / 5.5, 0.05 7.9 / 21.0 / 8.2; at the origin (3.69) and for small
+// calls the votes cost 0.5 to 2 %.
 // (Re-evaluating each pass's new entries made the bounds a room tighter and cost more: 200,000 rows, d = 768, k = 100,
 // 2,000 queries: these kernels 263 instead of 660 us.)
 // A wavefront takes a query with up to 512 entries, a workgroup one with more, in a launch of its own: 10,000 queries with
 // about a hundred each, k = 10, d = 128, by workgroups 130 to 205 us a pass, by wavefronts 16 to 57.  After the last pass a workgroup takes every query where there is much
 // to read again, want d >= 32,768 elements: d = 768, k = 100 by both kinds 442 us, by workgroups 222 (d = 300, k = 10, 3,000
 // queries, whole call: 658 by workgroups, 620 by wavefronts; d = 960, k = 10: no difference).
-struct RangeArgs {
-  const float *x, *q;
-  const float *sample_sq, *unscale, *q_norm, *q_rest;
-  const CallState *state;
-  uint32_t d, kb_n, metric, want, most;
-  bool last;   // pass
-  uint32_t few;   // entries that a wavefront takes
-  uint64_t *buf;
-  uint32_t *count;
-  uint32_t cap;
-  uint64_t *bound;
-};
-constexpr uint32_t kFewEntries = 8 * kWave;
-constexpr uint32_t range_room(int threads) { return threads == kWave ? kFewEntries : 4 * kSelThreads; }   // entries that may be among the best
 
-// Those that may be among the best to best[]; the score that `want` to `most` reach.
+// Those that may be among the best to best[]; the score that `want` to `most` reach; n_near (but in the last pass): how many lie
+// within two rooms of the best.
 template <int EPT, int THREADS>
-__device__ __forceinline__ uint64_t range_entries(const RangeArgs &a, uint32_t q, uint32_t n_ent, float room, uint64_t *best, uint32_t *n_best, uint32_t *red) {
+__device__ __forceinline__ uint64_t range_entries(const RangeArgs &a, uint32_t q, uint32_t n_ent, float room, uint64_t *best, uint32_t *n_best, uint32_t *red,
+                                                  uint32_t &n_near) {
   const uint32_t tid = threadIdx.x;
   Selector<EPT, THREADS> s;
   s.red = red;
@@ -1456,6 +1680,7 @@ __device__ __forceinline__ uint64_t range_entries(const RangeArgs &a, uint32_t q
     const uint32_t at = atomicAdd(n_best, 1u);
     if (at < range_room(THREADS)) best[at] = ((uint64_t)s.key[e] << 32) | s.id[e];
   }
+  if (!a.last && q % kVoters == 0) n_near = s.near_rank(a.rank, room);
   __syncthreads();
   return b;
 }
@@ -1467,25 +1692,26 @@ __global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
   __shared__ unsigned long long last_s;
   __shared__ uint64_t best[kRoomHere];
   const uint32_t q = blockIdx.x, tid = threadIdx.x;
-  const uint32_t found = a.count[q];
+  const uint32_t found = a.count[q], abandoned = a.state->abandoned;
   // (none, or taken by the other launch, which may only leave few of many; more than cap: entries were lost)
-  if (found == 0 || found > a.cap || (found <= a.few) != (THREADS == kWave)) return;
+  if (THREADS > kWave && !a.last && tid == 0 && !abandoned && found > a.cap) {
+    vote(a, q, found);
+    a.bound[q] = 0;   // (no number: the query has no more entries)
+  }
+  if (abandoned || found == 0 || found > a.cap || (found <= a.few) != (THREADS == kWave)) return;
   const uint64_t old_bound = a.bound[q];
   if (tid < 2) n_best[tid] = 0;
   if (tid == 0) last_s = 0;
   __syncthreads();
-  const float x_unit = ldexpf(1.0f, -half_exponent(rows_sq(a.sample_sq))), q_norm = a.q_norm[q], unscale = a.unscale[q];
-  const float value = unorder_f32((uint32_t)(old_bound >> 32)), q_rest = a.q_rest[q];
-  const uint32_t max_norm = a.state->max_norm, max_rest = a.state->max_rest;
-  float room = screen_room(q_norm, q_rest, value, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);
-  room = screen_room(q_norm, q_rest, value + 3.0f * room, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);   // (of entries up to two rooms beyond the bound)
+  const float room = entry_room(a, q, unorder_f32((uint32_t)(old_bound >> 32)));
   uint64_t b;
+  uint32_t n_near = 0;
   if constexpr (THREADS == kWave)
-    b = range_entries<8, THREADS>(a, q, found, room, best, n_best, red);
+    b = range_entries<8, THREADS>(a, q, found, room, best, n_best, red, n_near);
   else if (found <= 8 * kSelThreads)
-    b = range_entries<8, THREADS>(a, q, found, room, best, n_best, red);
+    b = range_entries<8, THREADS>(a, q, found, room, best, n_best, red, n_near);
   else
-    b = range_entries<32, THREADS>(a, q, found, room, best, n_best, red);
+    b = range_entries<32, THREADS>(a, q, found, room, best, n_best, red, n_near);
   const uint32_t n = n_best[0];
   const bool bounds = found > a.most && b < old_bound;   // (else the selection took all of them)
   if (!a.last) {
@@ -1494,6 +1720,7 @@ __global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
     if (tid == 0) {
       if (n <= kRoomHere) a.count[q] = n;
       if (bounds) a.bound[q] = b;
+      vote(a, q, n_near);
     }
     return;
   }
@@ -1672,6 +1899,30 @@ static ann_status launch_scores(ScoreArgs a, bool vec4, uint32_t n_cu, hipStream
   return ANN_OK;
 }
 
+// The same with both parts of the rows ahead, a slab of at most x_rows at a time.  A die's group
+// of query tiles is a megabyte of parts, four tiles at least (between 4 and 16 tiles within 1 %).
+static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
+  const uint64_t n = a.rows;
+  a.xfrag = xfrag;
+  a.norm = norm;
+  a.q_tiles = (a.nq + kPairQueries - 1) / kPairQueries;
+  a.q_group = 64 / a.kb_n > 4 ? 64 / a.kb_n : 4;
+  if (a.q_group > a.q_tiles) a.q_group = a.q_tiles;
+  for (a.first = 0; a.first < n; a.first += x_rows) {
+    a.rows = n - a.first < x_rows ? n - a.first : x_rows;
+    const uint32_t tiles = (uint32_t)((a.rows + kSB - 1) / kSB);
+    if (vec4)
+      bf_halve_rows_kernel<true, 2><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
+    else
+      bf_halve_rows_kernel<false, 2><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
+    choose_slabs(tiles, a.q_tiles, n_cu, a.slabs, a.tiles_per_slab);
+    const uint32_t grid = a.q_tiles * ((a.slabs + 7) / 8 * 8);
+    bf_pair_kernel<<<grid, 256, 0, st>>>(a);
+  }
+  ANN_HIP(hipGetLastError());
+  return ANN_OK;
+}
+
 // One pass of first parts, a slab of at most x_rows rows at a time.  A die's group
 // of query tiles is a megabyte of parts, four tiles at least (between 4 and 16 tiles within 1 %).
 static ann_status launch_screen(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
@@ -1685,9 +1936,9 @@ static ann_status launch_screen(ScoreArgs a, bool vec4, uint4 *xfrag, float *nor
     a.rows = n - a.first < x_rows ? n - a.first : x_rows;
     const uint32_t tiles = (uint32_t)((a.rows + kSB - 1) / kSB);
     if (vec4)
-      bf_halve_rows_kernel<true><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
+      bf_halve_rows_kernel<true, 1><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
     else
-      bf_halve_rows_kernel<false><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
+      bf_halve_rows_kernel<false, 1><<<tiles * (kSB / 32), 256, 0, st>>>(a, xfrag, norm);
     choose_slabs(tiles, a.q_tiles, n_cu, a.slabs, a.tiles_per_slab);
     const uint32_t grid = a.q_tiles * ((a.slabs + 7) / 8 * 8);
     bf_screen_kernel<<<grid, 256, 0, st>>>(a);
@@ -1699,6 +1950,8 @@ static ann_status launch_screen(ScoreArgs a, bool vec4, uint4 *xfrag, float *nor
 // ---------------------------------------------------------------------------
 // Queries whose result is not certain (see bf_select_entries_kernel): vectors far
 // from the origin, where the squares cancel, or many rows at the same distance.
+// Where first parts lost a quarter of them or more (see bf_range_kernel; with so many of a call's queries that the passes
+// were given up, all of these), the selection again with two parts.
 // After two parts, where these left more room than three for a quarter as many queries as are
 // uncertain, the selection again with three parts: rows much smaller or larger than the sample's
 // largest lose in half precision, not in bf16.  (300,000 x 128, norms spread like exp(3 z), 2,000
@@ -1888,9 +2141,9 @@ struct Selection {
   uint32_t *count, *cand;
   CallState *state;
   float *sample_sq, *unscale, *q_norm, *q_rest;
-  uint4 *xfrag;        // room for x_rows rows' first parts and their norms
+  uint4 *xfrag;        // room for x_rows rows' first parts, or pair_rows rows' parts, and their norms
   float *xnorm;
-  uint64_t x_rows;
+  uint64_t x_rows, pair_rows;   // first parts; both
 };
 
 // One round: the k nearest rows of the m queries at qr.
@@ -1921,7 +2174,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
   a.list_far = list_far;
   a.sample_sq = halves ? s.sample_sq : nullptr;
   a.unscale = halves ? s.unscale : nullptr;
-  const CertainArgs certain{qr, centre, t.d, s.kb_n, t.metric, s.state, a.sample_sq, a.unscale, s.below};
+  const CertainArgs certain{qr, centre, t.d, s.kb_n, t.metric, s.state, a.sample_sq, a.unscale, s.below, halves && s.x_rows};
   auto select_entries = [&](uint32_t *cnt, uint32_t *to, uint32_t up_to) {
     if (s.cap <= 2048)
       bf_select_entries_kernel<8><<<m, kSelThreads, 0, t.st>>>(s.buf, cnt, s.cap, s.want, up_to, s.bound, to, certain);
@@ -1955,15 +2208,28 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
     a.q_rest = s.q_rest;
     rc = launch_screen(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
     if (rc != ANN_OK) return rc;
+    // What the last pass will leave of a query is the rows up to two rooms beyond the bound that all rows will give, whose rank among
+    // those so far is want / all.  Below one, the best so far lies further out than that bound: by as much as the square
+    // root of the rank corrects (estimate over what was left, 1M x 128, k = 10, 7, 8 and 10 spreads from the origin, sample and first
+    // pass: 6.1 and 2.7, 5.3 and 2.4, 4.2 and 1.9 without; 1.6 and 1.4, 1.4 and 1.2, 1.1 and 1.0 with it).  The last pass notes up
+    // to three times what it leaves.
+    RangeArgs range{t.x, qr, s.sample_sq, s.unscale, s.q_norm, s.q_rest, s.state, t.d, s.kb_n, t.metric, s.want, s.most_bound, false, 1, 1.0f, 0.0f, kFewEntries,
+                    s.buf, s.count, s.part_cap, s.bound};
+    range.limit = (float)(s.part_cap / 3 < range_room(kSelThreads) ? s.part_cap / 3 : range_room(kSelThreads));
+    auto rows_so_far = [&](double all) {   // one in `all`
+      const double rank = s.want / all;
+      range.rank = rank > 1.0 ? (uint32_t)rank : 1u;
+      range.weight = (float)(rank > 1.0 ? all : all * sqrt(rank));
+    };
+    rows_so_far(a.stretch);
     bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
-                                                                                    nullptr);
+                                                                                    nullptr, range);
     a.scores = nullptr;
     a.stretch = 0.0;
     a.list_far = list_far;
     a.cap = s.part_cap;
     a.n = t.n;
     a.part_log2 = s.part_log2;
-    RangeArgs range{t.x, qr, s.sample_sq, s.unscale, s.q_norm, s.q_rest, s.state, t.d, s.kb_n, t.metric, s.want, s.most_bound, false, kFewEntries, s.buf, s.count, a.cap, s.bound};
     const uint32_t parts = 1u << s.part_log2;
     for (uint32_t from = 0, to = 1; from < parts; from = to, to *= 4) {
       a.part_from = from;
@@ -1972,6 +2238,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       rc = launch_screen(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
       if (rc != ANN_OK) return rc;
       range.last = to == parts;
+      rows_so_far((double)parts / to);
       if (range.last && (uint64_t)s.want * t.d >= 32768) range.few = 0;   // (see bf_range_kernel)
       if (s.vec4 && reinterpret_cast<uintptr_t>(qr) % 16 == 0) {
         if (range.few) bf_range_kernel<true, kWave><<<m, kWave, 0, t.st>>>(range);
@@ -1981,7 +2248,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
         bf_range_kernel<false, kSelThreads><<<m, kSelThreads, 0, t.st>>>(range);
       }
     }
-    // (at most most_bound entries now, unless there was no room for them)
+    // (at most most_bound entries now, of queries that are not lost)
     bf_select_entries_kernel<2><<<m, kSelThreads, 0, t.st>>>(s.buf, s.count, a.cap, s.want, s.most, s.bound, s.cand, certain);
   } else {
     double rows = (double)s.first;
@@ -1991,7 +2258,8 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       a.stretch = last ? 0.0 : (double)t.n / (double)a.rows;
       a.scores = p == 0 ? s.scores : nullptr;
       a.state = last ? s.state : nullptr;
-      rc = launch_scores(a, s.vec4, t.n_cu, t.st);
+      rc = halves && s.pair_rows && m >= 512 + s.kb_n * 16 ? launch_pairs(a, s.vec4, s.xfrag, s.xnorm, s.pair_rows, t.n_cu, t.st)
+                                                           : launch_scores(a, s.vec4, t.n_cu, t.st);
       if (rc != ANN_OK) return rc;
       if (p == 0 && s.first == kSampleRows)
         bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
@@ -2037,7 +2305,7 @@ static ann_status fp32_for(const Truth &t, const uint32_t *list, uint32_t m_all)
 // The uncertain queries list[0 .. n_list), `round` of them at a time in s: the
 // selection with centred rows, passes over what that leaves, and the fp32 kernel
 // for what these do.
-static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uint32_t *list, uint32_t n_list, uint32_t n_wide) {
+static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uint32_t *list, uint32_t n_list, uint32_t n_wide, uint32_t n_lost) {
   CallState *const state = s.state;
   // buffers for m queries at a time, the other lists and the centre
   uint64_t m = n_list < 2048 ? n_list : 2048;
@@ -2067,11 +2335,12 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_uncertain, 1, 0u);
   fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->max_norm, 1, 0u);   // (each selection finds that of the centred rows)
 
-  Selection three = s;
+  Selection two = s, three = s;
+  two.x_rows = 0;
   three.halves = false;
-  auto select_chunk = [&](uint32_t i0, uint32_t c, const float *around) -> ann_status {
+  auto select_chunk = [&](uint32_t i0, uint32_t c, const Selection &with, const float *around) -> ann_status {
     bf_gather_uncertain_kernel<<<c, 64, 0, t.st>>>(t.q, t.d, s.kb_n, t.k, t.metric, nullptr, list + i0, t.out_dist, nullptr, qg, nullptr, nullptr);
-    const ann_status rc = select_round(t, three, qg, c, around, false, ids, dist, places, 0);
+    const ann_status rc = select_round(t, with, qg, c, around, false, ids, dist, places, 0);
     if (rc != ANN_OK) return rc;
     bf_scatter_uncertain_kernel<<<c, 64, 0, t.st>>>(list + i0, t.k, nullptr, nullptr, ids, dist, t.out_ids, t.out_dist, nullptr, nullptr, nullptr);
     bf_next_list_kernel<<<1, 1024, 0, t.st>>>(places, list + i0, state, other);
@@ -2111,8 +2380,10 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
   };
   ann_status rc = ANN_OK;
   uint32_t n_fp32 = 0;
-  // pass -1: three parts; 0: centred rows; then the passes with a bound
-  int pass = s.halves && n_wide >= (n_list + 3) / 4 ? -1 : 0;
+  // pass -2: two parts; -1: three parts; 0: centred rows; then the passes with a bound
+  auto three_help = [&]() { return s.halves && n_wide >= (n_list + 3) / 4; };
+  int pass = n_lost >= (n_list + 3) / 4 ? -2 : (three_help() ? -1 : 0);
+  if (pass == -2) fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_wide, 1, 0u);
   for (; n_list > 0 && rc == ANN_OK; ++pass) {
     if (pass > (int)kMaxPasses) {
       rc = fp32_for(t, list, n_list);
@@ -2120,7 +2391,7 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
     }
     for (uint64_t i0 = 0; i0 < n_list && rc == ANN_OK; i0 += m) {
       const uint32_t c = (uint32_t)(n_list - i0 < m ? n_list - i0 : m);
-      rc = pass <= 0 ? select_chunk((uint32_t)i0, c, pass < 0 ? nullptr : centre) : pass_chunk((uint32_t)i0, c);
+      rc = pass <= 0 ? select_chunk((uint32_t)i0, c, pass == -2 ? two : three, pass < 0 ? nullptr : centre) : pass_chunk((uint32_t)i0, c);
     }
     if (rc != ANN_OK) break;
     uint32_t left[2] = {0, 0};
@@ -2131,6 +2402,14 @@ static ann_status settle(const Truth &t, const Selection &s, uint64_t round, uin
     }
     n_list = left[0];
     n_fp32 = left[1];
+    if (pass == -2) {
+      e = read_words(&state->n_wide, &n_wide, 1, t.st);
+      if (e != hipSuccess) {
+        rc = hip_fail(e, "the wait for a pass' counters");
+        break;
+      }
+      if (!three_help()) pass = -1;
+    }
     fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->n_next, 1, 0u);
     if (pass < 0) fill_u32_kernel<<<1, 64, 0, t.st>>>(&state->max_norm, 1, 0u);
     uint32_t *was = list;
@@ -2219,6 +2498,8 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   while ((double)(n >> part_log2) > 8.0 * kSampleRows) part_log2 += 2;
   const double part_growth = (double)n / (1u << part_log2) / kSampleRows;
   while ((double)part_cap < (part_growth > 3.0 ? part_growth : 3.0) * spread + most_bound && part_cap < 8192) part_cap <<= 1;
+  // (up to 4,096 where that takes no more rounds: a query may then have as many rows within the room as bf_range_kernel takes)
+  while (part_cap < 4096 && (512ull << 20) / (ld * 4 + 2ull * part_cap * 8) / 128 * 128 >= nq) part_cap <<= 1;
   const uint32_t room = cap > part_cap ? cap : part_cap;
   // queries per round: at most half a GiB of scores and entries, less if the card has no room
   const uint64_t per_query = ld * 4 + (uint64_t)room * 8;
@@ -2233,14 +2514,16 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   // 200,000 x 960, 512 803 / 795, 1,000 1,452 / 974; 100,000 x 300, 512 224 / 236, 700 274 / 255; 50,000 x 400, 700 235 / 291, 1,000
   // 319 / 317; 30,000 x 96, 700 133 / 132, 2,500 192 / 177.
   const bool halves = !dense && nq > 64 && kb_n >= 6;
-  uint64_t x_rows = 0;
+  uint64_t x_rows = 0, pair_rows = 0;
   if (halves && nq > 512 && ((uint64_t)nq * n >= 50'000'000 || nq >= 512 + kb_n * 16)) {
     x_rows = kScreenBytes / (kb_n * 32) / kSB * kSB;
     if (x_rows > (n + kSB - 1) / kSB * kSB) x_rows = (n + kSB - 1) / kSB * kSB;
+    pair_rows = kScreenBytes / (kb_n * 64) / kSB * kSB;
+    if (pair_rows > x_rows) pair_rows = x_rows;
   }
   auto parts = [&](uint64_t m, uint64_t (&at)[15]) {
     const uint64_t size[15] = {(m + 255) / 256 * 8 * kb_n * 192 * 16, m * ld * 4, m * room * 8, m * 8, m * 4, m * most * 4, m * 4, sizeof(CallState),
-                               (uint64_t)nq * 4, 64 * 4, m * 4, x_rows * kb_n * 32, x_rows * 4, m * 4, m * 4};
+                               (uint64_t)nq * 4, 64 * 4, m * 4, (x_rows > 2 * pair_rows ? x_rows : 2 * pair_rows) * kb_n * 32, x_rows * 4, m * 4, m * 4};
     uint64_t total = 0;
     for (int i = 0; i < 15; ++i) {
       at[i] = total;
@@ -2253,7 +2536,7 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   uint64_t m_fit = round;
   hipError_t e = alloc_some((void **)&base, m_fit, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
   if (e != hipSuccess && x_rows) {   // no room for the rows' first parts
-    x_rows = 0;
+    x_rows = pair_rows = 0;
     m_fit = round;
     e = alloc_some((void **)&base, m_fit, nq < 128 ? nq : 128, [&](uint64_t m) { return parts(m, at); });
   }
@@ -2291,12 +2574,13 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   s.xfrag = reinterpret_cast<uint4 *>(base + at[11]);
   s.xnorm = reinterpret_cast<float *>(base + at[12]);
   s.x_rows = x_rows;
+  s.pair_rows = pair_rows;
   s.q_norm = reinterpret_cast<float *>(base + at[13]);
   s.q_rest = reinterpret_cast<float *>(base + at[14]);
   const Truth t{x, n, d, q, k, metric, out_ids, out_dist, n_cu, st};
 
   ann_status rc = ANN_OK;
-  uint32_t found[3] = {0, 0, 0};   // uncertain queries, far rows, queries that three parts would leave less uncertain
+  uint32_t found[5] = {0, 0, 0, 0, 0};   // uncertain queries, far rows, queries that three parts would leave less uncertain, lost ones, passes given up
   bool idle = true;
   for (;;) {
     // the counters are cleared by the first kernel of either path
@@ -2306,16 +2590,20 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
       rc = select_round(t, s, q + q0 * d, m, nullptr, q0 == 0, out_ids + q0 * k, out_dist + q0 * k, uncertain, (uint32_t)q0);
     }
     // (100 queries x 10,000 rows x 128, read through pinned memory and with one launch less at the start: 65.9 -> 55.9 us)
-    const hipError_t e2 = rc == ANN_OK ? read_words(&state->n_uncertain, found, 3, st) : hipStreamSynchronize(st);
+    const hipError_t e2 = rc == ANN_OK ? read_words(&state->n_uncertain, found, 5, st) : hipStreamSynchronize(st);
     if (rc == ANN_OK && e2 != hipSuccess) rc = hip_fail(e2, "the wait for a call's counters");
     idle = e2 == hipSuccess;
+    if (rc == ANN_OK && s.x_rows && (found[4] || found[3] > nq / 8 * 3)) {   // (see bf_range_kernel; of so many, 2,048 at a time cost as much)
+      s.x_rows = 0;
+      continue;
+    }
     if (rc != ANN_OK || !s.halves || found[1] <= kFewFarRows) break;
     s.halves = false;   // inner product, more than a few rows outside half precision's range: three parts
   }
   if (rc == ANN_OK && found[1] > kFarRows) {
     rc = bruteforce_fp32(x, n, d, q, nq, k, metric, out_ids, out_dist, n_cu, st);
   } else if (rc == ANN_OK) {
-    if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0], found[2]);
+    if (found[0] > 0) rc = settle(t, s, round, uncertain, found[0], found[2], s.x_rows ? found[3] : 0u);
     if (rc == ANN_OK && found[1] > 0) rc = add_far_rows(t, nq, found[1], state);
     if (rc != ANN_OK) idle = hipStreamSynchronize(st) == hipSuccess;
   }

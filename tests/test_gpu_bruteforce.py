@@ -272,6 +272,69 @@ def test_first_parts(H, n, d, nq, k, metric, spread):
     _check_some(H, X, Q, k, metric)
 
 
+def _kernels(run):
+    import torch
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        out = run()
+        torch.cuda.synchronize()
+    return out, [e.name for e in prof.events()]
+
+
+# Far from the origin for their spread, narrow clusters: first parts leave thousands of rows to most queries.
+# Known from the sample, or a later pass; both kinds of score kernel; more queries than one round takes
+@pytest.mark.parametrize("n,d,nq,k,metric,kind", [
+    (100_000, 96, 1500, 10, oracle.L2, "offset"), (200_001, 68, 560, 10, oracle.L2, "offset"), (17_000, 66, 11_500, 10, oracle.L2, "offset"),
+    (60_000, 131, 700, 10, oracle.L2, "offset"), (300_000, 96, 1500, 10, oracle.L2, "clusters"), (300_000, 96, 1500, 10, oracle.IP, "clusters")])
+def test_first_parts_that_settle_little(H, n, d, nq, k, metric, kind):
+    """Two parts are certain for such data: no query goes on to centred rows because first parts were tried."""
+    X, Q = _points(n, d, n + d), _points(nq, d, k)
+    if kind == "offset":
+        X, Q = X + np.float32(20.0), Q + np.float32(20.0)
+    else:
+        spread = np.float32(0.05 if metric == oracle.L2 else 0.002)
+        centres = _points(20, d, 91)
+        X, Q = X * spread + centres[np.arange(n) % 20], Q * spread + centres[np.arange(nq) % 20]
+    (gid, gdist), names = _kernels(lambda: H.gpu_bruteforce(X, Q, k, metric))
+    assert any("bf_screen_kernel" in e for e in names)
+    assert any("bf_pair_kernel" in e or ", 4, 1, false, 2>" in e for e in names)
+    assert not any("bf_score_kernel" in e and ", 4, 1, true, 3>" in e for e in names)   # (centred rows, more than 32 queries)
+    some = np.unique(np.r_[np.arange(0, nq, nq // 30), nq - 1])
+    oid, odist = oracle.bruteforce_topk(X, Q[some], k, metric=metric)
+    H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
+
+
+@pytest.mark.parametrize("n,d,nq,k", [(300_000, 128, 1500, 10), (60_000, 131, 700, 100)])
+@pytest.mark.parametrize("kind", ["sizes", "one"])
+def test_first_parts_with_norms_of_many_sizes(H, n, d, nq, k, kind):
+    """What a large row loses does not count against the rows that can be near: no query is taken up again."""
+    X, Q = _points(n, d, 3), _points(nq, d, 4)
+    if kind == "sizes":
+        z = np.random.default_rng(5).standard_normal((n + nq, 1)).astype(np.float32)
+        X, Q = X * np.exp(z[:n]), Q * np.exp(z[n:])
+    else:
+        X, Q = X + np.float32(2.0), Q + np.float32(2.0)
+        X[n // 3] *= np.float32(20.0)
+    (gid, gdist), names = _kernels(lambda: H.gpu_bruteforce(X, Q, k, oracle.L2))
+    assert any("bf_screen_kernel" in e for e in names) and not any("bf_pair_kernel" in e or "bf_score_kernel" in e for e in names)
+    some = np.unique(np.r_[np.arange(0, nq, nq // 30), nq - 1])
+    oid, odist = oracle.bruteforce_topk(X, Q[some], k, metric=oracle.L2)
+    H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
+
+
+def test_first_parts_that_settle_most(H):
+    """One query in ten lies in a narrow cluster: only these are taken up again, with two parts."""
+    n, d, nq, k = 100_000, 96, 1500, 10
+    X, Q, centres = _points(n, d, 7), _points(nq, d, 8), _points(10, d, 9)
+    X[::2] = X[::2] * np.float32(0.05) + centres[np.arange(n // 2) % 10]
+    Q[::10] = Q[::10] * np.float32(0.05) + centres[np.arange(nq // 10) % 10]
+    (gid, gdist), names = _kernels(lambda: H.gpu_bruteforce(X, Q, k, oracle.L2))
+    assert any("bf_gather_uncertain_kernel" in e for e in names) and any(", 4, 1, false, 2>" in e for e in names)
+    assert not any("bf_pair_kernel" in e or "bf_score_kernel" in e and ", 4, 1, true, 3>" in e for e in names)
+    some = np.arange(0, nq, 25)
+    oid, odist = oracle.bruteforce_topk(X, Q[some], k, metric=oracle.L2)
+    H.check_rerank(gid[some], gdist[some], oid, odist.astype(np.float32), rel=1e-6)
+
+
 @pytest.mark.parametrize("nq,n", PARTS + [(100, 18_000), (700, 18_000)])
 @pytest.mark.parametrize("scale", [2.0 ** -40, 1e-6, 3e4, 2.0 ** 40])
 def test_two_parts_of_vectors_of_any_size(H, nq, n, scale):
