@@ -36,6 +36,8 @@
 // x 768, k = 100: 13.9 -> 1.39 to 1.43 (3.8, 2.27 to 2.41); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
 #include <math.h>
 
+#include <type_traits>
+
 #include "ann_internal.hpp"
 #include "device_utils.hpp"
 #include "kept_blocks.hpp"
@@ -498,8 +500,6 @@ struct ScoreArgs {
   const uint4 *qfrag;
   uint64_t first, rows;    // rows first .. first + rows - 1 of x, or of a sample of it
   double stretch;    // sample: rows of x per row of the sample; 0: none
-  uint64_t n;        // part_w != 0: rows of x; the pass takes part_w of every 2^part_log2 rows, see part_row()
-  uint32_t part_log2, part_from, part_w;
   uint32_t d, kb_n, nq, metric;
   uint32_t q_tiles, q_group, slabs, tiles_per_slab;
   float *scores;     // not NULL: every score goes here, [nq][ld]
@@ -511,17 +511,24 @@ struct ScoreArgs {
   const float *centre;     // [d] subtracted from every row (kernels with CENTRE)
   const float *sample_sq;  // [64] two parts: squared norms that settle the rows' scale
   const float *unscale;    // [nq] two parts: takes a product back
-  const uint4 *xfrag;      // rows' first parts (bf_screen_kernel) and their squared norms
+  const uint4 *xfrag;      // rows' parts (bf_pair_kernel; bf_screen_kernel: first parts) and their squared norms
   const float *norm;
-  const float *q_norm, *q_rest;   // bf_screen_kernel: [nq] at least |q|, and the norm of what its first part leaves
   CallState *state;        // inner product: norms are noted here (NULL: not in this pass)
   bool list_far;           // and the rows without one listed
+};
+static_assert(sizeof(ScoreArgs) == 176, "every launch of a score kernel pays for what is added here, see ScreenArgs");
+
+// A pass of first parts.  (Arguments of its own: with these in ScoreArgs the smallest calls took 0.3 us longer, of 56.)
+struct ScreenArgs : ScoreArgs {
+  uint64_t n;        // part_w != 0: rows of x; the pass takes part_w of every 2^part_log2 rows, see part_row()
+  uint32_t part_log2, part_from, part_w;
+  const float *q_norm, *q_rest;   // [nq] at least |q|, and the norm of what its first part leaves
 };
 
 // Row of x that row v of a pass over a part of the rows is: of each stretch of 2^part_log2 rows the pass takes
 // places part_from .. part_from + part_w - 1 of a random order (places exchanged by a random mask), so
 // that passes over disjoint places share out all rows and each is a stratified random sample.  n or more: no row.
-__device__ __forceinline__ uint64_t part_row(const ScoreArgs &a, uint64_t v) {
+__device__ __forceinline__ uint64_t part_row(const ScreenArgs &a, uint64_t v) {
   const uint32_t stretch = (uint32_t)v / a.part_w, place = a.part_from + ((uint32_t)v - stretch * a.part_w);
   uint32_t h = stretch * 0x9E3779B1u;
   h = (h ^ (h >> 15)) * 0x85EBCA77u;
@@ -594,25 +601,33 @@ __device__ __forceinline__ float screen_room(float nq, float q_rest, float value
 // SCREEN: the products are of first parts only, and what may reach the bound is written.
 template <int MB, int NQ, bool SCREEN = false>
 struct TileEnd {
-  const ScoreArgs &a;
+  using Args = std::conditional_t<SCREEN, ScreenArgs, ScoreArgs>;
+  const Args &a;
   uint32_t q0;        // the wavefront's first query
   uint64_t *hits;     // LDS [kHitList]: (score, row of the pass)
   uint8_t *hits_q;    // LDS [kHitList]: query - q0
   int n_hits = 0;     // the same in all lanes
   float top[NQ], scale[NQ];
 
-  __device__ __forceinline__ TileEnd(const ScoreArgs &args, uint32_t q0_, uint64_t *hits_, uint8_t *hits_q_) : a(args), q0(q0_), hits(hits_), hits_q(hits_q_) {
-    const float x_unit = SCREEN ? ldexpf(1.0f, -half_exponent(rows_sq(a.sample_sq))) : 1.0f;
-    const uint32_t max_norm = SCREEN ? *(volatile uint32_t *)&a.state->max_norm : 0u, max_rest = SCREEN ? *(volatile uint32_t *)&a.state->max_rest : 0u;
+  __device__ __forceinline__ TileEnd(const Args &args, uint32_t q0_, uint64_t *hits_, uint8_t *hits_q_) : a(args), q0(q0_), hits(hits_), hits_q(hits_q_) {
+    [[maybe_unused]] float x_unit = 1.0f;
+    [[maybe_unused]] uint32_t max_norm = 0, max_rest = 0;
+    if constexpr (SCREEN) {
+      x_unit = ldexpf(1.0f, -half_exponent(rows_sq(a.sample_sq)));
+      max_norm = *(volatile uint32_t *)&a.state->max_norm;
+      max_rest = *(volatile uint32_t *)&a.state->max_rest;
+    }
 #pragma unroll
     for (int f = 0; f < NQ; ++f) {
       const uint32_t q = q0 + f * 32 + lane_id() % 32;
       top[f] = a.scores == nullptr && q < a.nq ? unorder_f32((uint32_t)(a.bound[q] >> 32)) : -INFINITY;
-      // (no bound, FLT_MAX: everything; a lost query, NaN: nothing; a query whose norm is no float: nothing, its result is found to be uncertain)
-      if (SCREEN && top[f] > -INFINITY && top[f] < 0x1.fffffep127f) {
-        float room = screen_room(a.q_norm[q], a.q_rest[q], top[f], a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
-        room = screen_room(a.q_norm[q], a.q_rest[q], top[f] + room, a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
-        top[f] = room < INFINITY ? top[f] + 2.0f * room * (1.0f + 0x1p-20f) : -INFINITY;   // (a room for the bound, one for the score)
+      if constexpr (SCREEN) {
+        // (no bound, FLT_MAX: everything; a lost query, NaN: nothing; a query whose norm is no float: nothing, its result is found to be uncertain)
+        if (top[f] > -INFINITY && top[f] < 0x1.fffffep127f) {
+          float room = screen_room(a.q_norm[q], a.q_rest[q], top[f], a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
+          room = screen_room(a.q_norm[q], a.q_rest[q], top[f] + room, a.d, a.kb_n, a.metric, x_unit, a.unscale[q], max_norm, max_rest);
+          top[f] = room < INFINITY ? top[f] + 2.0f * room * (1.0f + 0x1p-20f) : -INFINITY;   // (a room for the bound, one for the score)
+        }
       }
       scale[f] = a.metric == ANN_L2 ? -2.0f : -1.0f;
       if (a.unscale != nullptr) scale[f] *= q < a.nq ? a.unscale[q] : 0.0f;   // (powers of two)
@@ -629,7 +644,10 @@ struct TileEnd {
     for (int e = lane_id(); e < n_hits; e += kWave) {
       const uint32_t q = q0 + hits_q[e];
       const uint64_t hit = hits[e];
-      const uint64_t row = a.first + (uint32_t)hit, id = a.part_w ? part_row(a, row) : (a.stretch != 0.0 ? sample_row(row, a.stretch) : row);
+      const uint64_t row = a.first + (uint32_t)hit;
+      uint64_t id = a.stretch != 0.0 ? sample_row(row, a.stretch) : row;
+      if constexpr (SCREEN)
+        if (a.part_w) id = part_row(a, row);
       const uint64_t ent = (hit & 0xFFFFFFFF00000000ull) | (uint32_t)id;
       if (!SCREEN && ent > a.bound[q]) continue;
       const uint32_t pos = atomicAdd(&a.count[q], 1u);
@@ -955,7 +973,7 @@ __global__ __launch_bounds__(256, 2) void bf_score_kernel(ScoreArgs a) {
 // the rows' squared norms, summed in fp64 (+inf: left out of the scores).  One workgroup per 32 rows, a wavefront
 // takes every fourth block of 16 columns.  Both parts: reading and writing 128 MB each way takes 47 us.
 template <bool VEC4, int PLANES>
-__global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *__restrict__ frag, float *__restrict__ norm) {
+__global__ __launch_bounds__(256) void bf_halve_rows_kernel(std::conditional_t<PLANES == 1, ScreenArgs, ScoreArgs> a, uint4 *__restrict__ frag, float *__restrict__ norm) {
   __shared__ double part_s[8][32];
   __shared__ float rest_s[8][32];
   const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
@@ -972,9 +990,14 @@ __global__ __launch_bounds__(256) void bf_halve_rows_kernel(ScoreArgs a, uint4 *
     return;
   }
   uint64_t r = at < a.rows ? at : a.rows - 1;
-  r = a.part_w ? part_row(a, a.first + r) : (a.stretch != 0.0 ? sample_row(a.first + r, a.stretch) : a.first + r);
-  const bool real = at < a.rows && (a.part_w == 0 || r < a.n);
-  if (!real && a.part_w) r = a.n - 1;
+  r = a.stretch != 0.0 ? sample_row(a.first + r, a.stretch) : a.first + r;
+  bool real = at < a.rows;
+  if constexpr (PLANES == 1)
+    if (a.part_w) {
+      r = part_row(a, r);
+      real = real && r < a.n;
+      if (!real) r = a.n - 1;
+    }
   const float *row = a.x + r * a.d;
   uint4 *to = frag + (uint64_t)blockIdx.x * a.kb_n * (64 * PLANES) + lane;
   double sq = 0.0;
@@ -1182,7 +1205,7 @@ __global__ __launch_bounds__(256, 2) void bf_pair_kernel(ScoreArgs a) {
 // on its way in an array, which the compiler kept in scratch memory, 2.38; with 64-bit addresses 1.6.
 constexpr int kScreenQueries = 256;
 constexpr int kScreenKb = 4;   // blocks of 16 columns staged at a time
-__global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScreenArgs a) {
   constexpr int MB = 4, NQ = 2, QT32 = 4 * NQ;
   static_assert(QT32 * 32 == kScreenQueries, "tile shape");
   __shared__ __align__(16) uint4 stage_s[2][4 * kScreenKb * 64];   // [row / 32][kb][lane]
@@ -1648,7 +1671,7 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
 // parts; below that the lost queries are taken up again by themselves.  10,000 queries x 1M x 128, two parts alone / first
 // parts, and centred rows for what these lost / this: 7 spreads from the origin 7.3 / 4.4 / 4.5 ms, 10 7.4 / 21.4 / 7.5, 20
 // 7.8 / 21.4 / 8.0; 100 clusters of spread 0.1 7.7 / 5.3 / 5.5, 0.05 7.9 / 21.0 / 8.2; at the origin (3.69) and for small
-// calls the votes cost 0.5 to 2 %.
+// calls (0.25) the votes cost 1 to 3 %.
 // (Re-evaluating each pass's new entries made the bounds a room tighter and cost more: 200,000 rows, d = 768, k = 100,
 // 2,000 queries: these kernels 263 instead of 660 us.)
 // A wavefront takes a query with up to 512 entries, a workgroup one with more, in a launch of its own: 10,000 queries with
@@ -1925,7 +1948,7 @@ static ann_status launch_pairs(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm
 
 // One pass of first parts, a slab of at most x_rows rows at a time.  A die's group
 // of query tiles is a megabyte of parts, four tiles at least (between 4 and 16 tiles within 1 %).
-static ann_status launch_screen(ScoreArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
+static ann_status launch_screen(ScreenArgs a, bool vec4, uint4 *xfrag, float *norm, uint64_t x_rows, uint32_t n_cu, hipStream_t st) {
   const uint64_t n = a.rows;
   a.xfrag = xfrag;
   a.norm = norm;
@@ -2199,14 +2222,15 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
     // the bounds is a few times a bound's rank per pass, and the best of it gives the next bounds.
     // (A sample of 4,096 rows, one of 64,000 and then all rows in order, three products each: 1M x 128, 10,000 queries 7,640 to
     // 7,940 us, with passes over parts 7,554, with first products only 3,510 to 3,660.)
-    a.rows = kSampleRows;
-    a.stretch = (double)t.n / kSampleRows;
-    a.scores = s.scores;
-    a.state = s.state;   // (the largest norm; the sample's rows come again)
-    a.list_far = false;
-    a.q_norm = s.q_norm;
-    a.q_rest = s.q_rest;
-    rc = launch_screen(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
+    ScreenArgs b{a};
+    b.rows = kSampleRows;
+    b.stretch = (double)t.n / kSampleRows;
+    b.scores = s.scores;
+    b.state = s.state;   // (the largest norm; the sample's rows come again)
+    b.list_far = false;
+    b.q_norm = s.q_norm;
+    b.q_rest = s.q_rest;
+    rc = launch_screen(b, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
     if (rc != ANN_OK) return rc;
     // What the last pass will leave of a query is the rows up to two rooms beyond the bound that all rows will give, whose rank among
     // those so far is want / all.  Below one, the best so far lies further out than that bound: by as much as the square
@@ -2221,21 +2245,21 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       range.rank = rank > 1.0 ? (uint32_t)rank : 1u;
       range.weight = (float)(rank > 1.0 ? all : all * sqrt(rank));
     };
-    rows_so_far(a.stretch);
-    bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, a.ld, a.rows, a.stretch, s.want, s.most_bound, s.bound,
+    rows_so_far(b.stretch);
+    bf_select_scores_kernel<kSampleRows / kSelThreads><<<m, kSelThreads, 0, t.st>>>(s.scores, b.ld, b.rows, b.stretch, s.want, s.most_bound, s.bound,
                                                                                     nullptr, range);
-    a.scores = nullptr;
-    a.stretch = 0.0;
-    a.list_far = list_far;
-    a.cap = s.part_cap;
-    a.n = t.n;
-    a.part_log2 = s.part_log2;
+    b.scores = nullptr;
+    b.stretch = 0.0;
+    b.list_far = list_far;
+    b.cap = s.part_cap;
+    b.n = t.n;
+    b.part_log2 = s.part_log2;
     const uint32_t parts = 1u << s.part_log2;
     for (uint32_t from = 0, to = 1; from < parts; from = to, to *= 4) {
-      a.part_from = from;
-      a.part_w = to - from;
-      a.rows = ((t.n + parts - 1) >> s.part_log2) * a.part_w;
-      rc = launch_screen(a, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
+      b.part_from = from;
+      b.part_w = to - from;
+      b.rows = ((t.n + parts - 1) >> s.part_log2) * b.part_w;
+      rc = launch_screen(b, s.vec4, s.xfrag, s.xnorm, s.x_rows, t.n_cu, t.st);
       if (rc != ANN_OK) return rc;
       range.last = to == parts;
       rows_so_far((double)parts / to);
@@ -2249,7 +2273,7 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
       }
     }
     // (at most most_bound entries now, of queries that are not lost)
-    bf_select_entries_kernel<2><<<m, kSelThreads, 0, t.st>>>(s.buf, s.count, a.cap, s.want, s.most, s.bound, s.cand, certain);
+    bf_select_entries_kernel<2><<<m, kSelThreads, 0, t.st>>>(s.buf, s.count, s.part_cap, s.want, s.most, s.bound, s.cand, certain);
   } else {
     double rows = (double)s.first;
     for (uint32_t p = 0; p <= s.samples; ++p, rows *= s.growth) {
