@@ -178,10 +178,14 @@ typedef struct {
  *                 on V itself: with m_s below the degree the table is used and
  *                 the result is the sequential one only for queries that report
  *                 0 rebuilds in out_counts.  ANN_VISITED_AUTO: the cache, or the
- *                 table (8192 slots by default) when m_s is active; with one
- *                 expansion per step and visited_slots = 0 a bit per node
- *                 (complete, never rebuilt) where that is faster: base sets whose
- *                 bits fit in LDS, for batches that are then resident at once.
+ *                 table (8192 slots by default) when m_s is active; with
+ *                 visited_slots = 0 a bit per node (complete, never rebuilt)
+ *                 where that is faster: base sets whose bits fit in LDS, for
+ *                 batches that are then resident at once, as many of them as
+ *                 streams have called for this index lately (up to four).  With
+ *                 m_s active and one expansion per step: batches up to twice
+ *                 that size, and any batch where two queries' bits fit a
+ *                 compute unit.  Which of these it was shows in out_counts only.
  *   alpha_s, m_s  the search-time edge filter of Algorithm 1 (Section 4.3): an
  *                 edge is followed only if its label <= alpha_s, and at most
  *                 m_s unvisited neighbours are taken per expansion, in stored

@@ -40,6 +40,7 @@ struct Workspace {
 // order, so calls on the same stream may share them; calls on different
 // streams get different sets and may be in flight together.
 constexpr int kMaxStreamWorkspaces = 8;
+constexpr uint64_t kRecentCalls = 4 * kMaxStreamWorkspaces;   // (a batch is up to three calls: scan, search, rescore)
 struct StreamWorkspaces {
   hipStream_t stream = nullptr;
   bool used = false;
@@ -133,6 +134,9 @@ struct WorkspaceLease {
   Workspace *ws = nullptr;
 };
 
+// Streams whose calls for the index may be in flight together, as far as can be told (at least one): those that one of the
+// last calls that took a workspace was for.  With the lock on the table.
+uint32_t streams_in_use(const ann_index *index);
 // The workspace of (level, stream), holding at least nq queries.
 ann_status workspace_for(ann_index *index, uint32_t level, uint32_t nq, hipStream_t stream, WorkspaceLease &lease);
 // Folds a batch into the given buffers (no allocation, no table lookup).

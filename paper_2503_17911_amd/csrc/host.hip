@@ -306,6 +306,12 @@ inline int grid_for(uint64_t total, int block) {
 
 }  // namespace
 
+uint32_t streams_in_use(const ann_index *ix) {
+  uint32_t n = 0;
+  for (const StreamWorkspaces &c : ix->stream_ws) n += c.used && ix->ws_clock - c.last_use < kRecentCalls ? 1u : 0u;
+  return n > 0 ? n : 1u;
+}
+
 ann_status workspace_for(ann_index *ix, uint32_t level, uint32_t nq, hipStream_t st, WorkspaceLease &lease) {
   if (!lease.lock.owns_lock()) lease.lock = std::unique_lock<std::mutex>(ix->ws_mutex);
   StreamWorkspaces *sw = nullptr, *free_slot = nullptr, *oldest = nullptr;

@@ -11,12 +11,14 @@ using namespace ann;
 namespace {
 
 constexpr size_t kChainLds = 160 << 10;   // a compute unit's
+constexpr uint32_t kQueues = 4;           // kernels in flight at once: hardware queues of a process (HIP's default)
 
 // What the argument checks settle before anything is launched.
 struct SearchPlan {
   uint32_t p = 1, vis_log2 = 0;
   bool cache = false, wide = false;
   bool any_set = false;   // how the visited set is kept is the library's choice
+  uint32_t streams = 1;   // on which batches like this one may be in flight
 };
 
 ann_status check_search_args(const char *fn, const ann_index *index, const float *q, uint32_t nq,
@@ -152,6 +154,12 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
   // FAST multi-expansion kernels: the staging area (64 m entries, at least 32 per expansion) must hold a step's ids
   const bool ids_fit = index->degree <= 32 || 64 * m >= (int)(64 * p_built);
   const bool fast = packed && !a.filtered && !a.prs_codes && !a.q15 && (!multi || (ids_fit && p == p_built));
+  // Queries that want to be resident at once: the kernels for small batches gain by what a query gets of a compute unit, and
+  // lose where several streams' batches do not fit next to each other (us a batch on 1 / 2 / 4 / 8 streams, search_team_kernel or
+  // search_small_kernel and these: 512 queries x 300,000 x 128, several expansions 210 / 109 / 61 / 63 and 151 / 90 / 86 / 87; x 100,000 x
+  // 960 4-bit 249 / 151 / 164 / 150 and 210 / 205 / 211 / 211; 1,000 x 300,000 x 128, one expansion 502 / 256 / 138 / 138 and
+  // 310 / 197 / 193 / 194; 100 x 1M x 128 323 / 162 / 112 / 87 and 229 / 117 / 86 / 68).
+  const uint64_t at_once = (uint64_t)nq * (plan.streams < kQueues ? plan.streams : kQueues);
   // (offsets of code rows are 32-bit in this kernel)
   if (fast && multi && index->n * L.row_stride < (1ull << 32)) {
     // Up to two or three queries to a compute unit: five wavefronts per query, one of which keeps the pool.  Four wavefronts
@@ -162,7 +170,7 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
     auto resident = [&](uint32_t words) {
       const size_t smem = relay_smem_bytes(m, (int)p_built, by_slot, words, w.tq_stride);
       const uint32_t by_lds = smem <= kChainLds ? (uint32_t)(128 / ((smem + 1279) / 1280)) : 0u, by_waves = relay_queries((int)L.bits, (int)L.search_lanes, m);
-      return nq <= (uint32_t)index->n_cu * (by_lds < by_waves ? by_lds : by_waves);
+      return at_once <= (uint32_t)index->n_cu * (by_lds < by_waves ? by_lds : by_waves);
     };
     const uint64_t bit_words = ((index->n + 127) / 128) * 4;
     const bool bits = plan.any_set && bit_words * 4 < kChainLds && resident((uint32_t)bit_words);
@@ -206,8 +214,9 @@ ann_status launch_search_with(const ann_index *index, const float *q, uint32_t n
     // With the cap the other choice is a complete table of 32 KB, slower for every batch (10,000 queries, 300,000 x 128,
     // ef = 100: 3,160 / 1,831 us, 600,000 x 96: 2,296 / 2,221) unless a query's bits fill the compute unit (1M x 64: 500
     // queries 410 / 330, 1,000 446 / 535).
-    if (a.m_s < a.degree) most = by_lds >= 2 ? nq : 2 * n_cu * by_lds;
-    if (nq <= most) {
+    const bool always = a.m_s < a.degree && by_lds >= 2;
+    if (a.m_s < a.degree) most = 2 * n_cu * by_lds;
+    if (always || at_once <= most) {
       a.q = q;
       return a.filtered ? launch_search_chain_filtered(a, L.bits, L.search_lanes, m, st) : launch_search_chain(a, L.bits, L.search_lanes, m, st);
     }
@@ -253,6 +262,7 @@ extern "C" ann_status ann_search_batch(ann_index *index, const float *q, uint32_
   WorkspaceLease lease;  // held until the search kernel is enqueued
   rc = workspace_for(index, 0, nq, st, lease);
   if (rc != ANN_OK) return rc;
+  plan.streams = streams_in_use(index);
   const bool folds = !params->reuse_folded_queries && search_folds(index, params);
   if (params->reuse_folded_queries) {
     if (lease.ws->folded_q != q || lease.ws->folded_nq != nq)

@@ -73,6 +73,41 @@ def test_few_nodes_and_options(n):
         ix.close()
 
 
+@pytest.mark.parametrize("mode,n,nq", [(0, 500_000, 300), (1, 100_000, 400)])
+def test_batches_on_several_streams(mode, n, nq):
+    """Bits for a batch that is resident at once; not while another stream's batches would not fit next to it (the cache then
+    forgets nodes, which the counts show), and again when that stream has been quiet for a while."""
+    import gpu_harness as H
+    import torch
+    d, ef, degree, p = 16, 400, 12, 8
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    adj = (np.arange(n, dtype=np.int64)[:, None] + rng.integers(1, n // degree, (n, degree)) + np.arange(degree) * (n // degree)) % n
+    adj = adj.astype(np.uint32)
+    lv = oracle.sq_fit(X, 8)
+    ix = H.GpuIndex(X, adj, 11, [lv], oracle.L2)
+    Q = np.tile(rng.standard_normal((20, d)).astype(np.float32), (nq // 20, 1))
+    kw = dict(mode=mode, expansions_per_step=p if mode else 0, visited_slots=0)
+    want = oracle.search_batch(lv, d, adj, 11, Q[:20], ef, expansions_per_step=p if mode else 1)
+    want = tuple(np.tile(w, (nq // 20, 1)) for w in want)
+
+    def forgotten():
+        got = ix.search(Q, ef, **kw)
+        assert all((g == w).all() for g, w in zip(got[:3], want)) and (got[3][:, 0] == want[3][:, 0]).all()
+        return int((got[3][:, 1].astype(np.int64) - want[3][:, 1]).sum())
+
+    assert forgotten() == 0
+    others = [torch.cuda.Stream() for _ in range(2)]
+    for s in others:
+        with torch.cuda.stream(s):
+            forgotten()
+    assert forgotten() > 0
+    for _ in range(32):
+        forgotten()
+    assert forgotten() == 0
+    ix.close()
+
+
 @pytest.mark.parametrize("n,degree,cap", [(9_000, 12, 0), (150_000, 12, 0), (600_000, 8, 3), (1_200_000, 8, 0), (1_200_000, 8, 3), (1_320_000, 8, 3)])
 def test_batches_and_base_sets_on_both_sides_of_what_is_resident(n, degree, cap):
     """(The largest base set's bits do not fit a compute unit's LDS.)"""
