@@ -385,7 +385,12 @@ ann_status ann_schedule_queries(const uint32_t *keys, uint32_t nq, uint32_t key_
  *   out_idot   [nq][ef] the int32 code/query dot products (NULL allowed; asking
  *              for them costs one more pass over the pool's code rows).
  *   out_counts [nq][4] (NULL allowed): expansions, distance evaluations,
- *              pool size, visited-table rebuilds.
+ *              pool size, visited-table rebuilds.  A node that the visited set
+ *              has forgotten counts again when it is evaluated again; in small
+ *              batches with mode 1 several wavefronts share a query's cache, and
+ *              which nodes it forgets depends on timing, so that this second
+ *              count may differ between identical calls (the other counts, ids,
+ *              keys and dot products never do).
  * Errors: ANN_EINVAL (NULL q/out_ids/params, nq == 0, k == 0, ef < k, unknown
  * mode, layout or visited_kind, visited_slots not a power of two or too small
  * for ef, ANN_VISITED_CACHE together with m_s below the degree),
@@ -470,8 +475,8 @@ ann_status ann_rerank_adaptive(ann_index *index, const float *q, uint32_t nq, co
  * on the matrix cores selects k + margin candidates per query, which are then
  * re-evaluated directly in fp64 and sorted by (distance, id).  Where the rounding
  * of the contraction leaves open whether another row is nearer (vectors far from
- * the origin, many rows at the same distance), the query is taken up again with
- * centred vectors and more candidates; only where thousands of rows lie within
+ * the origin, narrow clusters, many rows at the same distance), the query is taken
+ * up again with more exact products, centred vectors and more candidates; only where thousands of rows lie within
  * that rounding of the k-th do fp32 products decide among them.
  *   x [n][d], q [nq][d] fp32; out_ids/out_dist [nq][k]; k <= 256, d <= 2048,
  *   n < 2^31.  Rows are read 16 bytes at a time if d is a multiple of 4 and x is

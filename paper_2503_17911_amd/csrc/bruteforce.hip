@@ -32,8 +32,8 @@
 //
 // Whole calls, before (fp32 products, top-k lists in LDS kept by the contraction
 // kernel, every slab's list re-evaluated) and now: 10,000 queries x 1M x 128,
-// k = 10: 25.8 -> 3.51 to 3.66 ms (15.5 with three parts, 7.6 to 8.3 with two); 2,000 x 200,000
-// x 768, k = 100: 13.9 -> 1.39 to 1.43 (3.8, 2.27 to 2.41); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
+// k = 10: 25.8 -> 3.51 to 3.75 ms, by the card (15.5 with three parts, 7.4 to 8.3 with two); 2,000 x 200,000
+// x 768, k = 100: 13.9 -> 1.38 to 1.43 (3.8, 2.27 to 2.41); 100 x 10,000 x 128, k = 10: 2.56 -> 0.056.
 #include <math.h>
 
 #include <type_traits>
@@ -1715,13 +1715,17 @@ __global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
   __shared__ unsigned long long last_s;
   __shared__ uint64_t best[kRoomHere];
   const uint32_t q = blockIdx.x, tid = threadIdx.x;
-  const uint32_t found = a.count[q], abandoned = a.state->abandoned;
-  // (none, or taken by the other launch, which may only leave few of many; more than cap: entries were lost)
-  if (THREADS > kWave && !a.last && tid == 0 && !abandoned && found > a.cap) {
-    vote(a, q, found);
-    a.bound[q] = 0;   // (no number: the query has no more entries)
+  const uint32_t found = a.count[q];
+  // (none, or taken by the other launch, which may only leave few of many)
+  if (found == 0 || (found <= a.few) != (THREADS == kWave)) return;
+  if (a.state->abandoned) return;
+  if (found > a.cap) {   // entries were lost
+    if (!a.last && tid == 0) {
+      vote(a, q, found);
+      a.bound[q] = 0;   // (no number: the query has no more entries)
+    }
+    return;
   }
-  if (abandoned || found == 0 || found > a.cap || (found <= a.few) != (THREADS == kWave)) return;
   const uint64_t old_bound = a.bound[q];
   if (tid < 2) n_best[tid] = 0;
   if (tid == 0) last_s = 0;
@@ -2536,7 +2540,8 @@ extern "C" ann_status ann_bruteforce_topk(const float *x, uint64_t n, uint32_t d
   // question of the queries and, since a pass has a least time, of all scores.  Two parts / first parts, us: 1M x 128, 256 queries
   // 410 / 430, 512 656 / 491; 200,000 x 128, 512 207 / 224, 700 255 / 243; 200,000 x 768, k = 100, 400 743 / 743, 700 1,038 / 852;
   // 200,000 x 960, 512 803 / 795, 1,000 1,452 / 974; 100,000 x 300, 512 224 / 236, 700 274 / 255; 50,000 x 400, 700 235 / 291, 1,000
-  // 319 / 317; 30,000 x 96, 700 133 / 132, 2,500 192 / 177.
+  // 319 / 317; 30,000 x 96, 700 133 / 132, 2,500 192 / 177.  So up to 512 queries it depends on the rows, and most sets lose; a
+  // million rows would gain from somewhere between 256 and 512 queries on, and are kept with the others.
   const bool halves = !dense && nq > 64 && kb_n >= 6;
   uint64_t x_rows = 0, pair_rows = 0;
   if (halves && nq > 512 && ((uint64_t)nq * n >= 50'000'000 || nq >= 512 + kb_n * 16)) {

@@ -99,7 +99,7 @@ struct SearchArgs {
   const float *q;  // [nq][d]: the kernel (FOLDS) folds its query itself and leaves the result in tq, s, qlo, sum_t; or nullptr: they hold it
   const float *lo, *delta;  // [d] the level's codebook (with q)
   uint32_t d;
-  uint32_t vis_words;  // search_chain_kernel: words of the visited set
+  uint32_t vis_words;  // search_chain_kernel, search_relay_kernel: words of the visited set (the latter's may be the cache)
 };
 
 // All but the evaluation of a step is one wavefront's work (with several to a

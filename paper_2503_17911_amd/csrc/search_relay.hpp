@@ -17,7 +17,8 @@
 // what beats the pool's last entry (as of the hand-out: the merge drops the rest) goes to
 // LDS.  Two barriers a step, of LDS only.
 //
-// The visited set is a bit per node where those fit in LDS, else SearchWave's cache.
+// The visited set is a bit per node where those fit in LDS, else SearchWave's cache.  The workers enter nodes into the cache as
+// they come to them, so which node is forgotten, and how many are evaluated again, depends on timing; the pool does not.
 //
 // Bound: a step's chain, about 3,700 cycles at 1M x 128 (5,600 with search_team_kernel): hand-out and
 // barriers 500, adjacency and code rows 1,100 from behind the L2, keys and what goes to LDS 500, ranking 700, a merge
@@ -31,8 +32,12 @@ namespace ann {
 
 constexpr int kRelayWorkers = 4;
 // Wavefronts per SIMD a kernel is compiled for (five: 96 registers; four: 128), and queries to a compute unit: of a
-// query's five wavefronts two are on the first SIMD.  Long 4-bit rows and rows of sixteen lanes spill with 96 (1,000 x
-// 960 4-bit, ef = 256: 256 queries 184 -> 319 us).
+// query's five wavefronts two are on the first SIMD.  96 registers bring a third query and cost spills in most kernels with
+// four pool registers or more.  60,000 nodes, search call with 128 / 96: 128-byte rows, ef = 512, 100 queries 215 / 220 us, 512 234 /
+// 243, 768 (with 128 not resident: another kernel) 377 / 263; 200 dimensions, 4 bits, ef = 256 119 / 123, 135 / 140, 191 / 152; 400, 8
+// bits, ef = 128 115 / 115, 133 / 133, 163 / 140.  128 where 96 cost more than the third query gives: 16 lanes (900, 8 bits, ef =
+// 128 136 / 250, 168 / 351, 228 / 415), 4-bit rows of eight lanes (960, ef = 128 129 / 195, 149 / 233, 171 / 263) or with eight pool
+// registers (200, ef = 512 228 / 289, 269 / 344, 398 / 388).
 __host__ __device__ constexpr int relay_waves(int bits, int lpr, int m) { return (bits == 8 ? lpr <= 8 : lpr <= 4 && m < 8) ? 5 : 4; }
 __host__ __device__ constexpr uint32_t relay_queries(int bits, int lpr, int m) { return relay_waves(bits, lpr, m) == 5 ? 3u : 2u; }
 
