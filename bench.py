@@ -37,8 +37,8 @@ KERNEL_SOURCES = ("paper_2503_17911_amd/csrc/search_kernel.hpp", "paper_2503_179
                   "paper_2503_17911_amd/csrc/entry.hip")
 MEASURED_TRAFFIC = {
     # sha256 of KERNEL_SOURCES -> bytes per launch on c2, ef=128, multi-expansion, 10,000 queries scheduled by 256 pivots
-    # (medians over the 323 launches of that pool in one run of this script under rocprofv3 --pmc, profiles/)
-    "0c7041e1ec31760f98bf3b06c3501babecb6da6a2a5c566b0ca7fdd591fd4260": 842263.0 * 1024 * 2.0 + 5000.0 * 1024 * 1.0,
+    # (medians over the 547 launches of that kernel and grid in one run of this script under rocprofv3 --pmc, profiles/)
+    "0e6e69f8fde2aa7b033de25a57c244d195401549191e6f9851a2ae85811e87ea": 841945.0 * 1024 * 2.0 + 5000.0 * 1024 * 1.0,
 }
 
 

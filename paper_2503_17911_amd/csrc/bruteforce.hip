@@ -1295,10 +1295,10 @@ __global__ __launch_bounds__(256, 2) void bf_screen_kernel(ScreenArgs a) {
   };
 
   uint4 q0[2][NQ], q1[2][NQ];
-  fetch();
-  load_q(q0, 0);
   if (abandoned) return;
   if (blockIdx.x == 0 && tid == 0) a.state->n_hopeless = 0u;
+  fetch();
+  load_q(q0, 0);
   stage(0);
   advance();
   fetch();
@@ -1338,10 +1338,8 @@ struct RangeArgs {
   CallState *state;
   uint32_t d, kb_n, metric, want, most;
   bool last;   // pass
-  // what a pass tells of the last: entries up to two rooms beyond the one of rank `rank`, each of which stands for `weight`; more
-  // than `limit`, and the query will be lost
-  uint32_t rank;
-  float weight, limit;
+  // what a pass tells of the last (see vote())
+  float part, weight, limit;
   uint32_t few;   // entries that a wavefront takes
   uint64_t *buf;
   uint32_t *count;
@@ -1359,9 +1357,13 @@ __device__ __forceinline__ float entry_room(const RangeArgs &a, uint32_t q, floa
   const float room = screen_room(q_norm, q_rest, bound, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);
   return screen_room(q_norm, q_rest, bound + 3.0f * room, a.d, a.kb_n, a.metric, x_unit, unscale, max_norm, max_rest);
 }
-// A voting query tells whether the last pass will lose it.
-__device__ __forceinline__ void vote(const RangeArgs &a, uint32_t q, uint32_t n_near) {
-  if (q % kVoters == 0 && (float)n_near * a.weight > a.limit) atomicAdd(&a.state->n_hopeless, 1u);
+// A voting query tells whether the last pass will lose it: whether more than `limit` rows lie up to two rooms beyond the
+// bound that all rows will give.  That bound's rank among the rows so far lies between 1 (n_best entries are up to two rooms
+// beyond the best) and `want` (n_bound beyond the bound so far): `part` of the way, by its logarithm.  Each entry stands for
+// `weight` rows.
+__device__ __forceinline__ void vote(const RangeArgs &a, uint32_t q, uint32_t n_best, uint32_t n_bound) {
+  const float n = a.part > 0.0f ? __expf((1.0f - a.part) * __logf((float)n_best) + a.part * __logf((float)n_bound)) : (float)n_best;
+  if (q % kVoters == 0 && n * a.weight > a.limit) atomicAdd(&a.state->n_hopeless, 1u);
 }
 
 // ---------------------------------------------------------------------------
@@ -1477,12 +1479,9 @@ struct Selector {
     }
     return mn;
   }
-  // How many entries lie up to two rooms beyond the one of that rank, give or take a few places (a step of the bisection
-  // takes a microsecond in all: the smallest score for ranks up to four).
-  __device__ __forceinline__ uint32_t near_rank(uint32_t rank, float room) {
-    uint32_t n;
-    const uint32_t from = rank <= 4 ? lowest() : (uint32_t)(run(rank, rank + rank / 4 + 1, n) >> 32);
-    const float last = unorder_f32(from) + 2.0f * room;
+  // How many entries lie up to two rooms beyond the best.
+  __device__ __forceinline__ uint32_t near_best(float room) {
+    const float last = unorder_f32(lowest()) + 2.0f * room;
     return count_up_to(last < INFINITY ? order_u32(last) : kMaxScore);
   }
 };
@@ -1518,8 +1517,8 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_scores_kernel(const flo
     if (tid == 0) bound[q] = b;
     auto tell = [&](const RangeArgs &a) {
       if (q % kVoters != 0 || (uint32_t)(b >> 32) >= kMaxScore) return;
-      const uint32_t n_near = s.near_rank(a.rank, entry_room(a, q, unorder_f32((uint32_t)(b >> 32))));
-      if (tid == 0) vote(a, q, n_near);
+      const uint32_t n_near = s.near_best(entry_room(a, q, unorder_f32((uint32_t)(b >> 32))));
+      if (tid == 0) vote(a, q, n_near, n_near);
     };
     (tell(range), ...);
     return;
@@ -1670,8 +1669,8 @@ __global__ __launch_bounds__(kSelThreads) void bf_select_entries_kernel(const ui
 // select_round).  Once one voter in four will be lost the passes after it do nothing and the call is repeated with two
 // parts; below that the lost queries are taken up again by themselves.  10,000 queries x 1M x 128, two parts alone / first
 // parts, and centred rows for what these lost / this: 7 spreads from the origin 7.3 / 4.4 / 4.5 ms, 10 7.4 / 21.4 / 7.5, 20
-// 7.8 / 21.4 / 8.0; 100 clusters of spread 0.1 7.7 / 5.3 / 5.5, 0.05 7.9 / 21.0 / 8.2; at the origin (3.69) and for small
-// calls (0.25) the votes cost 1 to 3 %.
+// 7.8 / 21.4 / 8.0; 100 clusters of spread 0.1 7.7 / 5.3 / 5.5, 0.05 7.9 / 21.0 / 8.2.  Where nothing is lost the votes cost
+// 0 to 1 %; where the passes are given up, the sample and what is left of them 0.3 ms here, 0.1 with 2,000 queries.
 // (Re-evaluating each pass's new entries made the bounds a room tighter and cost more: 200,000 rows, d = 768, k = 100,
 // 2,000 queries: these kernels 263 instead of 660 us.)
 // A wavefront takes a query with up to 512 entries, a workgroup one with more, in a launch of its own: 10,000 queries with
@@ -1703,7 +1702,7 @@ __device__ __forceinline__ uint64_t range_entries(const RangeArgs &a, uint32_t q
     const uint32_t at = atomicAdd(n_best, 1u);
     if (at < range_room(THREADS)) best[at] = ((uint64_t)s.key[e] << 32) | s.id[e];
   }
-  if (!a.last && q % kVoters == 0) n_near = s.near_rank(a.rank, room);
+  if (!a.last && q % kVoters == 0) n_near = s.near_best(room);
   __syncthreads();
   return b;
 }
@@ -1721,7 +1720,7 @@ __global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
   if (a.state->abandoned) return;
   if (found > a.cap) {   // entries were lost
     if (!a.last && tid == 0) {
-      vote(a, q, found);
+      vote(a, q, found, found);
       a.bound[q] = 0;   // (no number: the query has no more entries)
     }
     return;
@@ -1747,7 +1746,7 @@ __global__ __launch_bounds__(THREADS) void bf_range_kernel(RangeArgs a) {
     if (tid == 0) {
       if (n <= kRoomHere) a.count[q] = n;
       if (bounds) a.bound[q] = b;
-      vote(a, q, n_near);
+      vote(a, q, n_near, n);
     }
     return;
   }
@@ -2238,15 +2237,15 @@ static ann_status select_round(const Truth &t, const Selection &s, const float *
     if (rc != ANN_OK) return rc;
     // What the last pass will leave of a query is the rows up to two rooms beyond the bound that all rows will give, whose rank among
     // those so far is want / all.  Below one, the best so far lies further out than that bound: by as much as the square
-    // root of the rank corrects (estimate over what was left, 1M x 128, k = 10, 7, 8 and 10 spreads from the origin, sample and first
-    // pass: 6.1 and 2.7, 5.3 and 2.4, 4.2 and 1.9 without; 1.6 and 1.4, 1.4 and 1.2, 1.1 and 1.0 with it).  The last pass notes up
-    // to three times what it leaves.
-    RangeArgs range{t.x, qr, s.sample_sq, s.unscale, s.q_norm, s.q_rest, s.state, t.d, s.kb_n, t.metric, s.want, s.most_bound, false, 1, 1.0f, 0.0f, kFewEntries,
+    // root of the rank corrects.  Estimate over what was left, after the sample and each pass: 1M x 128, k = 10, 8 spreads from the
+    // origin 2.2, 1.5, 1.0, 0.9 (without the root 5.3, 2.4), k = 100, 6 spreads 1.5, 1.1, 0.9, 0.9; 200,000 x 768, k = 100, 5 spreads 0.6,
+    // 0.9, 0.9; 100 clusters of spread 0.09 0.8, 0.9, 0.8, 0.9.  The last pass notes up to three times what it leaves.
+    RangeArgs range{t.x, qr, s.sample_sq, s.unscale, s.q_norm, s.q_rest, s.state, t.d, s.kb_n, t.metric, s.want, s.most_bound, false, 0.0f, 1.0f, 0.0f, kFewEntries,
                     s.buf, s.count, s.part_cap, s.bound};
     range.limit = (float)(s.part_cap / 3 < range_room(kSelThreads) ? s.part_cap / 3 : range_room(kSelThreads));
     auto rows_so_far = [&](double all) {   // one in `all`
       const double rank = s.want / all;
-      range.rank = rank > 1.0 ? (uint32_t)rank : 1u;
+      range.part = rank > 1.0 ? (float)(log(rank) / log((double)s.want)) : 0.0f;
       range.weight = (float)(rank > 1.0 ? all : all * sqrt(rank));
     };
     rows_so_far(b.stretch);
