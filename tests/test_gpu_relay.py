@@ -55,6 +55,47 @@ def test_long_adjacency_rows(degree, ef, p):
         ix.close()
 
 
+@pytest.mark.parametrize("bits,d", [(8, 40), (8, 200), (4, 300)])
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("metric", [oracle.L2, oracle.IP])
+def test_options(bits, d, p, metric):
+    """Entry nodes (some twice, some none), an order, pool sizes of each query's own and folded queries of an earlier call, with
+    bits and with the cache."""
+    import gpu_harness as H
+    import paper_2503_17911_amd as ann
+    import torch
+    rng = np.random.default_rng(d + p)
+    n, nq, degree, ef = 1100, 24, 20, 200 if p == 8 else 70
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    if metric == oracle.IP:
+        X /= np.linalg.norm(X, axis=1, keepdims=True)
+    adj = np.stack([rng.choice(n, degree, replace=False) for _ in range(n)]).astype(np.uint32)
+    lv = oracle.sq_fit(X, bits)
+    ix = H.GpuIndex(X, adj, 3, [lv], metric)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    ent = rng.integers(0, n, (nq, 6)).astype(np.uint32)
+    ent[::2, 1] = 0xFFFFFFFF
+    ent[:, 4] = ent[:, 0]
+    order = torch.from_numpy(rng.permutation(nq).astype(np.int32)).to(H.DEV)
+    efs = np.array([1, 2, 30, ef] * (nq // 4), np.uint32)
+    kw = dict(mode=1, expansions_per_step=p)
+    for visited in (dict(visited_slots=0), dict(visited_kind=ann.VISITED_CACHE)):
+        plain = oracle.search_batch(lv, d, adj, 3, Q, ef, metric=metric, expansions_per_step=p)
+        for more in (dict(), dict(same_queries_as_last_call=True, reuse_folded_queries=True), dict(query_order=order)):
+            got = ix.search(Q, ef, **kw, **visited, **more)
+            assert all((g == w).all() for g, w in zip(got[:3], plain)) and (got[3][:, 0] == plain[3][:, 0]).all()
+        want = oracle.search_batch(lv, d, adj, 3, Q, ef, metric=metric, entries=ent, expansions_per_step=p)
+        for more in (dict(), dict(query_order=order)):
+            got = ix.search(Q, ef, entries=ent, **kw, **visited, **more)
+            assert all((g == w).all() for g, w in zip(got[:3], want)) and (got[3][:, 0] == want[3][:, 0]).all()
+        got = ix.search(Q, ef, ef_per_query=torch.from_numpy(efs.view(np.int32)).to(H.DEV), **kw, **visited)
+        for e in np.unique(efs):
+            want = oracle.search_batch(lv, d, adj, 3, Q[efs == e], int(e), metric=metric, expansions_per_step=p)
+            assert (got[0][efs == e][:, :e] == want[0]).all() and (got[0][efs == e][:, e:] == 0xFFFFFFFF).all()
+            assert (got[1][efs == e][:, :e] == want[1]).all() and (got[3][efs == e][:, 0] == want[3][:, 0]).all()
+    ix.close()
+
+
 @pytest.mark.parametrize("n,degree", [(20_000, 12), (700_000, 6), (1_400_000, 6)])
 def test_batches_and_base_sets_on_both_sides_of_what_is_resident(n, degree):
     """(Bits for 512 queries, for 256, and for none.)"""
